@@ -101,8 +101,8 @@ typedef enum {
 
 /* Flag granularity and derived sizes for a problem; filled by the *_plan calls (host struct). */
 typedef struct {
-    int32_t tile_m, tile_n;       /* rows x cols covered by one ready flag */
-    int32_t tiles_m, tiles_n;     /* flag grid of one shard (GEMM+RS: M/P x N) or of C_local (AG+GEMM) */
+    int32_t tile_m, tile_n;       /* rows x cols covered by one ready flag (the kernels may compute in other tiles) */
+    int32_t tiles_m, tiles_n;     /* flag grid of one shard (GEMM+RS: M/P x N) or of one chunk's rows of C_local (AG+GEMM) */
     int64_t flags_per_slot;       /* tiles_m * tiles_n */
     int64_t local_m, local_n, local_k;   /* the per-rank GEMM */
     int64_t ar_flags_per_slot;    /* pk_gemm_ar_plan only: ceil((M/P) / PK_AR_ROWS) * tiles_n, else 0 */
@@ -159,8 +159,8 @@ const char* pk_status_str(int status);
  * first such call on a device outside a graph capture, default priority; a call on a capturing stream before that runs
  * in the plain order) and joins back into `stream` before the call's work counts as done there.  The reduce waits only for the own block (complete by then) and for the peers' flags, never for the second GEMM
  * launch, so either may be placed first.  Results are bit-identical to the plain call.  The flag needs both phases
- * (PK_ERR_ARG otherwise) and is ignored where it cannot help: when the own block takes every round of the schedule, and
- * next to the 256x256 fp8 kernel with bf16 slots, with a k-contiguous second operand, or with P other than 2, 4, 8.
+ * (PK_ERR_ARG otherwise) and is ignored where it cannot help: when all tiles run at once, or the own block takes every
+ * round of the schedule.
  * Calls with the flag from several host threads on one device are serialised while they enqueue.
  * comm_cus: as for pk_ag_gemm below, the number of compute units the GEMM phase leaves to communicator workgroups
  * (0 = none).  partial_dt: element type of
@@ -252,8 +252,8 @@ pk_status pk_gemm_ar(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype 
  * comm_cus (the paper's num_comm_sms, section 3.1.3, the paragraph on partitioning the SMs, appendix D) is the number of compute
  * units this call leaves free for the communicator workgroups that move the chunks while it runs: the GEMM is
  * launched on the remaining ones (rounded down to a multiple of 8, at least 8).  0 = use every compute unit:
- * communicator workgroups then run only where they fit beside a GEMM workgroup (it holds all of the compute unit's LDS
- * and leaves 80 registers per lane, bf16, or 48, fp8) or where the schedule leaves a compute unit empty.
+ * communicator workgroups then run only where they fit beside a GEMM workgroup (it holds most or all of the compute
+ * unit's LDS and leaves 96 registers per lane or more, bf16, or 64, fp8) or where the schedule leaves a compute unit empty.
  * Requirements: M % P == 0, N % P == 0, K % 64 == 0 (bf16) or % 128 == 0 (fp8), (N/P) % 8 == 0 (bf16) or
  * % 16 == 0 (fp8).  With P == 1 this is a plain GEMM with bf16 output (chunk_flags may then be NULL).
  */

@@ -1,31 +1,42 @@
 """Builds libpk.so (the C-ABI library with the gfx950 kernels) in-tree with hipcc."""
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libpk.so")
-SOURCES = [os.path.join(HERE, "csrc", "pk_kernels.hip")]
-HEADERS = [os.path.join(HERE, "csrc", "pk_device.h"), os.path.join(HERE, "csrc", "pk_gemm.h"),
-           os.path.join(os.path.dirname(HERE), "include", "pk.h")]
+CSRC = os.path.join(HERE, "csrc")
+SOURCES = [os.path.join(CSRC, n) for n in ("pk_kernels.hip", "gemm_rs.hip", "gemm_rs16.hip", "gemm_ag.hip", "gemm_agk.hip")]
+HEADERS = [os.path.join(CSRC, n) for n in ("pk_device.h", "pk_gemm.h", "pk_tiles.h")] + [
+    os.path.join(os.path.dirname(HERE), "include", "pk.h")]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed-fp32 VALU forms are kept off for every HIP source of this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
 
 def build_library(verbose=False):
-    """Compile libpk.so; always recompiles.  Returns the path."""
+    """Compile libpk.so; always recompiles (the sources side by side).  Returns the path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + SOURCES + ["-o", LIB_PATH]
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in SOURCES]
+        cmds = [[hipcc] + HIPCC_FLAGS + ["-c", s, "-o", o] for s, o in zip(SOURCES, objs)]
+        with ThreadPoolExecutor(max_workers=min(8, len(cmds))) as pool:
+            list(pool.map(lambda c: _run(c, verbose), cmds))
+        _run([hipcc] + HIPCC_FLAGS + ["-shared"] + objs + ["-o", LIB_PATH], verbose)
+    return LIB_PATH
+
+
+def _run(cmd, verbose):
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if verbose or res.returncode != 0:
         print(" ".join(cmd))
         print(res.stdout)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed building libpk.so")
-    return LIB_PATH
 
 
 C_LAUNCH_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi_launch.c")

@@ -71,9 +71,11 @@ __device__ __forceinline__ void dma_load16(const char* sbase, uint32_t voff, uin
 // 16-byte store that writes through to memory (system-coherent cache policy, streaming).  Together with an
 // explicit wait for the stores to complete (s_waitcnt vmcnt(0)) this is the "release" half of a signal without
 // the L2 write-back of a release fence: nothing dirty is left behind in the XCD's L2.  Inline assembly because
-// the cache-policy bits are not reachable from a plain store.
+// the cache-policy bits are not reachable from a plain store.  The no-op behind it: a store of more than 8 bytes reads its
+// data registers for two more wait states, in which no vector instruction may overwrite them; the compiler keeps that
+// distance for the stores it writes itself, not for one inside an assembly block.
 __device__ __forceinline__ void store16_writethrough(void* p, i32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 
 // Publish a flag whose data was written with store16_writethrough and has completed (every wave waited on its

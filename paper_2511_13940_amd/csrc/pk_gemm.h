@@ -34,16 +34,38 @@ namespace pk {
 // reduce-scatter with fp32 slots; all-gather of row chunks; reduce-scatter with bf16 slots; all-gather of column (K) chunks
 enum { EPI_RS = 0, EPI_AG = 1, EPI_RS16 = 2, EPI_AGK = 3 };
 
+// Division by a divisor that the host knows: q = floor(n * floor(2^32 / d) / 2^32) is n / d or one less, for every 32-bit n, so
+// one correction makes it exact.  Four scalar instructions where a general division takes some forty: the tile mapping stands
+// between a launch and its first load.
+struct FastDiv {
+    uint32_t d, m;
+    void set(int64_t div) {                   // host; 1 <= div < 2^31
+        d = (uint32_t)div;
+        m = div == 1 ? 0xFFFFFFFFu : (uint32_t)(((uint64_t)1 << 32) / (uint64_t)div);
+    }
+    __device__ __forceinline__ int div(int n) const {
+        const uint32_t q = __umulhi((uint32_t)n, m);
+        return (int)(q + ((uint32_t)n - q * d >= d ? 1u : 0u));
+    }
+};
+
 struct GemmArgs {
     const char* A;            // local first operand, row-major
     const char* B;            // local second operand, row-major
     int64_t lda, ldb;         // bytes per row
     int32_t n;                // columns of the local product
     int32_t ktiles;           // local k in k-tiles of KB bytes of A-row
-    // tile space: (P * tiles_m_shard) x tiles_n; a tile never crosses a multiple of rows_per_shard
-    int32_t rows_per_shard;   // M/P
-    int32_t tiles_m_shard;    // ceil(rows_per_shard / BM)
-    int32_t tiles_n;
+    int32_t rows_per_shard;   // rows of one shard (M/P; all rows for the scatter along the last dimension)
+    int32_t tiles_n;          // tile columns
+    // Tile rows.  All-gather: tile row t is the (t mod tiles_m_shard)-th tile of span t / tiles_m_shard of rows_per_span rows
+    // (one chunk, or all rows at once: a tile then waits for every chunk of rows_per_chunk rows that it touches).
+    int32_t rows_per_span, tiles_m_shard, rows_per_chunk;
+    // Reduce-scatter: the rows are cut into the row blocks of the ready flags (blks_per_shard blocks of blk_rows rows in every
+    // shard = span, the last one shorter); tile row t covers blks_per_tile consecutive blocks, possibly of several shards, at
+    // most BM rows together.  Likewise a tile column covers fcols_per_tile of the flag_cols flag columns of a shard.
+    int32_t blk_rows, blks_per_shard, blks_per_tile, n_blks;
+    int32_t fcols_per_tile, flag_cols;
+    int32_t late_signal;      // the flags are published behind this kernel (a tile is finer than a flag)
     // schedule: n_groups groups of grp_tile_rows tile rows, visited group0, group0+1, ... (mod n_groups);
     // inside a group each XCD (workgroup id mod 8) takes a contiguous run of tiles
     int32_t grp_tile_rows;
@@ -54,7 +76,7 @@ struct GemmArgs {
     // scatter along the last dimension (reduce-scatter modes only; 0 = scatter along rows): destination rank from the
     // tile column, tiles_n = P * tiles_n_shard, rows_per_shard = all rows, one row shard
     int32_t cols_per_shard;   // N/P
-    int32_t tiles_n_shard;    // ceil(cols_per_shard / BN)
+    int32_t tiles_n_shard;    // tile columns of one column block
     int32_t rank;
     // reduce-scatter epilogue
     void* partials;           // [P][rows_per_shard][n], fp32 (EPI_RS) or bf16 (EPI_RS16)
@@ -66,6 +88,7 @@ struct GemmArgs {
     // all-gather epilogue
     uint16_t* C;              // (P*rows_per_shard) x n bf16
     const uint32_t* chunk_flags;
+    int32_t acquire_all;      // A does not start on a 128-byte line: a line may hold the end of one chunk and the start of the next
     int32_t k_chunks;         // EPI_AGK: A arrives in this many column blocks of K/k_chunks (chunk q from rank q)
     int32_t act;              // pk_activation applied to the accumulator before the bf16 rounding (all-gather mode)
     const float* scale_a;     // fp8 only
@@ -76,6 +99,22 @@ struct GemmArgs {
     // stream-K tail: the first sk_dp_slots tile slots are computed whole, one per workgroup and round; the k range of the
     // remaining ones is shared out evenly (sk_dp_slots = all slots: no such tail)
     int32_t sk_dp_slots;
+    // divisors of the tile mapping (set_divisors)
+    FastDiv by_group, by_band, by_band_rows, by_last_rows, by_span, by_blks, by_chunk_rows, by_shard_cols;
+    int32_t last_band;        // index of the last band of a group
+    void set_divisors() {     // host, once the sizes above are final
+        const int b = band > 0 ? band : 1;
+        band = b;
+        last_band = (grp_tile_rows + b - 1) / b - 1;
+        by_group.set(wg_per_group);
+        by_band.set((int64_t)b * tiles_n);
+        by_band_rows.set(b);
+        by_last_rows.set(grp_tile_rows - last_band * b);
+        by_span.set(tiles_m_shard > 0 ? tiles_m_shard : 1);
+        by_blks.set(blks_per_shard > 0 ? blks_per_shard : 1);
+        by_chunk_rows.set(rows_per_chunk > 0 ? rows_per_chunk : 1);
+        by_shard_cols.set(tiles_n_shard > 0 ? tiles_n_shard : 1);
+    }
     // A launch may cover a range of the problem's tile rows only: its groups span n_groups * grp_tile_rows rows that start
     // at tile row row_rot and wrap around at all_tile_rows (0 = the groups cover every row, no rotation).
     int32_t row_rot, all_tile_rows;
@@ -88,10 +127,12 @@ struct GemmArgs {
 // runs the epilogue); any other piece (accumulators handed to the owner through ws_tiles)
 enum { UNIT_FULL = 0, UNIT_HEAD = 1, UNIT_PART = 2 };
 
-constexpr int kEpiStageBytes = 32 * 1024;   // LDS staging of the epilogue, shared out evenly to the waves
+// LDS staging of the epilogue, shared out evenly to the waves: 32 KB, or 16 KB where the ring leaves no more of the 160 KB
+template <int BM, int BN, int KB, int NS>
+constexpr int epi_stage_bytes() { return NS * (BM + BN) * KB + 32 * 1024 <= 160 * 1024 ? 32 * 1024 : 16 * 1024; }
 
 template <int BM, int BN, int KB, int NS>
-constexpr int gemm_lds_bytes() { return NS * (BM + BN) * KB + kEpiStageBytes; }
+constexpr int gemm_lds_bytes() { return NS * (BM + BN) * KB + epi_stage_bytes<BM, BN, KB, NS>(); }
 
 // s_waitcnt immediate for vmcnt(N) lgkmcnt(0) (gfx9 encoding, expcnt left alone)
 constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
@@ -99,13 +140,13 @@ constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 
 // BT: the second operand is stored k-contiguous (N x K row-major, the transpose of the K x N matrix): its tile then has
 // the layout of the A tile and its fragments come in with the same 16-byte reads, no transposing reads.
 // SK: built with the stream-K tail (its code paths cost registers, so launches that share out no tile use SK = false).
-template <int BM, int BN, int WM, int WN, int KB, int NS, bool FP8, int EPI, bool BT = false, bool SK = false>
-__global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g) {
+template <int BM, int BN, int WM, int WN, int WK, int KB, int NS, bool FP8, int EPI, bool BT = false, bool SK = false>
+__global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     PK_LDS char* lds = (PK_LDS char*)smem_generic;
 
     constexpr bool IS_RS = EPI == EPI_RS || EPI == EPI_RS16;
-    constexpr int NW = WM * WN;                          // waves per workgroup
+    constexpr int NW = WM * WN * WK;                     // waves per workgroup
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;  // 32x32 accumulators per wave: TM x TN
     constexpr int A_BYTES = BM * KB, B_BYTES = BN * KB, STAGE = A_BYTES + B_BYTES;
     constexpr int ELEM = FP8 ? 1 : 2;
@@ -116,19 +157,27 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
     constexpr int RPI = 64 / CPR;                        // B rows covered by one wave-wide load
     constexpr int NA = A_BYTES / 1024 / NW, NB = B_BYTES / 1024 / NW;   // wave-wide loads per wave per k-tile
     constexpr int NL = NA + NB;
-    constexpr int KS = FP8 ? KB / 64 : KB / 32;          // MFMA k-steps per k-tile
+    constexpr int KST = FP8 ? KB / 64 : KB / 32;         // MFMA k-steps per k-tile
+    constexpr int KS = KST / WK;                         // ... of which each of the WK wave groups takes its own share
     constexpr int EPI_OFF = NS * STAGE;                  // LDS offset of the epilogue staging area
+    constexpr int EPI_BYTES = epi_stage_bytes<BM, BN, KB, NS>();
+    // WK > 1: the groups' accumulators are summed at the end of a tile and shared out, OTM x OTN blocks to each wave
+    constexpr int OB = TM * TN / WK, OTM = OB >= TN ? OB / TN : 1, OTN = OB >= TN ? TN : OB;
+    static_assert(OB >= 1 && OB * WK == TM * TN && OTM * OTN == OB, "the blocks of a wave's sub-tile are shared out evenly");
+    static_assert(WK == 1 || (!SK && NW * (WK - 1) * OB * 4096 <= gemm_lds_bytes<BM, BN, KB, NS>()), "the exchange fits the LDS");
     static_assert(KB == 64 || KB == 128, "k-tile is 64 or 128 bytes of A row");
     static_assert(KS >= 1, "a k-tile holds at least one MFMA k-step");
-    static_assert(CPR >= 8 && RPI >= 1, "tile too narrow");
+    static_assert(CPR >= 4 && RPI >= 1, "tile too narrow");
+    static_assert(KST % WK == 0 && (KS & (KS - 1)) == 0, "the wave groups share the k-steps of a k-tile evenly");
     static_assert(NW % 2 == 0 && NA >= 1 && NB >= 1, "wave grid does not fit the tile");
-    static_assert((NS - 2) * NL <= 63, "too many loads in flight for the counter");
+    static_assert((NS - 1) * NL <= 63, "too many loads in flight for the counter");
     typedef typename std::conditional<FP8, i32x8, bf16x8>::type frag_t;
 
     const int tid = threadIdx.x;
     const int l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w / WN, wn = w % WN;
+    const int wk = w / (WM * WN), wm = (w / WN) % WM, wn = w % WN;
+    const int kk0 = wk * KS;                             // first k-step of this wave's group in every k-tile
     const int h = l >> 5;
 
     // A-tile swizzle: LDS chunk position = k-chunk ^ fA(row).
@@ -136,34 +185,42 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
     auto fA = [](int r) { return KB == 128 ? ((r & 7) ^ ((r >> 3) & 1)) : (((r >> 1) & 3) ^ ((r >> 3) & 1)); };
 
     // ---- per-lane LDS fragment addresses (relative to a stage) ----
-    const int fa = fA(l & 31);                           // rows of a fragment differ from (l & 31) by multiples of 32
-    const uint32_t a_row_off = (uint32_t)(wm * (BM / WM) + (l & 31)) * KB;
-    const int s16 = l & 15, nhalf = (l >> 4) & 1;
-    uint32_t b_off[TN];
-    const uint32_t bt_row_off = (uint32_t)(A_BYTES + (wn * (BN / WN) + (l & 31)) * KB);   // BT: B tile = BN rows of KB bytes
-    if constexpr (BT) {
+    // Set anew for every tile, from a lane id that the compiler cannot follow from one tile to the next: kept in registers
+    // across the epilogue (and its addresses across the main loop) they would not fit beside the accumulators.
+    int fa = 0, hf = 0;
+    uint32_t a_row_off = 0, b_off[TN];
+    auto set_frag_addresses = [&](int l) {
+        fa = fA(l & 31);                                     // rows of a fragment differ from (l & 31) by multiples of 32
+        hf = l >> 5;
+        const int h = l >> 5;
+        a_row_off = (uint32_t)(wm * (BM / WM) + (l & 31)) * KB;
+        const int s16 = l & 15, nhalf = (l >> 4) & 1;
+        const uint32_t bt_row_off = (uint32_t)(A_BYTES + (wn * (BN / WN) + (l & 31)) * KB);   // BT: B tile = BN rows of KB bytes
+        if constexpr (BT) {
 #pragma unroll
-        for (int tj = 0; tj < TN; ++tj) b_off[tj] = bt_row_off + (uint32_t)(tj * 32 * KB);
-    } else if constexpr (!FP8) {
-        // bf16 B tile: panels of 64 columns (128 bytes per k-row, k-rows consecutive);
-        // inside a row the two 32-byte pieces of each 64-byte half trade places on k-rows with bit 1 set
-        static_assert((BN / WN) % 64 == 0, "a wave column covers whole 64-column panels");
-        const int krow_base = 8 * h + (s16 >> 2);
+            for (int tj = 0; tj < TN; ++tj) b_off[tj] = bt_row_off + (uint32_t)(tj * 32 * KB);
+        } else if constexpr (!FP8) {
+            // bf16 B tile: panels of 64 columns (128 bytes per k-row, k-rows consecutive);
+            // inside a row the two 32-byte pieces of each 64-byte half trade places on k-rows with bit 1 set
+            static_assert(BN % 64 == 0, "the tile is made of whole 64-column panels");
+            const int krow_base = 16 * kk0 + 8 * h + (s16 >> 2);
 #pragma unroll
-        for (int tj = 0; tj < TN; ++tj) {
-            const int panel = wn * (BN / WN / 64) + (tj >> 1);
-            const int piece = (2 * (tj & 1) + nhalf) ^ ((s16 >> 3) & 1);
-            b_off[tj] = (uint32_t)(A_BYTES + panel * (B_ROWS * 128) + krow_base * 128 + piece * 32 + (s16 & 3) * 8);
+            for (int tj = 0; tj < TN; ++tj) {
+                const int c32 = wn * TN + tj;                // 32-column block of the tile
+                const int panel = c32 >> 1;
+                const int piece = (2 * (c32 & 1) + nhalf) ^ ((s16 >> 3) & 1);
+                b_off[tj] = (uint32_t)(A_BYTES + panel * (B_ROWS * 128) + krow_base * 128 + piece * 32 + (s16 & 3) * 8);
+            }
+        } else {
+            const int krow_base = 64 * kk0 + 32 * h + (s16 >> 1);
+            const int gsw = ((s16 >> 1) & 7) % (CPR / 2);
+#pragma unroll
+            for (int tj = 0; tj < TN; ++tj) {
+                const int c = wn * (BN / WN / 16) + tj * 2 + nhalf;
+                b_off[tj] = (uint32_t)(A_BYTES + krow_base * B_ROW_BYTES + (c ^ (2 * gsw)) * 16 + (s16 & 1) * 8);
+            }
         }
-    } else {
-        const int krow_base = 32 * h + (s16 >> 1);
-        const int gsw = ((s16 >> 1) & 7) % (CPR / 2);
-#pragma unroll
-        for (int tj = 0; tj < TN; ++tj) {
-            const int c = wn * (BN / WN / 16) + tj * 2 + nhalf;
-            b_off[tj] = (uint32_t)(A_BYTES + krow_base * B_ROW_BYTES + (c ^ (2 * gsw)) * 16 + (s16 & 1) * 8);
-        }
-    }
+    };
 
     // Fragment reads of k-step kk of the k-tile held in LDS stage `st`, as NU = TN + TM units in the order the
     // MFMAs need them: B fragments first, then A fragments.
@@ -173,12 +230,12 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
             // both operands: rows of KB bytes, 16-byte chunks XOR-swizzled by row; rows of a fragment differ by multiples of 32
             const uint32_t base = u < TN ? b_off[u] : a_row_off + (uint32_t)((u - TN) * 32 * KB);
             if constexpr (!FP8) {
-                const bf16x8 v = *(PK_LDS bf16x8*)(st + base + (uint32_t)((((2 * kk + h) ^ fa) & (CPA - 1)) * 16));
+                const bf16x8 v = *(PK_LDS bf16x8*)(st + base + (uint32_t)((((2 * (kk0 + kk) + hf) ^ fa) & (CPA - 1)) * 16));
                 if (u < TN) bfr[u] = v;
                 else af[u - TN] = v;
             } else {
-                i32x4 x0 = *(PK_LDS i32x4*)(st + base + (uint32_t)((((4 * kk + 2 * h) ^ fa) & (CPA - 1)) * 16));
-                i32x4 x1 = *(PK_LDS i32x4*)(st + base + (uint32_t)((((4 * kk + 2 * h + 1) ^ fa) & (CPA - 1)) * 16));
+                i32x4 x0 = *(PK_LDS i32x4*)(st + base + (uint32_t)((((4 * (kk0 + kk) + 2 * hf) ^ fa) & (CPA - 1)) * 16));
+                i32x4 x1 = *(PK_LDS i32x4*)(st + base + (uint32_t)((((4 * (kk0 + kk) + 2 * hf + 1) ^ fa) & (CPA - 1)) * 16));
                 const i32x8 v = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
                 if (u < TN) bfr[u] = v;
                 else af[u - TN] = v;
@@ -194,7 +251,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                 bfr[tj] = __builtin_bit_cast(bf16x8, both);
             } else {
                 const int ti = u - TN;
-                const uint32_t ao = a_row_off + (uint32_t)((((2 * kk + h) ^ fa) & (CPA - 1)) * 16);
+                const uint32_t ao = a_row_off + (uint32_t)((((2 * (kk0 + kk) + hf) ^ fa) & (CPA - 1)) * 16);
                 af[ti] = *(PK_LDS bf16x8*)(st + ao + ti * 32 * KB);
             }
         } else {
@@ -210,8 +267,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                 bfr[tj] = __builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7);
             } else {
                 const int ti = u - TN;
-                const uint32_t ao0 = a_row_off + (uint32_t)((((4 * kk + 2 * h) ^ fa) & (CPA - 1)) * 16);
-                const uint32_t ao1 = a_row_off + (uint32_t)((((4 * kk + 2 * h + 1) ^ fa) & (CPA - 1)) * 16);
+                const uint32_t ao0 = a_row_off + (uint32_t)((((4 * (kk0 + kk) + 2 * hf) ^ fa) & (CPA - 1)) * 16);
+                const uint32_t ao1 = a_row_off + (uint32_t)((((4 * (kk0 + kk) + 2 * hf + 1) ^ fa) & (CPA - 1)) * 16);
                 i32x4 x0 = *(PK_LDS i32x4*)(st + ao0 + ti * 32 * KB);
                 i32x4 x1 = *(PK_LDS i32x4*)(st + ao1 + ti * 32 * KB);
                 af[ti] = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -232,31 +289,52 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
     };
 
     // tile bookkeeping carried from one iteration to the next (the epilogue of a tile runs one iteration late)
-    int p_q = -1, p_flag = 0, p_row0 = 0, p_row_end = 0, p_col0 = 0, p_col_end = 0;
+    int p_q = -1, p_blk = 0, p_nblk = 0, p_fcol = 0, p_row0 = 0, p_row_end = 0, p_col0 = 0, p_col_end = 0;
     int p_kind = UNIT_FULL, p_part_lo = 0, p_tile_end = 0;
     bool p_dead = false;                                 // the previous tile was given up (a wait timed out): no signal
     const int slots_total = g.wg_per_group * g.n_groups;
     const int G = g.grp_tile_rows * g.tiles_n;
     float scale = 1.f;
     if constexpr (FP8) scale = g.scale_a[0] * g.scale_b[0];
-    // the non-linearity between the two GEMMs of the MLP (paper section 4.1), fused into the all-gather epilogue
-    auto activate = [&](float x) -> float {
-        switch (g.act) {
-            case PK_ACT_RELU: return fmaxf(x, 0.f);
-            case PK_ACT_GELU_TANH: return 0.5f * x * (1.f + tanhf(0.7978845608028654f * (x + 0.044715f * x * x * x)));
-            case PK_ACT_SILU: return x / (1.f + expf(-x));
-            default: return x;
+    // the non-linearity between the two GEMMs of the MLP (paper section 4.1), fused into the all-gather epilogue, in fp32 on
+    // the accumulators before the rounding.  x/2 (1 + tanh(u)) is x * sigmoid(2u), so both smooth ones are x / (1 + exp(-y)).
+    auto activate8 = [&](f32x4 a, f32x4 b) -> bf16x8 {
+        float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+        bf16x8 o;
+        if (g.act == PK_ACT_RELU) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (__bf16)fmaxf(x[e], 0.f);
+            return o;
         }
+        const bool silu = g.act == PK_ACT_SILU;
+        constexpr float kC1 = 1.5957691216057308f, kC3 = kC1 * 0.044715f;      // 2 sqrt(2/pi)
+        constexpr float kLog2e = 1.44269502f, kLog2eLo = 1.92596303e-8f, kLn2 = 0.693147182f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float y = silu ? x[e] : x[e] * __builtin_fmaf(kC3 * x[e], x[e], kC1);
+            y = -__builtin_amdgcn_fmed3f(y, -200.f, 200.f);          // exp() is 0 or infinite long before: no inf - inf below
+            // exp(y) = 2^(y log2 e), the product's rounding error carried along: 2^p (1 + r ln 2)
+            const float p = y * kLog2e;
+            const float r = __builtin_fmaf(y, kLog2eLo, __builtin_fmaf(y, kLog2e, -p));
+            const float ex = __builtin_amdgcn_exp2f(p) * __builtin_fmaf(r, kLn2, 1.f);
+            o[e] = (__bf16)(x[e] * __builtin_amdgcn_rcpf(1.f + ex));
+        }
+        return o;
     };
 
     auto signal_prev = [&]() {   // paper appendix C `signal` for the tile whose stores have completed
         if (SK && p_kind == UNIT_PART) {
             if (tid == 0) flag_publish(g.ws_flags + blockIdx.x, g.ws_epoch);
         } else if constexpr (IS_RS) {
-            if (tid == 0 && !p_dead) {
-                uint32_t* flags = (p_q == g.rank) ? g.flags_in + (int64_t)g.rank * g.flags_per_slot
-                                                  : g.flags_out + (int64_t)p_q * g.flags_per_slot;
-                flag_publish(flags + p_flag, g.epoch);
+            if (w == 0 && !p_dead && !g.late_signal) {
+                const int nf = min(g.fcols_per_tile, g.flag_cols - p_fcol);
+                for (int i = l; i < p_nblk * nf; i += 64) {   // one lane per flag of the tile
+                    const int bi = i / nf, blk = p_blk + bi;
+                    const int q = g.cols_per_shard > 0 ? p_q : g.by_blks.div(blk);
+                    const int fr = g.cols_per_shard > 0 ? blk : blk - q * g.blks_per_shard;
+                    uint32_t* flags = (q == g.rank ? g.flags_in : g.flags_out) + (int64_t)q * g.flags_per_slot;
+                    flag_publish(flags + (int64_t)fr * g.flag_cols + p_fcol + (i - bi * nf), g.epoch);
+                }
             }
         }
     };
@@ -298,12 +376,12 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
     }
     for (;;) {
         // ---- which tile (paper listing: interpret_task) ----
-        int q = 0, tmi = 0, tc = 0, row0 = 0, row_end = 0, col0 = 0, col_end = 0, flag = 0;
+        int q = 0, tc = 0, row0 = 0, row_end = 0, col0 = 0, col_end = 0, blk = 0, nblk = 0, fcol = 0;
         int kind = UNIT_FULL, kt0 = 0, nkt = KT, part_lo = 0, tile_end = 0;
         bool have = false;
         for (;;) {
             int slot, slot_index = 64;
-            bool may_defer = false;
+            bool may_defer = false, revisit = false;
             if (v < g.sk_dp_slots) {
                 slot = v;
                 slot_index = visit;
@@ -314,6 +392,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                 slot_index = __builtin_ctzll(deferred);
                 deferred &= deferred - 1;
                 slot = (int)blockIdx.x + slot_index * (int)gridDim.x;
+                revisit = true;
             } else if (SK && sk_c < sk_e) {
                 const int i = sk_c / KT;
                 tile_end = (i + 1) * KT;
@@ -327,16 +406,16 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
             } else {
                 break;
             }
-            const int gi = slot / g.wg_per_group;
+            const int gi = g.by_group.div(slot);
             const int u = slot - gi * g.wg_per_group;
             const int t = (u & 7) * (g.wg_per_group >> 3) + (u >> 3);
             if (t >= G) continue;
-            const int BAND = g.band > 0 ? g.band : 1;
-            const int band = t / (BAND * g.tiles_n);
-            const int rem = t - band * BAND * g.tiles_n;
-            const int rows_in_band = min(BAND, g.grp_tile_rows - band * BAND);
-            tc = rem / rows_in_band;
-            const int tr = band * BAND + (rem - tc * rows_in_band);
+            const int band = g.by_band.div(t);
+            const int rem = t - band * g.band * g.tiles_n;
+            const bool lastb = band == g.last_band;
+            const int rows_in_band = lastb ? (int)g.by_last_rows.d : g.band;
+            tc = (lastb ? g.by_last_rows : g.by_band_rows).div(rem);
+            const int tr = band * g.band + (rem - tc * rows_in_band);
             int grp = g.group0 + gi;
             if (grp >= g.n_groups) grp -= g.n_groups;
             int tile_row = grp * g.grp_tile_rows + tr;
@@ -344,41 +423,61 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                 tile_row += g.row_rot;
                 if (tile_row >= g.all_tile_rows) tile_row -= g.all_tile_rows;
             }
-            q = tile_row / g.tiles_m_shard;              // destination rank (RS) / source chunk (AG)
-            tmi = tile_row - q * g.tiles_m_shard;
-            row0 = q * g.rows_per_shard + tmi * BM;
-            row_end = (q + 1) * g.rows_per_shard;
             col0 = tc * BN;
             col_end = g.n;
-            flag = tmi * g.tiles_n + tc;
             if constexpr (IS_RS) {
-                if (g.cols_per_shard > 0) {              // destination rank from the tile column (q was 0: one row shard)
-                    q = tc / g.tiles_n_shard;
+                blk = tile_row * g.blks_per_tile;
+                nblk = min(g.blks_per_tile, g.n_blks - blk);
+                auto blk_start = [&](int b) {            // first row of a row block; the one past the last of a span starts the next
+                    const int sh = g.by_blks.div(b);
+                    return sh * g.rows_per_span + (b - sh * g.blks_per_shard) * g.blk_rows;
+                };
+                row0 = blk_start(blk);
+                row_end = blk_start(blk + nblk);
+                fcol = tc * g.fcols_per_tile;
+                if (g.cols_per_shard > 0) {              // destination rank from the tile column (one row shard)
+                    q = g.by_shard_cols.div(tc);
                     const int tci = tc - q * g.tiles_n_shard;
                     col0 = q * g.cols_per_shard + tci * BN;
                     col_end = (q + 1) * g.cols_per_shard;
-                    flag = tmi * g.tiles_n_shard + tci;
+                    fcol = tci * g.fcols_per_tile;
                 }
+            } else {
+                const int span = g.by_span.div(tile_row);
+                row0 = span * g.rows_per_span + (tile_row - span * g.tiles_m_shard) * BM;
+                row_end = (span + 1) * g.rows_per_span;
             }
             have = true;
 
-            // all-gather: the chunk this tile reads must have landed (paper appendix C `wait`)
+            // all-gather: the chunks this tile reads must have landed (paper appendix C `wait`)
             if constexpr (EPI == EPI_AG) {
-                if (!((seen_chunks >> (q & 63)) & 1)) {
-                    // lane 0 polls; the verdict (0 landed, 1 timed out, 2 not yet: put the slot aside) goes through a
-                    // word of the (idle) epilogue staging area, since the kernel leaves no LDS for a static variable
+                const int c_lo = g.by_chunk_rows.div(row0), c_hi = g.by_chunk_rows.div(min(row0 + BM, row_end) - 1);
+                const uint64_t need = ((2ull << (c_hi & 63)) - (1ull << (c_lo & 63))) & ~seen_chunks;
+                if (need) {
+                    // wave 0 polls, one lane per chunk; the verdict (0 landed, 1 timed out, 2 not yet: put the slot aside) goes
+                    // through a word of the (idle) epilogue staging area, since the kernel leaves no LDS for a static variable
                     PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
-                    if (tid == 0) {
+                    if (w == 0) {
+                        const bool mine = (need >> l) & 1;
+                        bool fence = g.acquire_all || revisit;
                         int vd = 0;
-                        if (!flag_ready(g.chunk_flags + q, g.epoch)) {
+                        if (__ballot(mine && !flag_ready(g.chunk_flags + l, g.epoch)) != 0) {
                             if (may_defer) {
                                 vd = 2;
-                            } else if (!flag_wait(g.chunk_flags + q, g.epoch, g.timeout_ticks)) {
-                                report_timeout(g.status, (uint32_t)q, 1u);
-                                vd = 1;
+                            } else {
+                                const bool late = mine && !flag_wait(g.chunk_flags + l, g.epoch, g.timeout_ticks);
+                                if (late) report_timeout(g.status, (uint32_t)l, 1u);
+                                if (__ballot(late) != 0) vd = 1;
+                                fence = true;
                             }
                         }
-                        *verdict = vd;
+                        // The acquire invalidates this XCD's whole L2, with every other workgroup's tiles in it (all 8 waves of
+                        // all workgroups doing so took 11 us of a 25 us call), so only this wave does it, and only where it had
+                        // to wait.  A chunk that is there at the first look needs none: the L2 was invalidated when the kernel
+                        // started, and nothing has read a line of the chunk into it since, because no workgroup reads a chunk
+                        // before its flag (and no line is shared between chunks unless acquire_all).
+                        if (fence && vd != 2) acquire_agent();
+                        if (l == 0) *verdict = vd;
                     }
                     __syncthreads();
                     const int vd_all = *verdict;
@@ -395,23 +494,41 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                         sk_c = sk_e;
                         break;
                     }
-                    acquire_agent();
-                    if (q < 64) seen_chunks |= 1ull << q;
+                    seen_chunks |= need;
                 }
             }
             break;
         }
+        int lt = l;                                  // the lane id, opaque: what is computed from it stays within this tile
+        asm volatile("" : "+v"(lt));
         uint32_t a_voff[NA], b_voff[NB];           // per-lane byte offsets from the k-tile base pointers
         const char* a_base = g.A;                    // wave-uniform, advanced by one k-tile per issue
         const char* b_base = g.B;
         const int64_t b_step = BT ? (int64_t)KB : (int64_t)B_ROWS * g.ldb;   // bytes from one k-tile of B to the next
         // k-tiles handled between two pipeline fills: all of them, or one column chunk of A at a time (EPI_AGK, own
         // chunk); once this workgroup has seen every chunk, its later tiles run the whole k range in one go
+        if (EPI == EPI_AGK && have && p_q < 0 && seen_chunks != all_chunks) {
+            // every chunk there already: no pipeline refill per chunk
+            PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
+            if (w == 0) {
+                const uint64_t missing = __ballot(l < g.k_chunks && !((seen_chunks >> l) & 1) && !flag_ready(g.chunk_flags + l, g.epoch));
+                if (!missing && g.acquire_all) acquire_agent();      // otherwise as above: nothing stale can be in the L2
+                if (l == 0) *verdict = missing != 0;
+            }
+            __syncthreads();
+            const int missing_all = *verdict;
+            __syncthreads();
+            if (!missing_all) seen_chunks = all_chunks;
+        }
         const bool by_chunk = (EPI == EPI_AGK) && seen_chunks != all_chunks;
         const int seg_ktiles = by_chunk ? g.ktiles / g.k_chunks : nkt;
-        if (by_chunk) {
-            a_base += (int64_t)g.rank * seg_ktiles * KB;
-            b_base += (int64_t)g.rank * seg_ktiles * b_step;
+        int until_wrap = 0;                          // EPI_AGK: k-tiles from the next one to issue to the end of the k range
+        if constexpr (EPI == EPI_AGK) {
+            // the k range is taken in ring order from the own chunk, whether or not the chunks are waited for one by one
+            const int first = g.rank * (g.ktiles / g.k_chunks);
+            a_base += (int64_t)first * KB;
+            b_base += (int64_t)first * b_step;
+            until_wrap = g.ktiles - first;
         } else {
             a_base += (int64_t)kt0 * KB;             // a piece of a stream-K tile starts at k-tile kt0
             b_base += (int64_t)kt0 * b_step;
@@ -420,7 +537,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
             // per-lane global source addresses of the direct-to-LDS loads.  Wave-wide load j of wave w fills
             // the 1 KB LDS block j*NW + w of the A (or B) tile.
             {
-                const int r_in = l / CPA, cp = l % CPA;
+                const int r_in = lt / CPA, cp = lt % CPA;
 #pragma unroll
                 for (int j = 0; j < NA; ++j) {
                     const int r = (64 / CPA) * (j * NW + w) + r_in;
@@ -430,7 +547,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
             }
             if constexpr (BT) {
                 // as the A tile: 1 KB block = 64 / CPA rows (columns of the product) of KB bytes
-                const int r_in = l / CPA, cp = l % CPA;
+                const int r_in = lt / CPA, cp = lt % CPA;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
                     const int r = (64 / CPA) * (j * NW + w) + r_in;
@@ -439,7 +556,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                 }
             } else if constexpr (!FP8) {
                 // 1 KB block bi of the B tile = 8 k-rows of one 64-column panel
-                const int kr_in = l >> 3, cp = l & 7;
+                const int kr_in = lt >> 3, cp = lt & 7;
                 const int n_bytes = g.n * 2;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
@@ -451,7 +568,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                     b_voff[j] = (uint32_t)((int64_t)kr * g.ldb + colbyte);
                 }
             } else {
-                const int kr_in = l / CPR, cp = l % CPR;
+                const int kr_in = lt / CPR, cp = lt % CPR;
                 const int n_bytes = g.n;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
@@ -472,6 +589,11 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
             if (i == NL - 1) {
                 a_base += KB;
                 b_base += b_step;
+                if (EPI == EPI_AGK && --until_wrap == 0) {
+                    a_base = g.A;
+                    b_base = g.B;
+                    until_wrap = g.ktiles;
+                }
             }
         };
         auto issue_loads = [&](int stage) {
@@ -547,87 +669,139 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
         }
         if (p_q >= 0 && !skip_epilogue) {
             // lane holds, for each 32x32 block, rows (l & 31) and columns 8*b + 4*h + {0..3}.  Per pass a slab of
-            // ROWS_PASS rows x (BN/WN) columns goes through the wave's private staging area, then out as whole
-            // row segments, 16 bytes per lane.
-            PK_LDS char* stg = lds + EPI_OFF + w * (kEpiStageBytes / NW);
-            constexpr int WCOLS = BN / WN;                   // columns of the wave's sub-tile
+            // ROWS_PASS rows of the wave's part of the tile goes through the wave's private staging area, then out as whole
+            // row segments, 16 bytes per lane.  The passes are a loop, not unrolled, around one read-back: a workgroup runs
+            // most of this code once per launch, out of a cold instruction cache (unrolled, with the activation inlined per
+            // element, it took 5-7 us per 256x128 tile instead of 2).
+            constexpr int WCOLS = OTN * 32;                  // columns of the wave's part of the tile
             constexpr int OUT_ELEM = (EPI == EPI_RS) ? 4 : 2;
-            constexpr int ROW_BYTES = WCOLS * OUT_ELEM;
-            constexpr int ROWS_PASS = (kEpiStageBytes / NW) / ROW_BYTES >= 32 ? 32 : (kEpiStageBytes / NW) / ROW_BYTES;
-            static_assert(ROWS_PASS == 32 || ROWS_PASS == 16 || ROWS_PASS == 8, "staging area too small");
-            constexpr int CH = ROW_BYTES / 16;               // 16-byte chunks per staged row
-            constexpr int LANES_ROW = CH;                    // lanes that cover one row on the way out
-            constexpr int ROWS_INSTR = 64 / LANES_ROW;       // rows written by one wave-wide store
-            const int col_w0 = p_col0 + wn * WCOLS;
-            char* dst_base;
-            int64_t dst_pitch;
-            int dst_row0;                                    // global row -> row inside the destination
-            int dst_col0 = 0;                                // global column -> column inside the destination
+            PK_LDS char* stg = lds + EPI_OFF + w * (EPI_BYTES / NW);
+            const int row_w0 = p_row0 + wm * (BM / WM) + (wk * OB / TN) * 32;
+            const int col_w0 = p_col0 + wn * (BN / WN) + (wk * OB % TN) * 32;
+            // destination of row r, column c: dst + r * dst_pitch + c * OUT_ELEM.  Scatter along rows: shard q's slot lies
+            // behind those of the shards before it, so row r of the product is row r of `outgoing` (of `partials` if it is own)
+            uint64_t dst;
+            int64_t own_delta = 0;
+            int64_t dst_pitch = (int64_t)g.n * OUT_ELEM;
+            int own_row0 = 0, own_rows = 0;
             if constexpr (IS_RS) {
-                dst_base = (p_q == g.rank) ? (char*)g.partials + (int64_t)g.rank * g.slot_elems * OUT_ELEM
-                                           : (char*)g.outgoing + (int64_t)p_q * g.slot_elems * OUT_ELEM;
                 if (g.cols_per_shard > 0) {
                     dst_pitch = (int64_t)g.cols_per_shard * OUT_ELEM;
-                    dst_row0 = 0;
-                    dst_col0 = p_q * g.cols_per_shard;
+                    dst = (uint64_t)(p_q == g.rank ? g.partials : g.outgoing) + (int64_t)p_q * (g.slot_elems - g.cols_per_shard) * OUT_ELEM;
                 } else {
-                    dst_pitch = (int64_t)g.n * OUT_ELEM;
-                    dst_row0 = p_q * g.rows_per_shard;
+                    dst = (uint64_t)g.outgoing;
+                    own_delta = (int64_t)((uint64_t)g.partials - (uint64_t)g.outgoing);
+                    own_row0 = g.rank * g.rows_per_shard;
+                    own_rows = g.rows_per_shard;
                 }
             } else {
-                dst_base = (char*)g.C;
-                dst_pitch = (int64_t)g.n * 2;
-                dst_row0 = 0;
+                dst = (uint64_t)g.C;
             }
-#pragma unroll
-            for (int ti = 0; ti < TM; ++ti) {
-#pragma unroll
-                for (int half = 0; half < 32 / ROWS_PASS; ++half) {
+            auto emit = [&](auto act_c) {
+                constexpr bool ACT = decltype(act_c)::value;     // staged as fp32, activated on the way out
+                constexpr int ST_ELEM = (EPI == EPI_RS || ACT) ? 4 : 2;
+                constexpr int ROW_BYTES = WCOLS * ST_ELEM;
+                constexpr int ROWS_PASS = (EPI_BYTES / NW) / ROW_BYTES >= 32 ? 32 : (EPI_BYTES / NW) / ROW_BYTES;
+                static_assert(ROWS_PASS == 32 || ROWS_PASS == 16 || ROWS_PASS == 8 || ROWS_PASS == 4, "staging area too small");
+                constexpr int CH = ROW_BYTES / 16;               // 16-byte chunks per staged row
+                constexpr int LANES_ROW = WCOLS * OUT_ELEM / 16; // lanes that cover one row on the way out
+                constexpr int ROWS_INSTR = 64 / LANES_ROW;       // rows written by one wave-wide store
+                static_assert(ROWS_PASS >= ROWS_INSTR, "a wave-wide store takes at most one pass");
+                const int cl = lt % LANES_ROW, rl0 = lt / LANES_ROW, h = lt >> 5;
+                const int col = col_w0 + cl * (16 / OUT_ELEM);
+                int row = row_w0 + rl0;
+                uint64_t dp = dst + (int64_t)row * dst_pitch + (int64_t)col * OUT_ELEM;
+                const int64_t dp_step = ROWS_INSTR * dst_pitch;
+                constexpr int NPASS = OTM * (32 / ROWS_PASS);
+                auto pass = [&](int ps) {
                     // write: lanes whose row falls in this pass store their quads; chunk position swizzled by row
-                    const int rl = l & 31;
-                    if (ROWS_PASS == 32 || (rl / ROWS_PASS) == half) {
-                        const int rs = rl % ROWS_PASS;
+                    int rl = lt & 31;
+                    // opaque, so that neither the addresses below nor the scaled results are computed for all passes at once
+                    asm volatile("" : "+v"(rl));
+                    float sc = scale;
+                    if constexpr (FP8) asm volatile("" : "+v"(sc));
+                    const int rs = rl % ROWS_PASS;
+                    const int pti = ps / (32 / ROWS_PASS);
+                    if (ROWS_PASS == 32 || (rl / ROWS_PASS) == ps % (32 / ROWS_PASS)) {
+                        auto put = [&](auto ti_c) {
+                            constexpr int ti = decltype(ti_c)::value;
 #pragma unroll
-                        for (int tj = 0; tj < TN; ++tj)
+                            for (int tj = 0; tj < OTN; ++tj)
 #pragma unroll
-                            for (int b = 0; b < 4; ++b) {
-                                const int colw = tj * 32 + 8 * b + 4 * h;     // column inside the wave sub-tile
-                                if constexpr (EPI == EPI_RS) {
-                                    const int ch = colw >> 2;                  // 16-byte chunk (4 floats)
-                                    f32x4 val = {acc[ti][tj][4 * b] * scale, acc[ti][tj][4 * b + 1] * scale,
-                                                 acc[ti][tj][4 * b + 2] * scale, acc[ti][tj][4 * b + 3] * scale};
-                                    *(PK_LDS f32x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16)) = val;
-                                } else {
-                                    const int ch = colw >> 3;                  // 16-byte chunk (8 bf16)
-                                    float x0 = acc[ti][tj][4 * b] * scale, x1 = acc[ti][tj][4 * b + 1] * scale,
-                                          x2 = acc[ti][tj][4 * b + 2] * scale, x3 = acc[ti][tj][4 * b + 3] * scale;
-                                    if constexpr (!IS_RS) if (g.act != PK_ACT_NONE) {
-                                        x0 = activate(x0);
-                                        x1 = activate(x1);
-                                        x2 = activate(x2);
-                                        x3 = activate(x3);
+                                for (int b = 0; b < 4; ++b) {
+                                    const int colw = tj * 32 + 8 * b + 4 * h;     // column inside the wave's part
+                                    f32x4 val = {acc[ti][tj][4 * b] * sc, acc[ti][tj][4 * b + 1] * sc,
+                                                 acc[ti][tj][4 * b + 2] * sc, acc[ti][tj][4 * b + 3] * sc};
+                                    if constexpr (ST_ELEM == 4) {
+                                        const int ch = colw >> 2;                  // 16-byte chunk (4 floats)
+                                        *(PK_LDS f32x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16)) = val;
+                                    } else {
+                                        const int ch = colw >> 3;                  // 16-byte chunk (8 bf16)
+                                        bf16x4 v16 = {(__bf16)val[0], (__bf16)val[1], (__bf16)val[2], (__bf16)val[3]};
+                                        *(PK_LDS bf16x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16) + (h * 8)) = v16;
                                     }
-                                    bf16x4 val = {(__bf16)x0, (__bf16)x1, (__bf16)x2, (__bf16)x3};
-                                    *(PK_LDS bf16x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16) + (h * 8)) = val;
                                 }
-                            }
+                            // a different last statement in each case: the compiler would otherwise merge the cases into one
+                            // that indexes the accumulators at run time, and move them to scratch memory
+                            asm volatile("; slab %0" : : "n"(ti));
+                        };
+                        static_assert(OTM <= 4, "up to four slabs of 32 rows");
+                        if (pti == 0) put(std::integral_constant<int, 0>{});
+                        if constexpr (OTM > 1) if (pti == 1) put(std::integral_constant<int, 1>{});
+                        if constexpr (OTM > 2) if (pti == 2) put(std::integral_constant<int, 2>{});
+                        if constexpr (OTM > 3) if (pti == 3) put(std::integral_constant<int, 3>{});
                     }
-                    // read back row-wise and store: lane -> (row = i*ROWS_INSTR + l / LANES_ROW, chunk = l % LANES_ROW)
-#pragma unroll
-                    for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) {
-                        const int rs = i * ROWS_INSTR + l / LANES_ROW;
-                        const int ch = l % LANES_ROW;
-                        i32x4 val = *(PK_LDS i32x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16));
-                        const int row = p_row0 + wm * (BM / WM) + ti * 32 + half * ROWS_PASS + rs;
-                        const int col = col_w0 + ch * (16 / OUT_ELEM);
-                        if (row < p_row_end && col < p_col_end) {
-                            char* dp = dst_base + (int64_t)(row - dst_row0) * dst_pitch + (int64_t)(col - dst_col0) * OUT_ELEM;
-                            // reduce-scatter tiles are consumed by another kernel through a flag: write through
-                            if constexpr (IS_RS) store16_writethrough(dp, val);
-                            else __builtin_nontemporal_store(val, (i32x4*)dp);
+                    // read back row-wise and store: lane -> (row = i*ROWS_INSTR + l / LANES_ROW, chunk = l % LANES_ROW).  All the
+                    // reads of a pass come first: a read behind the bounds check of its store would be waited for by itself.
+                    auto get = [&](int i) -> i32x4 {
+                        const int rr = i * ROWS_INSTR + rl0;
+                        if constexpr (ACT) {
+                            const f32x4 x0 = *(PK_LDS f32x4*)(stg + rr * ROW_BYTES + (((2 * cl) ^ (rr & (CH - 1))) * 16));
+                            const f32x4 x1 = *(PK_LDS f32x4*)(stg + rr * ROW_BYTES + (((2 * cl + 1) ^ (rr & (CH - 1))) * 16));
+                            return __builtin_bit_cast(i32x4, activate8(x0, x1));
+                        } else {
+                            return *(PK_LDS i32x4*)(stg + rr * ROW_BYTES + ((cl ^ (rr & (CH - 1))) * 16));
                         }
+                    };
+                    auto out = [&](i32x4 val) {
+                        if (row < p_row_end && col < p_col_end) {
+                            uint64_t d = dp;
+                            if (IS_RS && (uint32_t)(row - own_row0) < (uint32_t)own_rows) d += own_delta;
+                            // reduce-scatter tiles are consumed by another kernel through a flag: write through
+                            if constexpr (IS_RS) store16_writethrough((void*)d, val);
+                            else __builtin_nontemporal_store(val, (i32x4*)d);
+                        }
+                        row += ROWS_INSTR;
+                        dp += dp_step;
+                    };
+                    if constexpr (ACT) {
+#pragma clang loop unroll(disable)
+                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) out(get(i));
+                    } else {
+                        i32x4 v[ROWS_PASS / ROWS_INSTR];
+#pragma unroll
+                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) v[i] = get(i);
+#pragma unroll
+                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) asm volatile("" : "+v"(v[i]));
+#pragma unroll
+                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) out(v[i]);
                     }
+                };
+                if constexpr (ACT || (ST_ELEM == 4 && BM * BN < 256 * 256)) {
+#pragma clang loop unroll(disable)
+                    for (int ps = 0; ps < NPASS; ++ps) pass(ps);
+                } else {
+                    // unrolled: in a loop the compiler would round all accumulators ahead of it (bf16); a 256x256 tile's
+                    // workgroup runs it once per round, and the passes overlap
+#pragma unroll
+                    for (int ps = 0; ps < NPASS; ++ps) pass(ps);
                 }
+            };
+            if constexpr (IS_RS) {
+                emit(std::false_type{});
+            } else {
+                if (g.act != PK_ACT_NONE) emit(std::true_type{});
+                else emit(std::false_type{});
             }
         }
         if (!have) break;
@@ -639,28 +813,36 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-        // the first k-tiles have landed; the previous tile's stores (same counter) are complete as well
-        __builtin_amdgcn_s_waitcnt(PK_WAIT_VMCNT0);
-        __syncthreads();
-        if (p_q >= 0) signal_prev();
+        if (p_q < 0 && seg_ktiles >= NS) {
+            // the workgroup's first tile: its first k-tile has landed, the others follow
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 1) * NL));
+            __syncthreads();
+        } else {
+            // the first k-tiles have landed; the previous tile's stores (same counter) are complete as well
+            __builtin_amdgcn_s_waitcnt(PK_WAIT_VMCNT0);
+            __syncthreads();
+            if (p_q >= 0) signal_prev();
+        }
 
         // ---- main loop ----
+        set_frag_addresses(lt);
         frag_t af0[TM], bf0[TN], af1[TM], bf1[TN];
         // One k-tile: KS-1 pipelined k-steps, the barrier, then the last k-step, under which the loads of
-        // k-tile kt+NS (LOADS) and the first fragments of k-tile kt+1 (NEXT) are issued.  At the barrier every
-        // wave has finished reading k-tile kt's stage, so it can be refilled, and k-tile kt+1 has landed: in the
-        // steady state only the loads of the NS-2 k-tiles after it may still be in flight.
+        // k-tile kt+NS (LOADS) and the first fragments of k-tile kt+1 are issued (behind the last k-tile: stale bytes that
+        // nothing uses).  At the barrier every wave has finished reading k-tile kt's stage, so it can be refilled, and
+        // k-tile kt+1 has landed: in the steady state only the loads of the NS-2 k-tiles after it may still be in flight.
         // One k-step: the NM MFMAs on fragment set (ca, cb), with, pinned between them in this order, the reads
         // of the next step's fragments into (na, nb) behind the first half of the MFMAs (they then have the
         // second half of the step to arrive) and the direct-to-LDS loads of a later k-tile behind the second half.
         auto kstep = [&](const frag_t (&ca)[TM], const frag_t (&cb)[TN], frag_t (&na)[TM], frag_t (&nb)[TN],
-                         PK_LDS char* rd_stage, int rd_kk, auto reads_c, int ld_stage, auto loads_c) {
-            constexpr bool READS = decltype(reads_c)::value, LOADS = decltype(loads_c)::value;
+                         PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto loads_c) {
+            constexpr bool LOADS = decltype(loads_c)::value;
             constexpr int NM = TM * TN, H = NM / 2;
+            static_assert(NM >= 2, "a k-step has at least two MFMAs");
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 mfma_one(i / TN, i % TN, ca, cb);
-                if constexpr (READS && FP8) {
+                if constexpr (FP8) {
                     // 8-bit fragments are 8 registers each: two full sets next to the accumulators do not fit.  The MFMAs run
                     // row by row (ti-major), so the A fragment of row ti is dead after MFMA ti*TN + TN-1, and the next step's
                     // A fragment of that row is read right behind it, into the same registers; only the B fragments are double.
@@ -669,7 +851,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                         for (int u = 0; u < TN; ++u) read_unit(rd_stage, rd_kk, u, na, nb);
                     }
                     if (i % TN == TN - 1) read_unit(rd_stage, rd_kk, TN + i / TN, na, nb);
-                } else if constexpr (READS) {
+                } else {
                     if (i < H) {
 #pragma unroll
                         for (int u = (NU * i) / H; u < (NU * (i + 1)) / H; ++u) read_unit(rd_stage, rd_kk, u, na, nb);
@@ -685,25 +867,35 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto ktile = [&](int kt, auto loads_c, auto next_c, auto par_c) {
+        auto ktile = [&](int kt, int nkt, auto loads_c, auto par_c) {
             constexpr bool LOADS = decltype(loads_c)::value;
             constexpr int P0 = decltype(par_c)::value;   // fragment set that holds this k-tile's first fragments
             const int sidx = kt % NS;
             PK_LDS char* st = lds + sidx * STAGE;
             PK_LDS char* nx = lds + (sidx + 1 == NS ? 0 : sidx + 1) * STAGE;
             // fragment set `par` is consumed, the other one refilled
-            auto step = [&](auto par, PK_LDS char* rd_stage, int rd_kk, auto reads_c, int ld_stage, auto lds_c) {
-                if constexpr (decltype(par)::value) kstep(af1, bf1, af0, bf0, rd_stage, rd_kk, reads_c, ld_stage, lds_c);
-                else kstep(af0, bf0, af1, bf1, rd_stage, rd_kk, reads_c, ld_stage, lds_c);
+            auto step = [&](auto par, PK_LDS char* rd_stage, int rd_kk, auto lds_c) {
+                if constexpr (decltype(par)::value) kstep(af1, bf1, af0, bf0, rd_stage, rd_kk, sidx, lds_c);
+                else kstep(af0, bf0, af1, bf1, rd_stage, rd_kk, sidx, lds_c);
             };
-            if constexpr (KS >= 2) step(std::integral_constant<int, P0>{}, st, 1, std::true_type{}, 0, std::false_type{});
-            if constexpr (KS >= 3) step(std::integral_constant<int, P0 ^ 1>{}, st, 2, std::true_type{}, 0, std::false_type{});
-            if constexpr (KS >= 4) step(std::integral_constant<int, P0>{}, st, 3, std::true_type{}, 0, std::false_type{});
+            if constexpr (KS >= 2) step(std::integral_constant<int, P0>{}, st, 1, std::false_type{});
+            if constexpr (KS >= 3) step(std::integral_constant<int, P0 ^ 1>{}, st, 2, std::false_type{});
+            if constexpr (KS >= 4) step(std::integral_constant<int, P0>{}, st, 3, std::false_type{});
             static_assert(KS <= 4, "at most four k-steps per k-tile");
-            if constexpr (LOADS) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * NL));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+            static_assert(NS >= 2 && NS <= 6, "ring of 2 to 6 stages");
+            if constexpr (LOADS) {
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * NL));
+            } else {
+                // at the end of the range: of the k-tiles left, only those behind the next one may still be in flight
+                const int left = nkt - kt;
+                if (left >= NS) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * NL));
+                else if (NS > 5 && left == 5) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(3 * NL));
+                else if (NS > 4 && left == 4) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * NL));
+                else if (NS > 3 && left == 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(NL));
+                else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+            }
             __syncthreads();
-            step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, next_c, sidx, loads_c);
+            step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, loads_c);
         };
         // the k-tiles of one pipeline fill: the first NS are in flight or landed, stage 0 holds the first
         auto run_ktiles = [&](int nkt) {
@@ -714,31 +906,39 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
             load_frags(lds, 0, af0, bf0);
             int kt = 0;
             if constexpr (KS % 2 == 0) {
-                for (; kt + NS < nkt; ++kt) ktile(kt, T{}, T{}, E{});
-                for (; kt + 1 < nkt; ++kt) ktile(kt, F{}, T{}, E{});
-                ktile(kt, F{}, F{}, E{});
+#pragma clang loop unroll(disable)
+                for (; kt + NS < nkt; ++kt) ktile(kt, nkt, T{}, E{});
+#pragma clang loop unroll(disable)
+                for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{});
             } else {
-                // odd k-steps per k-tile: the starting set alternates, so k-tiles go in pairs (nkt and NS are even: the
-                // host admits only k ranges of whole 128-byte units)
-                static_assert(KS % 2 == 0 || NS % 2 == 0, "pairs of k-tiles need an even ring");
-                for (; kt + NS < nkt; kt += 2) {
-                    ktile(kt, T{}, T{}, E{});
-                    ktile(kt + 1, T{}, T{}, O{});
+                // odd k-steps per k-tile: the starting set alternates, so k-tiles go in pairs (with 64-byte k-tiles nkt is even:
+                // the host admits only k ranges of whole 128-byte units)
+                constexpr bool EVEN = KB == 64;
+                static_assert(!EVEN || NS % 2 == 0, "pairs of k-tiles need an even ring");
+#pragma clang loop unroll(disable)
+                for (; kt + (EVEN ? 0 : 1) + NS < nkt; kt += 2) {
+                    ktile(kt, nkt, T{}, E{});
+                    ktile(kt + 1, nkt, T{}, O{});
                 }
-                for (; kt + 2 < nkt; kt += 2) {
-                    ktile(kt, F{}, T{}, E{});
-                    ktile(kt + 1, F{}, T{}, O{});
+                if (!EVEN && kt + NS < nkt) {            // one more with loads: the rest starts on set 1
+                    ktile(kt, nkt, T{}, E{});
+                    ktile(kt + 1, nkt, F{}, O{});
+                    kt += 2;
                 }
-                ktile(kt, F{}, T{}, E{});
-                ktile(kt + 1, F{}, F{}, O{});
+#pragma clang loop unroll(disable)
+                for (; kt < nkt; kt += 2) {
+                    ktile(kt, nkt, F{}, E{});
+                    if (EVEN || kt + 1 < nkt) ktile(kt + 1, nkt, F{}, O{});
+                }
             }
         };
         const uint64_t t_loop0 = clock64();
-        run_ktiles(seg_ktiles);
-        if (by_chunk) {
-            // the other column chunks of A, in ring order from the own one; the first tile that touches a chunk waits for
-            // its flag (paper appendix C `wait`), later tiles of this workgroup know it has landed
-            for (int sgm = 1; sgm < g.k_chunks; ++sgm) {
+        const int n_seg = by_chunk ? g.k_chunks : 1;
+#pragma clang loop unroll(disable)
+        for (int sgm = 0; sgm < n_seg; ++sgm) {
+            if (EPI == EPI_AGK && sgm > 0) {
+                // another column chunk of A, in ring order from the own one; the first tile that touches a chunk waits for
+                // its flag (paper appendix C `wait`), later tiles of this workgroup know it has landed
                 int c = g.rank + sgm;
                 if (c >= g.k_chunks) c -= g.k_chunks;
                 if (!((seen_chunks >> c) & 1)) {
@@ -747,23 +947,70 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
                         const int late = flag_wait(g.chunk_flags + c, g.epoch, g.timeout_ticks) ? 0 : 1;
                         if (late) report_timeout(g.status, (uint32_t)c, 1u);
                         *verdict = late;
+                        acquire_agent();
                     }
                     __syncthreads();
                     const int late_all = *verdict;
                     __syncthreads();
                     if (late_all) return;                 // drain: this tile and the rest of this workgroup's stay untouched
-                    acquire_agent();
                     seen_chunks |= 1ull << c;
                 }
-                a_base = g.A + (int64_t)c * seg_ktiles * KB;
-                b_base = g.B + (int64_t)c * seg_ktiles * b_step;
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
                     if (s < seg_ktiles) issue_loads(s);
                 __builtin_amdgcn_s_waitcnt(PK_WAIT_VMCNT0);
                 __syncthreads();
-                run_ktiles(seg_ktiles);
             }
+            run_ktiles(seg_ktiles);
+        }
+        if constexpr (WK > 1) {
+            // The groups' accumulators are added in group order through the LDS (the ring is free: every wave passed the barrier
+            // of the last k-tile after its last fragment reads).  Group r ends up with blocks [r*OB, (r+1)*OB) of the sub-tile,
+            // in acc[0..OTM)[0..OTN).
+            const int sub = w % (WM * WN);
+            auto piece = [&](int from, int to, int i) {      // LDS address of block i of those that group `from` hands to group `to`
+                return lds + ((((sub * WK + to) * (WK - 1) + (from < to ? from : from - 1)) * OB + i) * 4096) + l * 16;
+            };
+#pragma unroll
+            for (int gr = 0; gr < WK; ++gr)
+                if (wk == gr) {
+#pragma unroll
+                    for (int bl = 0; bl < TM * TN; ++bl)
+                        if (bl / OB != gr) {
+                            PK_LDS char* dp = piece(gr, bl / OB, bl % OB);
+#pragma unroll
+                            for (int b = 0; b < 4; ++b) {
+                                const f32x16& x = acc[bl / TN][bl % TN];
+                                *(PK_LDS f32x4*)(dp + b * 1024) = f32x4{x[4 * b], x[4 * b + 1], x[4 * b + 2], x[4 * b + 3]};
+                            }
+                        }
+                }
+            __syncthreads();
+#pragma unroll
+            for (int gr = 0; gr < WK; ++gr)
+                if (wk == gr) {
+#pragma unroll
+                    for (int i = 0; i < OB; ++i) {
+                        f32x16 sum;
+#pragma unroll
+                        for (int from = 0; from < WK; ++from) {
+                            f32x16 x;
+                            if (from == gr) {
+                                x = acc[(gr * OB + i) / TN][(gr * OB + i) % TN];
+                            } else {
+#pragma unroll
+                                for (int b = 0; b < 4; ++b) {
+                                    const f32x4 v = *(PK_LDS f32x4*)(piece(from, gr, i) + b * 1024);
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) x[4 * b + e] = v[e];
+                                }
+                            }
+                            sum = from == 0 ? x : sum + x;
+                        }
+                        acc[i / OTN][i % OTN] = sum;
+                    }
+                }
+            __syncthreads();                                 // the next tile's loads may fill the ring
         }
 
         t_loops += clock64() - t_loop0;
@@ -773,7 +1020,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_kernel(const GemmArgs g)
         p_part_lo = part_lo;
         p_tile_end = tile_end;
         p_q = q;
-        p_flag = flag;
+        p_blk = blk;
+        p_nblk = nblk;
+        p_fcol = fcol;
         p_row0 = row0;
         p_row_end = row_end;
         p_col0 = col0;

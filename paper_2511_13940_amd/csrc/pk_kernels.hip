@@ -5,7 +5,7 @@
 #include <mutex>
 
 #include "pk_device.h"
-#include "pk_gemm.h"
+#include "pk_tiles.h"
 
 namespace pk {
 
@@ -19,7 +19,9 @@ namespace pk {
 struct ReduceArgs {
     const void* partials;     // [P][rows][n] fp32, or bf16 when the kernel is instantiated with S16
     uint16_t* out;            // rows x n bf16
-    const uint32_t* flags_in; // [P][flags_per_slot]
+    uint32_t* flags_in;       // [P][flags_per_slot]
+    uint32_t* flags_out;      // late_signal only
+    int32_t late_signal;      // the GEMM in front of this kernel left its flags unpublished (its tiles are finer than a flag)
     int32_t P, rows, n;
     int32_t tile_m, tile_n, tiles_n, sub, rows_sub;
     int64_t slot_elems, flags_per_slot;
@@ -42,7 +44,7 @@ constexpr int kCoherentStream = 1 | 2 | 16;
 
 // PT > 0: compile-time P; PT == 0: runtime P.  S16: the slots hold bf16.  AR: all-reduce mode (the reduced rows are also
 // pushed to the other ranks and announced).  NARROW: 4 output elements per thread and pass instead of 8 (one 16-byte load
-// per slot in flight: under 48 registers), for launches that must fit beside a GEMM workgroup that leaves few registers.
+// per slot in flight: under 48 registers), for launches that run beside a GEMM that leaves few registers or little bandwidth.
 template <int PT, bool S16, bool AR, bool NARROW = false>
 __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     const int tid = threadIdx.x;
@@ -51,10 +53,15 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     const int sb = blockIdx.x - tile * r.sub;
     const int tmi = tile / r.tiles_n, tc = tile - tmi * r.tiles_n;
 
+    // `signal` for the tiles of the GEMM in front: it has ended, so everything it wrote (through) is in memory
+    const int own = r.late_signal ? r.rank : -1;
+    if (r.late_signal && sb == 0 && tid < P)
+        flag_publish((tid == r.rank ? r.flags_in : r.flags_out) + (int64_t)tid * r.flags_per_slot + tile, r.epoch);
+
     // wait (paper appendix C): one lane per source rank polls that rank's flag for this tile
     int late = 0;
     if constexpr (AR) {
-        if (tid < P) {
+        if (tid < P && tid != own) {
             if (!flag_wait(r.flags_in + (int64_t)tid * r.flags_per_slot + tile, r.epoch, r.timeout_ticks)) {
                 report_timeout(r.status, (uint32_t)tile, 2u);
                 late = 1;
@@ -65,7 +72,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
         // every wave polls for itself and decides with a ballot: this instantiation uses no LDS, not even the word a
         // workgroup-wide vote takes, so that its workgroups fit on a compute unit whose LDS a GEMM workgroup holds whole
         for (int p = tid & 63; p < P; p += 64) {
-            if (!flag_wait(r.flags_in + (int64_t)p * r.flags_per_slot + tile, r.epoch, r.timeout_ticks)) {
+            if (p != own && !flag_wait(r.flags_in + (int64_t)p * r.flags_per_slot + tile, r.epoch, r.timeout_ticks)) {
                 if (tid < 64) report_timeout(r.status, (uint32_t)tile, 2u);
                 late = 1;
             }
@@ -182,6 +189,14 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     }
 }
 
+// `signal` for a GEMM launched without its reduce phase whose tiles are finer than a flag: one thread per flag.
+__global__ __launch_bounds__(256) void signal_kernel(uint32_t* flags_in, uint32_t* flags_out, int P, int rank, int64_t flags_per_slot,
+                                                     uint32_t epoch) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= P * flags_per_slot) return;
+    flag_publish((i / flags_per_slot == rank ? flags_in : flags_out) + i, epoch);
+}
+
 // Completion of the all-reduce on this rank: one thread per flag of ar_flags_in waits (bounded) for the epoch.
 __global__ __launch_bounds__(256) void ar_wait_kernel(const uint32_t* flags, int64_t n_flags, uint32_t epoch,
                                                       uint32_t* status, uint64_t timeout_ticks) {
@@ -278,14 +293,25 @@ static TileCfg pick_tile(int P, int64_t rows_per_shard, int64_t n) {
     return {128, 128};
 }
 
-// Shape of an XCD's run of tiles inside a scheduling group.  The run (`run` consecutive tiles in the group's
-// linear order) should be a compact block so that the tiles an XCD works on at the same time share A and B
-// panels in its L2: up to 32 tiles are resident per XCD, ideally 4 rows x 8 columns.  When a run is no longer
-// than a tile row (all-gather: one chunk's tiles are split 8 ways), plain row-major keeps each XCD on one A
-// panel and on the same B column strip in every chunk.
-static int pick_band(int grp_tile_rows, int tiles_n, int run) {
-    if (run <= tiles_n) return 1;
-    return grp_tile_rows < 4 ? grp_tile_rows : 4;
+// Tile rows that are swept column by column inside a scheduling group, so that the tiles an XCD works on at the same time
+// (`run` consecutive ones in the group's linear order, at most one per compute unit of the XCD) share A and B panels in its L2.
+// One group for the whole problem: the block of tiles with the smallest half perimeter (1000 x 8192 x 2752, 256x128 tiles: 43.3
+// us with 4 x 8 tiles per XCD, 49.9 us with 1 x 32).  One group per chunk of an all-gather (a chunk's tiles are split 8 ways):
+// while a run is no longer than a tile row, plain row-major keeps each XCD on one A panel and on the same B columns in every
+// chunk.
+static int pick_band(int grp_tile_rows, int tiles_n, int run, int n_groups, int bm, int bn) {
+    if (n_groups > 1) return run <= tiles_n ? 1 : (grp_tile_rows < 4 ? grp_tile_rows : 4);
+    const int block = run < 32 ? run : 32;
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int b = 1; b <= grp_tile_rows && b <= block; ++b) {
+        const int64_t cost = (int64_t)b * bm + ceil_div(block, b) * bn;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = b;
+        }
+    }
+    return best;
 }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -371,86 +397,43 @@ static pk_status make_plan_cols(int P, int64_t M, int64_t N, int64_t K, pk_dtype
     return PK_OK;
 }
 
-// Persistent launch: one workgroup per CU (a multiple of 8 so that workgroup id mod 8 stays the XCD), or fewer
-// when there are fewer tile slots.
-// one launch of one instantiation; the dynamic LDS size of an instantiation is raised once per device
-template <int BM, int BN, int WM, int WN, int KB, int NS, bool FP8, int EPI, bool BT, bool SK>
-static pk_status launch_kernel(const GemmArgs& a, int grid, hipStream_t stream) {
-    static std::atomic<uint64_t> configured{0};              // bit d = done on device d
-    auto kern = gemm_kernel<BM, BN, WM, WN, KB, NS, FP8, EPI, BT, SK>;
-    constexpr int lds = gemm_lds_bytes<BM, BN, KB, NS>();
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return PK_ERR_HIP;
-    const uint64_t bit = 1ull << (dev & 63);
-    if (!(configured.load(std::memory_order_acquire) & bit)) {
-        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-            return PK_ERR_HIP;
-        configured.fetch_or(bit, std::memory_order_release);
-    }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), lds, stream, a);
-    return hipGetLastError() == hipSuccess ? PK_OK : PK_ERR_HIP;
-}
-
 // workgroups of a launch that shares out no tile: one per compute unit left to the GEMM (a multiple of 8, so that
 // workgroup id mod 8 stays the XCD), or the fewest that finish in the same number of rounds (448 slots on 256 CUs: 2
 // rounds of 224)
+static int max_grid(int comm_cus) {      // compute units left to a GEMM, a multiple of 8 (see schedule_grid)
+    const int grid = (num_cus() - comm_cus) / 8 * 8;
+    return grid < 8 ? 8 : grid;
+}
 static int schedule_grid(int slots, int comm_cus) {
-    int grid = (num_cus() - comm_cus) / 8 * 8;
-    if (grid < 8) grid = 8;
+    const int grid = max_grid(comm_cus);
     const int rounds = (slots + grid - 1) / grid;
     const int even = ((slots + rounds - 1) / rounds + 7) / 8 * 8;
     return even < grid ? even : grid;
 }
 
-template <int BM, int BN, int WM, int WN, int KB, int NS, bool FP8, int EPI, bool BT = false>
-static pk_status launch_gemm(GemmArgs a, int slots, int comm_cus, void* ws, size_t ws_bytes, hipStream_t stream) {
-    a.ktiles = a.ktiles * 128 / KB;          // callers count k-tiles of 128 bytes
-    constexpr bool HAS_SK = !BT && (EPI == EPI_RS || EPI == EPI_AG);   // the stream-K tail is built for these
-    int grid = (num_cus() - comm_cus) / 8 * 8;
-    if (grid < 8) grid = 8;
-    a.sk_dp_slots = slots;
+// Launches a GEMM whose tile space is set up in `a`: with a workspace and a last round that is not full, with the stream-K tail
+// (`ws`: only for tile shapes that have one), otherwise whole tiles.
+template <int EPI>
+static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt, void* ws, size_t ws_bytes, hipStream_t stream) {
+    const int bm = kTileDim[tile].bm, bn = kTileDim[tile].bn;
+    const int64_t G = (int64_t)a.grp_tile_rows * a.tiles_n;
+    a.wg_per_group = (int32_t)(8 * ceil_div(G, 8));
+    a.band = pick_band(a.grp_tile_rows, a.tiles_n, a.wg_per_group / 8, a.n_groups, bm, bn);
+    const int slots = a.wg_per_group * a.n_groups;
+    const int grid = max_grid(comm_cus);
     const int rem = slots % grid;
-    if (ws && HAS_SK && slots > grid && rem != 0 && a.ktiles >= 8 * NS && grid <= (int)(kWsFlagBytes / 4)) {
+    a.sk_dp_slots = slots;
+    if (ws && slots > grid && rem != 0 && a.ktiles >= 16 && grid <= (int)(kWsFlagBytes / 4)) {
         // With a workspace every compute unit works to the end: whole rounds of tiles, then the k range of the left-over
         // tiles shared out evenly (448 slots on 256 CUs: 256 whole tiles, then 192 tiles as 256 pieces of 3/4 tile).
-        if (ws_bytes < kWsFlagBytes + (size_t)grid * BM * BN * 4) return PK_ERR_ARG;
+        if (ws_bytes < kWsFlagBytes + (size_t)grid * bm * bn * 4) return PK_ERR_ARG;
         a.sk_dp_slots = slots - rem;
         a.ws_flags = (uint32_t*)ws;
         a.ws_tiles = (char*)ws + kWsFlagBytes;
         if (a.ws_epoch == 0) a.ws_epoch = a.epoch;     // a caller's workspace follows the caller's epochs
-    } else {
-        grid = schedule_grid(slots, comm_cus);
+        return launch_gemm<EPI>(a, tile == T256x256 ? T256x256 : T128x128_SK, fp8, bt, true, grid, stream);
     }
-    if constexpr (HAS_SK) {
-        if (a.sk_dp_slots != slots) return launch_kernel<BM, BN, WM, WN, KB, NS, FP8, EPI, BT, true>(a, grid, stream);
-    }
-    return launch_kernel<BM, BN, WM, WN, KB, NS, FP8, EPI, BT, false>(a, grid, stream);
-}
-
-template <int EPI>
-static pk_status dispatch_gemm(const GemmArgs& a, int slots, int comm_cus, const TileCfg& tc, bool fp8,
-                               void* ws, size_t ws_bytes, hipStream_t stream, bool bt = false) {
-    if (bt) {
-        // second operand stored k-contiguous: built for the two base epilogues only
-        if constexpr (EPI == EPI_RS || EPI == EPI_AG) {
-            // 128-byte k-tiles in a ring of 2 stages: a k-contiguous operand is fetched as one piece per row and k-tile, and
-            // 64-byte pieces use half of every 128-byte line they touch (measured: 7% slower than the row-major path)
-            if (tc.bm == 256)
-                return fp8 ? launch_gemm<256, 256, 2, 4, 128, 2, true, EPI, true>(a, slots, comm_cus, ws, ws_bytes, stream)
-                           : launch_gemm<256, 256, 2, 4, 128, 2, false, EPI, true>(a, slots, comm_cus, ws, ws_bytes, stream);
-            return fp8 ? launch_gemm<128, 128, 2, 2, 128, 2, true, EPI, true>(a, slots, comm_cus, ws, ws_bytes, stream)
-                       : launch_gemm<128, 128, 2, 2, 128, 2, false, EPI, true>(a, slots, comm_cus, ws, ws_bytes, stream);
-        } else {
-            return PK_ERR_ARG;
-        }
-    }
-    if (tc.bm == 256) {
-        // 8 waves, 64-byte k-tiles (32 bf16 or 64 fp8 of k) in a ring of 4 LDS stages
-        return fp8 ? launch_gemm<256, 256, 2, 4, 64, 4, true, EPI>(a, slots, comm_cus, ws, ws_bytes, stream)
-                   : launch_gemm<256, 256, 2, 4, 64, 4, false, EPI>(a, slots, comm_cus, ws, ws_bytes, stream);
-    }
-    return fp8 ? launch_gemm<128, 128, 2, 2, 128, 2, true, EPI>(a, slots, comm_cus, ws, ws_bytes, stream)
-               : launch_gemm<128, 128, 2, 2, 128, 2, false, EPI>(a, slots, comm_cus, ws, ws_bytes, stream);
+    return launch_gemm<EPI>(a, tile, fp8, bt, false, schedule_grid(slots, comm_cus), stream);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -557,6 +540,32 @@ static pk_status side_stream_of_device(SideStream** out) {   // call with side_l
     return PK_OK;
 }
 
+// How gemm_rs_impl cuts the local product into tiles.
+struct RsTiling {
+    int tile;             // shape
+    bool late;            // finer than a ready flag: the flags are published behind the GEMM
+    int blks_per_tile;    // row blocks of the ready flags in a tile row (late: the tile's own rows are one block)
+    int fcols_per_tile;   // flag columns in a tile column
+};
+// false: the shape cannot take this problem that way
+static bool rs_tiling(const pk_plan& pl, int tile, bool late, int64_t rows, RsTiling* t) {
+    const int bm = kTileDim[tile].bm, bn = kTileDim[tile].bn;
+    *t = {tile, late, 1, 1};
+    if (late) return true;
+    if (bn < pl.tile_n) return false;
+    t->fcols_per_tile = bn / pl.tile_n;
+    // a shard of one block may be lower than a flag tile: several of them then share a tile
+    const int blk = pl.tiles_m == 1 ? (int)rows : pl.tile_m;
+    t->blks_per_tile = bm / blk;
+    return t->blks_per_tile >= 1;
+}
+static void rs_tile_space(const pk_plan& pl, const RsTiling& t, int P, int64_t m_all, int64_t slot_cols, int n_blks, bool cols,
+                          int* tile_rows, int* tile_cols) {
+    const int c = t.late ? tiles_across(slot_cols, kTileDim[t.tile].bn) : (pl.tiles_n + t.fcols_per_tile - 1) / t.fcols_per_tile;
+    *tile_rows = t.late ? tiles_across(m_all, kTileDim[t.tile].bm) : (n_blks + t.blks_per_tile - 1) / t.blks_per_tile;
+    *tile_cols = cols ? P * c : c;
+}
+
 struct AllReduceOut {
     uint16_t* bcast_out;
     uint32_t* ar_flags_in;
@@ -592,18 +601,51 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         !aligned16(out_shard))
         return PK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)stream;
-    const TileCfg tc = {pl.tile_m, pl.tile_n};
+    // one shard (slot): rows x cols.  Scatter along rows: M/P x N; along the last dimension: M x N/P
+    const int64_t rows = cols ? M : M / P;
+    const int64_t slot_cols = cols ? N / P : N;
+    const int64_t m_all = cols ? M : P * rows;
+    const int n_blks = cols ? pl.tiles_m : P * pl.tiles_m;      // row blocks of the ready flags
+    const int grid = max_grid(comm_cus);
+
+    // The tile shape.  A tile covers whole ready flags (several, where it is larger) and signals them itself, or it is finer than
+    // a flag and the flags are published behind the GEMM: that only where all tiles run at once (they end together anyway) and
+    // costs a kernel of its own if the reduce phase is not part of the call.
+    RsTiling t = {pl.tile_m == 256 ? T256x256 : T128x128, false, 1, 1};
+    if (do_gemm && pl.tile_m != 256 && !(ws && !bt && !bf16_slots)) {
+        int64_t best = INT64_MAX;
+        for (int id = 0; id < N_TILES; ++id)
+            for (int late = 0; late < 2; ++late) {
+                RsTiling c;
+                if (!rs_tiling(pl, id, late != 0, rows, &c)) continue;
+                int tile_rows, tile_cols;
+                rs_tile_space(pl, c, P, m_all, slot_cols, n_blks, cols, &tile_rows, &tile_cols);
+                const int tiles = tile_rows * tile_cols;
+                if (late && (tiles + 7) / 8 * 8 > grid) continue;
+                const int64_t cost = tile_cost(id, fp8, tiles, (int)(pl.local_k >> (fp8 ? 7 : 6)), grid) + (late && !do_reduce ? 4000 * grid : 0);
+                if (cost < best) {
+                    best = cost;
+                    t = c;
+                }
+            }
+    }
+    int all_rows, tiles_n_all;                                   // the tile space of the whole local product
+    rs_tile_space(pl, t, P, m_all, slot_cols, n_blks, cols, &all_rows, &tiles_n_all);
+
     // Overlapped reduce: the GEMM is launched in two parts, the tile rows of this rank's own block (plus as many of the
     // next ranks' as fill whole rounds) and the rest; the reduce runs on the library's second stream beside the second
     // part: its workgroups use no LDS and few enough registers to sit next to a GEMM workgroup.  It waits for nothing
     // the second part produces, so whichever of the two the hardware places first, both finish.
-    bool overlap = (phases & PK_PHASE_OVERLAP) && do_gemm && do_reduce && !ar && !cols && P > 1;
+    bool overlap = (phases & PK_PHASE_OVERLAP) && do_gemm && do_reduce && !ar && !cols && P > 1 && !t.late;
+    if (ceil_div((int64_t)all_rows * tiles_n_all, 8) * 8 <= grid) overlap = false;   // all tiles at once: nothing to run beside
     int first_rows = 0;                      // tile rows of the first part (0: one launch for everything)
-    // Registers per lane that the 256x256 GEMM kernels leave beside their two waves per SIMD: bf16 96, bf16 with the second
-    // operand k-contiguous 48, fp8 48 (32 with bf16 slots, 16 with the second operand k-contiguous: too few).  Next to the
-    // ones that leave 48 the narrow reduce kernel runs, built for fp32 slots and P of 2, 4 or 8; otherwise no overlap there.
-    const bool narrow_reduce = pl.tile_m == 256 && (fp8 || bt);
-    if (narrow_reduce && (bf16_slots || (fp8 && bt) || (P != 2 && P != 4 && P != 8))) overlap = false;
+    const int own_row = rank * pl.tiles_m / t.blks_per_tile;    // the tile rows that hold this rank's own blocks
+    const int own_rows = ((rank + 1) * pl.tiles_m - 1) / t.blks_per_tile - own_row + 1;
+    // Registers per lane that the 256x256 GEMM kernels leave beside their two waves per SIMD: bf16 128, bf16 with the second
+    // operand k-contiguous 96, fp8 80 (64 with the second operand k-contiguous); a wave of the reduce kernel takes 64 at most.
+    // Next to the fp8 kernel the narrow form runs, where it is built: with twice the loads in flight the reduce takes more
+    // bandwidth and clock from a GEMM that lives on both (16384 x 16384 x 2048: 676 us against 706 us a call).
+    const bool narrow_reduce = fp8 && !bf16_slots && (P == 2 || P == 4 || P == 8);
     if (overlap) {
         // a stream that is being captured into a graph takes the second stream along only if that one exists already
         // (it is created by the first eager call with the flag): no stream is created in the middle of a capture
@@ -616,23 +658,15 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
             if (!side_streams[dev].ready) overlap = false;
         }
     }
-    // one shard (slot): rows x cols.  Scatter along rows: M/P x N; along the last dimension: M x N/P
-    const int64_t rows = cols ? M : M / P;
-    const int64_t slot_cols = cols ? N / P : N;
 
     GemmArgs a = {};
-    const int all_rows = cols ? pl.tiles_m : P * pl.tiles_m;     // tile rows of the whole local product
-    const int tiles_n_all = cols ? P * pl.tiles_n : pl.tiles_n;
     // one launch over `n_rows` tile rows that start at tile row `row0` (wrapping around at all_rows)
     auto gemm = [&](int row0, int n_rows) {
         a.grp_tile_rows = n_rows;
         a.row_rot = row0;
         a.all_tile_rows = (row0 == 0 && n_rows == all_rows) ? 0 : all_rows;
-        const int64_t G = (int64_t)n_rows * a.tiles_n;
-        a.wg_per_group = (int32_t)(8 * ceil_div(G, 8));
-        a.band = pick_band(n_rows, a.tiles_n, a.wg_per_group / 8);
-        return bf16_slots ? dispatch_gemm<EPI_RS16>(a, a.wg_per_group, comm_cus, tc, fp8, ws, ws_bytes, s)
-                          : dispatch_gemm<EPI_RS>(a, a.wg_per_group, comm_cus, tc, fp8, ws, ws_bytes, s, bt);
+        return bf16_slots ? run_gemm<EPI_RS16>(a, t.tile, comm_cus, fp8, false, nullptr, 0, s)
+                          : run_gemm<EPI_RS>(a, t.tile, comm_cus, fp8, bt, bt ? nullptr : ws, ws_bytes, s);
     };
     if (do_gemm) {
         const int elem = fp8 ? 1 : 2;
@@ -643,22 +677,33 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         a.n = (int32_t)pl.local_n;
         a.ktiles = (int32_t)(pl.local_k / (fp8 ? 128 : 64));
         a.rows_per_shard = (int32_t)rows;
-        a.tiles_m_shard = pl.tiles_m;
         a.tiles_n = tiles_n_all;
         a.cols_per_shard = cols ? (int32_t)slot_cols : 0;
-        a.tiles_n_shard = cols ? pl.tiles_n : 0;
+        a.tiles_n_shard = cols ? tiles_n_all / P : 0;
+        a.late_signal = t.late;
+        a.blks_per_tile = t.blks_per_tile;
+        if (t.late) {                        // the tiles ignore the flags' blocks: blocks of their own height over all rows
+            a.blk_rows = kTileDim[t.tile].bm;
+            a.n_blks = a.blks_per_shard = all_rows;
+            a.rows_per_span = (int32_t)m_all;
+        } else {
+            a.blk_rows = pl.tile_m;
+            a.blks_per_shard = pl.tiles_m;
+            a.n_blks = n_blks;
+            a.rows_per_span = (int32_t)rows;
+            a.fcols_per_tile = t.fcols_per_tile;
+            a.flag_cols = pl.tiles_n;
+        }
         a.n_groups = 1;
         a.group0 = 0;
         if (overlap) {
             // The first part: the own block's rows rounded up to whole bands of 4, then as many more bands (up to 7) as
             // waste the least of its last round.  No second part left: one launch, reduce afterwards.
-            int grid = (num_cus() - comm_cus) / 8 * 8;
-            if (grid < 8) grid = 8;
             const int band = 4;
             int best = 0;
             double best_waste = 2.0;
             for (int k = 0; k < 8; ++k) {
-                const int r1 = (int)ceil_div(pl.tiles_m, band) * band + k * band;
+                const int r1 = (int)ceil_div(own_rows, band) * band + k * band;
                 if (r1 >= all_rows) break;
                 const int64_t t1 = (int64_t)r1 * tiles_n_all;
                 const double waste = (double)(ceil_div(t1, grid) * grid - t1) / grid + 0.02 * k;
@@ -682,8 +727,13 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         a.epoch = epoch;
         a.status = status;
         a.timeout_ticks = timeout_ticks(timeout_us);
-        st = overlap ? gemm(rank * pl.tiles_m, first_rows) : gemm(0, all_rows);
+        st = overlap ? gemm(own_row, first_rows) : gemm(0, all_rows);
         if (st != PK_OK) return st;
+        if (t.late && !do_reduce) {
+            hipLaunchKernelGGL(signal_kernel, dim3((unsigned)ceil_div(P * pl.flags_per_slot, 256)), dim3(256), 0, s, flags_in, flags_out,
+                               P, rank, pl.flags_per_slot, epoch);
+            if (hipGetLastError() != hipSuccess) return PK_ERR_HIP;
+        }
     }
     std::unique_lock<std::mutex> side_guard(side_lock, std::defer_lock);
     SideStream* side = nullptr;
@@ -696,7 +746,7 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
             return PK_ERR_HIP;
         reduce_stream = side->stream;
         // the rest of the GEMM is enqueued before the reduce, so that it is first in line for the compute units
-        st = gemm((rank * pl.tiles_m + first_rows) % all_rows, all_rows - first_rows);
+        st = gemm((own_row + first_rows) % all_rows, all_rows - first_rows);
         if (st != PK_OK) return st;
     }
     if (do_reduce) {
@@ -704,6 +754,8 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         r.partials = partials;
         r.out = (uint16_t*)out_shard;
         r.flags_in = flags_in;
+        r.flags_out = flags_out;
+        r.late_signal = do_gemm && t.late;
         r.P = P;
         r.rows = (int32_t)rows;
         r.n = (int32_t)slot_cols;
@@ -792,7 +844,6 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     if (P > 1 && !chunk_flags) return PK_ERR_NULL;
     if (fp8 && (!scale_a || !scale_b)) return PK_ERR_DTYPE;
     if (!aligned16(A_gathered) || !aligned16(B_local) || !aligned16(C_local)) return PK_ERR_ALIGN;
-    const TileCfg tc = {pl.tile_m, pl.tile_n};
     const int elem = fp8 ? 1 : 2;
     GemmArgs a = {};
     a.A = (const char*)A_gathered;
@@ -801,18 +852,50 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     a.ldb = (bt ? pl.local_k : pl.local_n) * elem;
     a.n = (int32_t)pl.local_n;
     a.ktiles = (int32_t)(pl.local_k / (fp8 ? 128 : 64));
-    // row chunks: one scheduling group per chunk, visited from the own one; column chunks: every tile needs every chunk
-    a.rows_per_shard = (int32_t)(k_chunks ? M : M / P);
-    a.tiles_m_shard = pl.tiles_m;
-    a.tiles_n = pl.tiles_n;
-    a.grp_tile_rows = pl.tiles_m;
-    a.n_groups = k_chunks ? 1 : P;
-    a.group0 = k_chunks ? 0 : rank;
     a.k_chunks = k_chunks ? P : 0;
     a.act = activation;
-    const int64_t G = (int64_t)a.grp_tile_rows * a.tiles_n;
-    a.wg_per_group = (int32_t)(8 * ceil_div(G, 8));
-    a.band = pick_band(a.grp_tile_rows, a.tiles_n, a.wg_per_group / 8);
+    // column chunks: a row piece of a chunk is a whole number of 128-byte lines
+    a.acquire_all = ((uintptr_t)A_gathered & 127) != 0;
+    // The tile shape, and how tile rows and row chunks go together.  Where all tiles run at once, or a chunk is lower than a
+    // tile: tile rows over all rows, from the one that holds the own chunk on; a tile waits for every chunk it touches.
+    // Otherwise one scheduling group per chunk, visited from the own one.  Column chunks: every tile needs every chunk.
+    const int64_t chunk_rows = M / P;
+    const int grid = max_grid(comm_cus);
+    auto tiles_of = [&](int id, bool* one_span) -> int {
+        const int bm = kTileDim[id].bm;
+        const int all = tiles_across(M, bm), tn = tiles_across(pl.local_n, kTileDim[id].bn);
+        *one_span = k_chunks || P == 1 || chunk_rows < bm || (all * tn + 7) / 8 * 8 <= grid;
+        return (*one_span ? all : P * tiles_across(chunk_rows, bm)) * tn;
+    };
+    bool one_span = k_chunks;
+    int tile = pl.tile_m == 256 ? T256x256 : T128x128;
+    const int64_t plan_slots = ((int64_t)pl.tiles_m * pl.tiles_n + 7) / 8 * 8 * P;
+    const bool sk = ws && !bt && !k_chunks && plan_slots > grid && plan_slots % grid != 0 && a.ktiles >= 16 && grid <= (int)(kWsFlagBytes / 4);
+    if (!sk) {
+        int64_t best = INT64_MAX;
+        for (int id = 0; id < N_TILES; ++id) {
+            bool span;
+            const int64_t cost = tile_cost(id, fp8, tiles_of(id, &span), a.ktiles, grid);
+            if (cost < best) {
+                best = cost;
+                tile = id;
+                one_span = span;
+            }
+        }
+    }
+    const int bm = kTileDim[tile].bm;
+    a.rows_per_shard = (int32_t)(k_chunks ? M : chunk_rows);
+    a.rows_per_chunk = a.rows_per_shard;
+    a.rows_per_span = (int32_t)(one_span ? M : chunk_rows);
+    a.tiles_m_shard = (int32_t)ceil_div(a.rows_per_span, bm);
+    a.tiles_n = (int32_t)ceil_div(pl.local_n, kTileDim[tile].bn);
+    a.grp_tile_rows = a.tiles_m_shard;
+    a.n_groups = one_span ? 1 : P;
+    a.group0 = one_span ? 0 : rank;
+    if (one_span && !k_chunks) {
+        a.row_rot = (int32_t)(rank * chunk_rows / bm);
+        a.all_tile_rows = a.tiles_m_shard;
+    }
     a.rank = rank;
     a.C = (uint16_t*)C_local;
     a.chunk_flags = chunk_flags;
@@ -828,8 +911,8 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         if (hipGetLastError() != hipSuccess) return PK_ERR_HIP;
         a.ws_epoch = 1;
     }
-    return k_chunks ? dispatch_gemm<EPI_AGK>(a, a.wg_per_group, comm_cus, tc, fp8, nullptr, 0, (hipStream_t)stream)
-                    : dispatch_gemm<EPI_AG>(a, a.wg_per_group * P, comm_cus, tc, fp8, ws, ws_bytes, (hipStream_t)stream, bt);
+    return k_chunks ? run_gemm<EPI_AGK>(a, tile, comm_cus, fp8, false, nullptr, 0, (hipStream_t)stream)
+                    : run_gemm<EPI_AG>(a, tile, comm_cus, fp8, bt, sk ? ws : nullptr, ws_bytes, (hipStream_t)stream);
 }
 
 static pk_status make_order(const int* order, int n_order, int P, EmuOrder* o) {

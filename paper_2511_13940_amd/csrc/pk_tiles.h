@@ -1,0 +1,121 @@
+// The tile shapes that gemm_kernel is built for, and the choice among them (host side).
+#pragma once
+#include "pk_gemm.h"
+
+namespace pk {
+
+// A tile shape; the last one serves the stream-K tail only (its pieces are exchanged between whole workgroups, WK = 1).
+enum Tile { T256x256, T256x128, T128x256, T128x128, T128x64, T64x64, N_TILES, T128x128_SK = N_TILES };
+
+struct TileDim {
+    int bm, bn;
+};
+constexpr TileDim kTileDim[N_TILES + 1] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}, {128, 64}, {64, 64}, {128, 128}};
+
+// waves (WM x WN x WK), k-tile bytes and ring stages of a tile shape.  bf16: the smaller tiles split the k-steps of a k-tile
+// over two groups of waves (WK = 2), which keeps the wave's sub-tile large and with it the LDS reads per flop low: 64 x 64
+// sub-tiles of one 128 x 128 tile ran 16.4 us against 18.5 us for four waves without the split (2048 x 1024 x 2048).  fp8 has
+// only two k-steps in a 128-byte k-tile and half as many fragment reads per flop: there the split gains nothing.
+// A k-contiguous second operand is fetched as one piece per row and k-tile, and 64-byte pieces use half of every 128-byte line
+// they touch: 128-byte k-tiles throughout.
+struct TileWaves {
+    int wm, wn, wk, kb, ns;
+};
+constexpr TileWaves tile_waves(int tile, bool fp8, bool bt) {
+    switch (tile) {
+        case T256x256: return bt ? TileWaves{2, 4, 1, 128, 2} : TileWaves{2, 4, 1, 64, 4};
+        case T256x128: return fp8 ? TileWaves{4, 2, 1, 128, 3} : TileWaves{2, 2, 2, 128, 3};
+        case T128x256: return bt ? TileWaves{2, 4, 1, 128, 3} : TileWaves{2, 4, 1, 64, 4};
+        case T128x128: return fp8 ? TileWaves{4, 2, 1, 128, 4} : TileWaves{2, 2, 2, 128, 4};
+        case T128x64: return fp8 ? TileWaves{2, 2, 1, 128, 6} : TileWaves{2, 2, 2, 128, 4};
+        case T64x64: return fp8 ? TileWaves{2, 1, 1, 128, 6} : TileWaves{2, 1, 2, 128, 6};
+        default: return TileWaves{2, 2, 1, 128, 2};      // T128x128_SK
+    }
+}
+
+// Estimated time, in nanoseconds x grid, of `tiles` tiles over `kt` 128-byte k-tiles on `grid` workgroups: rounds x (fixed part
+// + k-tile time), the k-tile time rising with the share of the compute units at work (clock, L2 and memory traffic).  The
+// figures are fitted to 24 shapes of bf16 and 7 of fp8 GEMMs from 64 x 3584 x 8192 to 8192 x 8192 x 3584, timed with every
+// tile shape: the tile of least estimated time was the fastest one, or within 3.2% of it, on all of them.
+struct TileCost {
+    int lo, hi, fixed;        // ns per k-tile with few and with all compute units at work, ns per tile
+};
+constexpr TileCost kTileCost[2][N_TILES] = {
+    {{771, 1583, 6660}, {449, 825, 5610}, {536, 901, 3320}, {292, 464, 3640}, {216, 322, 2020}, {180, 214, 2440}},
+    {{754, 1401, 6070}, {442, 770, 4580}, {509, 749, 4030}, {313, 472, 2620}, {279, 354, 2020}, {215, 281, 1820}}};
+inline int64_t tile_cost(int tile, bool fp8, int tiles, int kt, int grid) {
+    const TileCost& c = kTileCost[fp8 ? 1 : 0][tile];
+    const int rounds = (int)((((unsigned)tiles + 7) / 8 * 8 + grid - 1) / (unsigned)grid);
+    return (int64_t)rounds * grid * (c.fixed + (int64_t)kt * c.lo) + (int64_t)kt * (c.hi - c.lo) * tiles;
+}
+inline int tiles_across(int64_t size, int tile_size) {       // size / tile_size, rounded up; tile_size is 64, 128 or 256
+    const int shift = tile_size == 64 ? 6 : tile_size == 128 ? 7 : 8;
+    return (int)((size + tile_size - 1) >> shift);
+}
+
+// Launches one GEMM on `grid` workgroups with the given tile shape (defined in the gemm_*.hip file of its mode).  a.ktiles
+// counts k-tiles of 128 bytes.  `sk`: with the stream-K tail that `a` describes (T256x256 or T128x128_SK, not with bt).
+template <int EPI>
+pk_status launch_gemm(GemmArgs a, int tile, bool fp8, bool bt, bool sk, int grid, hipStream_t stream);
+
+// ---- definition, included by the gemm_*.hip files only ----
+#ifdef PK_DEFINE_LAUNCH
+template <int TILE, bool FP8, int EPI, bool BT, bool SK>
+static pk_status launch_kernel(GemmArgs a, int grid, hipStream_t stream) {
+    constexpr int BM = kTileDim[TILE].bm, BN = kTileDim[TILE].bn;
+    constexpr TileWaves W = tile_waves(TILE, FP8, BT);
+    static std::atomic<uint64_t> configured{0};              // bit d = dynamic LDS size raised on device d
+    auto kern = gemm_kernel<BM, BN, W.wm, W.wn, W.wk, W.kb, W.ns, FP8, EPI, BT, SK>;
+    constexpr int lds = gemm_lds_bytes<BM, BN, W.kb, W.ns>();
+    static_assert(lds <= 160 * 1024, "a compute unit has 160 KB of LDS");
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return PK_ERR_HIP;
+    const uint64_t bit = 1ull << (dev & 63);
+    if (!(configured.load(std::memory_order_acquire) & bit)) {
+        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+            return PK_ERR_HIP;
+        configured.fetch_or(bit, std::memory_order_release);
+    }
+    a.ktiles = a.ktiles * 128 / W.kb;
+    a.set_divisors();
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * W.wm * W.wn * W.wk), lds, stream, a);
+    return hipGetLastError() == hipSuccess ? PK_OK : PK_ERR_HIP;
+}
+
+template <int EPI>
+pk_status launch_gemm(GemmArgs a, int tile, bool fp8, bool bt, bool sk, int grid, hipStream_t stream) {
+    constexpr bool BASE = EPI == EPI_RS || EPI == EPI_AG;    // the modes with a k-contiguous second operand and a stream-K tail
+    if ((bt || sk) && !BASE) return PK_ERR_ARG;
+    if constexpr (BASE) {
+        if (sk) {
+            if (bt) return PK_ERR_ARG;
+            if (tile == T256x256)
+                return fp8 ? launch_kernel<T256x256, true, EPI, false, true>(a, grid, stream)
+                           : launch_kernel<T256x256, false, EPI, false, true>(a, grid, stream);
+            return fp8 ? launch_kernel<T128x128_SK, true, EPI, false, true>(a, grid, stream)
+                       : launch_kernel<T128x128_SK, false, EPI, false, true>(a, grid, stream);
+        }
+    }
+    auto go = [&](auto tile_c) -> pk_status {
+        constexpr int T = decltype(tile_c)::value;
+        if constexpr (BASE) {
+            if (bt)
+                return fp8 ? launch_kernel<T, true, EPI, true, false>(a, grid, stream)
+                           : launch_kernel<T, false, EPI, true, false>(a, grid, stream);
+        }
+        return fp8 ? launch_kernel<T, true, EPI, false, false>(a, grid, stream)
+                   : launch_kernel<T, false, EPI, false, false>(a, grid, stream);
+    };
+    switch (tile) {
+        case T256x256: return go(std::integral_constant<int, T256x256>{});
+        case T256x128: return go(std::integral_constant<int, T256x128>{});
+        case T128x256: return go(std::integral_constant<int, T128x256>{});
+        case T128x128: return go(std::integral_constant<int, T128x128>{});
+        case T128x64: return go(std::integral_constant<int, T128x64>{});
+        case T64x64: return go(std::integral_constant<int, T64x64>{});
+        default: return PK_ERR_ARG;
+    }
+}
+#endif  // PK_DEFINE_LAUNCH
+
+}  // namespace pk

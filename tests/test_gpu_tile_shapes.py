@@ -1,0 +1,141 @@
+"""Every tile shape of the GEMM kernels at the sizes where it can go wrong: ragged rows and columns, k ranges shorter and longer
+than the load ring, tiles that cover several ready flags or several chunks, and flags published behind the GEMM (tiles finer
+than a flag).  The tile shape that each size leads to is named beside it (chosen by estimated time, csrc/pk_tiles.h).
+
+Bounds as in test_gpu_gemm_rs.py: fp32 accumulation of k products in any order, 2*k*2^-24 * sum|a||b|, and half a bf16 ulp."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import codec, tp_gemm
+from paper_2511_13940_amd import pk, workloads as wl
+from tests import harness as hz
+from tests.test_gpu_gemm_rs import check_rs
+
+pytestmark = pytest.mark.gpu
+
+U32 = 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype,P,rank,M,N,kl,layout", [
+    ("bf16", 8, 3, 1024, 4104, 1600, "kn"),    # 256x128: two flags per tile, the last column tile 8 wide
+    ("bf16", 2, 1, 2800, 4104, 128, "kn"),     # 256x256: four flags per tile, shards of 11 flag rows (odd)
+    ("bf16", 8, 5, 8 * 96, 8200, 512, "nk"),   # 128x256 over shards of 96 rows
+    ("bf16", 5, 4, 5 * 300, 1544, 128, "kn"),  # 128x128, flags behind the GEMM: tiles cross shards of 300 rows
+    ("bf16", 4, 0, 2048, 1024, 448, "nk"),     # 128x64: finer than a flag, seven k-tiles in a ring of four
+    ("bf16", 2, 1, 256, 248, 64, "kn"),        # one k-tile
+    ("bf16", 8, 7, 64, 520, 4032, "kn"),       # 64x64: shards of 8 rows, one tile row for all of them
+    ("fp8", 8, 2, 8 * 33, 4112, 256, "kn"),    # 128x64
+    ("fp8", 2, 0, 2000, 4112, 256, "nk"),      # 256x256: shards of 1000 rows
+    ("fp8", 3, 2, 3 * 500, 2064, 2176, "kn"),  # 128x128 or larger, 17 k-tiles
+    ("fp8", 1, 0, 130, 144, 1152, "kn"),       # 64x64, nine k-tiles in a ring of six
+])
+def test_gemm_rs(dtype, P, rank, M, N, kl, layout):
+    inp = wl.gemm_rs_inputs(P, M, N, P * kl, dtype, rank, seed=M + N)
+    B = np.ascontiguousarray(inp["B_local"].T) if layout == "nk" else inp["B_local"]
+    res = hz.run_gemm_rs(P, rank, M, N, P * kl, dtype, inp["A_local"], B, inp["partials"], inp["scale_a"], inp["scale_b"],
+                         epoch=6, b_layout=layout)
+    check_rs(P, rank, dtype, inp, res, kl)
+    assert np.all(res["flags_in"][rank] == 6) and (P == 1 or np.all(res["flags_out"][(rank + 1) % P] == 6))
+    # the phases as calls of their own: the same bits, and every flag is out before the reduce is launched
+    g = hz.run_gemm_rs(P, rank, M, N, P * kl, dtype, inp["A_local"], B, inp["partials"], inp["scale_a"], inp["scale_b"],
+                       epoch=9, b_layout=layout, phases=pk.PHASE_GEMM)
+    assert np.all(g["flags_in"][rank] == 9) and all(np.all(g["flags_out"][q] == 9) for q in range(P) if q != rank)
+    assert P == 1 or np.all(g["flags_out"][rank] == 0)
+
+
+@pytest.mark.parametrize("P,rank,M,N,kl,dtype", [
+    (4, 1, 1000, 8192, 256, "bf16"),           # 128x256 inside column blocks of 2048
+    (4, 2, 333, 4 * 1032, 128, "bf16"),        # 128x64, flags behind the GEMM, column blocks of 1032
+    (2, 0, 1500, 2 * 2064, 128, "fp8"),        # 128x256, the last tile of a column block 16 wide
+])
+def test_gemm_rs_cols(P, rank, M, N, kl, dtype):
+    inp = wl.gemm_rs_inputs(P, M * P, N, P * kl, dtype, rank, seed=M)
+    A = np.ascontiguousarray(inp["A_local"][:M])
+    partials = (np.random.default_rng(M).standard_normal((P, M, N // P)) * 0.02).astype(np.float32)
+    res = hz.run_gemm_rs(P, rank, M, N, P * kl, dtype, A, inp["B_local"], partials, inp["scale_a"], inp["scale_b"], epoch=4, cols=True)
+    assert res["status"][0] == 0
+    ref = tp_gemm.gemm_rs_cols(P, rank, A, inp["B_local"], dtype, partials, inp["scale_a"], inp["scale_b"])
+    mag = tp_gemm.abs_product(A, inp["B_local"], dtype, inp["scale_a"], inp["scale_b"])
+    ns = N // P
+    # the 8-bit MFMA adds the 64 products of one instruction with an error of up to 2^-14 of the largest of them (see
+    # test_gpu_special_values.py); 448 is the largest code
+    mfma8 = (kl // 64) * 2.0 ** -14 * 448.0 ** 2 * inp["scale_a"] * inp["scale_b"] if dtype == "fp8" else 0.0
+    for q in range(P):
+        got = res["partials_after"][rank] if q == rank else res["outgoing"][q]
+        assert np.all(np.abs(got - ref["outgoing"][q]) <= 2 * kl * U32 * mag[:, q * ns:(q + 1) * ns] + mfma8 + 1e-30), q
+        assert q == rank or np.all(res["flags_out"][q] == 4)
+
+
+@pytest.mark.parametrize("dtype,P,rank,M,N,K,layout,act", [
+    ("bf16", 8, 2, 1024, 8 * 4104, 1600, "kn", "none"),   # 256x128, one tile covers two chunks of 128 rows
+    ("bf16", 3, 1, 2100, 3 * 2056, 192, "nk", "relu"),    # 128x256, chunks of 700 rows
+    ("bf16", 8, 6, 8 * 189, 8 * 1720, 576, "kn", "silu"), # 128x128 across chunks of 189 rows
+    ("bf16", 4, 3, 1000, 4 * 1544, 320, "nk", "gelu_tanh"),  # 128x64
+    ("bf16", 64, 40, 64 * 3, 64 * 72, 1024, "kn", "none"),   # 64 chunks of 3 rows: a tile waits for 21 and more of them
+    ("bf16", 2, 0, 6000, 2 * 1800, 64, "kn", "silu"),     # several rounds, chunk by chunk
+    ("fp8", 5, 2, 5 * 77, 5 * 1040, 640, "kn", "gelu_tanh"),
+    ("fp8", 8, 7, 2048, 8 * 3600, 256, "nk", "silu"),
+])
+def test_ag_gemm(dtype, P, rank, M, N, K, layout, act):
+    inp = wl.ag_gemm_inputs(P, M, N, K, dtype, rank, seed=M + N)
+    B = np.ascontiguousarray(inp["B_local"].T) if layout == "nk" else inp["B_local"]
+    runs = [hz.run_ag_gemm(P, rank, M, N, K, dtype, inp["chunks"], B, inp["scale_a"], inp["scale_b"], epoch=3, act=act,
+                           b_layout=layout, deliver=d, order=inp["order"]) for d in ("pre", "emu")]
+    A = tp_gemm.gather_chunks(inp["chunks"])
+    x = tp_gemm.local_product(A, inp["B_local"], dtype, inp["scale_a"], inp["scale_b"])
+    mag = tp_gemm.abs_product(A, inp["B_local"], dtype, inp["scale_a"], inp["scale_b"])
+    want = tp_gemm.activation(x, act)
+    for res in runs:
+        assert res["status"][0] == 0
+        got = codec.bf16_decode(res["C_bits"])
+        # the slope of every activation is at most 1.13; the fp32 evaluation adds a few units of 2^-23
+        assert np.all(np.abs(got - want) <= 1.13 * 2 * K * U32 * mag + (2.0 ** -8 + 2.0 ** -20) * np.abs(want) + 2.0 ** -133)
+    assert np.array_equal(runs[0]["C_bits"], runs[1]["C_bits"])   # whatever arrives when
+
+
+def test_ag_gemm_chunks_that_share_a_cache_line():
+    """A_gathered starts 16 bytes into a 128-byte line, so the last line of a chunk holds the first bytes of the next one."""
+    P, rank, M, N, K = 4, 1, 4 * 48, 4 * 264, 128
+    inp = wl.ag_gemm_inputs(P, M, N, K, "bf16", rank, seed=5)
+    full = hz.dev(tp_gemm.gather_chunks(inp["chunks"]).view(np.int16))
+    mem = torch.full((M * K + 64,), 0x7FC1, dtype=torch.int16, device="cuda")
+    A = mem[8:8 + M * K].view(M, K)
+    assert A.data_ptr() % 128 == 16
+    A[rank * 48:(rank + 1) * 48] = full[rank * 48:(rank + 1) * 48]
+    B = hz.elem_view(inp["B_local"], "bf16")
+    C = torch.zeros((M, N // P), dtype=torch.int16, device="cuda")
+    flags = torch.zeros(P, dtype=torch.int32, device="cuda")
+    status = torch.zeros(8, dtype=torch.int32, device="cuda")
+    counters = torch.zeros(pk.EMU_MAX_ORDER, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    pk.pk_emu_deliver_chunks(P, M, K, 2, full, A, flags, 1, [3, 0, 2], 5, counters, stream=side)
+    pk.pk_ag_gemm(P, rank, M, N, K, "bf16", A, B, None, None, flags, 1, C, status)
+    torch.cuda.synchronize()
+    assert status[0].item() == 0
+    A_bits = tp_gemm.gather_chunks(inp["chunks"])
+    want = tp_gemm.local_product(A_bits, inp["B_local"], "bf16")
+    mag = tp_gemm.abs_product(A_bits, inp["B_local"], "bf16")
+    assert np.all(np.abs(codec.bf16_decode(hz.bits_of(C)) - want) <= 2 * K * U32 * mag + 2.0 ** -8 * np.abs(want) + 2.0 ** -133)
+
+
+@pytest.mark.parametrize("dtype,P,rank,M,N,K", [
+    ("bf16", 4, 2, 999, 4 * 2056, 4 * 64),     # 128x128, one k-tile per chunk
+    ("bf16", 8, 5, 1500, 8 * 640, 8 * 192),    # 64x64
+    ("fp8", 2, 1, 300, 2 * 528, 2 * 384),      # 64x64, three k-tiles per chunk
+])
+def test_ag_gemm_k(dtype, P, rank, M, N, K):
+    g = wl.global_problem(M, N, K, dtype, seed=M)
+    kp, ns = K // P, N // P
+    chunks = [np.ascontiguousarray(g["A"][:, q * kp:(q + 1) * kp]) for q in range(P)]
+    B = np.ascontiguousarray(g["B"][:, rank * ns:(rank + 1) * ns])
+    runs = [hz.run_ag_gemm_k(P, rank, M, N, K, dtype, chunks, B, g["scale_a"], g["scale_b"], epoch=2, deliver=d) for d in ("pre", "dma")]
+    want = tp_gemm.local_product(g["A"], B, dtype, g["scale_a"], g["scale_b"])
+    mag = tp_gemm.abs_product(g["A"], B, dtype, g["scale_a"], g["scale_b"])
+    for res in runs:
+        assert res["status"][0] == 0
+        got = codec.bf16_decode(res["C_bits"])
+        assert np.all(np.abs(got - want) <= 2 * K * U32 * mag + 2.0 ** -8 * np.abs(want) + 2.0 ** -133)
+    # all chunks there from the start, or one by one: the k range is summed in the same order
+    assert np.array_equal(runs[0]["C_bits"], runs[1]["C_bits"])
