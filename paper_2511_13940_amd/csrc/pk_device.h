@@ -78,6 +78,12 @@ __device__ __forceinline__ void store16_writethrough(void* p, i32x4 v) {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 
+// The same for data that only later kernels read: streaming, write-back.  An assembly block as well, so that a kernel that
+// counts its outstanding loads and stores knows their order.
+__device__ __forceinline__ void store16_stream(void* p, i32x4 v) {
+    asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+
 // Publish a flag whose data was written with store16_writethrough and has completed (every wave waited on its
 // stores and passed a workgroup barrier): a relaxed device-scope store is then enough.
 __device__ __forceinline__ void flag_publish(uint32_t* flag, uint32_t epoch) {

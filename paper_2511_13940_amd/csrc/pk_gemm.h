@@ -136,6 +136,7 @@ constexpr int gemm_lds_bytes() { return NS * (BM + BN) * KB + epi_stage_bytes<BM
 
 // s_waitcnt immediate for vmcnt(N) lgkmcnt(0) (gfx9 encoding, expcnt left alone)
 constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
+constexpr int kWaitLgkm0 = waitcnt_vm_lgkm0(63);   // vmcnt as high as it goes: not waited for
 
 // BT: the second operand is stored k-contiguous (N x K row-major, the transpose of the K x N matrix): its tile then has
 // the layout of the A tile and its fragments come in with the same 16-byte reads, no transposing reads.
@@ -153,31 +154,46 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int CPA = KB / 16;                         // 16-byte chunks per A tile row (8 or 4)
     constexpr int B_ROWS = KB / ELEM;                    // k-rows in a B tile
     constexpr int B_ROW_BYTES = BN * ELEM;
+    constexpr int PB = BN >= 64 ? 128 : 64;              // bytes per k-row of a panel of the bf16 B tile
     constexpr int CPR = B_ROW_BYTES / 16;                // 16-byte chunks per B tile row
     constexpr int RPI = 64 / CPR;                        // B rows covered by one wave-wide load
-    constexpr int NA = A_BYTES / 1024 / NW, NB = B_BYTES / 1024 / NW;   // wave-wide loads per wave per k-tile
+    // A single wave per group (WM = WN = 1): the groups share no data, so each takes whole k-tiles of its own (every WK-th)
+    // through a ring of its own, and the main loop has no barrier
+    constexpr bool PRIV = WM * WN == 1 && WK > 1;
+    constexpr int RINGS = PRIV ? WK : 1, NWL = PRIV ? 1 : NW;           // rings; waves that share a k-tile's loads
+    constexpr int NA = A_BYTES / 1024 / NWL, NB = B_BYTES / 1024 / NWL; // wave-wide loads per wave per k-tile
+    static_assert(!PRIV || (EPI != EPI_AGK && !SK), "rings of their own: not built for k ranges in pieces");
     constexpr int NL = NA + NB;
     constexpr int KST = FP8 ? KB / 64 : KB / 32;         // MFMA k-steps per k-tile
-    constexpr int KS = KST / WK;                         // ... of which each of the WK wave groups takes its own share
-    constexpr int EPI_OFF = NS * STAGE;                  // LDS offset of the epilogue staging area
-    constexpr int EPI_BYTES = epi_stage_bytes<BM, BN, KB, NS>();
-    // WK > 1: the groups' accumulators are summed at the end of a tile and shared out, OTM x OTN blocks to each wave
-    constexpr int OB = TM * TN / WK, OTM = OB >= TN ? OB / TN : 1, OTN = OB >= TN ? TN : OB;
-    static_assert(OB >= 1 && OB * WK == TM * TN && OTM * OTN == OB, "the blocks of a wave's sub-tile are shared out evenly");
-    static_assert(WK == 1 || (!SK && NW * (WK - 1) * OB * 4096 <= gemm_lds_bytes<BM, BN, KB, NS>()), "the exchange fits the LDS");
+    constexpr int KS = PRIV ? KST : KST / WK;            // ... of which each of the WK wave groups takes its own share
+    constexpr int EPI_OFF = RINGS * NS * STAGE;          // LDS offset of the epilogue staging area
+    constexpr int EPI_BYTES = epi_stage_bytes<BM, BN, KB, RINGS * NS>();
+    // WK > 1: the groups' accumulators are summed at the end of a tile and shared out, OTM x OTN blocks to each wave of the
+    // first NOWN groups
+    constexpr int OB = TM * TN >= WK ? TM * TN / WK : 1, NOWN = TM * TN / OB;
+    constexpr int OTM = OB >= TN ? OB / TN : 1, OTN = OB >= TN ? TN : OB;
+    static_assert(NOWN <= WK && OB * NOWN == TM * TN && OTM * OTN == OB, "the blocks of a wave's sub-tile are shared out evenly");
+    static_assert(WK == 1 || (!SK && WM * WN * NOWN * (WK - 1) * OB * 4096 <= gemm_lds_bytes<BM, BN, KB, RINGS * NS>()), "the exchange fits the LDS");
     static_assert(KB == 64 || KB == 128, "k-tile is 64 or 128 bytes of A row");
     static_assert(KS >= 1, "a k-tile holds at least one MFMA k-step");
-    static_assert(CPR >= 4 && RPI >= 1, "tile too narrow");
-    static_assert(KST % WK == 0 && (KS & (KS - 1)) == 0, "the wave groups share the k-steps of a k-tile evenly");
-    static_assert(NW % 2 == 0 && NA >= 1 && NB >= 1, "wave grid does not fit the tile");
+    static_assert(CPR >= 2 && RPI >= 1, "tile too narrow");
+    static_assert((PRIV || KST % WK == 0) && (KS & (KS - 1)) == 0, "the wave groups share the k-steps of a k-tile evenly");
+    static_assert(NW % 2 == 0 && NA * NWL * 1024 == A_BYTES && NB * NWL * 1024 == B_BYTES, "wave grid does not fit the tile");
     static_assert((NS - 1) * NL <= 63, "too many loads in flight for the counter");
     typedef typename std::conditional<FP8, i32x8, bf16x8>::type frag_t;
+
+    constexpr int OUT_ELEM = EPI == EPI_RS ? 4 : 2;
+    constexpr int EPI_STORES = OTM * OTN * OUT_ELEM;     // 16-byte-per-lane stores of a wave for a whole tile (1 KB each)
+    // The stores of a tile may still be on their way while the next tile's main loop starts (shapes that run many rounds)
+    constexpr bool DEFER = BM * BN == 256 * 256 && NS >= 4 && !SK && EPI != EPI_AGK && EPI_STORES <= 62;
 
     const int tid = threadIdx.x;
     const int l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = w / (WM * WN), wm = (w / WN) % WM, wn = w % WN;
-    const int kk0 = wk * KS;                             // first k-step of this wave's group in every k-tile
+    const int kk0 = PRIV ? 0 : wk * KS;                  // first k-step of this wave's group in every k-tile
+    const int wl = PRIV ? 0 : w;                         // this wave among those that share a k-tile's loads
+    PK_LDS char* ring = lds + (PRIV ? wk * (NS * STAGE) : 0);
     const int h = l >> 5;
 
     // A-tile swizzle: LDS chunk position = k-chunk ^ fA(row).
@@ -201,19 +217,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             for (int tj = 0; tj < TN; ++tj) b_off[tj] = bt_row_off + (uint32_t)(tj * 32 * KB);
         } else if constexpr (!FP8) {
             // bf16 B tile: panels of 64 columns (128 bytes per k-row, k-rows consecutive);
-            // inside a row the two 32-byte pieces of each 64-byte half trade places on k-rows with bit 1 set
-            static_assert(BN % 64 == 0, "the tile is made of whole 64-column panels");
+            // inside a row the two 32-byte pieces of each 64-byte half trade places on k-rows with bit 1 set.  A tile of 32
+            // columns is one panel of 64 bytes per k-row: the 32 lanes of a transposing read then cover 256 bytes in a row.
+            static_assert(BN % 64 == 0 || BN == 32, "the tile is made of whole panels");
             const int krow_base = 16 * kk0 + 8 * h + (s16 >> 2);
 #pragma unroll
             for (int tj = 0; tj < TN; ++tj) {
                 const int c32 = wn * TN + tj;                // 32-column block of the tile
                 const int panel = c32 >> 1;
-                const int piece = (2 * (c32 & 1) + nhalf) ^ ((s16 >> 3) & 1);
-                b_off[tj] = (uint32_t)(A_BYTES + panel * (B_ROWS * 128) + krow_base * 128 + piece * 32 + (s16 & 3) * 8);
+                const int piece = BN == 32 ? nhalf : (2 * (c32 & 1) + nhalf) ^ ((s16 >> 3) & 1);
+                b_off[tj] = (uint32_t)(A_BYTES + panel * (B_ROWS * PB) + krow_base * PB + piece * 32 + (s16 & 3) * 8);
             }
         } else {
             const int krow_base = 64 * kk0 + 32 * h + (s16 >> 1);
-            const int gsw = ((s16 >> 1) & 7) % (CPR / 2);
+            const int gsw = CPR >= 4 ? ((s16 >> 1) & 7) % (CPR / 2) : 0;
 #pragma unroll
             for (int tj = 0; tj < TN; ++tj) {
                 const int c = wn * (BN / WN / 16) + tj * 2 + nhalf;
@@ -244,9 +261,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             if (u < TN) {
                 const int tj = u;
                 s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (PK_LDS s16x4*)(st + b_off[tj] + (16 * kk) * 128));
+                    (PK_LDS s16x4*)(st + b_off[tj] + (16 * kk) * PB));
                 s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (PK_LDS s16x4*)(st + b_off[tj] + (16 * kk + 4) * 128));
+                    (PK_LDS s16x4*)(st + b_off[tj] + (16 * kk + 4) * PB));
                 s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 bfr[tj] = __builtin_bit_cast(bf16x8, both);
             } else {
@@ -291,6 +308,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     // tile bookkeeping carried from one iteration to the next (the epilogue of a tile runs one iteration late)
     int p_q = -1, p_blk = 0, p_nblk = 0, p_fcol = 0, p_row0 = 0, p_row_end = 0, p_col0 = 0, p_col_end = 0;
     int p_kind = UNIT_FULL, p_part_lo = 0, p_tile_end = 0;
+    bool p_full = false;                                 // ... was stored by exactly EPI_STORES stores of every wave
     bool p_dead = false;                                 // the previous tile was given up (a wait timed out): no signal
     const int slots_total = g.wg_per_group * g.n_groups;
     const int G = g.grp_tile_rows * g.tiles_n;
@@ -530,6 +548,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             b_base += (int64_t)first * b_step;
             until_wrap = g.ktiles - first;
         } else {
+            if (PRIV) kt0 = wk;
             a_base += (int64_t)kt0 * KB;             // a piece of a stream-K tile starts at k-tile kt0
             b_base += (int64_t)kt0 * b_step;
         }
@@ -540,7 +559,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 const int r_in = lt / CPA, cp = lt % CPA;
 #pragma unroll
                 for (int j = 0; j < NA; ++j) {
-                    const int r = (64 / CPA) * (j * NW + w) + r_in;
+                    const int r = (64 / CPA) * (j * NWL + wl) + r_in;
                     const int grow = min(row0 + r, row_end - 1);
                     a_voff[j] = (uint32_t)((int64_t)grow * g.lda + (cp ^ fA(r)) * 16);
                 }
@@ -550,20 +569,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 const int r_in = lt / CPA, cp = lt % CPA;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    const int r = (64 / CPA) * (j * NW + w) + r_in;
+                    const int r = (64 / CPA) * (j * NWL + wl) + r_in;
                     const int gcol = min(col0 + r, g.n - 1);        // edge tile: valid memory, never stored
                     b_voff[j] = (uint32_t)((int64_t)gcol * g.ldb + (cp ^ fA(r)) * 16);
                 }
             } else if constexpr (!FP8) {
-                // 1 KB block bi of the B tile = 8 k-rows of one 64-column panel
-                const int kr_in = lt >> 3, cp = lt & 7;
+                // 1 KB block bi of the B tile = 1024 / PB k-rows of one panel
+                constexpr int KR = 1024 / PB;
+                const int kr_in = lt / (PB / 16), cp = lt % (PB / 16);
                 const int n_bytes = g.n * 2;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    const int bi = j * NW + w;
-                    const int panel = bi / (B_ROWS / 8);
-                    const int kr = (bi % (B_ROWS / 8)) * 8 + kr_in;
-                    int colbyte = (col0 + panel * 64) * 2 + (cp ^ (2 * ((kr >> 1) & 1))) * 16;
+                    const int bi = j * NWL + wl;
+                    const int panel = bi / (B_ROWS / KR);
+                    const int kr = (bi % (B_ROWS / KR)) * KR + kr_in;
+                    int colbyte = (col0 + panel * 64) * 2 + (PB == 64 ? cp : cp ^ (2 * ((kr >> 1) & 1))) * 16;
                     if (colbyte >= n_bytes) colbyte = n_bytes - 16;   // edge tile: valid memory, never stored
                     b_voff[j] = (uint32_t)((int64_t)kr * g.ldb + colbyte);
                 }
@@ -572,8 +592,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 const int n_bytes = g.n;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    const int kr = (j * NW + w) * RPI + kr_in;
-                    const int sw = 2 * ((kr & 7) % (CPR / 2));
+                    const int kr = (j * NWL + wl) * RPI + kr_in;
+                    const int sw = CPR >= 4 ? 2 * ((kr & 7) % (CPR / 2)) : 0;
                     int colbyte = col0 + (cp ^ sw) * 16;
                     if (colbyte >= n_bytes) colbyte = n_bytes - 16;   // edge tile: valid memory, never stored
                     b_voff[j] = (uint32_t)((int64_t)kr * g.ldb + colbyte);
@@ -581,14 +601,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
         }
         // load number i (0 .. NL-1) of this wave for the next k-tile to fetch, into LDS stage `stage`
-        const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+        const uint32_t lds_base = (uint32_t)(uintptr_t)ring;
+        // k-tiles of this wave: all, or (a ring of its own) every WK-th from the wk-th on
+        const int my_ktiles = PRIV ? (seg_ktiles - wk + WK - 1) / WK : seg_ktiles;
+        constexpr int STRIDE = PRIV ? WK : 1;
         auto issue_load = [&](int stage, int i) {
-            const uint32_t sa = lds_base + stage * STAGE + w * 1024;
-            if (i < NA) dma_load16(a_base, a_voff[i], sa + i * NW * 1024);
-            else dma_load16(b_base, b_voff[i - NA], sa + A_BYTES + (i - NA) * NW * 1024);
+            const uint32_t sa = lds_base + stage * STAGE + wl * 1024;
+            if (i < NA) dma_load16(a_base, a_voff[i], sa + i * NWL * 1024);
+            else dma_load16(b_base, b_voff[i - NA], sa + A_BYTES + (i - NA) * NWL * 1024);
             if (i == NL - 1) {
-                a_base += KB;
-                b_base += b_step;
+                a_base += KB * STRIDE;
+                b_base += b_step * STRIDE;
                 if (EPI == EPI_AGK && --until_wrap == 0) {
                     a_base = g.A;
                     b_base = g.B;
@@ -605,7 +628,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         if (have) {
 #pragma unroll
             for (int s = 0; s < NS; ++s)
-                if (s < seg_ktiles) issue_loads(s);
+                if (s < my_ktiles) issue_loads(s);
         }
 
         // ---- epilogue of the previous tile (the storer), under the latency of the loads just issued ----
@@ -667,14 +690,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 }
             }
         }
-        if (p_q >= 0 && !skip_epilogue) {
+        if (p_q >= 0 && !skip_epilogue && (NOWN == WK || wk < NOWN)) {
             // lane holds, for each 32x32 block, rows (l & 31) and columns 8*b + 4*h + {0..3}.  Per pass a slab of
             // ROWS_PASS rows of the wave's part of the tile goes through the wave's private staging area, then out as whole
             // row segments, 16 bytes per lane.  The passes are a loop, not unrolled, around one read-back: a workgroup runs
             // most of this code once per launch, out of a cold instruction cache (unrolled, with the activation inlined per
             // element, it took 5-7 us per 256x128 tile instead of 2).
             constexpr int WCOLS = OTN * 32;                  // columns of the wave's part of the tile
-            constexpr int OUT_ELEM = (EPI == EPI_RS) ? 4 : 2;
             PK_LDS char* stg = lds + EPI_OFF + w * (EPI_BYTES / NW);
             const int row_w0 = p_row0 + wm * (BM / WM) + (wk * OB / TN) * 32;
             const int col_w0 = p_col0 + wn * (BN / WN) + (wk * OB % TN) * 32;
@@ -697,41 +719,45 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             } else {
                 dst = (uint64_t)g.C;
             }
-            auto emit = [&](auto act_c) {
+            // FULL: the tile lies inside the matrix and goes to one buffer, so no store is predicated and a wave issues exactly
+            // EPI_STORES of them.
+            auto emit = [&](auto act_c, auto full_c) {
                 constexpr bool ACT = decltype(act_c)::value;     // staged as fp32, activated on the way out
+                constexpr bool FULL = decltype(full_c)::value;
                 constexpr int ST_ELEM = (EPI == EPI_RS || ACT) ? 4 : 2;
-                constexpr int ROW_BYTES = WCOLS * ST_ELEM;
-                constexpr int ROWS_PASS = (EPI_BYTES / NW) / ROW_BYTES >= 32 ? 32 : (EPI_BYTES / NW) / ROW_BYTES;
+                constexpr int STG = EPI_BYTES / NW;
+                // columns of a pass: 32 where the slab then has 32 rows, so that all lanes write (fp32 slabs of 16 rows x 64
+                // columns keep half of them idle)
+                constexpr int CP = (ST_ELEM == 4 && !ACT && STG >= 32 * 32 * 4) ? 32 : WCOLS;
+                constexpr int ROW_BYTES = CP * ST_ELEM;
+                constexpr int ROWS_PASS = STG / ROW_BYTES >= 32 ? 32 : STG / ROW_BYTES;
                 static_assert(ROWS_PASS == 32 || ROWS_PASS == 16 || ROWS_PASS == 8 || ROWS_PASS == 4, "staging area too small");
                 constexpr int CH = ROW_BYTES / 16;               // 16-byte chunks per staged row
-                constexpr int LANES_ROW = WCOLS * OUT_ELEM / 16; // lanes that cover one row on the way out
+                constexpr int LANES_ROW = CP * OUT_ELEM / 16;    // lanes that cover one row on the way out
                 constexpr int ROWS_INSTR = 64 / LANES_ROW;       // rows written by one wave-wide store
                 static_assert(ROWS_PASS >= ROWS_INSTR, "a wave-wide store takes at most one pass");
+                constexpr int HALVES = 32 / ROWS_PASS, CSLABS = WCOLS / CP, NSLABS = OTM * CSLABS, NPASS = NSLABS * HALVES;
+                constexpr int NOUT = ROWS_PASS / ROWS_INSTR;
+                static_assert(NPASS * NOUT == EPI_STORES, "stores per wave and tile");
                 const int cl = lt % LANES_ROW, rl0 = lt / LANES_ROW, h = lt >> 5;
-                const int col = col_w0 + cl * (16 / OUT_ELEM);
-                int row = row_w0 + rl0;
-                uint64_t dp = dst + (int64_t)row * dst_pitch + (int64_t)col * OUT_ELEM;
-                const int64_t dp_step = ROWS_INSTR * dst_pitch;
-                constexpr int NPASS = OTM * (32 / ROWS_PASS);
-                auto pass = [&](int ps) {
-                    // write: lanes whose row falls in this pass store their quads; chunk position swizzled by row
+                // write pass ps: lanes whose row falls in it store their quads; chunk position swizzled by row
+                auto write = [&](int ps) {
                     int rl = lt & 31;
                     // opaque, so that neither the addresses below nor the scaled results are computed for all passes at once
                     asm volatile("" : "+v"(rl));
                     float sc = scale;
                     if constexpr (FP8) asm volatile("" : "+v"(sc));
-                    const int rs = rl % ROWS_PASS;
-                    const int pti = ps / (32 / ROWS_PASS);
-                    if (ROWS_PASS == 32 || (rl / ROWS_PASS) == ps % (32 / ROWS_PASS)) {
-                        auto put = [&](auto ti_c) {
-                            constexpr int ti = decltype(ti_c)::value;
+                    const int rs = rl % ROWS_PASS, slab = ps / HALVES;
+                    if (ROWS_PASS == 32 || (rl / ROWS_PASS) == ps % HALVES) {
+                        auto put = [&](auto slab_c) {
+                            constexpr int ti = decltype(slab_c)::value / CSLABS, tj0 = decltype(slab_c)::value % CSLABS * (CP / 32);
 #pragma unroll
-                            for (int tj = 0; tj < OTN; ++tj)
+                            for (int tj = 0; tj < CP / 32; ++tj)
 #pragma unroll
                                 for (int b = 0; b < 4; ++b) {
-                                    const int colw = tj * 32 + 8 * b + 4 * h;     // column inside the wave's part
-                                    f32x4 val = {acc[ti][tj][4 * b] * sc, acc[ti][tj][4 * b + 1] * sc,
-                                                 acc[ti][tj][4 * b + 2] * sc, acc[ti][tj][4 * b + 3] * sc};
+                                    const int colw = tj * 32 + 8 * b + 4 * h;     // column inside the slab
+                                    const f32x16& x = acc[ti][tj0 + tj];
+                                    f32x4 val = {x[4 * b] * sc, x[4 * b + 1] * sc, x[4 * b + 2] * sc, x[4 * b + 3] * sc};
                                     if constexpr (ST_ELEM == 4) {
                                         const int ch = colw >> 2;                  // 16-byte chunk (4 floats)
                                         *(PK_LDS f32x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16)) = val;
@@ -743,66 +769,97 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                                 }
                             // a different last statement in each case: the compiler would otherwise merge the cases into one
                             // that indexes the accumulators at run time, and move them to scratch memory
-                            asm volatile("; slab %0" : : "n"(ti));
+                            asm volatile("; slab %0" : : "n"(decltype(slab_c)::value));
                         };
-                        static_assert(OTM <= 4, "up to four slabs of 32 rows");
-                        if (pti == 0) put(std::integral_constant<int, 0>{});
-                        if constexpr (OTM > 1) if (pti == 1) put(std::integral_constant<int, 1>{});
-                        if constexpr (OTM > 2) if (pti == 2) put(std::integral_constant<int, 2>{});
-                        if constexpr (OTM > 3) if (pti == 3) put(std::integral_constant<int, 3>{});
-                    }
-                    // read back row-wise and store: lane -> (row = i*ROWS_INSTR + l / LANES_ROW, chunk = l % LANES_ROW).  All the
-                    // reads of a pass come first: a read behind the bounds check of its store would be waited for by itself.
-                    auto get = [&](int i) -> i32x4 {
-                        const int rr = i * ROWS_INSTR + rl0;
-                        if constexpr (ACT) {
-                            const f32x4 x0 = *(PK_LDS f32x4*)(stg + rr * ROW_BYTES + (((2 * cl) ^ (rr & (CH - 1))) * 16));
-                            const f32x4 x1 = *(PK_LDS f32x4*)(stg + rr * ROW_BYTES + (((2 * cl + 1) ^ (rr & (CH - 1))) * 16));
-                            return __builtin_bit_cast(i32x4, activate8(x0, x1));
-                        } else {
-                            return *(PK_LDS i32x4*)(stg + rr * ROW_BYTES + ((cl ^ (rr & (CH - 1))) * 16));
-                        }
-                    };
-                    auto out = [&](i32x4 val) {
-                        if (row < p_row_end && col < p_col_end) {
-                            uint64_t d = dp;
-                            if (IS_RS && (uint32_t)(row - own_row0) < (uint32_t)own_rows) d += own_delta;
-                            // reduce-scatter tiles are consumed by another kernel through a flag: write through
-                            if constexpr (IS_RS) store16_writethrough((void*)d, val);
-                            else __builtin_nontemporal_store(val, (i32x4*)d);
-                        }
-                        row += ROWS_INSTR;
-                        dp += dp_step;
-                    };
-                    if constexpr (ACT) {
-#pragma clang loop unroll(disable)
-                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) out(get(i));
-                    } else {
-                        i32x4 v[ROWS_PASS / ROWS_INSTR];
-#pragma unroll
-                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) v[i] = get(i);
-#pragma unroll
-                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) asm volatile("" : "+v"(v[i]));
-#pragma unroll
-                        for (int i = 0; i < ROWS_PASS / ROWS_INSTR; ++i) out(v[i]);
+                        static_assert(NSLABS <= 8, "up to eight slabs");
+                        if (slab == 0) put(std::integral_constant<int, 0>{});
+                        if constexpr (NSLABS > 1) if (slab == 1) put(std::integral_constant<int, 1>{});
+                        if constexpr (NSLABS > 2) if (slab == 2) put(std::integral_constant<int, 2>{});
+                        if constexpr (NSLABS > 3) if (slab == 3) put(std::integral_constant<int, 3>{});
+                        if constexpr (NSLABS > 4) if (slab == 4) put(std::integral_constant<int, 4>{});
+                        if constexpr (NSLABS > 5) if (slab == 5) put(std::integral_constant<int, 5>{});
+                        if constexpr (NSLABS > 6) if (slab == 6) put(std::integral_constant<int, 6>{});
+                        if constexpr (NSLABS > 7) if (slab == 7) put(std::integral_constant<int, 7>{});
                     }
                 };
-                if constexpr (ACT || (ST_ELEM == 4 && BM * BN < 256 * 256)) {
+                // read back row-wise: lane -> (row = i*ROWS_INSTR + l / LANES_ROW, chunk = l % LANES_ROW)
+                auto get = [&](int i) -> i32x4 {
+                    const int rr = i * ROWS_INSTR + rl0;
+                    if constexpr (ACT) {
+                        const f32x4 x0 = *(PK_LDS f32x4*)(stg + rr * ROW_BYTES + (((2 * cl) ^ (rr & (CH - 1))) * 16));
+                        const f32x4 x1 = *(PK_LDS f32x4*)(stg + rr * ROW_BYTES + (((2 * cl + 1) ^ (rr & (CH - 1))) * 16));
+                        return __builtin_bit_cast(i32x4, activate8(x0, x1));
+                    } else {
+                        return *(PK_LDS i32x4*)(stg + rr * ROW_BYTES + ((cl ^ (rr & (CH - 1))) * 16));
+                    }
+                };
+                auto store = [&](int ps, int i, i32x4 val) {
+                    const int row = row_w0 + (ps / HALVES / CSLABS) * 32 + (ps % HALVES) * ROWS_PASS + i * ROWS_INSTR + rl0;
+                    const int col = col_w0 + (ps / HALVES % CSLABS) * CP + cl * (16 / OUT_ELEM);
+                    uint64_t d = dst + (int64_t)row * dst_pitch + (int64_t)col * OUT_ELEM;
+                    if constexpr (!FULL) {
+                        if (row >= p_row_end || col >= p_col_end) return;
+                        if (IS_RS && (uint32_t)(row - own_row0) < (uint32_t)own_rows) d += own_delta;
+                    }
+                    // reduce-scatter tiles are consumed by another kernel through a flag: write through
+                    if constexpr (IS_RS) store16_writethrough((void*)d, val);
+                    else store16_stream((void*)d, val);
+                };
+                if constexpr (ACT) {
 #pragma clang loop unroll(disable)
-                    for (int ps = 0; ps < NPASS; ++ps) pass(ps);
+                    for (int ps = 0; ps < NPASS; ++ps) {
+                        write(ps);
+#pragma clang loop unroll(disable)
+                        for (int i = 0; i < NOUT; ++i) store(ps, i, get(i));
+                    }
                 } else {
-                    // unrolled: in a loop the compiler would round all accumulators ahead of it (bf16); a 256x256 tile's
-                    // workgroup runs it once per round, and the passes overlap
+                    // All the reads of a pass come before its stores (a read behind the bounds check of its store would be waited
+                    // for by itself) and before the next pass is written over them: a wave's LDS operations stay in order.
+                    auto pass = [&](int ps) {
+                        i32x4 v[NOUT];
 #pragma unroll
-                    for (int ps = 0; ps < NPASS; ++ps) pass(ps);
+                        for (int i = 0; i < NOUT; ++i) v[i] = get(i);
+                        if (ps + 1 < NPASS) write(ps + 1);
+#pragma unroll
+                        for (int i = 0; i < NOUT; ++i) asm volatile("" : "+v"(v[i]));
+#pragma unroll
+                        for (int i = 0; i < NOUT; ++i) store(ps, i, v[i]);
+                    };
+                    write(0);
+                    if constexpr (ST_ELEM == 4 && BM * BN < 256 * 256) {
+#pragma clang loop unroll(disable)
+                        for (int ps = 0; ps < NPASS; ++ps) pass(ps);
+                    } else {
+                        // unrolled: in a loop the compiler would round all accumulators ahead of it (bf16); a 256x256 tile's
+                        // workgroup runs it once per round
+#pragma unroll
+                        for (int ps = 0; ps < NPASS; ++ps) pass(ps);
+                    }
                 }
             };
+            using T = std::true_type;
+            using F = std::false_type;
+            constexpr bool BIG = BM * BN == 256 * 256 && !SK;    // shapes that run many rounds
+            bool full = BIG && p_row0 + BM <= p_row_end && p_col0 + BN <= p_col_end;
             if constexpr (IS_RS) {
-                emit(std::false_type{});
+                if (full && own_rows > 0) {                  // all rows own, none, or (not full) some of them
+                    const bool all = p_row0 >= own_row0 && p_row_end <= own_row0 + own_rows;
+                    const bool none = p_row_end <= own_row0 || p_row0 >= own_row0 + own_rows;
+                    if (all) dst += own_delta;
+                    full = all || none;
+                }
+                if (BIG && full) emit(F{}, T{});
+                else emit(F{}, F{});
             } else {
-                if (g.act != PK_ACT_NONE) emit(std::true_type{});
-                else emit(std::false_type{});
+                if (g.act != PK_ACT_NONE) {
+                    if (BIG && full) emit(T{}, T{});
+                    else emit(T{}, F{});
+                } else {
+                    if (BIG && full) emit(F{}, T{});
+                    else emit(F{}, F{});
+                }
             }
+            p_full = full;
         }
         if (!have) break;
 
@@ -813,10 +870,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-        if (p_q < 0 && seg_ktiles >= NS) {
+        bool stores_pending = false;                     // the previous tile's stores may not be complete yet
+        if (p_q < 0 && my_ktiles >= NS) {
             // the workgroup's first tile: its first k-tile has landed, the others follow
             __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 1) * NL));
             __syncthreads();
+        } else if (DEFER && p_full && p_q >= 0 && my_ktiles >= 2 * NS) {
+            // the first NS k-tiles have landed: they were issued before the previous tile's EPI_STORES stores, and the counter
+            // goes down in order
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(EPI_STORES));
+            __syncthreads();
+            stores_pending = true;
         } else {
             // the first k-tiles have landed; the previous tile's stores (same counter) are complete as well
             __builtin_amdgcn_s_waitcnt(PK_WAIT_VMCNT0);
@@ -837,8 +901,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         auto kstep = [&](const frag_t (&ca)[TM], const frag_t (&cb)[TN], frag_t (&na)[TM], frag_t (&nb)[TN],
                          PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto loads_c) {
             constexpr bool LOADS = decltype(loads_c)::value;
-            constexpr int NM = TM * TN, H = NM / 2;
-            static_assert(NM >= 2, "a k-step has at least two MFMAs");
+            constexpr int NM = TM * TN, H = NM >= 2 ? NM / 2 : 1;
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 mfma_one(i / TN, i % TN, ca, cb);
@@ -867,12 +930,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto ktile = [&](int kt, int nkt, auto loads_c, auto par_c) {
-            constexpr bool LOADS = decltype(loads_c)::value;
+        // LANDED: k-tile kt+1 is known to be there.
+        auto ktile = [&](int kt, int nkt, auto loads_c, auto par_c, auto landed_c) {
+            constexpr bool LOADS = decltype(loads_c)::value, LANDED = decltype(landed_c)::value;
             constexpr int P0 = decltype(par_c)::value;   // fragment set that holds this k-tile's first fragments
             const int sidx = kt % NS;
-            PK_LDS char* st = lds + sidx * STAGE;
-            PK_LDS char* nx = lds + (sidx + 1 == NS ? 0 : sidx + 1) * STAGE;
+            PK_LDS char* st = ring + sidx * STAGE;
+            PK_LDS char* nx = ring + (sidx + 1 == NS ? 0 : sidx + 1) * STAGE;
             // fragment set `par` is consumed, the other one refilled
             auto step = [&](auto par, PK_LDS char* rd_stage, int rd_kk, auto lds_c) {
                 if constexpr (decltype(par)::value) kstep(af1, bf1, af0, bf0, rd_stage, rd_kk, sidx, lds_c);
@@ -882,19 +946,24 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             if constexpr (KS >= 3) step(std::integral_constant<int, P0 ^ 1>{}, st, 2, std::false_type{});
             if constexpr (KS >= 4) step(std::integral_constant<int, P0>{}, st, 3, std::false_type{});
             static_assert(KS <= 4, "at most four k-steps per k-tile");
-            static_assert(NS >= 2 && NS <= 6, "ring of 2 to 6 stages");
-            if constexpr (LOADS) {
+            static_assert(NS >= 2, "a ring has two stages or more");
+            if constexpr (LANDED) {
+                __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+            } else if constexpr (LOADS) {
                 __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * NL));
             } else {
                 // at the end of the range: of the k-tiles left, only those behind the next one may still be in flight
                 const int left = nkt - kt;
-                if (left >= NS) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * NL));
-                else if (NS > 5 && left == 5) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(3 * NL));
-                else if (NS > 4 && left == 4) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * NL));
-                else if (NS > 3 && left == 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(NL));
-                else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+                auto wait = [&](auto self, auto j_c) -> void {
+                    constexpr int J = decltype(j_c)::value;
+                    if constexpr (J < 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+                    else if (left >= J) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((J - 2) * NL));
+                    else self(self, std::integral_constant<int, J - 1>{});
+                };
+                wait(wait, std::integral_constant<int, NS>{});
             }
-            __syncthreads();
+            if constexpr (PRIV) asm volatile("" : : : "memory");   // the loads have written the LDS behind the compiler's back
+            else __syncthreads();
             step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, loads_c);
         };
         // the k-tiles of one pipeline fill: the first NS are in flight or landed, stage 0 holds the first
@@ -903,13 +972,34 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             using F = std::false_type;
             using E = std::integral_constant<int, 0>;    // k-tile starts on fragment set 0
             using O = std::integral_constant<int, 1>;    // ... on set 1
-            load_frags(lds, 0, af0, bf0);
+            load_frags(ring, 0, af0, bf0);
             int kt = 0;
+            if (DEFER && stores_pending) {
+                // the first NS k-tiles are there; the barrier of k-tile NS-1 waits for k-tile NS, whose loads were issued behind
+                // the previous tile's stores: they are complete then
+                static_assert(!DEFER || KS % 2 == 0 || NS % 2 == 0, "the main loop starts on set 0");
+                if constexpr (KS % 2 == 0) {
+#pragma clang loop unroll(disable)
+                    for (; kt < NS - 1; ++kt) ktile(kt, nkt, T{}, E{}, T{});
+                    ktile(kt, nkt, T{}, E{}, F{});
+                    ++kt;
+                } else {
+#pragma clang loop unroll(disable)
+                    for (; kt < NS - 2; kt += 2) {
+                        ktile(kt, nkt, T{}, E{}, T{});
+                        ktile(kt + 1, nkt, T{}, O{}, T{});
+                    }
+                    ktile(kt, nkt, T{}, E{}, T{});
+                    ktile(kt + 1, nkt, T{}, O{}, F{});
+                    kt += 2;
+                }
+                signal_prev();
+            }
             if constexpr (KS % 2 == 0) {
 #pragma clang loop unroll(disable)
-                for (; kt + NS < nkt; ++kt) ktile(kt, nkt, T{}, E{});
+                for (; kt + NS < nkt; ++kt) ktile(kt, nkt, T{}, E{}, F{});
 #pragma clang loop unroll(disable)
-                for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{});
+                for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{});
             } else {
                 // odd k-steps per k-tile: the starting set alternates, so k-tiles go in pairs (with 64-byte k-tiles nkt is even:
                 // the host admits only k ranges of whole 128-byte units)
@@ -917,18 +1007,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 static_assert(!EVEN || NS % 2 == 0, "pairs of k-tiles need an even ring");
 #pragma clang loop unroll(disable)
                 for (; kt + (EVEN ? 0 : 1) + NS < nkt; kt += 2) {
-                    ktile(kt, nkt, T{}, E{});
-                    ktile(kt + 1, nkt, T{}, O{});
+                    ktile(kt, nkt, T{}, E{}, F{});
+                    ktile(kt + 1, nkt, T{}, O{}, F{});
                 }
                 if (!EVEN && kt + NS < nkt) {            // one more with loads: the rest starts on set 1
-                    ktile(kt, nkt, T{}, E{});
-                    ktile(kt + 1, nkt, F{}, O{});
+                    ktile(kt, nkt, T{}, E{}, F{});
+                    ktile(kt + 1, nkt, F{}, O{}, F{});
                     kt += 2;
                 }
 #pragma clang loop unroll(disable)
                 for (; kt < nkt; kt += 2) {
-                    ktile(kt, nkt, F{}, E{});
-                    if (EVEN || kt + 1 < nkt) ktile(kt + 1, nkt, F{}, O{});
+                    ktile(kt, nkt, F{}, E{}, F{});
+                    if (EVEN || kt + 1 < nkt) ktile(kt + 1, nkt, F{}, O{}, F{});
                 }
             }
         };
@@ -961,15 +1051,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 __builtin_amdgcn_s_waitcnt(PK_WAIT_VMCNT0);
                 __syncthreads();
             }
-            run_ktiles(seg_ktiles);
+            run_ktiles(my_ktiles);
         }
         if constexpr (WK > 1) {
             // The groups' accumulators are added in group order through the LDS (the ring is free: every wave passed the barrier
             // of the last k-tile after its last fragment reads).  Group r ends up with blocks [r*OB, (r+1)*OB) of the sub-tile,
             // in acc[0..OTM)[0..OTN).
+            if constexpr (PRIV) __syncthreads();             // every wave is through with its ring
             const int sub = w % (WM * WN);
             auto piece = [&](int from, int to, int i) {      // LDS address of block i of those that group `from` hands to group `to`
-                return lds + ((((sub * WK + to) * (WK - 1) + (from < to ? from : from - 1)) * OB + i) * 4096) + l * 16;
+                return lds + ((((sub * NOWN + to) * (WK - 1) + (from < to ? from : from - 1)) * OB + i) * 4096) + l * 16;
             };
 #pragma unroll
             for (int gr = 0; gr < WK; ++gr)
@@ -987,7 +1078,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 }
             __syncthreads();
 #pragma unroll
-            for (int gr = 0; gr < WK; ++gr)
+            for (int gr = 0; gr < NOWN; ++gr)
                 if (wk == gr) {
 #pragma unroll
                     for (int i = 0; i < OB; ++i) {
