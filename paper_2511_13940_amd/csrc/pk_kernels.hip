@@ -873,7 +873,7 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     const bool sk = ws && !bt && !k_chunks && plan_slots > grid && plan_slots % grid != 0 && a.ktiles >= 16 && grid <= (int)(kWsFlagBytes / 4);
     if (!sk) {
         int64_t best = INT64_MAX;
-        for (int id = 0; id < N_TILES; ++id) {
+        for (int id = 0; id < (k_chunks ? T32x64 : N_TILES); ++id) {
             bool span;
             const int64_t cost = tile_cost(id, fp8, tiles_of(id, &span), a.ktiles, grid);
             if (cost < best) {

@@ -4,13 +4,15 @@
 
 namespace pk {
 
-// A tile shape; the last one serves the stream-K tail only (its pieces are exchanged between whole workgroups, WK = 1).
-enum Tile { T256x256, T256x128, T128x256, T128x128, T128x64, T64x64, N_TILES, T128x128_SK = N_TILES };
+// A tile shape.  From T32x64 on the waves take k-tiles of their own (WM = WN = 1: not for the all-gather of column chunks); the
+// last one serves the stream-K tail only (its pieces are exchanged between whole workgroups, WK = 1).
+enum Tile { T256x256, T256x128, T128x256, T128x128, T128x64, T64x64, T32x64, T32x32, N_TILES, T128x128_SK = N_TILES };
 
 struct TileDim {
     int bm, bn;
 };
-constexpr TileDim kTileDim[N_TILES + 1] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}, {128, 64}, {64, 64}, {128, 128}};
+constexpr TileDim kTileDim[N_TILES + 1] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}, {128, 64},
+                                           {64, 64},   {32, 64},   {32, 32},   {128, 128}};
 
 // waves (WM x WN x WK), k-tile bytes and ring stages of a tile shape.  bf16: the smaller tiles split the k-steps of a k-tile
 // over two groups of waves (WK = 2), which keeps the wave's sub-tile large and with it the LDS reads per flop low: 64 x 64
@@ -18,6 +20,10 @@ constexpr TileDim kTileDim[N_TILES + 1] = {{256, 256}, {256, 128}, {128, 256}, {
 // only two k-steps in a 128-byte k-tile and half as many fragment reads per flop: there the split gains nothing.
 // A k-contiguous second operand is fetched as one piece per row and k-tile, and 64-byte pieces use half of every 128-byte line
 // they touch: 128-byte k-tiles throughout.
+// The two smallest serve calls of a few dozen rows, which stream the second operand past a handful of flops: what bounds them is
+// how many compute units load at once, and the time from a load to the MFMA behind it.  A wave that takes every fourth k-tile
+// through a ring of its own needs no barrier per k-tile (64 x 3584 x 8192, second operand k-contiguous: 64x32 tiles 19.3 us with
+// the ring shared, 19.0 us without; 32x32 tiles 15.4 us, 64x64 tiles 24.0 us).
 struct TileWaves {
     int wm, wn, wk, kb, ns;
 };
@@ -29,27 +35,30 @@ constexpr TileWaves tile_waves(int tile, bool fp8, bool bt) {
         case T128x128: return fp8 ? TileWaves{4, 2, 1, 128, 4} : TileWaves{2, 2, 2, 128, 4};
         case T128x64: return fp8 ? TileWaves{2, 2, 1, 128, 6} : TileWaves{2, 2, 2, 128, 4};
         case T64x64: return fp8 ? TileWaves{2, 1, 1, 128, 6} : TileWaves{2, 1, 2, 128, 6};
+        case T32x64: return TileWaves{1, 1, 4, 128, 3};
+        case T32x32: return TileWaves{1, 1, 4, 128, 4};
         default: return TileWaves{2, 2, 1, 128, 2};      // T128x128_SK
     }
 }
 
 // Estimated time, in nanoseconds x grid, of `tiles` tiles over `kt` 128-byte k-tiles on `grid` workgroups: rounds x (fixed part
 // + k-tile time), the k-tile time rising with the share of the compute units at work (clock, L2 and memory traffic).  The
-// figures are fitted to 24 shapes of bf16 and 7 of fp8 GEMMs from 64 x 3584 x 8192 to 8192 x 8192 x 3584, timed with every
-// tile shape: the tile of least estimated time was the fastest one, or within 3.2% of it, on all of them.
+// figures are fitted to 36 shapes of bf16 and 17 of fp8 GEMMs from 16 x 3584 x 8192 to 8192 x 8192 x 3584, timed with every
+// tile shape: the tile of least estimated time was the fastest one, or within 3.2% of it, on all of them (and on 17 shapes with
+// a k-contiguous second operand).
 struct TileCost {
     int lo, hi, fixed;        // ns per k-tile with few and with all compute units at work, ns per tile
 };
 constexpr TileCost kTileCost[2][N_TILES] = {
-    {{771, 1583, 6660}, {449, 825, 5610}, {536, 901, 3320}, {292, 464, 3640}, {216, 322, 2020}, {180, 214, 2440}},
-    {{754, 1401, 6070}, {442, 770, 4580}, {509, 749, 4030}, {313, 472, 2620}, {279, 354, 2020}, {215, 281, 1820}}};
+    {{765, 1584, 6699}, {445, 825, 5628}, {537, 901, 3314}, {293, 464, 3635}, {197, 321, 2071}, {170, 217, 2498}, {150, 176, 1767}, {119, 151, 1343}},
+    {{754, 1401, 6071}, {442, 770, 4585}, {509, 749, 4034}, {313, 472, 2616}, {277, 376, 1982}, {245, 295, 1913}, {196, 248, 1638}, {162, 220, 1349}}};
 inline int64_t tile_cost(int tile, bool fp8, int tiles, int kt, int grid) {
     const TileCost& c = kTileCost[fp8 ? 1 : 0][tile];
     const int rounds = (int)((((unsigned)tiles + 7) / 8 * 8 + grid - 1) / (unsigned)grid);
     return (int64_t)rounds * grid * (c.fixed + (int64_t)kt * c.lo) + (int64_t)kt * (c.hi - c.lo) * tiles;
 }
-inline int tiles_across(int64_t size, int tile_size) {       // size / tile_size, rounded up; tile_size is 64, 128 or 256
-    const int shift = tile_size == 64 ? 6 : tile_size == 128 ? 7 : 8;
+inline int tiles_across(int64_t size, int tile_size) {       // size / tile_size, rounded up; tile_size is 32, 64, 128 or 256
+    const int shift = tile_size == 32 ? 5 : tile_size == 64 ? 6 : tile_size == 128 ? 7 : 8;
     return (int)((size + tile_size - 1) >> shift);
 }
 
@@ -66,7 +75,7 @@ static pk_status launch_kernel(GemmArgs a, int grid, hipStream_t stream) {
     constexpr TileWaves W = tile_waves(TILE, FP8, BT);
     static std::atomic<uint64_t> configured{0};              // bit d = dynamic LDS size raised on device d
     auto kern = gemm_kernel<BM, BN, W.wm, W.wn, W.wk, W.kb, W.ns, FP8, EPI, BT, SK>;
-    constexpr int lds = gemm_lds_bytes<BM, BN, W.kb, W.ns>();
+    constexpr int lds = gemm_lds_bytes<BM, BN, W.kb, W.ns * (W.wm * W.wn == 1 ? W.wk : 1)>();
     static_assert(lds <= 160 * 1024, "a compute unit has 160 KB of LDS");
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return PK_ERR_HIP;
@@ -113,8 +122,13 @@ pk_status launch_gemm(GemmArgs a, int tile, bool fp8, bool bt, bool sk, int grid
         case T128x128: return go(std::integral_constant<int, T128x128>{});
         case T128x64: return go(std::integral_constant<int, T128x64>{});
         case T64x64: return go(std::integral_constant<int, T64x64>{});
-        default: return PK_ERR_ARG;
+        default: break;
     }
+    if constexpr (EPI != EPI_AGK) {
+        if (tile == T32x64) return go(std::integral_constant<int, T32x64>{});
+        if (tile == T32x32) return go(std::integral_constant<int, T32x32>{});
+    }
+    return PK_ERR_ARG;
 }
 #endif  // PK_DEFINE_LAUNCH
 

@@ -18,17 +18,21 @@ U32 = 2.0 ** -24
 
 
 @pytest.mark.parametrize("dtype,P,rank,M,N,kl,layout", [
-    ("bf16", 8, 3, 1024, 4104, 1600, "kn"),    # 256x128: two flags per tile, the last column tile 8 wide
+    ("bf16", 8, 3, 1024, 4104, 2560, "kn"),    # 256x128: two flags per tile, the last column tile 8 wide
     ("bf16", 2, 1, 2800, 4104, 128, "kn"),     # 256x256: four flags per tile, shards of 11 flag rows (odd)
     ("bf16", 8, 5, 8 * 96, 8200, 512, "nk"),   # 128x256 over shards of 96 rows
     ("bf16", 5, 4, 5 * 300, 1544, 128, "kn"),  # 128x128, flags behind the GEMM: tiles cross shards of 300 rows
     ("bf16", 4, 0, 2048, 1024, 448, "nk"),     # 128x64: finer than a flag, seven k-tiles in a ring of four
-    ("bf16", 2, 1, 256, 248, 64, "kn"),        # one k-tile
-    ("bf16", 8, 7, 64, 520, 4032, "kn"),       # 64x64: shards of 8 rows, one tile row for all of them
+    ("bf16", 2, 1, 700, 1480, 832, "kn"),      # 64x64 or 128x64, 13 k-tiles
+    ("bf16", 4, 2, 4 * 75, 1000, 1088, "nk"),  # 32x64: shards of 75 rows, 17 k-tiles over four waves
+    ("bf16", 2, 1, 256, 248, 64, "kn"),        # 32x32: one k-tile, three of the four waves without work
+    ("bf16", 8, 7, 64, 520, 4032, "kn"),       # 32x32: shards of 8 rows, 63 k-tiles
+    ("bf16", 3, 1, 6000, 5008, 512, "kn"),     # 256x256 in two rounds: stores still under way in the next main loop, or not (edges)
+    ("fp8", 2, 0, 4600, 8208, 512, "kn"),      # the same in three rounds
     ("fp8", 8, 2, 8 * 33, 4112, 256, "kn"),    # 128x64
     ("fp8", 2, 0, 2000, 4112, 256, "nk"),      # 256x256: shards of 1000 rows
     ("fp8", 3, 2, 3 * 500, 2064, 2176, "kn"),  # 128x128 or larger, 17 k-tiles
-    ("fp8", 1, 0, 130, 144, 1152, "kn"),       # 64x64, nine k-tiles in a ring of six
+    ("fp8", 1, 0, 130, 144, 1152, "kn"),       # 32x32, nine k-tiles over four waves
 ])
 def test_gemm_rs(dtype, P, rank, M, N, kl, layout):
     inp = wl.gemm_rs_inputs(P, M, N, P * kl, dtype, rank, seed=M + N)
@@ -68,12 +72,16 @@ def test_gemm_rs_cols(P, rank, M, N, kl, dtype):
 
 
 @pytest.mark.parametrize("dtype,P,rank,M,N,K,layout,act", [
-    ("bf16", 8, 2, 1024, 8 * 4104, 1600, "kn", "none"),   # 256x128, one tile covers two chunks of 128 rows
+    ("bf16", 8, 2, 1024, 8 * 4104, 2560, "kn", "none"),   # 256x128, one tile covers two chunks of 128 rows
     ("bf16", 3, 1, 2100, 3 * 2056, 192, "nk", "relu"),    # 128x256, chunks of 700 rows
     ("bf16", 8, 6, 8 * 189, 8 * 1720, 576, "kn", "silu"), # 128x128 across chunks of 189 rows
     ("bf16", 4, 3, 1000, 4 * 1544, 320, "nk", "gelu_tanh"),  # 128x64
     ("bf16", 64, 40, 64 * 3, 64 * 72, 1024, "kn", "none"),   # 64 chunks of 3 rows: a tile waits for 21 and more of them
-    ("bf16", 2, 0, 6000, 2 * 1800, 64, "kn", "silu"),     # several rounds, chunk by chunk
+    ("bf16", 2, 0, 6000, 2 * 1800, 64, "kn", "silu"),     # 256x256
+    ("bf16", 2, 1, 9000, 2 * 2312, 256, "kn", "gelu_tanh"),  # 256x256 in two rounds, chunk by chunk
+    ("bf16", 8, 3, 64, 8 * 1000, 2048, "kn", "silu"),     # 32x32
+    ("bf16", 4, 3, 4 * 25, 4 * 4000, 320, "nk", "none"),  # 32x64, five k-tiles over four waves
+    ("fp8", 8, 0, 24, 8 * 3600, 896, "kn", "none"),       # 32x32, seven k-tiles
     ("fp8", 5, 2, 5 * 77, 5 * 1040, 640, "kn", "gelu_tanh"),
     ("fp8", 8, 7, 2048, 8 * 3600, 256, "nk", "silu"),
 ])
