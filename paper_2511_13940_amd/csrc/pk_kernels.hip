@@ -23,7 +23,8 @@ struct ReduceArgs {
     uint32_t* flags_out;      // late_signal only
     int32_t late_signal;      // the GEMM in front of this kernel left its flags unpublished (its tiles are finer than a flag)
     int32_t P, rows, n;
-    int32_t tile_m, tile_n, tiles_n, sub, rows_sub;
+    int32_t tile_m, tile_n, tiles_n, rows_sub;
+    FastDiv by_sub, by_tiles_n, by_cpr, by_cpr_last;   // work items of a flag tile; tile columns; 8-element chunks per tile row
     int64_t slot_elems, flags_per_slot;
     uint32_t epoch;
     uint32_t* status;
@@ -49,9 +50,12 @@ template <int PT, bool S16, bool AR, bool NARROW = false>
 __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     const int tid = threadIdx.x;
     const int P = PT > 0 ? PT : r.P;
-    const int tile = blockIdx.x / r.sub;
-    const int sb = blockIdx.x - tile * r.sub;
-    const int tmi = tile / r.tiles_n, tc = tile - tmi * r.tiles_n;
+    const int tile = r.by_sub.div(blockIdx.x);
+    const int sb = blockIdx.x - tile * r.by_sub.d;
+    const int tmi = r.by_tiles_n.div(tile), tc = tile - tmi * r.tiles_n;
+    const int row_start = tmi * r.tile_m + sb * r.rows_sub;
+    const int row_stop = min(min(row_start + r.rows_sub, (tmi + 1) * r.tile_m), r.rows);
+    if (row_start >= row_stop) return;               // below the last row of the shard (never the first work item of a tile)
 
     // `signal` for the tiles of the GEMM in front: it has ended, so everything it wrote (through) is in memory
     const int own = r.late_signal ? r.rank : -1;
@@ -87,10 +91,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
         return __builtin_amdgcn_make_buffer_rsrc((char*)r.partials + (int64_t)p * r.slot_elems * SLOT_ELEM, 0, (int)slot_bytes,
                                                  0x00020000);
     };
-    const int row_start = tmi * r.tile_m + sb * r.rows_sub;
-    const int row_stop = min(min(row_start + r.rows_sub, (tmi + 1) * r.tile_m), r.rows);
     const int col0 = tc * r.tile_n;
-    const int cpr = min(r.tile_n, r.n - col0) >> 3;          // 8-element chunks per row of this tile
+    const FastDiv by_cpr = tc == r.tiles_n - 1 ? r.by_cpr_last : r.by_cpr;
+    const int cpr = by_cpr.d;                                // 8-element chunks per row of this tile
     const int total = (row_stop - row_start) * cpr;
     // bf16 -> fp32 of the 8 values of one 16-byte load, added to (s0, s1)
     auto add16 = [](f32x4& s0, f32x4& s1, i32x4 v) {
@@ -110,8 +113,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     if constexpr (NARROW) {
         static_assert(!NARROW || (!S16 && !AR && PT > 0), "the narrow form is built for fp32 slots, compile-time P, no all-reduce");
         const int cpr4 = cpr * 2;
+#pragma clang loop unroll(disable)
         for (int idx = tid; idx < total * 2; idx += 256) {
-            const int rr = idx / cpr4, cc = idx - rr * cpr4;
+            const int rr = by_cpr.div(idx >> 1), cc = idx - rr * cpr4;
             const int64_t off = (int64_t)(row_start + rr) * r.n + col0 + cc * 4;
             const uint32_t boff = (uint32_t)(off * 4);
             f32x4 v[PT > 0 ? PT : 1];
@@ -126,8 +130,10 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
         }
         return;
     }
+    // (not unrolled: 64 registers at most, so that the kernel fits beside a GEMM workgroup; 48 for bf16 slots)
+#pragma clang loop unroll(disable)
     for (int idx = tid; idx < total; idx += 256) {
-        const int rr = idx / cpr, cc = idx - rr * cpr;
+        const int rr = by_cpr.div(idx), cc = idx - rr * cpr;
         const int64_t off = (int64_t)(row_start + rr) * r.n + col0 + cc * 8;
         const uint32_t boff = (uint32_t)(off * SLOT_ELEM);
         f32x4 s0, s1;
@@ -139,7 +145,11 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
 #pragma unroll
                 for (int p = 0; p < PT; ++p) v[p] = __builtin_amdgcn_raw_buffer_load_b128(slot(p), boff, 0, kCoherentStream);
 #pragma unroll
-                for (int p = 0; p < PT; ++p) add16(s0, s1, v[p]);
+                for (int p = 0; p < PT; ++p) {
+                    // one slot after the other: unpacked all at once they took 76 registers, too many beside the fp8 GEMM
+                    __builtin_amdgcn_sched_barrier(0);
+                    add16(s0, s1, v[p]);
+                }
             } else {
                 for (int p = 0; p < P; ++p) add16(s0, s1, __builtin_amdgcn_raw_buffer_load_b128(slot(p), boff, 0, kCoherentStream));
             }
@@ -177,7 +187,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
             __builtin_nontemporal_store(o, (bf16x8*)(r.out + off));
         }
     }
-    if (AR && row_start < r.rows) {
+    if (AR) {
         // `signal` per destination for this 8-row block: every wave waits for its stores, then one lane per rank
         __builtin_amdgcn_s_waitcnt(PK_WAIT_VMCNT0);
         __syncthreads();
@@ -763,7 +773,12 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         r.tile_n = pl.tile_n;
         r.tiles_n = pl.tiles_n;
         r.rows_sub = 8;                       // 8 rows x tile_n columns x P slots per work item
-        r.sub = pl.tile_m / r.rows_sub;
+        // work items of a flag tile; a shard lower than a flag tile has fewer (a decode step's 8 rows: one instead of 16)
+        const int sub = (int)ceil_div(pl.tiles_m == 1 ? rows : pl.tile_m, r.rows_sub);
+        r.by_sub.set(sub);
+        r.by_tiles_n.set(pl.tiles_n);
+        r.by_cpr.set(pl.tile_n / 8);
+        r.by_cpr_last.set((slot_cols - (int64_t)(pl.tiles_n - 1) * pl.tile_n) / 8);
         r.slot_elems = rows * slot_cols;
         r.flags_per_slot = pl.flags_per_slot;
         r.epoch = epoch;
@@ -776,7 +791,7 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
             r.ar_flags_out = ar->ar_flags_out;
             r.ar_flags_per_slot = ar->ar_flags_per_slot;
         }
-        const int grid = (int)(pl.flags_per_slot * r.sub);   // one workgroup per work item
+        const int grid = (int)(pl.flags_per_slot * sub);   // one workgroup per work item
         hipStream_t s = reduce_stream;
         auto launch = [&](auto s16, auto armode) {
             constexpr bool S16 = decltype(s16)::value, AR = decltype(armode)::value;
