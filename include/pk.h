@@ -111,13 +111,13 @@ typedef struct {
 } pk_plan;
 
 /*
- * Workspace (pk_gemm_rs, pk_ag_gemm; optional).  When the tiles do not fill a whole number of rounds on the compute
- * units (448 tiles on 256 units), the k range of the left-over tiles is shared out evenly over all workgroups
+ * Workspace (pk_gemm_rs, pk_ag_gemm; optional).  When a plan's 256 x 256 tiles do not fill a whole number of rounds on the
+ * compute units (448 tiles on 256 units), the k range of the left-over tiles is shared out evenly over all workgroups
  * (paper section 3.1.3: the schedule depends on the problem size) and workgroups hand partial accumulator tiles to
  * one another through this memory.  Layout: PK_WS_FLAG_BYTES of ready flags, then one fp32 tile per workgroup.  The
  * caller zeroes the flag bytes once; afterwards the workspace belongs to one call site: its epochs must grow from
  * call to call, and two calls that may run at the same time must not share it.  workspace = NULL: whole tiles only (also
- * with PK_B_K_CONTIGUOUS and with bf16 slots, for which the tail is not built).
+ * with PK_B_K_CONTIGUOUS, with bf16 slots and with plans of 128 x 128 tiles, for which the tail is not built).
  * A workspace smaller than plan.workspace_bytes may be rejected with PK_ERR_ARG.
  */
 #define PK_WS_FLAG_BYTES 4096

@@ -421,8 +421,19 @@ static int schedule_grid(int slots, int comm_cus) {
     return even < grid ? even : grid;
 }
 
-// Launches a GEMM whose tile space is set up in `a`: with a workspace and a last round that is not full, with the stream-K tail
-// (`ws`: only for tile shapes that have one), otherwise whole tiles.
+// Whether a workspace takes a launch of `slots` tile slots to the stream-K tail (where the plan's tile is 256 x 256), and whether
+// the given one is too small for it.  Plans with 128 x 128 tiles take no tail: there the choice among all tile shapes fills the
+// compute units better than a tail of 128 x 128 tiles did (4096 x 14336 x 4096 over 8 ranks: 60 us against 91 us), and a workspace
+// is only checked for its size.
+static bool sk_applies(int64_t slots, int grid, int64_t ktiles) {
+    return slots > grid && slots % grid != 0 && ktiles >= 16 && grid <= (int)(kWsFlagBytes / 4);
+}
+static bool sk_too_small(int64_t slots, int grid, int64_t ktiles, int tile, size_t ws_bytes) {
+    return sk_applies(slots, grid, ktiles) && ws_bytes < kWsFlagBytes + (size_t)grid * tile * tile * 4;
+}
+
+// Launches a GEMM whose tile space is set up in `a`: with a workspace (256 x 256 tiles only) and a last round that is not full, with
+// the stream-K tail, otherwise whole tiles.
 template <int EPI>
 static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt, void* ws, size_t ws_bytes, hipStream_t stream) {
     const int bm = kTileDim[tile].bm, bn = kTileDim[tile].bn;
@@ -433,15 +444,15 @@ static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt
     const int grid = max_grid(comm_cus);
     const int rem = slots % grid;
     a.sk_dp_slots = slots;
-    if (ws && slots > grid && rem != 0 && a.ktiles >= 16 && grid <= (int)(kWsFlagBytes / 4)) {
+    if (ws && sk_applies(slots, grid, a.ktiles)) {
         // With a workspace every compute unit works to the end: whole rounds of tiles, then the k range of the left-over
         // tiles shared out evenly (448 slots on 256 CUs: 256 whole tiles, then 192 tiles as 256 pieces of 3/4 tile).
-        if (ws_bytes < kWsFlagBytes + (size_t)grid * bm * bn * 4) return PK_ERR_ARG;
+        if (sk_too_small(slots, grid, a.ktiles, 256, ws_bytes)) return PK_ERR_ARG;
         a.sk_dp_slots = slots - rem;
         a.ws_flags = (uint32_t*)ws;
         a.ws_tiles = (char*)ws + kWsFlagBytes;
         if (a.ws_epoch == 0) a.ws_epoch = a.epoch;     // a caller's workspace follows the caller's epochs
-        return launch_gemm<EPI>(a, tile == T256x256 ? T256x256 : T128x128_SK, fp8, bt, true, grid, stream);
+        return launch_gemm<EPI>(a, tile, fp8, bt, true, grid, stream);
     }
     return launch_gemm<EPI>(a, tile, fp8, bt, false, schedule_grid(slots, comm_cus), stream);
 }
@@ -583,6 +594,25 @@ struct AllReduceOut {
     int64_t ar_flags_per_slot;
 };
 
+// Tile rows in the first part of an overlapped GEMM + reduce-scatter: the own block's rows rounded up to whole bands of 4, then as
+// many more bands (up to 7) as waste the least of its last round.  0: no second part left, one launch, reduce afterwards.
+static int first_part(int own_rows, int all_rows, int tiles_n, int grid) {
+    const int band = 4;
+    int best = 0;
+    double best_waste = 2.0;
+    for (int k = 0; k < 8; ++k) {
+        const int r1 = (int)ceil_div(own_rows, band) * band + k * band;
+        if (r1 >= all_rows) break;
+        const int64_t t1 = (int64_t)r1 * tiles_n;
+        const double waste = (double)(ceil_div(t1, grid) * grid - t1) / grid + 0.02 * k;
+        if (waste < best_waste) {
+            best_waste = waste;
+            best = r1;
+        }
+    }
+    return best;
+}
+
 // GEMM + reduce-scatter; with `ar` the reduce phase also hands the reduced rows to every rank (all-reduce)
 static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype dt,
                               const void* A_local, const void* B_local, const float* scale_a, const float* scale_b,
@@ -618,11 +648,35 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     const int n_blks = cols ? pl.tiles_m : P * pl.tiles_m;      // row blocks of the ready flags
     const int grid = max_grid(comm_cus);
 
+    // Overlapped reduce: the GEMM is launched in two parts, the tile rows of this rank's own block (plus as many of the
+    // next ranks' as fill whole rounds) and the rest; the reduce runs on the library's second stream beside the second
+    // part: its workgroups use no LDS and few enough registers to sit next to a GEMM workgroup.  It waits for nothing
+    // the second part produces, so whichever of the two the hardware places first, both finish.
+    bool overlap = (phases & PK_PHASE_OVERLAP) && do_gemm && do_reduce && !ar && !cols && P > 1;
+    if (overlap) {
+        // a stream that is being captured into a graph takes the second stream along only if that one exists already
+        // (it is created by the first eager call with the flag): no stream is created in the middle of a capture
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) return PK_ERR_HIP;
+        if (cap != hipStreamCaptureStatusNone) {
+            std::lock_guard<std::mutex> guard(side_lock);
+            int dev = 0;
+            if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return PK_ERR_HIP;
+            if (!side_streams[dev].ready) overlap = false;
+        }
+    }
+    if (do_gemm && ws && pl.tile_m != 256 && !bt && !bf16_slots) {
+        const int plan_rows = P * pl.tiles_m, kt = (int)(pl.local_k / (fp8 ? 128 : 64));
+        const int first = overlap ? first_part(pl.tiles_m, plan_rows, pl.tiles_n, grid) : 0;
+        for (int n_rows : {first, plan_rows - first})
+            if (sk_too_small(ceil_div((int64_t)n_rows * pl.tiles_n, 8) * 8, grid, kt, 128, ws_bytes)) return PK_ERR_ARG;
+    }
+
     // The tile shape.  A tile covers whole ready flags (several, where it is larger) and signals them itself, or it is finer than
     // a flag and the flags are published behind the GEMM: that only where all tiles run at once (they end together anyway) and
     // costs a kernel of its own if the reduce phase is not part of the call.
     RsTiling t = {pl.tile_m == 256 ? T256x256 : T128x128, false, 1, 1};
-    if (do_gemm && pl.tile_m != 256 && !(ws && !bt && !bf16_slots)) {
+    if (do_gemm && pl.tile_m != 256) {
         int64_t best = INT64_MAX;
         for (int id = 0; id < N_TILES; ++id)
             for (int late = 0; late < 2; ++late) {
@@ -642,12 +696,7 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     int all_rows, tiles_n_all;                                   // the tile space of the whole local product
     rs_tile_space(pl, t, P, m_all, slot_cols, n_blks, cols, &all_rows, &tiles_n_all);
 
-    // Overlapped reduce: the GEMM is launched in two parts, the tile rows of this rank's own block (plus as many of the
-    // next ranks' as fill whole rounds) and the rest; the reduce runs on the library's second stream beside the second
-    // part: its workgroups use no LDS and few enough registers to sit next to a GEMM workgroup.  It waits for nothing
-    // the second part produces, so whichever of the two the hardware places first, both finish.
-    bool overlap = (phases & PK_PHASE_OVERLAP) && do_gemm && do_reduce && !ar && !cols && P > 1 && !t.late;
-    if (ceil_div((int64_t)all_rows * tiles_n_all, 8) * 8 <= grid) overlap = false;   // all tiles at once: nothing to run beside
+    if (t.late || ceil_div((int64_t)all_rows * tiles_n_all, 8) * 8 <= grid) overlap = false;   // all tiles at once: nothing to run beside
     int first_rows = 0;                      // tile rows of the first part (0: one launch for everything)
     const int own_row = rank * pl.tiles_m / t.blks_per_tile;    // the tile rows that hold this rank's own blocks
     const int own_rows = ((rank + 1) * pl.tiles_m - 1) / t.blks_per_tile - own_row + 1;
@@ -656,18 +705,6 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     // Next to the fp8 kernel the narrow form runs, where it is built: with twice the loads in flight the reduce takes more
     // bandwidth and clock from a GEMM that lives on both (16384 x 16384 x 2048: 676 us against 706 us a call).
     const bool narrow_reduce = fp8 && !bf16_slots && (P == 2 || P == 4 || P == 8);
-    if (overlap) {
-        // a stream that is being captured into a graph takes the second stream along only if that one exists already
-        // (it is created by the first eager call with the flag): no stream is created in the middle of a capture
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &cap) != hipSuccess) return PK_ERR_HIP;
-        if (cap != hipStreamCaptureStatusNone) {
-            std::lock_guard<std::mutex> guard(side_lock);
-            int dev = 0;
-            if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return PK_ERR_HIP;
-            if (!side_streams[dev].ready) overlap = false;
-        }
-    }
 
     GemmArgs a = {};
     // one launch over `n_rows` tile rows that start at tile row `row0` (wrapping around at all_rows)
@@ -676,7 +713,7 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         a.row_rot = row0;
         a.all_tile_rows = (row0 == 0 && n_rows == all_rows) ? 0 : all_rows;
         return bf16_slots ? run_gemm<EPI_RS16>(a, t.tile, comm_cus, fp8, false, nullptr, 0, s)
-                          : run_gemm<EPI_RS>(a, t.tile, comm_cus, fp8, bt, bt ? nullptr : ws, ws_bytes, s);
+                          : run_gemm<EPI_RS>(a, t.tile, comm_cus, fp8, bt, bt || pl.tile_m != 256 ? nullptr : ws, ws_bytes, s);
     };
     if (do_gemm) {
         const int elem = fp8 ? 1 : 2;
@@ -707,22 +744,7 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         a.n_groups = 1;
         a.group0 = 0;
         if (overlap) {
-            // The first part: the own block's rows rounded up to whole bands of 4, then as many more bands (up to 7) as
-            // waste the least of its last round.  No second part left: one launch, reduce afterwards.
-            const int band = 4;
-            int best = 0;
-            double best_waste = 2.0;
-            for (int k = 0; k < 8; ++k) {
-                const int r1 = (int)ceil_div(own_rows, band) * band + k * band;
-                if (r1 >= all_rows) break;
-                const int64_t t1 = (int64_t)r1 * tiles_n_all;
-                const double waste = (double)(ceil_div(t1, grid) * grid - t1) / grid + 0.02 * k;
-                if (waste < best_waste) {
-                    best_waste = waste;
-                    best = r1;
-                }
-            }
-            first_rows = best;
+            first_rows = first_part(own_rows, all_rows, tiles_n_all, grid);
             if (first_rows == 0) overlap = false;
         }
         a.rank = rank;
@@ -883,9 +905,10 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         return (*one_span ? all : P * tiles_across(chunk_rows, bm)) * tn;
     };
     bool one_span = k_chunks;
-    int tile = pl.tile_m == 256 ? T256x256 : T128x128;
+    int tile = T256x256;
     const int64_t plan_slots = ((int64_t)pl.tiles_m * pl.tiles_n + 7) / 8 * 8 * P;
-    const bool sk = ws && !bt && !k_chunks && plan_slots > grid && plan_slots % grid != 0 && a.ktiles >= 16 && grid <= (int)(kWsFlagBytes / 4);
+    if (ws && !bt && !k_chunks && sk_too_small(plan_slots, grid, a.ktiles, pl.tile_m, ws_bytes)) return PK_ERR_ARG;
+    const bool sk = ws && !bt && !k_chunks && pl.tile_m == 256 && sk_applies(plan_slots, grid, a.ktiles);
     if (!sk) {
         int64_t best = INT64_MAX;
         for (int id = 0; id < (k_chunks ? T32x64 : N_TILES); ++id) {
@@ -919,7 +942,7 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     a.epoch = epoch;
     a.status = status;
     a.timeout_ticks = timeout_ticks(timeout_us);
-    if (ws_is_static) {
+    if (ws_is_static && sk) {
         // the library's own scratch keeps the last call's flags, whatever its epoch was: clear them (with a kernel, so
         // that the call can be captured into a graph) and use an epoch of its own
         hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(1024), 0, (hipStream_t)stream, (uint32_t*)ws, (int)(kWsFlagBytes / 4));

@@ -4,15 +4,13 @@
 
 namespace pk {
 
-// A tile shape.  From T32x64 on the waves take k-tiles of their own (WM = WN = 1: not for the all-gather of column chunks); the
-// last one serves the stream-K tail only (its pieces are exchanged between whole workgroups, WK = 1).
-enum Tile { T256x256, T256x128, T128x256, T128x128, T128x64, T64x64, T32x64, T32x32, N_TILES, T128x128_SK = N_TILES };
+// A tile shape.  From T32x64 on the waves take k-tiles of their own (WM = WN = 1: not for the all-gather of column chunks).
+enum Tile { T256x256, T256x128, T128x256, T128x128, T128x64, T64x64, T32x64, T32x32, N_TILES };
 
 struct TileDim {
     int bm, bn;
 };
-constexpr TileDim kTileDim[N_TILES + 1] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}, {128, 64},
-                                           {64, 64},   {32, 64},   {32, 32},   {128, 128}};
+constexpr TileDim kTileDim[N_TILES] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}, {128, 64}, {64, 64}, {32, 64}, {32, 32}};
 
 // waves (WM x WN x WK), k-tile bytes and ring stages of a tile shape.  bf16: the smaller tiles split the k-steps of a k-tile
 // over two groups of waves (WK = 2), which keeps the wave's sub-tile large and with it the LDS reads per flop low: 64 x 64
@@ -36,8 +34,7 @@ constexpr TileWaves tile_waves(int tile, bool fp8, bool bt) {
         case T128x64: return fp8 ? TileWaves{2, 2, 1, 128, 6} : TileWaves{2, 2, 2, 128, 4};
         case T64x64: return fp8 ? TileWaves{2, 1, 1, 128, 6} : TileWaves{2, 1, 2, 128, 6};
         case T32x64: return TileWaves{1, 1, 4, 128, 3};
-        case T32x32: return TileWaves{1, 1, 4, 128, 4};
-        default: return TileWaves{2, 2, 1, 128, 2};      // T128x128_SK
+        default: return TileWaves{1, 1, 4, 128, 4};      // T32x32
     }
 }
 
@@ -63,7 +60,7 @@ inline int tiles_across(int64_t size, int tile_size) {       // size / tile_size
 }
 
 // Launches one GEMM on `grid` workgroups with the given tile shape (defined in the gemm_*.hip file of its mode).  a.ktiles
-// counts k-tiles of 128 bytes.  `sk`: with the stream-K tail that `a` describes (T256x256 or T128x128_SK, not with bt).
+// counts k-tiles of 128 bytes.  `sk`: with the stream-K tail that `a` describes (T256x256, not with bt).
 template <int EPI>
 pk_status launch_gemm(GemmArgs a, int tile, bool fp8, bool bt, bool sk, int grid, hipStream_t stream);
 
@@ -97,12 +94,9 @@ pk_status launch_gemm(GemmArgs a, int tile, bool fp8, bool bt, bool sk, int grid
     if ((bt || sk) && !BASE) return PK_ERR_ARG;
     if constexpr (BASE) {
         if (sk) {
-            if (bt) return PK_ERR_ARG;
-            if (tile == T256x256)
-                return fp8 ? launch_kernel<T256x256, true, EPI, false, true>(a, grid, stream)
-                           : launch_kernel<T256x256, false, EPI, false, true>(a, grid, stream);
-            return fp8 ? launch_kernel<T128x128_SK, true, EPI, false, true>(a, grid, stream)
-                       : launch_kernel<T128x128_SK, false, EPI, false, true>(a, grid, stream);
+            if (bt || tile != T256x256) return PK_ERR_ARG;
+            return fp8 ? launch_kernel<T256x256, true, EPI, false, true>(a, grid, stream)
+                       : launch_kernel<T256x256, false, EPI, false, true>(a, grid, stream);
         }
     }
     auto go = [&](auto tile_c) -> pk_status {

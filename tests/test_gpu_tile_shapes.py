@@ -147,3 +147,18 @@ def test_ag_gemm_k(dtype, P, rank, M, N, K):
         assert np.all(np.abs(got - want) <= 2 * K * U32 * mag + 2.0 ** -8 * np.abs(want) + 2.0 ** -133)
     # all chunks there from the start, or one by one: the k range is summed in the same order
     assert np.array_equal(runs[0]["C_bits"], runs[1]["C_bits"])
+
+
+def test_a_workspace_changes_nothing_where_the_plan_has_128x128_tiles():
+    """288 flag tiles of 128 x 128: the same bits with and without a workspace, and one that is too small is refused."""
+    P, rank, M, N, K = 2, 1, 2304, 2048, 2 * 1024
+    inp = wl.gemm_rs_inputs(P, M, N, K, "bf16", rank, seed=9)
+    plan = pk.pk_gemm_rs_plan(P, M, N, K, "bf16")
+    assert plan.tile_m == 128 and P * plan.tiles_m * plan.tiles_n > 256
+    args = (P, rank, M, N, K, "bf16", inp["A_local"], inp["B_local"], inp["partials"])
+    plain, with_ws = hz.run_gemm_rs(*args), hz.run_gemm_rs(*args, workspace=True)
+    assert np.array_equal(plain["out_bits"], with_ws["out_bits"])
+    assert np.array_equal(plain["outgoing"][1 - rank], with_ws["outgoing"][1 - rank])
+    with pytest.raises(pk.PkError) as e:
+        hz.run_gemm_rs(*args, workspace=torch.zeros(4096, dtype=torch.int32, device="cuda"))
+    assert e.value.code == pk.ERR_ARG
