@@ -159,8 +159,9 @@ const char* pk_status_str(int status);
  * first such call on a device outside a graph capture, default priority; a call on a capturing stream before that runs
  * in the plain order) and joins back into `stream` before the call's work counts as done there.  The reduce waits only for the own block (complete by then) and for the peers' flags, never for the second GEMM
  * launch, so either may be placed first.  Results are bit-identical to the plain call.  The flag needs both phases
- * (PK_ERR_ARG otherwise) and is ignored where it cannot help: when all tiles run at once, or the own block takes every
- * round of the schedule.
+ * (PK_ERR_ARG otherwise) and is ignored where it cannot help: when all tiles run at once, when the own block takes
+ * every round of the schedule, or for fp8 operands with less than 192 MiB of slots if these hold bf16, or P is
+ * none of 2, 4 and 8, or the second operand is k-contiguous.
  * Calls with the flag from several host threads on one device are serialised while they enqueue.
  * comm_cus: as for pk_ag_gemm below, the number of compute units the GEMM phase leaves to communicator workgroups
  * (0 = none).  partial_dt: element type of

@@ -704,7 +704,11 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     // operand k-contiguous 96, fp8 80 (64 with the second operand k-contiguous); a wave of the reduce kernel takes 64 at most.
     // Next to the fp8 kernel the narrow form runs, where it is built: with twice the loads in flight the reduce takes more
     // bandwidth and clock from a GEMM that lives on both (16384 x 16384 x 2048: 676 us against 706 us a call).
+    // The wide form beside it pays from about 200 MB of slots on (fp8, bf16 slots, P = 8: 16384 x 8192 x 2048 288 -> 272 us; 8192 x
+    // 8192, half the bytes, x 1024 102 -> 107 us; 15728 x 1376 x 1152 45 -> 57 us): splitting the GEMM costs about 12 us.  The same line for a k-contiguous second operand
+    // (6064 x 2640 x 3328, fp32 slots: 88 -> 95 us; at 128 MB 105 -> 103).
     const bool narrow_reduce = fp8 && !bf16_slots && (P == 2 || P == 4 || P == 8);
+    if (fp8 && (bt || !narrow_reduce) && m_all * N * (bf16_slots ? 2 : 4) < (192 << 20)) overlap = false;
 
     GemmArgs a = {};
     // one launch over `n_rows` tile rows that start at tile row `row0` (wrapping around at all_rows)
@@ -913,7 +917,10 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         int64_t best = INT64_MAX;
         for (int id = 0; id < (k_chunks ? T32x64 : N_TILES); ++id) {
             bool span;
-            const int64_t cost = tile_cost(id, fp8, tiles_of(id, &span), a.ktiles, grid);
+            int64_t cost = tile_cost(id, fp8, tiles_of(id, &span), a.ktiles, grid);
+            // Many rounds of fp8 tiles run at a lower clock than those the estimate was fitted to, and the largest tile loses least
+            // by it: another one has to be a sixteenth better (6960 x 7728 x 4096: 256x256 265 us, 128x256, estimated at 3% less, 273)
+            if (fp8 && pl.tile_m == 256 && id != T256x256) cost += cost / 16;
             if (cost < best) {
                 best = cost;
                 tile = id;

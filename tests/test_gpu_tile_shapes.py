@@ -28,6 +28,7 @@ U32 = 2.0 ** -24
     ("bf16", 2, 1, 256, 248, 64, "kn"),        # 32x32: one k-tile, three of the four waves without work
     ("bf16", 8, 7, 64, 520, 4032, "kn"),       # 32x32: shards of 8 rows, 63 k-tiles
     ("bf16", 3, 1, 6000, 5008, 512, "kn"),     # 256x256 in two rounds: stores still under way in the next main loop, or not (edges)
+    ("bf16", 2, 1, 5124, 4840, 320, "kn"),     # the same with rows that do not start on 64 bytes
     ("fp8", 2, 0, 4600, 8208, 512, "kn"),      # the same in three rounds
     ("fp8", 8, 2, 8 * 33, 4112, 256, "kn"),    # 128x64
     ("fp8", 2, 0, 2000, 4112, 256, "nk"),      # 256x256: shards of 1000 rows
@@ -162,3 +163,17 @@ def test_a_workspace_changes_nothing_where_the_plan_has_128x128_tiles():
     with pytest.raises(pk.PkError) as e:
         hz.run_gemm_rs(*args, workspace=torch.zeros(4096, dtype=torch.int32, device="cuda"))
     assert e.value.code == pk.ERR_ARG
+
+
+def test_overlap_flag_beside_the_fp8_kernel_with_bf16_slots():
+    """256 MiB of slots: the wide reduce kernel beside the second part of the GEMM (with less the flag is ignored there)."""
+    P, rank, M, N, K = 8, 5, 16384, 8192, 8 * 128
+    inp = wl.gemm_rs_inputs(P, M, N, K, "fp8", rank, seed=10)
+    p16 = wl.to_bf16_bits(inp["partials"])
+    args = (P, rank, M, N, K, "fp8", inp["A_local"], inp["B_local"], p16, inp["scale_a"], inp["scale_b"])
+    plain = hz.run_gemm_rs(*args, partial_dtype="bf16")
+    over = hz.run_gemm_rs(*args, partial_dtype="bf16", phases=pk.PHASE_ALL | pk.PHASE_OVERLAP)
+    assert plain["status"][0] == 0 and over["status"][0] == 0
+    assert np.array_equal(over["out_bits"], plain["out_bits"])
+    for q in range(P):
+        assert q == rank or np.array_equal(over["outgoing"][q], plain["outgoing"][q])
