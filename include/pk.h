@@ -117,7 +117,8 @@ typedef struct {
  * one another through this memory.  Layout: PK_WS_FLAG_BYTES of ready flags, then one fp32 tile per workgroup.  The
  * caller zeroes the flag bytes once; afterwards the workspace belongs to one call site: its epochs must grow from
  * call to call, and two calls that may run at the same time must not share it.  workspace = NULL: whole tiles only (also
- * with PK_B_K_CONTIGUOUS, with bf16 slots and with plans of 128 x 128 tiles, for which the tail is not built).
+ * with PK_B_K_CONTIGUOUS, with bf16 slots and with plans of 128 x 128 tiles, for which the tail is not built, and where
+ * PK_PHASE_OVERLAP splits the GEMM into two launches).
  * A workspace smaller than plan.workspace_bytes may be rejected with PK_ERR_ARG.
  */
 #define PK_WS_FLAG_BYTES 4096
@@ -158,7 +159,8 @@ const char* pk_status_str(int status);
  * and the reduce then run side by side, the reduce on a second stream that the library keeps per device (created at the
  * first such call on a device outside a graph capture, default priority; a call on a capturing stream before that runs
  * in the plain order) and joins back into `stream` before the call's work counts as done there.  The reduce waits only for the own block (complete by then) and for the peers' flags, never for the second GEMM
- * launch, so either may be placed first.  Results are bit-identical to the plain call.  The flag needs both phases
+ * launch, so either may be placed first.  Results are bit-identical to the plain call without a workspace (the two launches use
+ * none).  The flag needs both phases
  * (PK_ERR_ARG otherwise) and is ignored where it cannot help: when all tiles run at once, when the own block takes
  * every round of the schedule, or for fp8 operands with less than 192 MiB of slots if these hold bf16, or P is
  * none of 2, 4 and 8, or the second operand is k-contiguous.

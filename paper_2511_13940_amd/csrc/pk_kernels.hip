@@ -432,10 +432,10 @@ static bool sk_too_small(int64_t slots, int grid, int64_t ktiles, int tile, size
     return sk_applies(slots, grid, ktiles) && ws_bytes < kWsFlagBytes + (size_t)grid * tile * tile * 4;
 }
 
-// Launches a GEMM whose tile space is set up in `a`: with a workspace (256 x 256 tiles only) and a last round that is not full, with
-// the stream-K tail, otherwise whole tiles.
+// Launches a GEMM whose tile space is set up in `a`: with a workspace (256 x 256 tiles only; the caller has checked its size) and a
+// last round that is not full, with the stream-K tail, otherwise whole tiles.
 template <int EPI>
-static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt, void* ws, size_t ws_bytes, hipStream_t stream) {
+static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt, void* ws, hipStream_t stream) {
     const int bm = kTileDim[tile].bm, bn = kTileDim[tile].bn;
     const int64_t G = (int64_t)a.grp_tile_rows * a.tiles_n;
     a.wg_per_group = (int32_t)(8 * ceil_div(G, 8));
@@ -447,7 +447,6 @@ static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt
     if (ws && sk_applies(slots, grid, a.ktiles)) {
         // With a workspace every compute unit works to the end: whole rounds of tiles, then the k range of the left-over
         // tiles shared out evenly (448 slots on 256 CUs: 256 whole tiles, then 192 tiles as 256 pieces of 3/4 tile).
-        if (sk_too_small(slots, grid, a.ktiles, 256, ws_bytes)) return PK_ERR_ARG;
         a.sk_dp_slots = slots - rem;
         a.ws_flags = (uint32_t*)ws;
         a.ws_tiles = (char*)ws + kWsFlagBytes;
@@ -665,12 +664,7 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
             if (!side_streams[dev].ready) overlap = false;
         }
     }
-    if (do_gemm && ws && pl.tile_m != 256 && !bt && !bf16_slots) {
-        const int plan_rows = P * pl.tiles_m, kt = (int)(pl.local_k / (fp8 ? 128 : 64));
-        const int first = overlap ? first_part(pl.tiles_m, plan_rows, pl.tiles_n, grid) : 0;
-        for (int n_rows : {first, plan_rows - first})
-            if (sk_too_small(ceil_div((int64_t)n_rows * pl.tiles_n, 8) * 8, grid, kt, 128, ws_bytes)) return PK_ERR_ARG;
-    }
+    const bool overlap_asked = overlap;
 
     // The tile shape.  A tile covers whole ready flags (several, where it is larger) and signals them itself, or it is finer than
     // a flag and the flags are published behind the GEMM: that only where all tiles run at once (they end together anyway) and
@@ -697,7 +691,6 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     rs_tile_space(pl, t, P, m_all, slot_cols, n_blks, cols, &all_rows, &tiles_n_all);
 
     if (t.late || ceil_div((int64_t)all_rows * tiles_n_all, 8) * 8 <= grid) overlap = false;   // all tiles at once: nothing to run beside
-    int first_rows = 0;                      // tile rows of the first part (0: one launch for everything)
     const int own_row = rank * pl.tiles_m / t.blks_per_tile;    // the tile rows that hold this rank's own blocks
     const int own_rows = ((rank + 1) * pl.tiles_m - 1) / t.blks_per_tile - own_row + 1;
     // Registers per lane that the 256x256 GEMM kernels leave beside their two waves per SIMD: bf16 128, bf16 with the second
@@ -709,6 +702,23 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     // (6064 x 2640 x 3328, fp32 slots: 88 -> 95 us; at 128 MB 105 -> 103).
     const bool narrow_reduce = fp8 && !bf16_slots && (P == 2 || P == 4 || P == 8);
     if (fp8 && (bt || !narrow_reduce) && m_all * N * (bf16_slots ? 2 : 4) < (192 << 20)) overlap = false;
+    int first_rows = 0;                      // tile rows of the first part (0: one launch for everything)
+    if (overlap) {
+        first_rows = first_part(own_rows, all_rows, tiles_n_all, grid);
+        if (first_rows == 0) overlap = false;
+    }
+    if (do_gemm && ws && !bt && !bf16_slots) {
+        // the size of a workspace, checked over the launches of the plan's tiles, whether or not these take the tail
+        const bool parts = pl.tile_m == 256 ? overlap : overlap_asked;
+        const int plan_rows = P * pl.tiles_m, kt = (int)(pl.local_k / (fp8 ? 128 : 64));
+        const int first = parts ? first_part(pl.tiles_m, plan_rows, pl.tiles_n, grid) : 0;
+        for (int n_rows : {first, plan_rows - first})
+            if (sk_too_small(ceil_div((int64_t)n_rows * pl.tiles_n, 8) * 8, grid, kt, pl.tile_m, ws_bytes)) return PK_ERR_ARG;
+    }
+    // The stream-K tail is for one launch: two launches of a call would share the workspace's flags under one epoch, and a tile's
+    // owner in the second would take the pieces of the first for its own.  Beside the reduce a tail does not pay either (bf16, P = 8,
+    // us a call: 8192 x 7168 x 28672 389 without against 457 with it, 8192 x 5120 x 28672 285 / 331, 8192 x 7168 x 8192 171 / 219).
+    if (overlap || bt || bf16_slots || pl.tile_m != 256) ws = nullptr;
 
     GemmArgs a = {};
     // one launch over `n_rows` tile rows that start at tile row `row0` (wrapping around at all_rows)
@@ -716,8 +726,8 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         a.grp_tile_rows = n_rows;
         a.row_rot = row0;
         a.all_tile_rows = (row0 == 0 && n_rows == all_rows) ? 0 : all_rows;
-        return bf16_slots ? run_gemm<EPI_RS16>(a, t.tile, comm_cus, fp8, false, nullptr, 0, s)
-                          : run_gemm<EPI_RS>(a, t.tile, comm_cus, fp8, bt, bt || pl.tile_m != 256 ? nullptr : ws, ws_bytes, s);
+        return bf16_slots ? run_gemm<EPI_RS16>(a, t.tile, comm_cus, fp8, false, nullptr, s)
+                          : run_gemm<EPI_RS>(a, t.tile, comm_cus, fp8, bt, ws, s);
     };
     if (do_gemm) {
         const int elem = fp8 ? 1 : 2;
@@ -747,10 +757,6 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         }
         a.n_groups = 1;
         a.group0 = 0;
-        if (overlap) {
-            first_rows = first_part(own_rows, all_rows, tiles_n_all, grid);
-            if (first_rows == 0) overlap = false;
-        }
         a.rank = rank;
         a.partials = partials;
         a.outgoing = outgoing;
@@ -956,8 +962,8 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         if (hipGetLastError() != hipSuccess) return PK_ERR_HIP;
         a.ws_epoch = 1;
     }
-    return k_chunks ? run_gemm<EPI_AGK>(a, tile, comm_cus, fp8, false, nullptr, 0, (hipStream_t)stream)
-                    : run_gemm<EPI_AG>(a, tile, comm_cus, fp8, bt, sk ? ws : nullptr, ws_bytes, (hipStream_t)stream);
+    return k_chunks ? run_gemm<EPI_AGK>(a, tile, comm_cus, fp8, false, nullptr, (hipStream_t)stream)
+                    : run_gemm<EPI_AG>(a, tile, comm_cus, fp8, bt, sk ? ws : nullptr, (hipStream_t)stream);
 }
 
 static pk_status make_order(const int* order, int n_order, int P, EmuOrder* o) {

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import codec
 from paper_2511_13940_amd import pk, workloads as wl
 from tests import harness as hz
 from tests.test_gpu_bf16_slots import check as check16
@@ -119,3 +120,44 @@ def test_overlap_flag_with_a_k_contiguous_second_operand(dtype):
     assert over["plan"].tile_m == 256
     check_rs(P, rank, dtype, inp, over, K // P)
     assert np.array_equal(over["out_bits"], plain["out_bits"])
+
+
+# Sizes at which both launches of the call are more than one round of workgroups with a partial last one, the condition for a
+# stream-K tail when a launch stands alone.
+@pytest.mark.parametrize("P,rank,M,N,K,dtype,comm_cus", [
+    (4, 1, 4096, 4352, 4 * 1024, "bf16", 192),        # 64 workgroups: 204 + 68 tiles
+    (8, 0, 8192, 6144, 8192, "bf16", 0),              # 480 + 288 tiles
+    (3, 2, 12288, 5120, 6144, "fp8", 0),              # 480 + 480 tiles
+])
+def test_overlapped_reduce_with_a_workspace(P, rank, M, N, K, dtype, comm_cus):
+    """The two launches must not meet in the workspace: the same bits as the plain call without one, three calls with rising epochs
+    on one workspace, which stays the call site's own (a plain call with it follows)."""
+    inp = wl.gemm_rs_inputs(P, M, N, K, dtype, rank, seed=15)
+    kw = dict(scale_a=inp.get("scale_a"), scale_b=inp.get("scale_b"), comm_cus=comm_cus)
+    args = (P, rank, M, N, K, dtype, inp["A_local"], inp["B_local"], inp["partials"])
+    plain = hz.run_gemm_rs(*args, epoch=1, **kw)
+    if M * N * K // P < 2 ** 36:
+        check_rs(P, rank, dtype, inp, plain, K // P)
+    ws = torch.zeros(plain["plan"].workspace_bytes // 4, dtype=torch.int32, device="cuda")
+    for epoch in (1, 2, 3):
+        over = hz.run_gemm_rs(*args, epoch=epoch, phases=OVERLAP, workspace=ws, **kw)
+        assert over["status"][0] == 0
+        assert np.array_equal(over["out_bits"], plain["out_bits"]), epoch
+        assert np.array_equal(over["partials_after"][rank].view(np.uint32), plain["partials_after"][rank].view(np.uint32)), epoch
+        for q in range(P):
+            if q != rank:
+                assert np.array_equal(over["outgoing"][q].view(np.uint32), plain["outgoing"][q].view(np.uint32)), (epoch, q)
+    tail = hz.run_gemm_rs(*args, epoch=4, workspace=ws, **kw)
+    assert tail["status"][0] == 0
+    # another order of the same fp32 sums: neighbouring bf16 values at most
+    a, b = codec.bf16_decode(tail["out_bits"]), codec.bf16_decode(plain["out_bits"])
+    assert np.max(np.abs(a - b) / (np.abs(b) + 1.0)) <= 1e-2
+
+
+def test_a_workspace_too_small_for_either_launch_is_refused_before_anything_runs():
+    P, rank, M, N, K = 4, 1, 4096, 4352, 4 * 1024
+    inp = wl.gemm_rs_inputs(P, M, N, K, "bf16", rank, seed=16)
+    with pytest.raises(pk.PkError) as e:
+        hz.run_gemm_rs(P, rank, M, N, K, "bf16", inp["A_local"], inp["B_local"], inp["partials"], phases=OVERLAP, comm_cus=192,
+                       workspace=torch.zeros(2048, dtype=torch.int32, device="cuda"))
+    assert e.value.code == pk.ERR_ARG
