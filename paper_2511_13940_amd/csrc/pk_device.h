@@ -39,7 +39,7 @@ __device__ __forceinline__ bool flag_ready(const uint32_t* flag, uint32_t epoch)
 
 // Paper appendix C, `wait`: poll with relaxed loads until the flag reaches the expected value.
 // Bounded: returns false once `timeout_ticks` of the 100 MHz wall clock have passed.
-// The caller issues the acquire fence (after its workgroup barrier).
+// The caller issues the acquire fence.
 __device__ __forceinline__ bool flag_wait(const uint32_t* flag, uint32_t epoch, uint64_t timeout_ticks) {
     if (flag_ready(flag, epoch)) return true;
     const uint64_t t0 = wall_clock64();

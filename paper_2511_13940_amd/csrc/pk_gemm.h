@@ -88,8 +88,7 @@ struct GemmArgs {
     // all-gather epilogue
     uint16_t* C;              // (P*rows_per_shard) x n bf16
     const uint32_t* chunk_flags;
-    int32_t acquire_all;      // A does not start on a 128-byte line: a line may hold the end of one chunk and the start of the next
-    int32_t k_chunks;         // EPI_AGK: A arrives in this many column blocks of K/k_chunks (chunk q from rank q)
+    int32_t n_chunks;         // chunks that A arrives in (chunk q from rank q): blocks of rows, EPI_AGK: column blocks of K/n_chunks
     int32_t act;              // pk_activation applied to the accumulator before the bf16 rounding (all-gather mode)
     const float* scale_a;     // fp8 only
     const float* scale_b;
@@ -364,7 +363,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     uint64_t t_loops = 0;
     uint32_t n_tiles_done = 0;
     uint64_t seen_chunks = 1ull << (g.rank & 63);
-    const uint64_t all_chunks = g.k_chunks >= 64 ? ~0ull : (1ull << g.k_chunks) - 1;
+    const uint64_t all_chunks = g.n_chunks >= 64 ? ~0ull : (1ull << g.n_chunks) - 1;
     int v = blockIdx.x;
     // EPI_AG: a slot whose chunk has not landed when it is first visited is put aside (bit i = this workgroup's i-th slot)
     // and taken up again, now waiting, once the workgroup has gone through its other slots: tiles of chunks that are
@@ -399,7 +398,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         bool have = false;
         for (;;) {
             int slot, slot_index = 64;
-            bool may_defer = false, revisit = false;
+            bool may_defer = false;
             if (v < g.sk_dp_slots) {
                 slot = v;
                 slot_index = visit;
@@ -410,7 +409,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 slot_index = __builtin_ctzll(deferred);
                 deferred &= deferred - 1;
                 slot = (int)blockIdx.x + slot_index * (int)gridDim.x;
-                revisit = true;
             } else if (SK && sk_c < sk_e) {
                 const int i = sk_c / KT;
                 tile_end = (i + 1) * KT;
@@ -472,33 +470,38 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 const int c_lo = g.by_chunk_rows.div(row0), c_hi = g.by_chunk_rows.div(min(row0 + BM, row_end) - 1);
                 const uint64_t need = ((2ull << (c_hi & 63)) - (1ull << (c_lo & 63))) & ~seen_chunks;
                 if (need) {
-                    // wave 0 polls, one lane per chunk; the verdict (0 landed, 1 timed out, 2 not yet: put the slot aside) goes
-                    // through a word of the (idle) epilogue staging area, since the kernel leaves no LDS for a static variable
+                    // wave 0 polls, one lane per chunk; the verdict (0 landed, 1 timed out, 2 not yet: put the slot aside) and the
+                    // chunks that have landed go through words of the (idle) epilogue staging area, since the kernel leaves no
+                    // LDS for a static variable
                     PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
+                    PK_LDS uint64_t* landed = (PK_LDS uint64_t*)(lds + EPI_OFF + 8);
                     if (w == 0) {
-                        const bool mine = (need >> l) & 1;
-                        bool fence = g.acquire_all || revisit;
+                        uint64_t there = __ballot(l < g.n_chunks && flag_ready(g.chunk_flags + l, g.epoch));
                         int vd = 0;
-                        if (__ballot(mine && !flag_ready(g.chunk_flags + l, g.epoch)) != 0) {
+                        if (need & ~there) {
                             if (may_defer) {
                                 vd = 2;
                             } else {
-                                const bool late = mine && !flag_wait(g.chunk_flags + l, g.epoch, g.timeout_ticks);
+                                const bool late = ((need >> l) & 1) && !flag_wait(g.chunk_flags + l, g.epoch, g.timeout_ticks);
                                 if (late) report_timeout(g.status, (uint32_t)l, 1u);
                                 if (__ballot(late) != 0) vd = 1;
-                                fence = true;
+                                there |= need;
                             }
                         }
-                        // The acquire invalidates this XCD's whole L2, with every other workgroup's tiles in it (all 8 waves of
-                        // all workgroups doing so took 11 us of a 25 us call), so only this wave does it, and only where it had
-                        // to wait.  A chunk that is there at the first look needs none: the L2 was invalidated when the kernel
-                        // started, and nothing has read a line of the chunk into it since, because no workgroup reads a chunk
-                        // before its flag (and no line is shared between chunks unless acquire_all).
-                        if (fence && vd != 2) acquire_agent();
-                        if (l == 0) *verdict = vd;
+                        // Also for chunks that are there at the first look: since this kernel started, another one may have read
+                        // what their memory held before (an earlier call on the same buffer, on another stream) into this XCD's L2.
+                        // An acquire invalidates that whole L2, with the other workgroups' tiles in it: one wave does it, once for
+                        // all the chunks that have landed (128x64 tiles, 256 workgroups that need one chunk each, 2048 x 1024 x
+                        // 2048: 1.2 us of a call; done by all waves 11 us).
+                        if (vd == 0) acquire_agent();
+                        if (l == 0) {
+                            *verdict = vd;
+                            *landed = there;
+                        }
                     }
                     __syncthreads();
                     const int vd_all = *verdict;
+                    const uint64_t there_all = *landed;
                     __syncthreads();
                     if (vd_all == 2) {
                         deferred |= 1ull << slot_index;
@@ -512,7 +515,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                         sk_c = sk_e;
                         break;
                     }
-                    seen_chunks |= need;
+                    seen_chunks |= there_all;
                 }
             }
             break;
@@ -529,8 +532,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             // every chunk there already: no pipeline refill per chunk
             PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
             if (w == 0) {
-                const uint64_t missing = __ballot(l < g.k_chunks && !((seen_chunks >> l) & 1) && !flag_ready(g.chunk_flags + l, g.epoch));
-                if (!missing && g.acquire_all) acquire_agent();      // otherwise as above: nothing stale can be in the L2
+                const uint64_t missing = __ballot(l < g.n_chunks && !((seen_chunks >> l) & 1) && !flag_ready(g.chunk_flags + l, g.epoch));
+                if (!missing) acquire_agent();
                 if (l == 0) *verdict = missing != 0;
             }
             __syncthreads();
@@ -539,11 +542,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             if (!missing_all) seen_chunks = all_chunks;
         }
         const bool by_chunk = (EPI == EPI_AGK) && seen_chunks != all_chunks;
-        const int seg_ktiles = by_chunk ? g.ktiles / g.k_chunks : nkt;
+        const int seg_ktiles = by_chunk ? g.ktiles / g.n_chunks : nkt;
         int until_wrap = 0;                          // EPI_AGK: k-tiles from the next one to issue to the end of the k range
         if constexpr (EPI == EPI_AGK) {
             // the k range is taken in ring order from the own chunk, whether or not the chunks are waited for one by one
-            const int first = g.rank * (g.ktiles / g.k_chunks);
+            const int first = g.rank * (g.ktiles / g.n_chunks);
             a_base += (int64_t)first * KB;
             b_base += (int64_t)first * b_step;
             until_wrap = g.ktiles - first;
@@ -1027,14 +1030,14 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
         };
         const uint64_t t_loop0 = clock64();
-        const int n_seg = by_chunk ? g.k_chunks : 1;
+        const int n_seg = by_chunk ? g.n_chunks : 1;
 #pragma clang loop unroll(disable)
         for (int sgm = 0; sgm < n_seg; ++sgm) {
             if (EPI == EPI_AGK && sgm > 0) {
                 // another column chunk of A, in ring order from the own one; the first tile that touches a chunk waits for
                 // its flag (paper appendix C `wait`), later tiles of this workgroup know it has landed
                 int c = g.rank + sgm;
-                if (c >= g.k_chunks) c -= g.k_chunks;
+                if (c >= g.n_chunks) c -= g.n_chunks;
                 if (!((seen_chunks >> c) & 1)) {
                     PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
                     if (tid == 0) {

@@ -899,10 +899,8 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     a.ldb = (bt ? pl.local_k : pl.local_n) * elem;
     a.n = (int32_t)pl.local_n;
     a.ktiles = (int32_t)(pl.local_k / (fp8 ? 128 : 64));
-    a.k_chunks = k_chunks ? P : 0;
+    a.n_chunks = P;
     a.act = activation;
-    // column chunks: a row piece of a chunk is a whole number of 128-byte lines
-    a.acquire_all = ((uintptr_t)A_gathered & 127) != 0;
     // The tile shape, and how tile rows and row chunks go together.  Where all tiles run at once, or a chunk is lower than a
     // tile: tile rows over all rows, from the one that holds the own chunk on; a tile waits for every chunk it touches.
     // Otherwise one scheduling group per chunk, visited from the own one.  Column chunks: every tile needs every chunk.

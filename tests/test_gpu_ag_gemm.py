@@ -6,6 +6,7 @@ import itertools
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import codec, tp_gemm
 from paper_2511_13940_amd import pk, workloads as wl
@@ -210,3 +211,37 @@ def test_ten_seeded_arrival_orders_of_seven_chunks_bitwise_identical():
                              gap_us=(0, 20, 120)[s % 3], epoch=s + 1, fetch_A=False)
         assert res["status"][0] == 0
         assert np.array_equal(res["C_bits"], base["C_bits"]), f"order {order}"
+
+
+def test_chunk_memory_read_by_another_kernel_before_the_chunk_lands():
+    """A kernel on a third stream reads what the buffer held before (NaN) while the call computes on other chunks, so that lines of
+    it are in the L2s when the chunks land; they land before the call's first look at them (its second round of tiles).  What
+    counts is memory at the time of the flag: the same bits as with all chunks in place."""
+    P, rank, M, n, K = 4, 1, 4096, 7168, 8192             # 448 tiles of 256 x 256: two rounds of some 180 us
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    full = (torch.randn(M, K, generator=g, device="cuda") / K ** 0.5).bfloat16()
+    B = (torch.randn(K, n, generator=g, device="cuda") / K ** 0.5).bfloat16()
+    status = torch.zeros(8, dtype=torch.int32, device="cuda")
+    counters = torch.zeros(pk.EMU_MAX_ORDER, dtype=torch.int32, device="cuda")
+    flags = torch.full((P,), 1, dtype=torch.int32, device="cuda")
+    want, C = (torch.zeros((M, n), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    pk.pk_ag_gemm(P, rank, M, P * n, K, "bf16", full, B, None, None, flags, 1, want, status)
+    mp = M // P
+    A = torch.empty_like(full)
+    feeder, reader = torch.cuda.Stream(), torch.cuda.Stream()
+    order = [(rank + d) % P for d in range(1, P)]
+    for epoch, gap in ((2, 40), (3, 60), (4, 20)):
+        A.fill_(float("nan"))
+        A[rank * mp:(rank + 1) * mp] = full[rank * mp:(rank + 1) * mp]
+        counters.zero_()
+        C.zero_()
+        torch.cuda.synchronize()
+        pk.pk_emu_deliver_chunks(P, M, K, 2, full, A, flags, epoch, order, gap, counters, stream=feeder)
+        pk.pk_ag_gemm(P, rank, M, P * n, K, "bf16", A, B, None, None, flags, epoch, C, status, comm_cus=32)
+        with torch.cuda.stream(reader):
+            seen = [A[q * mp:(q + 1) * mp].clone() for q in order[1:]]
+        torch.cuda.synchronize()
+        assert status[0].item() == 0
+        assert torch.equal(C.view(torch.int16), want.view(torch.int16)), epoch
+        del seen
