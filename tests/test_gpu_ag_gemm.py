@@ -150,6 +150,29 @@ def test_fused_activation(act, dtype, P, M, N, K, rank):
         assert np.all(got >= 0) and np.any(got == 0) and np.any(got > 0)
 
 
+@pytest.mark.parametrize("act,lowest", [("silu", -88.5), ("gelu_tanh", -10.0)])
+@pytest.mark.parametrize("K", [64, 4096])                   # 32 x 32 tiles; 256 x 128 or larger with 4200 rows
+def test_activation_of_every_bf16_value(act, lowest, K):
+    """x * 1 is exact, so every row holds the activation of one bf16 value, down to results near the smallest normal number.  Both
+    are x / (1 + exp(-y)), with y = x or GELU's inner polynomial (in this form, since 1 + tanh() cancels in float64 as well).
+    Bound: half a bf16 ulp, and in units of 2^-24 of the value 4 for the exponential, the sum and the quotient and, for GELU, the
+    five roundings of y and its constants, which the exponential turns into 5 |y|."""
+    bits = np.arange(1 << 16, dtype=np.uint32).astype(np.uint16)
+    x = codec.bf16_decode(bits)
+    x = x[np.isfinite(x) & (np.abs(x) >= 2.0 ** -10) & (x >= lowest) & (x <= 88.5)]
+    M, N = x.size, 2048 if K > 64 else 8
+    A = np.zeros((M, K), dtype=np.uint16)
+    A[:, K - 1] = codec.bf16_encode(x)
+    B = np.zeros((K, N), dtype=np.uint16)
+    B[K - 1, :] = 0x3F80                                      # 1.0
+    res = hz.run_ag_gemm(1, 0, M, N, K, "bf16", [A], B, act=act)
+    assert res["status"][0] == 0
+    y = x if act == "silu" else 2 * np.sqrt(2 / np.pi) * (x + 0.044715 * x ** 3)
+    want, units = (x / (1 + np.exp(-y)))[:, None], (4 + (0 if act == "silu" else 5) * np.abs(y))[:, None]
+    got = codec.bf16_decode(res["C_bits"])
+    assert np.all(np.abs(got - want) <= (2.0 ** -8 + units * 2.0 ** -24) * np.abs(want) + 2.0 ** -134)
+
+
 def test_mlp_block_chain_matches_the_oracle():
     """AG + GEMM with fused SiLU, its bf16 output fed to GEMM + RS as the local operand (paper section 4.1), against the
     oracle's chained definition."""
