@@ -612,6 +612,69 @@ static int first_part(int own_rows, int all_rows, int tiles_n, int grid) {
     return best;
 }
 
+// Which way a GEMM + reduce-scatter goes: the tiles, and whether the GEMM is cut into two launches with the reduce beside the second.
+struct RsRoute {
+    RsTiling t;
+    int all_rows, tiles_n;    // the tile space of the whole local product
+    int own_row, own_rows;    // the tile rows that hold this rank's own blocks
+    int first_rows;           // tile rows of the first launch (0: one launch for everything)
+    bool overlap;             // two launches
+    bool narrow_reduce;       // then the reduce runs in its narrow form
+};
+static RsRoute rs_route(const pk_plan& pl, int P, int rank, int64_t rows, int64_t slot_cols, bool fp8, bool bt, bool bf16_slots, bool cols,
+                        bool do_gemm, bool do_reduce, bool overlap, int grid) {
+    const int64_t m_all = cols ? rows : P * rows;
+    const int n_blks = cols ? pl.tiles_m : P * pl.tiles_m;       // row blocks of the ready flags
+    RsRoute r = {};
+    // The tile shape.  A tile covers whole ready flags (several, where it is larger) and signals them itself, or it is finer than
+    // a flag and the flags are published behind the GEMM: that only where all tiles run at once (they end together anyway) and
+    // costs a kernel of its own if the reduce phase is not part of the call.
+    r.t = {pl.tile_m == 256 ? T256x256 : T128x128, false, 1, 1};
+    if (do_gemm && pl.tile_m != 256) {
+        int64_t best = INT64_MAX;
+        for (int id = 0; id < N_TILES; ++id)
+            for (int late = 0; late < 2; ++late) {
+                RsTiling c;
+                if (!rs_tiling(pl, id, late != 0, rows, &c)) continue;
+                int tile_rows, tile_cols;
+                rs_tile_space(pl, c, P, m_all, slot_cols, n_blks, cols, &tile_rows, &tile_cols);
+                const int tiles = tile_rows * tile_cols;
+                if (late && (tiles + 7) / 8 * 8 > grid) continue;
+                const int64_t cost = tile_cost(id, fp8, tiles, (int)(pl.local_k >> (fp8 ? 7 : 6)), grid) + (late && !do_reduce ? 4000 * grid : 0);
+                if (cost < best) {
+                    best = cost;
+                    r.t = c;
+                }
+            }
+    }
+    rs_tile_space(pl, r.t, P, m_all, slot_cols, n_blks, cols, &r.all_rows, &r.tiles_n);
+
+    if (r.t.late || ceil_div((int64_t)r.all_rows * r.tiles_n, 8) * 8 <= grid) overlap = false;   // all tiles at once: nothing to run beside
+    r.own_row = rank * pl.tiles_m / r.t.blks_per_tile;
+    r.own_rows = ((rank + 1) * pl.tiles_m - 1) / r.t.blks_per_tile - r.own_row + 1;
+    // Registers per lane that the 256x256 GEMM kernels leave beside their two waves per SIMD (512 less twice their own, in steps of 8):
+    // bf16 96 (80 with bf16 slots), fp8 48 (64 with the second operand k-contiguous).  A wave of the reduce kernel takes 64 at most,
+    // 48 where it runs beside fp8: its narrow form for fp32 slots and P = 2, 4, 8, else the form for bf16 slots or a run-time P.
+    // The narrow form is also the faster one there: with twice the loads in flight the reduce takes more bandwidth and clock from a
+    // GEMM that lives on both (16384 x 16384 x 2048: 676 us against 706 us a call).
+    // The other forms pay from about 200 MB of slots on (fp8, bf16 slots, P = 8: 16384 x 8192 x 2048 288 -> 272 us; 8192 x 8192 x 1024,
+    // half the bytes, 102 -> 107 us; 15728 x 1376 x 1152 45 -> 57 us): splitting the GEMM costs about 12 us.  The same line for a
+    // k-contiguous second operand (6064 x 2640 x 3328, fp32 slots: 88 -> 95 us; at 128 MB 105 -> 103).
+    r.narrow_reduce = fp8 && !bf16_slots && (P == 2 || P == 4 || P == 8);
+    if (fp8 && (bt || !r.narrow_reduce) && m_all * slot_cols * (bf16_slots ? 2 : 4) < (192 << 20)) overlap = false;
+    if (overlap) r.first_rows = first_part(r.own_rows, r.all_rows, r.tiles_n, grid);
+    r.overlap = r.first_rows > 0;
+    return r;
+}
+
+// Whether a workspace may take the call to the stream-K tail.  The tail is for one launch: two launches of a call would share the
+// workspace's flags under one epoch, and a tile's owner in the second would take the pieces of the first for its own.  Beside the
+// reduce a tail does not pay either (bf16, P = 8, us a call: 8192 x 7168 x 28672 389 without against 457 with it, 8192 x 5120 x 28672
+// 285 / 331, 8192 x 7168 x 8192 171 / 219).
+static bool rs_takes_tail(const pk_plan& pl, const RsRoute& r, bool bt, bool bf16_slots) {
+    return pl.tile_m == 256 && !r.overlap && !bt && !bf16_slots;
+}
+
 // GEMM + reduce-scatter; with `ar` the reduce phase also hands the reduced rows to every rank (all-reduce)
 static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype dt,
                               const void* A_local, const void* B_local, const float* scale_a, const float* scale_b,
@@ -664,61 +727,19 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
             if (!side_streams[dev].ready) overlap = false;
         }
     }
-    const bool overlap_asked = overlap;
-
-    // The tile shape.  A tile covers whole ready flags (several, where it is larger) and signals them itself, or it is finer than
-    // a flag and the flags are published behind the GEMM: that only where all tiles run at once (they end together anyway) and
-    // costs a kernel of its own if the reduce phase is not part of the call.
-    RsTiling t = {pl.tile_m == 256 ? T256x256 : T128x128, false, 1, 1};
-    if (do_gemm && pl.tile_m != 256) {
-        int64_t best = INT64_MAX;
-        for (int id = 0; id < N_TILES; ++id)
-            for (int late = 0; late < 2; ++late) {
-                RsTiling c;
-                if (!rs_tiling(pl, id, late != 0, rows, &c)) continue;
-                int tile_rows, tile_cols;
-                rs_tile_space(pl, c, P, m_all, slot_cols, n_blks, cols, &tile_rows, &tile_cols);
-                const int tiles = tile_rows * tile_cols;
-                if (late && (tiles + 7) / 8 * 8 > grid) continue;
-                const int64_t cost = tile_cost(id, fp8, tiles, (int)(pl.local_k >> (fp8 ? 7 : 6)), grid) + (late && !do_reduce ? 4000 * grid : 0);
-                if (cost < best) {
-                    best = cost;
-                    t = c;
-                }
-            }
-    }
-    int all_rows, tiles_n_all;                                   // the tile space of the whole local product
-    rs_tile_space(pl, t, P, m_all, slot_cols, n_blks, cols, &all_rows, &tiles_n_all);
-
-    if (t.late || ceil_div((int64_t)all_rows * tiles_n_all, 8) * 8 <= grid) overlap = false;   // all tiles at once: nothing to run beside
-    const int own_row = rank * pl.tiles_m / t.blks_per_tile;    // the tile rows that hold this rank's own blocks
-    const int own_rows = ((rank + 1) * pl.tiles_m - 1) / t.blks_per_tile - own_row + 1;
-    // Registers per lane that the 256x256 GEMM kernels leave beside their two waves per SIMD: bf16 128, bf16 with the second
-    // operand k-contiguous 96, fp8 80 (64 with the second operand k-contiguous); a wave of the reduce kernel takes 64 at most.
-    // Next to the fp8 kernel the narrow form runs, where it is built: with twice the loads in flight the reduce takes more
-    // bandwidth and clock from a GEMM that lives on both (16384 x 16384 x 2048: 676 us against 706 us a call).
-    // The wide form beside it pays from about 200 MB of slots on (fp8, bf16 slots, P = 8: 16384 x 8192 x 2048 288 -> 272 us; 8192 x
-    // 8192, half the bytes, x 1024 102 -> 107 us; 15728 x 1376 x 1152 45 -> 57 us): splitting the GEMM costs about 12 us.  The same line for a k-contiguous second operand
-    // (6064 x 2640 x 3328, fp32 slots: 88 -> 95 us; at 128 MB 105 -> 103).
-    const bool narrow_reduce = fp8 && !bf16_slots && (P == 2 || P == 4 || P == 8);
-    if (fp8 && (bt || !narrow_reduce) && m_all * N * (bf16_slots ? 2 : 4) < (192 << 20)) overlap = false;
-    int first_rows = 0;                      // tile rows of the first part (0: one launch for everything)
-    if (overlap) {
-        first_rows = first_part(own_rows, all_rows, tiles_n_all, grid);
-        if (first_rows == 0) overlap = false;
-    }
+    const RsRoute rt = rs_route(pl, P, rank, rows, slot_cols, fp8, bt, bf16_slots, cols, do_gemm, do_reduce, overlap, grid);
+    const RsTiling& t = rt.t;
+    const int all_rows = rt.all_rows, tiles_n_all = rt.tiles_n, own_row = rt.own_row, first_rows = rt.first_rows;
     if (do_gemm && ws && !bt && !bf16_slots) {
         // the size of a workspace, checked over the launches of the plan's tiles, whether or not these take the tail
-        const bool parts = pl.tile_m == 256 ? overlap : overlap_asked;
+        const bool parts = pl.tile_m == 256 ? rt.overlap : overlap;
         const int plan_rows = P * pl.tiles_m, kt = (int)(pl.local_k / (fp8 ? 128 : 64));
         const int first = parts ? first_part(pl.tiles_m, plan_rows, pl.tiles_n, grid) : 0;
         for (int n_rows : {first, plan_rows - first})
             if (sk_too_small(ceil_div((int64_t)n_rows * pl.tiles_n, 8) * 8, grid, kt, pl.tile_m, ws_bytes)) return PK_ERR_ARG;
     }
-    // The stream-K tail is for one launch: two launches of a call would share the workspace's flags under one epoch, and a tile's
-    // owner in the second would take the pieces of the first for its own.  Beside the reduce a tail does not pay either (bf16, P = 8,
-    // us a call: 8192 x 7168 x 28672 389 without against 457 with it, 8192 x 5120 x 28672 285 / 331, 8192 x 7168 x 8192 171 / 219).
-    if (overlap || bt || bf16_slots || pl.tile_m != 256) ws = nullptr;
+    overlap = rt.overlap;
+    if (!rs_takes_tail(pl, rt, bt, bf16_slots)) ws = nullptr;
 
     GemmArgs a = {};
     // one launch over `n_rows` tile rows that start at tile row `row0` (wrapping around at all_rows)
@@ -836,7 +857,7 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
             }
         };
         const bool ar_mode = r.ar_flags_in != nullptr;
-        if (overlap && narrow_reduce) {
+        if (overlap && rt.narrow_reduce) {
             switch (P) {
                 case 2: hipLaunchKernelGGL((reduce_kernel<2, false, false, true>), dim3(grid), dim3(256), 0, s, r); break;
                 case 4: hipLaunchKernelGGL((reduce_kernel<4, false, false, true>), dim3(grid), dim3(256), 0, s, r); break;
@@ -872,6 +893,44 @@ static pk_status make_plan_ag_k(int P, int64_t M, int64_t N, int64_t K, pk_dtype
     return PK_OK;
 }
 
+// Which way an all-gather + GEMM goes.
+struct AgRoute {
+    int tile;
+    bool one_span;            // tile rows over all rows instead of chunk by chunk
+    bool sk;                  // with the stream-K tail
+};
+static int64_t ag_plan_slots(const pk_plan& pl, int P) { return ((int64_t)pl.tiles_m * pl.tiles_n + 7) / 8 * 8 * P; }
+static AgRoute ag_route(const pk_plan& pl, int P, int64_t M, bool fp8, bool k_chunks, bool ws, int grid) {
+    const int ktiles = (int)(pl.local_k / (fp8 ? 128 : 64));
+    AgRoute r = {T256x256, k_chunks, ws && !k_chunks && pl.tile_m == 256 && sk_applies(ag_plan_slots(pl, P), grid, ktiles)};
+    if (r.sk) return r;
+    // The tile shape, and how tile rows and row chunks go together.  Where all tiles run at once, or a chunk is lower than a
+    // tile: tile rows over all rows, from the one that holds the own chunk on; a tile waits for every chunk it touches.
+    // Otherwise one scheduling group per chunk, visited from the own one.  Column chunks: every tile needs every chunk.
+    const int64_t chunk_rows = M / P;
+    auto tiles_of = [&](int id, bool* one_span) -> int {
+        const int bm = kTileDim[id].bm;
+        const int all = tiles_across(M, bm), tn = tiles_across(pl.local_n, kTileDim[id].bn);
+        *one_span = k_chunks || P == 1 || chunk_rows < bm || (all * tn + 7) / 8 * 8 <= grid;
+        return (*one_span ? all : P * tiles_across(chunk_rows, bm)) * tn;
+    };
+    int64_t best = INT64_MAX;
+    for (int id = 0; id < (k_chunks ? T32x64 : N_TILES); ++id) {
+        bool span;
+        int64_t cost = tile_cost(id, fp8, tiles_of(id, &span), ktiles, grid);
+        // Many rounds of fp8 tiles run at a lower clock than those the estimate was fitted to, and the largest tile loses least by
+        // it: another one has to be a sixteenth better (6960 x 7728 x 4096: 128x256, estimated at 3% less than 256x256, takes 284
+        // us for 210; 5000 x 5200 x 4096 129 for 109)
+        if (fp8 && pl.tile_m == 256 && id != T256x256) cost += cost / 16;
+        if (cost < best) {
+            best = cost;
+            r.tile = id;
+            r.one_span = span;
+        }
+    }
+    return r;
+}
+
 static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype dt,
                               const void* A_gathered, const void* B_local, const float* scale_a, const float* scale_b,
                               const uint32_t* chunk_flags, uint32_t epoch, void* C_local, int comm_cus, int activation,
@@ -901,37 +960,12 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     a.ktiles = (int32_t)(pl.local_k / (fp8 ? 128 : 64));
     a.n_chunks = P;
     a.act = activation;
-    // The tile shape, and how tile rows and row chunks go together.  Where all tiles run at once, or a chunk is lower than a
-    // tile: tile rows over all rows, from the one that holds the own chunk on; a tile waits for every chunk it touches.
-    // Otherwise one scheduling group per chunk, visited from the own one.  Column chunks: every tile needs every chunk.
     const int64_t chunk_rows = M / P;
     const int grid = max_grid(comm_cus);
-    auto tiles_of = [&](int id, bool* one_span) -> int {
-        const int bm = kTileDim[id].bm;
-        const int all = tiles_across(M, bm), tn = tiles_across(pl.local_n, kTileDim[id].bn);
-        *one_span = k_chunks || P == 1 || chunk_rows < bm || (all * tn + 7) / 8 * 8 <= grid;
-        return (*one_span ? all : P * tiles_across(chunk_rows, bm)) * tn;
-    };
-    bool one_span = k_chunks;
-    int tile = T256x256;
-    const int64_t plan_slots = ((int64_t)pl.tiles_m * pl.tiles_n + 7) / 8 * 8 * P;
-    if (ws && !bt && !k_chunks && sk_too_small(plan_slots, grid, a.ktiles, pl.tile_m, ws_bytes)) return PK_ERR_ARG;
-    const bool sk = ws && !bt && !k_chunks && pl.tile_m == 256 && sk_applies(plan_slots, grid, a.ktiles);
-    if (!sk) {
-        int64_t best = INT64_MAX;
-        for (int id = 0; id < (k_chunks ? T32x64 : N_TILES); ++id) {
-            bool span;
-            int64_t cost = tile_cost(id, fp8, tiles_of(id, &span), a.ktiles, grid);
-            // Many rounds of fp8 tiles run at a lower clock than those the estimate was fitted to, and the largest tile loses least
-            // by it: another one has to be a sixteenth better (6960 x 7728 x 4096: 256x256 265 us, 128x256, estimated at 3% less, 273)
-            if (fp8 && pl.tile_m == 256 && id != T256x256) cost += cost / 16;
-            if (cost < best) {
-                best = cost;
-                tile = id;
-                one_span = span;
-            }
-        }
-    }
+    if (ws && !bt && !k_chunks && sk_too_small(ag_plan_slots(pl, P), grid, a.ktiles, pl.tile_m, ws_bytes)) return PK_ERR_ARG;
+    const AgRoute rt = ag_route(pl, P, M, fp8, k_chunks, ws && !bt, grid);
+    const int tile = rt.tile;
+    const bool one_span = rt.one_span, sk = rt.sk;
     const int bm = kTileDim[tile].bm;
     a.rows_per_shard = (int32_t)(k_chunks ? M : chunk_rows);
     a.rows_per_chunk = a.rows_per_shard;
@@ -1223,6 +1257,38 @@ pk_status pk_partition_destroy(void* compute_stream, void* comm_stream) {
     if (compute_stream && hipStreamDestroy((hipStream_t)compute_stream) != hipSuccess) st = PK_ERR_HIP;
     if (comm_stream && hipStreamDestroy((hipStream_t)comm_stream) != hipSuccess) st = PK_ERR_HIP;
     return st;
+}
+
+// Which way a call goes, for the tests: host only, launches nothing, not part of the interface.  op: 0 pk_gemm_rs, 1 pk_gemm_rs_cols,
+// 2 pk_gemm_ar, 3 pk_ag_gemm, 4 pk_ag_gemm_k.  route: rows and columns of the tiles; 1 if their ready flags are published behind the
+// GEMM; tiles of the first and of the second launch (0: one launch); 1 with a stream-K tail; 1 if tile rows run over all chunks.
+pk_status pk_test_route(int op, int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype dt, int partial_dt, int b_layout, uint32_t phases,
+                        int comm_cus, int has_workspace, int32_t* route) {
+    const bool fp8 = dt == PK_FP8_E4M3, bt = b_layout == PK_B_K_CONTIGUOUS, s16 = partial_dt == PK_PARTIAL_BF16;
+    const bool cols = op == 1, k_chunks = op == 4;
+    const int grid = max_grid(comm_cus);
+    pk_plan pl;
+    if (op >= 3) {
+        const pk_status st = k_chunks ? make_plan_ag_k(P, M, N, K, dt, &pl) : make_plan(P, M, N, K, dt, false, &pl);
+        if (st != PK_OK) return st;
+        const AgRoute r = ag_route(pl, P, M, fp8, k_chunks, has_workspace && !bt, grid);
+        const TileDim d = kTileDim[r.tile];
+        const int64_t rows = r.one_span ? tiles_across(M, d.bm) : P * (int64_t)tiles_across(M / P, d.bm);
+        const int32_t v[7] = {d.bm, d.bn, 0, (int32_t)(rows * tiles_across(pl.local_n, d.bn)), 0, r.sk, r.one_span};
+        for (int i = 0; i < 7; ++i) route[i] = v[i];
+        return PK_OK;
+    }
+    const pk_status st = cols ? make_plan_cols(P, M, N, K, dt, &pl) : make_plan(P, M, N, K, dt, true, &pl);
+    if (st != PK_OK) return st;
+    const bool overlap = (phases & PK_PHASE_OVERLAP) && op == 0 && P > 1;
+    const RsRoute r = rs_route(pl, P, rank, cols ? M : M / P, cols ? N / P : N, fp8, bt, s16, cols, phases & PK_PHASE_GEMM, phases & PK_PHASE_REDUCE,
+                               overlap, grid);
+    const int tiles = r.all_rows * r.tiles_n, first = r.first_rows * r.tiles_n;
+    const int kt = (int)(pl.local_k / (fp8 ? 128 : 64));
+    const bool sk = has_workspace && op == 0 && rs_takes_tail(pl, r, bt, s16) && sk_applies(ceil_div(tiles, 8) * 8, grid, kt);
+    const int32_t v[7] = {kTileDim[r.t.tile].bm, kTileDim[r.t.tile].bn, r.t.late, r.overlap ? first : tiles, r.overlap ? tiles - first : 0, sk, 0};
+    for (int i = 0; i < 7; ++i) route[i] = v[i];
+    return PK_OK;
 }
 
 }  // extern "C"
