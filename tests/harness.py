@@ -1,11 +1,30 @@
 """Glue for the GPU parity tests: uploads seeded numpy inputs, calls libpk through its binding,
 downloads the results.  No arithmetic of the method happens here."""
+import collections
+import ctypes
+
 import numpy as np
 import torch
 
 from paper_2511_13940_amd import pk
 
 NAN_POISON = float("nan")
+
+
+OPS = {"gemm_rs": 0, "gemm_rs_cols": 1, "gemm_ar": 2, "ag_gemm": 3, "ag_gemm_k": 4}
+Route = collections.namedtuple("Route", "tile late first second stream_k one_span")
+
+
+def route(op, P, rank, M, N, K, dtype, phases=pk.PHASE_ALL, partial_dtype="f32", b_layout="kn", comm_cus=0, workspace=False):
+    """Which way a call goes (decided on the host; needs no GPU): tile "rows x columns", flags published behind the GEMM or not, tiles
+    of the first and the second launch (0: one launch), stream-K tail or not, tile rows over all chunks or not."""
+    r = (ctypes.c_int32 * 7)()
+    f = pk.lib().pk_test_route
+    f.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3 + [ctypes.c_uint32] + [ctypes.c_int] * 2 + [ctypes.c_void_p]
+    st = f(OPS[op], P, rank, M, N, K, pk.DTYPES[dtype], pk.PARTIALS[partial_dtype], pk.B_LAYOUTS[b_layout], phases, comm_cus,
+           1 if workspace else 0, r)
+    assert st == pk.OK, pk.status_str(st)
+    return Route(f"{r[0]}x{r[1]}", bool(r[2]), r[3], r[4], bool(r[5]), bool(r[6]))
 
 
 def dev(x):
@@ -77,6 +96,7 @@ def run_gemm_rs(P, rank, M, N, K, dtype, A_bits, B_bits, partials, scale_a=None,
     the emulated peers on the second.
     partial_dtype = "bf16": `partials` holds uint16 bit patterns; outgoing / partials_after come back as uint16.
     workspace: None, True (a fresh zeroed workspace of plan.workspace_bytes) or a device tensor to reuse.
+    phases: one mask, or a tuple of masks for as many calls in a row on the same buffers.
     cols = True: pk_gemm_rs_cols (scatter along the last dimension): slots and the output are M x N/P.
 
     deliver = "pre": peer slots and their flags are in place before the call.
@@ -121,9 +141,10 @@ def run_gemm_rs(P, rank, M, N, K, dtype, A_bits, B_bits, partials, scale_a=None,
         deliver_slots(P, P * mp, ncols, plan.tile_m, plan.tile_n, staging, part, flags_in, epoch, list(order), gap_us, side,
                       n_wg, s16)
     extra = {} if cols else {"workspace": make_workspace(plan, workspace), "b_layout": b_layout}
-    op(P, rank, M, N, K, dtype, A, B, sa, sb, part, outgoing if P > 1 else None,
-       flags_in, flags_out if P > 1 else None, epoch, out, phases, status, timeout_us, stream=main,
-       comm_cus=comm_cus, partial_dtype=partial_dtype, **extra)
+    for ph in phases if isinstance(phases, tuple) else (phases,):
+        op(P, rank, M, N, K, dtype, A, B, sa, sb, part, outgoing if P > 1 else None,
+           flags_in, flags_out if P > 1 else None, epoch, out, ph, status, timeout_us, stream=main,
+           comm_cus=comm_cus, partial_dtype=partial_dtype, **extra)
     torch.cuda.synchronize()
     res = {"out_bits": bits_of(out), "flags_out": flags_out.cpu().numpy(), "flags_in": flags_in.cpu().numpy(),
            "status": status.cpu().numpy(), "plan": plan}

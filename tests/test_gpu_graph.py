@@ -62,10 +62,16 @@ def test_captured_mlp_block_replays_bit_identically():
     assert torch.all(flags_in[rank] == 3) and torch.all(flags_out[(rank + 1) % P] == 3)
 
 
-def test_captured_gemm_rs_with_the_reduce_beside_the_gemm_replays_bit_identically():
+@pytest.mark.parametrize("M,N,parts", [
+    (4096, 2048, (256, 0)),                            # all tiles at once: the flag is ignored, one launch
+    (4096, 8192, (256, 256)),                          # the own block's rows and the rest, two launches
+])
+def test_captured_gemm_rs_with_the_reduce_beside_the_gemm_replays_bit_identically(M, N, parts):
     """PK_PHASE_OVERLAP forks to the library's second stream and joins it back: inside a capture that stream becomes part
     of the graph.  The library's stream and events exist from the eager call on."""
-    P, rank, M, N, K = 4, 1, 4096, 2048, 1024          # 512 tiles of 128: the own block's rows and the rest, two launches
+    P, rank, K = 4, 1, 1024
+    r = hz.route("gemm_rs", P, rank, M, N, K, "bf16", phases=pk.PHASE_ALL | pk.PHASE_OVERLAP)
+    assert (r.first, r.second) == parts
     inp = wl.gemm_rs_inputs(P, M, N, K, "bf16", rank, seed=53)
     A, B = hz.elem_view(inp["A_local"], "bf16"), hz.elem_view(inp["B_local"], "bf16")
     plan = pk.pk_gemm_rs_plan(P, M, N, K, "bf16")

@@ -1,6 +1,6 @@
 """pk_gemm_rs with PK_PHASE_OVERLAP (the reduce beside the second part of the GEMM, on the library's own stream):
 parity against the float64 oracle and bit-identity with the plain call, on shapes whose schedule has more rounds than
-the own block takes (so that the two-launch path is really taken) and on one where the flag must fall back."""
+the own block takes (so that the two-launch path is really taken, which is checked) and on some where the flag must fall back."""
 import numpy as np
 import pytest
 import torch
@@ -16,19 +16,29 @@ pytestmark = pytest.mark.gpu
 OVERLAP = pk.PHASE_ALL | pk.PHASE_OVERLAP
 
 CASES = [
-    # P, rank, M, N, K, dtype, tile
-    (8, 3, 4096, 2048, 2048, "bf16", 128),            # 512 tiles of 128: 2 rounds, own block = a quarter of the first
-    (8, 7, 8192, 4096, 4096, "bf16", 256),            # 512 tiles of 256, last rank: the row rotation wraps around
-    (4, 1, 4400, 2056, 1024, "bf16", 128),            # 9 ragged tile rows per block (not a multiple of the band), ragged columns
-    (8, 2, 8192, 4096, 8192, "fp8", 256),             # 256x256 fp8 kernel: the narrow reduce kernel runs beside it
-    (4, 3, 8192, 4096 + 272, 4096, "fp8", 256),       # the same with a ragged last column tile
-    (2, 0, 4096, 8192, 1024, "bf16", 256),            # own block = half of all tiles, two rounds of four
+    # P, rank, M, N, K, dtype, the plan's tile, tiles of the two launches (0: the flag is ignored, all tiles run at once)
+    (8, 3, 4096, 2048, 2048, "bf16", 128, (256, 0)),
+    (8, 7, 8192, 4096, 4096, "bf16", 256, (256, 256)),       # last rank: the row rotation wraps around
+    (4, 1, 4400, 2056, 1024, "bf16", 128, (162, 0)),         # ragged
+    (8, 2, 8192, 4096, 8192, "fp8", 256, (256, 256)),        # 256x256 fp8 kernel: the narrow reduce kernel runs beside it
+    (4, 3, 8192, 4096 + 272, 4096, "fp8", 256, (504, 72)),   # the same with a ragged last column tile
+    (2, 0, 4096, 8192, 1024, "bf16", 256, (256, 256)),       # own block = half of all tiles, two rounds of four
+    (8, 3, 8 * 250, 8208, 8 * 256, "bf16", 128, (132, 396)),     # 128x256 tiles, blocks of two flag rows, the second ragged
+    (8, 7, 8 * 200, 12304, 8 * 128, "bf16", 128, (196, 196)),    # 256x256 tiles over flags of 128x128, blocks of 200 rows
+    (8, 5, 8 * 250, 8208, 8 * 256, "fp8", 128, (132, 396)),      # fp8 128x256 tiles beside the narrow reduce kernel
+    (3, 1, 12288, 4128, 3 * 256, "fp8", 256, (476, 340)),        # 194 MiB of slots, P = 3: the run-time-P reduce beside the fp8 kernel
 ]
 
 
-@pytest.mark.parametrize("P,rank,M,N,K,dtype,tile", CASES)
+def launches(*args, **kw):
+    r = hz.route("gemm_rs", *args, phases=OVERLAP, **kw)
+    return r.first, r.second
+
+
+@pytest.mark.parametrize("P,rank,M,N,K,dtype,tile,parts", CASES)
 @pytest.mark.parametrize("deliver", ["pre", "emu"])
-def test_overlapped_reduce_matches_oracle_and_plain_call(P, rank, M, N, K, dtype, tile, deliver):
+def test_overlapped_reduce_matches_oracle_and_plain_call(P, rank, M, N, K, dtype, tile, parts, deliver):
+    assert launches(P, rank, M, N, K, dtype) == parts
     inp = wl.gemm_rs_inputs(P, M, N, K, dtype, rank, seed=11)
     kw = dict(scale_a=inp.get("scale_a"), scale_b=inp.get("scale_b"), deliver=deliver, order=inp["order"], epoch=5,
               timeout_us=2_000_000)
@@ -52,10 +62,15 @@ def test_flag_falls_back_when_the_own_block_takes_every_round():
     check_rs(c.P, 1, c.dtype, inp, res, c.K // c.P)
 
 
-def test_bf16_slots_and_repeated_calls_with_rising_epochs():
+@pytest.mark.parametrize("P,rank,M,N,K,parts", [
+    (8, 4, 4096, 2048, 2048, (256, 0)),
+    (8, 4, 4096, 8192, 2048, (256, 256)),                    # 256x256 tiles
+    (8, 6, 8 * 250, 8208, 8 * 256, (132, 396)),              # 128x256 tiles
+])
+def test_bf16_slots_and_repeated_calls_with_rising_epochs(P, rank, M, N, K, parts):
     """bf16 partial slots next to the bf16 kernel, three calls in a row on the same buffers (the second stream and its
     events are reused; every call's reduce must see that call's own block)."""
-    P, rank, M, N, K = 8, 4, 4096, 2048, 2048
+    assert launches(P, rank, M, N, K, "bf16", partial_dtype="bf16") == parts
     outs = []
     for seed, epoch in ((1, 1), (2, 2), (1, 3)):
         inp = wl.gemm_rs_inputs(P, M, N, K, "bf16", rank, seed=seed)
@@ -82,6 +97,7 @@ def test_overlap_on_a_compute_unit_partition_with_live_peers():
     """The GEMM launches on the compute stream of a partition (224 workgroups), the peers' partials arrive through the
     communicator stream while it runs, the reduce on the library's own stream: same bits as the plain pre-landed call."""
     P, rank, M, N, K = 4, 3, 4096, 4096, 4 * 256
+    assert launches(P, rank, M, N, K, "bf16", comm_cus=32) == (192, 64)
     inp = wl.gemm_rs_inputs(P, M, N, K, "bf16", rank, seed=21)
     base = hz.run_gemm_rs(P, rank, M, N, K, "bf16", inp["A_local"], inp["B_local"], inp["partials"])
     check_rs(P, rank, "bf16", inp, base, K // P)
@@ -108,10 +124,14 @@ def test_overlap_flag_with_a_single_rank_is_the_plain_gemm():
     check_rs(1, 0, "bf16", inp, res, 512)
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
-def test_overlap_flag_with_a_k_contiguous_second_operand(dtype):
-    """bf16: the narrow reduce kernel beside the k-contiguous GEMM kernel; fp8: no room beside that kernel, plain order."""
-    P, rank, M, N, K = 8, 6, 8192, 4096, 8192
+@pytest.mark.parametrize("dtype,M,N,K,parts", [
+    ("bf16", 8192, 4096, 8192, (256, 256)),                  # the wide reduce kernel beside the k-contiguous GEMM kernel
+    ("fp8", 8192, 4096, 8192, (512, 0)),                     # less than 192 MiB of slots: the flag is ignored
+    ("fp8", 16384, 4096, 8 * 256, (256, 768)),               # 256 MiB: the narrow reduce kernel beside the k-contiguous fp8 kernel
+])
+def test_overlap_flag_with_a_k_contiguous_second_operand(dtype, M, N, K, parts):
+    P, rank = 8, 6
+    assert launches(P, rank, M, N, K, dtype, b_layout="nk") == parts
     inp = wl.gemm_rs_inputs(P, M, N, K, dtype, rank, seed=13)
     Bt = np.ascontiguousarray(inp["B_local"].T)
     kw = dict(scale_a=inp.get("scale_a"), scale_b=inp.get("scale_b"), epoch=3)
@@ -132,6 +152,7 @@ def test_overlap_flag_with_a_k_contiguous_second_operand(dtype):
 def test_overlapped_reduce_with_a_workspace(P, rank, M, N, K, dtype, comm_cus):
     """The two launches must not meet in the workspace: the same bits as the plain call without one, three calls with rising epochs
     on one workspace, which stays the call site's own (a plain call with it follows)."""
+    assert all(t > (256 - comm_cus) and t % (256 - comm_cus) for t in launches(P, rank, M, N, K, dtype, comm_cus=comm_cus, workspace=True))
     inp = wl.gemm_rs_inputs(P, M, N, K, dtype, rank, seed=15)
     kw = dict(scale_a=inp.get("scale_a"), scale_b=inp.get("scale_b"), comm_cus=comm_cus)
     args = (P, rank, M, N, K, dtype, inp["A_local"], inp["B_local"], inp["partials"])

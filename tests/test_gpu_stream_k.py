@@ -40,6 +40,7 @@ def test_ag_gemm_with_a_workspace(dtype, K, comm_cus):
     P, rank, M, N = 2, 1, 4608, 8192
     inp = wl.ag_gemm_inputs(P, M, N, K, dtype, rank, seed=31)
     kw = dict(scale_a=inp["scale_a"], scale_b=inp["scale_b"], comm_cus=comm_cus)
+    assert hz.route("ag_gemm", P, rank, M, N, K, dtype, comm_cus=comm_cus, workspace=True).stream_k
     res = hz.run_ag_gemm(P, rank, M, N, K, dtype, inp["chunks"], inp["B_local"], workspace=True, **kw)
     check_ag(P, rank, dtype, inp, res, K)
     again = hz.run_ag_gemm(P, rank, M, N, K, dtype, inp["chunks"], inp["B_local"], workspace=True, epoch=7, **kw)
@@ -66,17 +67,22 @@ def test_ag_gemm_workspace_reused_across_epochs_and_arrival_orders():
 
 
 def test_ag_gemm_small_tiles_with_a_workspace():
-    """288 tiles of 128 x 128 (a problem too small for the large tiles), 16 k-tiles each."""
+    """288 tiles of 128 x 128 (a problem too small for the large tiles), 16 k-tiles each: such plans take no tail, and the bits are
+    those of the call without a workspace."""
     P, rank, M, N, K = 1, 0, 2304, 2048, 1024
     inp = wl.ag_gemm_inputs(P, M, N, K, "bf16", rank, seed=33)
     assert pk.pk_ag_gemm_plan(P, M, N, K, "bf16").tile_m == 128
+    assert not hz.route("ag_gemm", P, rank, M, N, K, "bf16", workspace=True).stream_k
     res = hz.run_ag_gemm(P, rank, M, N, K, "bf16", inp["chunks"], inp["B_local"], workspace=True)
     check_ag(P, rank, "bf16", inp, res, K)
+    plain = hz.run_ag_gemm(P, rank, M, N, K, "bf16", inp["chunks"], inp["B_local"])
+    assert np.array_equal(res["C_bits"], plain["C_bits"])
 
 
 @pytest.mark.parametrize("comm_cus", [0, 192])
 def test_gemm_rs_with_a_workspace(comm_cus):
     P, rank, M, N, K = 2, 0, 4608, 4096, 2048
+    assert hz.route("gemm_rs", P, rank, M, N, K, "bf16", comm_cus=comm_cus, workspace=True).stream_k
     inp = wl.gemm_rs_inputs(P, M, N, K, "bf16", rank, seed=34)
     res = hz.run_gemm_rs(P, rank, M, N, K, "bf16", inp["A_local"], inp["B_local"], inp["partials"], workspace=True,
                          comm_cus=comm_cus)

@@ -1,0 +1,61 @@
+"""Which way a call goes (tile shape, one or two launches, stream-K tail), decided on the host: checked without a GPU for the cases
+that the GPU tests name, so that another choice does not take a test past the path it is there for."""
+import random
+
+import pytest
+
+from paper_2511_13940_amd import pk
+from tests import harness as hz
+from tests import test_gpu_overlap_reduce as ov
+from tests import test_gpu_tile_shapes as ts
+
+OVERLAP = pk.PHASE_ALL | pk.PHASE_OVERLAP
+
+
+@pytest.mark.parametrize("dtype,P,rank,M,N,kl,layout,slots,whole,alone", ts.RS_CASES)
+def test_gemm_rs_cases(dtype, P, rank, M, N, kl, layout, slots, whole, alone):
+    kw = dict(partial_dtype=slots, b_layout=layout)
+    assert ts.tile("gemm_rs", P, rank, M, N, P * kl, dtype, **kw) == whole
+    assert ts.tile("gemm_rs", P, rank, M, N, P * kl, dtype, phases=pk.PHASE_GEMM, **kw) == alone
+
+
+def test_other_cases():
+    for P, rank, M, N, kl, dtype, want in ts.COLS_CASES:
+        assert ts.tile("gemm_rs_cols", P, rank, M, N, P * kl, dtype) == want
+    for dtype, P, rank, M, N, K, layout, _, want in ts.AG_CASES:
+        assert ts.tile("ag_gemm", P, rank, M, N, K, dtype, b_layout=layout) == want
+    for dtype, P, rank, M, N, K, want in ts.AGK_CASES:
+        assert ts.tile("ag_gemm_k", P, rank, M, N, K, dtype) == want
+
+
+def test_every_tile_shape_is_among_the_cases():
+    for dtype in ("bf16", "fp8"):
+        seen = {c[8].split()[0] for c in ts.RS_CASES + ts.AG_CASES if c[0] == dtype}
+        assert {"256x256", "128x256", "128x128", "128x64", "64x64", "32x32"} <= seen, (dtype, seen)
+
+
+def test_two_launches_never_take_a_tail_and_their_tiles_add_up():
+    rng = random.Random(7)
+    two = tails = 0
+    for _ in range(4000):
+        dtype = rng.choice(["bf16", "fp8"])
+        P = rng.choice([1, 2, 3, 4, 5, 8])
+        M, N, K = P * rng.randrange(1, 4096), 16 * rng.randrange(1, 1024), P * 128 * rng.randrange(1, 40)
+        kw = dict(workspace=True, comm_cus=rng.choice([0, 0, 32, 192]), partial_dtype=rng.choice(["f32", "f32", "bf16"]))
+        if kw["partial_dtype"] == "f32":
+            kw["b_layout"] = rng.choice(["kn", "kn", "nk"])
+        rank = rng.randrange(P)
+        over, plain = (hz.route("gemm_rs", P, rank, M, N, K, dtype, phases=ph, **kw) for ph in (OVERLAP, pk.PHASE_ALL))
+        assert over.tile == plain.tile and over.late == plain.late and plain.second == 0
+        assert over.first + over.second == plain.first
+        assert not (over.second and (over.stream_k or over.late))
+        assert over.second or over.stream_k == plain.stream_k
+        two += over.second > 0
+        tails += plain.stream_k
+    assert two > 200 and tails > 200
+
+
+@pytest.mark.parametrize("P,rank,M,N,K,dtype,tile,parts", ov.CASES)
+def test_overlap_cases(P, rank, M, N, K, dtype, tile, parts):
+    assert pk.pk_gemm_rs_plan(P, M, N, K, dtype).tile_m == tile
+    assert ov.launches(P, rank, M, N, K, dtype) == parts
