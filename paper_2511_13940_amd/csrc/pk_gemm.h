@@ -1010,24 +1010,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 #pragma clang loop unroll(disable)
                 for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{});
             } else {
-                // odd k-steps per k-tile: the starting set alternates, so k-tiles go in pairs (with 64-byte k-tiles nkt is even:
-                // the host admits only k ranges of whole 128-byte units)
-                constexpr bool EVEN = KB == 64;
-                static_assert(!EVEN || NS % 2 == 0, "pairs of k-tiles need an even ring");
+                // odd k-steps per k-tile: the starting set alternates, so k-tiles go in pairs (such k-tiles are 64 bytes, and the
+                // host admits only k ranges of whole 128-byte units)
+                static_assert(KS % 2 == 0 || (KB == 64 && NS % 2 == 0), "pairs of k-tiles need an even number of them and an even ring");
 #pragma clang loop unroll(disable)
-                for (; kt + (EVEN ? 0 : 1) + NS < nkt; kt += 2) {
+                for (; kt + NS < nkt; kt += 2) {
                     ktile(kt, nkt, T{}, E{}, F{});
                     ktile(kt + 1, nkt, T{}, O{}, F{});
-                }
-                if (!EVEN && kt + NS < nkt) {            // one more with loads: the rest starts on set 1
-                    ktile(kt, nkt, T{}, E{}, F{});
-                    ktile(kt + 1, nkt, F{}, O{}, F{});
-                    kt += 2;
                 }
 #pragma clang loop unroll(disable)
                 for (; kt < nkt; kt += 2) {
                     ktile(kt, nkt, F{}, E{}, F{});
-                    if (EVEN || kt + 1 < nkt) ktile(kt + 1, nkt, F{}, O{}, F{});
+                    ktile(kt + 1, nkt, F{}, O{}, F{});
                 }
             }
         };
