@@ -173,6 +173,28 @@ def test_activation_of_every_bf16_value(act, lowest, K):
     assert np.all(np.abs(got - want) <= (2.0 ** -8 + units * 2.0 ** -24) * np.abs(want) + 2.0 ** -134)
 
 
+@pytest.mark.parametrize("act", ["silu", "gelu_tanh", "relu"])
+def test_activation_of_special_values(act):
+    """Infinities, NaN, the largest values and zeros among ordinary ones: x * sigmoid(y) is NaN at -infinity (0 times infinity), zero
+    with its sign for large negative values, x for large positive ones; max(x, 0) takes no NaN."""
+    x = np.array([np.inf, -np.inf, np.nan, 3e38, -3e38, 1e4, -1e4, 0.0, -0.0, 1.5, 88.0, -200.0])
+    relu = act == "relu"
+    want = np.array([np.inf, 0.0 if relu else np.nan, 0.0 if relu else np.nan, 3e38, 0.0, 1e4, 0.0, 0.0, 0.0, np.nan, 88.0, 0.0])
+    M, N, K = 96, 16, 64
+    A, B = np.zeros((M, K), dtype=np.uint16), np.zeros((K, N), dtype=np.uint16)
+    A[:, 0] = np.resize(codec.bf16_encode(np.where(np.isfinite(x), x, 0.0)), M)
+    A[:, 0] = np.where(np.resize(x, M) == np.inf, 0x7F80, np.where(np.resize(x, M) == -np.inf, 0xFF80, A[:, 0]))
+    A[np.isnan(np.resize(x, M)), 0] = 0x7FC0
+    B[0, :] = 0x3F80
+    res = hz.run_ag_gemm(1, 0, M, N, K, "bf16", [A], B, act=act)
+    got = codec.bf16_decode(res["C_bits"])
+    for i in range(M):
+        w = want[i % x.size]
+        if i % x.size == 9:
+            w = tp_gemm.activation(1.5, act)                  # an ordinary value beside the special ones
+        assert np.all(np.isnan(got[i]) if np.isnan(w) else np.isclose(got[i], w, rtol=2.0 ** -8, atol=0)), (i, x[i % x.size], got[i, 0])
+
+
 def test_mlp_block_chain_matches_the_oracle():
     """AG + GEMM with fused SiLU, its bf16 output fed to GEMM + RS as the local operand (paper section 4.1), against the
     oracle's chained definition."""
