@@ -755,17 +755,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             // FULL: the tile lies inside the matrix and goes to one buffer, so no store is predicated and a wave issues exactly
             // EPI_STORES of them (fp32 slots: and its rows start on 128-byte lines).
             constexpr bool BIG = BM * BN == 256 * 256 && !SK;    // shapes that run many rounds
-            auto emit = [&](auto act_c, auto full_c) {
+            auto emit = [&](auto act_c, auto full_c, auto lines_c) {
                 constexpr bool ACT = decltype(act_c)::value;     // staged as fp32, activated on the way out
                 constexpr bool FULL = decltype(full_c)::value;
+                constexpr bool LINES = decltype(lines_c)::value; // the tile's rows start on 128-byte lines
                 constexpr int ST_ELEM = (EPI == EPI_RS || ACT) ? 4 : 2;
                 constexpr int STG = EPI_BYTES / NW;
                 // columns of a pass: 32 where the slab then has 32 rows, so that all lanes write (fp32 slabs of 16 rows x 64
-                // columns keep half of them idle).  Not in the general form of a 256x256 tile, which also serves rows that do
-                // not start on 128-byte lines: a row piece then writes parts of lines at both of its ends, and the longer the
-                // pieces, the fewer of them (5120 x 4840 x 2304, fp32 slots: 177 us in 128-byte pieces, 161 in 256; smaller
-                // tiles: no difference).
-                constexpr int CP = (ST_ELEM == 4 && !ACT && STG >= 32 * 32 * 4 && (FULL || !BIG)) ? 32 : WCOLS;
+                // columns keep half of them idle).  Not where rows do not start on 128-byte lines: a row piece then writes parts
+                // of lines at both of its ends, and the longer the pieces, the fewer of them (256x256 tiles, 5120 x 4840 x 2304: 177
+                // us in 128-byte pieces, 161 in 256; 128x256 tiles, 6000 x 1160 x 320: 32.6 and 29.7; on lines, 4096 x 2048 x 320,
+                // 22.7 and 23.1).
+                constexpr int CP = (ST_ELEM == 4 && !ACT && STG >= 32 * 32 * 4 && LINES) ? 32 : WCOLS;
                 constexpr int ROW_BYTES = CP * ST_ELEM;
                 constexpr int ROWS_PASS = STG / ROW_BYTES >= 32 ? 32 : STG / ROW_BYTES;
                 static_assert(ROWS_PASS == 32 || ROWS_PASS == 16 || ROWS_PASS == 8 || ROWS_PASS == 4, "staging area too small");
@@ -876,8 +877,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             };
             using T = std::true_type;
             using F = std::false_type;
+            const bool lines = ((dst + (uint64_t)p_col0 * OUT_ELEM | (uint64_t)dst_pitch) & 127) == 0;
             bool full = BIG && p_row0 + BM <= p_row_end && p_col0 + BN <= p_col_end;
-            if (EPI == EPI_RS) full = full && ((dst | (uint64_t)dst_pitch) & 127) == 0;
+            if (EPI == EPI_RS) full = full && lines;
             if constexpr (IS_RS) {
                 if (full && own_rows > 0) {                  // all rows own, none, or (not full) some of them
                     const bool all = p_row0 >= own_row0 && p_row_end <= own_row0 + own_rows;
@@ -885,15 +887,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                     if (all) dst += own_delta;
                     full = all || none;
                 }
-                if (BIG && full) emit(F{}, T{});
-                else emit(F{}, F{});
+                if (BIG && full) emit(F{}, T{}, T{});
+                else if (EPI == EPI_RS && !BIG && lines) emit(F{}, F{}, T{});
+                else emit(F{}, F{}, F{});
             } else {
                 if (g.act != PK_ACT_NONE) {
-                    if (BIG && full) emit(T{}, T{});
-                    else emit(T{}, F{});
+                    if (BIG && full) emit(T{}, T{}, T{});
+                    else emit(T{}, F{}, F{});
                 } else {
-                    if (BIG && full) emit(F{}, T{});
-                    else emit(F{}, F{});
+                    if (BIG && full) emit(F{}, T{}, T{});
+                    else emit(F{}, F{}, F{});
                 }
             }
             p_full = full;

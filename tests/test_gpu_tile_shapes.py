@@ -40,6 +40,16 @@ RS_CASES = [
     ("fp8", 2, 0, 2000, 4112, 256, "nk", "f32", "256x256", "256x256"),        # shards of 1000 rows
     ("fp8", 3, 2, 3 * 500, 2064, 2176, "kn", "f32", "128x128", "128x128"),    # 17 k-tiles
     ("fp8", 1, 0, 130, 144, 1152, "kn", "f32", "32x32 late", "128x128"),      # nine k-tiles over four waves
+    # fp32 rows that start on 128-byte lines (written in pieces of 32 columns; those of the cases above mostly do not)
+    ("bf16", 8, 3, 1024, 4128, 2560, "kn", "f32", "256x128", "256x128"),
+    ("bf16", 8, 1, 6000, 1184, 320, "kn", "f32", "128x256 late", "128x256"),
+    ("bf16", 8, 1, 6000, 1160, 320, "kn", "f32", "128x256 late", "128x256"),  # (not on lines)
+    ("bf16", 8, 3, 1024, 4096, 2560, "kn", "f32", "128x128", "128x128"),
+    ("bf16", 8, 2, 8 * 77, 1024, 1152, "kn", "f32", "64x64 late", "128x128"),
+    ("bf16", 4, 2, 4 * 75, 992, 1088, "nk", "f32", "32x64 late", "32x64 late"),
+    ("bf16", 8, 7, 64, 512, 4032, "kn", "f32", "32x32 late", "32x32 late"),
+    ("fp8", 8, 2, 8 * 33, 4096, 256, "kn", "f32", "128x64 late", "128x128"),
+    ("fp8", 2, 0, 520, 1536, 256, "kn", "f32", "64x64 late", "128x128"),
     ("bf16", 8, 3, 1024, 4104, 2560, "kn", "bf16", "256x128", "256x128"),     # bf16 slots from here on
     ("bf16", 8, 2, 8 * 77, 1040, 1152, "kn", "bf16", "64x64 late", "128x128"),
     ("bf16", 8, 7, 64, 520, 4032, "kn", "bf16", "32x32 late", "32x32 late"),
