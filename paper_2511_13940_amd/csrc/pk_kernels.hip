@@ -655,12 +655,14 @@ static RsRoute rs_route(const pk_plan& pl, int P, int rank, int64_t rows, int64_
     // Registers per lane that the 256x256 GEMM kernels leave beside their two waves per SIMD (512 less twice their own, in steps of 8):
     // bf16 96 (80 with bf16 slots), fp8 48 (64 with the second operand k-contiguous).  A wave of the reduce kernel takes 64 at most,
     // 48 where it runs beside fp8: its narrow form for fp32 slots and P = 2, 4, 8, else the form for bf16 slots or a run-time P.
-    // The narrow form is also the faster one there: with twice the loads in flight the reduce takes more bandwidth and clock from a
-    // GEMM that lives on both (16384 x 16384 x 2048: 676 us against 706 us a call).
-    // The other forms pay from about 200 MB of slots on (fp8, bf16 slots, P = 8: 16384 x 8192 x 2048 288 -> 272 us; 8192 x 8192 x 1024,
-    // half the bytes, 102 -> 107 us; 15728 x 1376 x 1152 45 -> 57 us): splitting the GEMM costs about 12 us.  The same line for a
+    // The narrow form is also the faster one beside fp8, and beside the 256x256 bf16 kernel with the second operand k-contiguous: with
+    // twice the loads in flight the reduce takes more bandwidth and clock from the GEMM (fp8 16384 x 16384 x 2048: 676 us against
+    // 706 us a call; bf16 k-contiguous 3624 x 12472 x 576 152 against 165, 8192 x 4096 x 512 91 against 98, 8192 x 8192 x 3584 419
+    // against 417).
+    r.narrow_reduce = (fp8 || (bt && pl.tile_m == 256)) && !bf16_slots && (P == 2 || P == 4 || P == 8);
+    // Beside fp8 the other forms pay from about 200 MB of slots on (bf16 slots, P = 8: 16384 x 8192 x 2048 288 -> 272 us; 8192 x 8192 x
+    // 1024, half the bytes, 102 -> 107 us; 15728 x 1376 x 1152 45 -> 57 us): splitting the GEMM costs about 12 us.  The same line for a
     // k-contiguous second operand (6064 x 2640 x 3328, fp32 slots: 88 -> 95 us; at 128 MB 105 -> 103).
-    r.narrow_reduce = fp8 && !bf16_slots && (P == 2 || P == 4 || P == 8);
     if (fp8 && (bt || !r.narrow_reduce) && m_all * slot_cols * (bf16_slots ? 2 : 4) < (192 << 20)) overlap = false;
     if (overlap) r.first_rows = first_part(r.own_rows, r.all_rows, r.tiles_n, grid);
     r.overlap = r.first_rows > 0;

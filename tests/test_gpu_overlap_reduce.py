@@ -125,7 +125,7 @@ def test_overlap_flag_with_a_single_rank_is_the_plain_gemm():
 
 
 @pytest.mark.parametrize("dtype,M,N,K,parts", [
-    ("bf16", 8192, 4096, 8192, (256, 256)),                  # the wide reduce kernel beside the k-contiguous GEMM kernel
+    ("bf16", 8192, 4096, 8192, (256, 256)),                  # the narrow reduce kernel beside the k-contiguous GEMM kernel
     ("fp8", 8192, 4096, 8192, (512, 0)),                     # less than 192 MiB of slots: the flag is ignored
     ("fp8", 16384, 4096, 8 * 256, (256, 768)),               # 256 MiB: the narrow reduce kernel beside the k-contiguous fp8 kernel
 ])
