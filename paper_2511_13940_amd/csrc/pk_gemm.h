@@ -315,14 +315,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     if constexpr (FP8) scale = g.scale_a[0] * g.scale_b[0];
     // the non-linearity between the two GEMMs of the MLP (paper section 4.1), fused into the all-gather epilogue, in fp32 on
     // the accumulators before the rounding.  x/2 (1 + tanh(u)) is x * sigmoid(2u), so both smooth ones are x / (1 + exp(-y)).
-    // |y| <= 87 (all values of the wave): exp(-y) = 2^n 2^f with the rounding error of y log2 e carried in f, and the quotient by a
+    // exp(-y) = 2^n 2^f with the rounding error of y log2 e carried in f.  |y| <= 87 (all values of the wave): the quotient by a
     // reciprocal and one Newton step, which needs no scaling while 1 + exp(-y) < 2^126; for GELU the step also takes back the
-    // rounding of 1 + exp(-y).  Otherwise the library's exponential and division.  Error in units of 2^-24 of the value: SiLU 3.1 at
+    // rounding of 1 + exp(-y).  Otherwise by a full division, for GELU with y > 1 as x - x exp(-y) / (1 + exp(-y)), so that the errors
+    // of the exponential and the quotient enter times exp(-y).  Error in units of 2^-24 of the value: SiLU 3.1 at
     // most (0.61 rms) down to x = -88.7, as with the library functions throughout; GELU 1.7 (0.48 rms) for x > 0 (by tanh() 2.5 and
     // 0.66) and for x < 0 what the rounding of y leaves, 3.6 down to x = -1 and 108 down to -8.
     // us a call, with the library functions throughout / so / with the hardware's exponential and reciprocal as they are (SiLU 4.3
     // units, and zero below -87.3; GELU 3.2): SiLU 64 x 3584 x 8192 26.0 / 25.4 / 25.3, 13884 x 1736 x 512 65.7 / 51.4 / 49.6, 8192 x
-    // 3584 x 8192 402 / 388 / 386; GELU 1512 x 1720 x 5120 40.2 / 38.7 / 38.1, 13884 x 1736 x 512 65.5 / 55.8 / 49.6.
+    // 3584 x 8192 402 / 388 / 386; GELU 1512 x 1720 x 5120 40.2 / 38.7 / 38.1, 13884 x 1736 x 512 65.5 / 54 / 49.6.
     auto activate8 = [&](f32x4 a, f32x4 b) -> bf16x8 {
 #pragma clang fp contract(off)
         float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
@@ -334,20 +335,24 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         }
         constexpr float kC1 = 1.5957691216057308f, kC3 = kC1 * 0.044715f;      // 2 sqrt(2/pi)
         constexpr float kLog2e = 1.44269502f, kLog2eLo = 1.92596303e-8f;
+        auto exp_minus = [&](float y) -> float {                               // |y| <= 200
+#pragma clang fp contract(off)
+            const float p = y * -kLog2e, n = __builtin_rintf(p);
+            const float f = (p - n) + __builtin_fmaf(y, -kLog2eLo, __builtin_fmaf(y, -kLog2e, -p));
+            return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
+        };
         auto smooth = [&](auto silu_c) {
 #pragma clang fp contract(off)
             constexpr bool SILU = decltype(silu_c)::value;
-            float y[8], top = 0.f;
+            auto arg = [&](float x) { return SILU ? x : x * __builtin_fmaf(kC3 * x, x, kC1); };
+            float top = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                y[e] = SILU ? x[e] : x[e] * __builtin_fmaf(kC3 * x[e], x[e], kC1);
-                top = fmaxf(top, fabsf(y[e]));                                 // (a NaN passes through either way)
-            }
-            if (__any(top > 87.f)) {
+            for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(x[e]));         // (a NaN passes through either way)
+            if (__any(top > (SILU ? 87.f : 9.9f))) {                           // GELU: |y| is 85 at 9.9
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float ex = expf(-y[e]);
-                    const bool rest = !SILU && y[e] > 1.f && ex > 0.f;         // (ex = 0: x may be infinite)
+                    const float y = arg(x[e]), ex = exp_minus(__builtin_amdgcn_fmed3f(y, -200.f, 200.f));
+                    const bool rest = !SILU && y > 1.f && ex > 0.f;            // (ex = 0: x may be infinite)
                     const float q = (rest ? x[e] * ex : x[e]) / (1.f + ex);
                     o[e] = (__bf16)(rest ? x[e] - q : q);
                 }
@@ -355,10 +360,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float p = y[e] * -kLog2e, n = __builtin_rintf(p);
-                const float f = (p - n) + __builtin_fmaf(y[e], -kLog2eLo, __builtin_fmaf(y[e], -kLog2e, -p));
-                const float ex = __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
-                const float d = 1.f + ex, r = __builtin_amdgcn_rcpf(d), q = x[e] * r;
+                const float ex = exp_minus(arg(x[e])), d = 1.f + ex, r = __builtin_amdgcn_rcpf(d), q = x[e] * r;
                 float rem = __builtin_fmaf(-d, q, x[e]);
                 if constexpr (!SILU) rem = __builtin_fmaf(-((1.f - d) + ex), q, rem);
                 o[e] = (__bf16)__builtin_fmaf(rem, r, q);
