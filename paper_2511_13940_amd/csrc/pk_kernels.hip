@@ -57,30 +57,24 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     const int row_stop = min(min(row_start + r.rows_sub, (tmi + 1) * r.tile_m), r.rows);
     if (row_start >= row_stop) return;               // below the last row of the shard (never the first work item of a tile)
 
-    // `signal` for the tiles of the GEMM in front: it has ended, so everything it wrote (through) is in memory
-    const int own = r.late_signal ? r.rank : -1;
+    // wait (paper appendix C): one lane per source rank polls that rank's flag for this tile.  Every wave polls for itself and
+    // decides with a ballot: the instantiations without all-reduce mode use no LDS, not even the word a workgroup-wide vote takes,
+    // so that their workgroups fit on a compute unit whose LDS a GEMM workgroup holds whole.
+    const int p = tid & 63, own = r.late_signal ? r.rank : -1;
+    const uint32_t* flag = r.flags_in + (int64_t)p * r.flags_per_slot + tile;
+    const bool mine = (!AR || tid < 64) && p < P && p != own;
+    bool late = mine && !flag_ready(flag, r.epoch);
+    // `signal` for the tiles of the GEMM in front: it has ended, so everything it wrote (through) is in memory.  Behind the first
+    // look, whose answer then does not wait for this store (a wave's memory operations complete in order), and before any waiting.
     if (r.late_signal && sb == 0 && tid < P)
         flag_publish((tid == r.rank ? r.flags_in : r.flags_out) + (int64_t)tid * r.flags_per_slot + tile, r.epoch);
-
-    // wait (paper appendix C): one lane per source rank polls that rank's flag for this tile
-    int late = 0;
+    if (late) {
+        late = !flag_wait(flag, r.epoch, r.timeout_ticks);
+        if (late && tid < 64) report_timeout(r.status, (uint32_t)tile, 2u);
+    }
     if constexpr (AR) {
-        if (tid < P && tid != own) {
-            if (!flag_wait(r.flags_in + (int64_t)tid * r.flags_per_slot + tile, r.epoch, r.timeout_ticks)) {
-                report_timeout(r.status, (uint32_t)tile, 2u);
-                late = 1;
-            }
-        }
         if (__syncthreads_or(late)) return;      // the whole workgroup leaves together: it meets at a barrier below
     } else {
-        // every wave polls for itself and decides with a ballot: this instantiation uses no LDS, not even the word a
-        // workgroup-wide vote takes, so that its workgroups fit on a compute unit whose LDS a GEMM workgroup holds whole
-        for (int p = tid & 63; p < P; p += 64) {
-            if (p != own && !flag_wait(r.flags_in + (int64_t)p * r.flags_per_slot + tile, r.epoch, r.timeout_ticks)) {
-                if (tid < 64) report_timeout(r.status, (uint32_t)tile, 2u);
-                late = 1;
-            }
-        }
         if (__ballot(late) != 0) return;
     }
 

@@ -233,3 +233,16 @@ def test_overlap_flag_beside_the_fp8_kernel_with_bf16_slots():
     assert np.array_equal(over["out_bits"], plain["out_bits"])
     for q in range(P):
         assert q == rank or np.array_equal(over["outgoing"][q], plain["outgoing"][q])
+
+
+@pytest.mark.parametrize("P,rank,M,N,kl", [(4, 1, 1600, 376, 256), (8, 7, 64, 520, 4032)])
+def test_flags_published_behind_the_gemm_do_not_wait_for_a_late_peer(P, rank, M, N, kl):
+    """One flag of one peer never comes: that tile's reduce gives up after the time limit, but every flag of this rank's own work is
+    out, also those of that tile (other ranks wait for them)."""
+    assert hz.route("gemm_rs", P, rank, M, N, P * kl, "bf16").late
+    inp = wl.gemm_rs_inputs(P, M, N, P * kl, "bf16", rank, seed=3)
+    res = hz.run_gemm_rs(P, rank, M, N, P * kl, "bf16", inp["A_local"], inp["B_local"], inp["partials"], epoch=5, timeout_us=20000,
+                         withhold=((rank + 1) % P, 0))
+    assert res["status"][0] == pk.ERR_TIMEOUT and res["status"][1] == 0 and res["status"][2] == 2
+    assert np.all(res["flags_in"][rank] == 5)
+    assert all(np.all(res["flags_out"][q] == 5) for q in range(P) if q != rank)
