@@ -37,6 +37,10 @@
  *     (index = tile); phase 3: pk_gemm_ar's closing wait (index = flag); phase 4: a GEMM workgroup waiting for another
  *     one's piece of a shared tile (index = workgroup).
  *     timeout_us = 0 selects the default (2 s).  The caller zeroes `status` (PK_STATUS_WORDS x uint32) before the call.
+ *   - a call's result does not depend on what arrives when, nor on other calls: the same call gives the same bits.  The
+ *     order in which the products along k are added depends on the tiles that the call computes in, and these are chosen by
+ *     the sizes, the element type, the layout of the second operand, comm_cus, whether the GEMM and the reduce are one call
+ *     or two (`phases`), and a workspace: calls that differ in one of these may differ in the last bits of their fp32 sums.
  *   - status[4..7] receive a timing report from workgroup 0 of the call's GEMM kernel: [4] ticks of the 100 MHz
  *     wall clock and [5] core-clock cycles from its start to its end ([5] / [4] x 100 MHz = the clock the chip
  *     held), [6] core-clock cycles inside its main loops, [7] the number of tiles it computed.
@@ -119,7 +123,8 @@ typedef struct {
  * call to call, and two calls that may run at the same time must not share it.  workspace = NULL: whole tiles only (also
  * with PK_B_K_CONTIGUOUS, with bf16 slots and with plans of 128 x 128 tiles, for which the tail is not built, and where
  * PK_PHASE_OVERLAP splits the GEMM into two launches).
- * A workspace smaller than plan.workspace_bytes may be rejected with PK_ERR_ARG.
+ * A workspace smaller than plan.workspace_bytes may be rejected with PK_ERR_ARG, also where the call would not use it (plans
+ * of 128 x 128 tiles report and check the size that a tail of theirs would take).
  */
 #define PK_WS_FLAG_BYTES 4096
 
@@ -256,7 +261,8 @@ pk_status pk_gemm_ar(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype 
  * units this call leaves free for the communicator workgroups that move the chunks while it runs: the GEMM is
  * launched on the remaining ones (rounded down to a multiple of 8, at least 8).  0 = use every compute unit:
  * communicator workgroups then run only where they fit beside a GEMM workgroup (it holds most or all of the compute
- * unit's LDS and leaves 96 registers per lane or more, bf16, or 64, fp8) or where the schedule leaves a compute unit empty.
+ * unit's LDS and leaves 80 registers per lane or more, bf16, or 48, fp8; none in a call that a workspace takes to the stream-K
+ * tail) or where the schedule leaves a compute unit empty.
  * Requirements: M % P == 0, N % P == 0, K % 64 == 0 (bf16) or % 128 == 0 (fp8), (N/P) % 8 == 0 (bf16) or
  * % 16 == 0 (fp8).  With P == 1 this is a plain GEMM with bf16 output (chunk_flags may then be NULL).
  */

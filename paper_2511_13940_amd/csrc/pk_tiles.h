@@ -41,8 +41,9 @@ constexpr TileWaves tile_waves(int tile, bool fp8, bool bt) {
 // Estimated time, in nanoseconds x grid, of `tiles` tiles over `kt` 128-byte k-tiles on `grid` workgroups: rounds x (fixed part
 // + k-tile time), the k-tile time rising with the share of the compute units at work (clock, L2 and memory traffic).  The
 // figures are fitted to 36 shapes of bf16 and 17 of fp8 GEMMs from 16 x 3584 x 8192 to 8192 x 8192 x 3584, timed with every
-// tile shape: the tile of least estimated time was the fastest one, or within 3.2% of it, on all of them (and on 17 shapes with
-// a k-contiguous second operand).
+// tile shape: the tile of least estimated time was the fastest one, or within 3.2% of it, on those (and on 17 shapes with
+// a k-contiguous second operand).  Elsewhere it can be further off: many rounds of fp8 tiles (see ag_route), or calls that the
+// stores of fp32 slots bound, which the estimate does not count.
 struct TileCost {
     int lo, hi, fixed;        // ns per k-tile with few and with all compute units at work, ns per tile
 };
