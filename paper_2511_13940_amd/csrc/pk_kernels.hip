@@ -1264,6 +1264,8 @@ pk_status pk_test_route(int op, int P, int rank, int64_t M, int64_t N, int64_t K
     const bool cols = op == 1, k_chunks = op == 4;
     const int grid = max_grid(comm_cus);
     pk_plan pl;
+    if (!route) return PK_ERR_NULL;
+    if (op < 0 || op > 4) return PK_ERR_ARG;
     if (op >= 3) {
         const pk_status st = k_chunks ? make_plan_ag_k(P, M, N, K, dt, &pl) : make_plan(P, M, N, K, dt, false, &pl);
         if (st != PK_OK) return st;
