@@ -175,6 +175,14 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int NL = NA + NB;
     constexpr int KST = FP8 ? KB / 64 : KB / 32;         // MFMA k-steps per k-tile
     constexpr int KS = PRIV ? KST : KST / WK;            // ... of which each of the WK wave groups takes its own share
+    // SPREAD: the loads of a k-tile are issued a share per k-step over the KS steps that follow the barrier which frees its stage, not
+    // all in the first of them: NW * NL KB at once are more than the L1 takes in the time of that step, and a wave whose load does
+    // not go out issues no MFMA behind it.  Cycles per 128-byte k-tile, at once / spread: 256x128 bf16 1315 / 1132 (k-contiguous 1278 /
+    // 1126), fp8 1295 / 1213; 128x256 k-contiguous 1409 / 1166.  Where few compute units work that is the time (1024 x 1792 x 4096, 56
+    // tiles: 41.9 / 37.6 us), on all of them the clock gives most of it back (1024 x 8192 x 3584 reduce-scatter 65.1 / 63.1 us).
+    // The smaller tiles are bound by what the L1 takes in all (128x128 k-contiguous, 1512 x 1720 x 5120: 38.6 / 39.0 us), two stages
+    // leave no time to land (256x256 k-contiguous 2405 / 2792 cycles), and a 64-byte k-tile has half the loads.
+    constexpr bool SPREAD = KS % 2 == 0 && KB == 128 && NS >= 3 && BM * BN >= 256 * 128;
     constexpr int EPI_OFF = RINGS * NS * STAGE;          // LDS offset of the epilogue staging area
     constexpr int EPI_BYTES = epi_stage_bytes<BM, BN, KB, RINGS * NS>();
     // WK > 1: the groups' accumulators are summed at the end of a tile and shared out, OTM x OTN blocks to each wave of the
@@ -951,11 +959,14 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         // k-tile kt+1 has landed: in the steady state only the loads of the NS-2 k-tiles after it may still be in flight.
         // One k-step: the NM MFMAs on fragment set (ca, cb), with, pinned between them in this order, the reads
         // of the next step's fragments into (na, nb) behind the first half of the MFMAs (they then have the
-        // second half of the step to arrive) and the direct-to-LDS loads of a later k-tile behind the second half.
+        // second half of the step to arrive) and the direct-to-LDS loads of a later k-tile behind the second half, or (SPREAD)
+        // share `part` of them (none if negative) between all of the MFMAs.
         auto kstep = [&](const frag_t (&ca)[TM], const frag_t (&cb)[TN], frag_t (&na)[TM], frag_t (&nb)[TN],
-                         PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto loads_c) {
-            constexpr bool LOADS = decltype(loads_c)::value;
-            constexpr int NM = TM * TN, H = NM >= 2 ? NM / 2 : 1;
+                         PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto part_c) {
+            constexpr int PART = decltype(part_c)::value, PARTS = SPREAD ? KS : 1;
+            constexpr bool LOADS = PART >= 0;
+            constexpr int X0 = LOADS ? NL * PART / PARTS : 0, XN = LOADS ? NL * (PART + 1) / PARTS - X0 : 0;
+            constexpr int NM = TM * TN, H = NM >= 2 ? NM / 2 : 1, FIRST = SPREAD ? 0 : NM - H;   // MFMAs with loads behind them
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 mfma_one(i / TN, i % TN, ca, cb);
@@ -975,30 +986,33 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                     }
                 }
                 if constexpr (LOADS) {
-                    if (i >= NM - H) {
+                    if (i >= FIRST) {
 #pragma unroll
-                        for (int x = (NL * (i - (NM - H))) / H; x < (NL * (i - (NM - H) + 1)) / H; ++x)
-                            issue_load(ld_stage, x);
+                        for (int x = XN * (i - FIRST) / (NM - FIRST); x < XN * (i - FIRST + 1) / (NM - FIRST); ++x)
+                            issue_load(ld_stage, X0 + x);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // LANDED: k-tile kt+1 is known to be there.
-        auto ktile = [&](int kt, int nkt, auto loads_c, auto par_c, auto landed_c) {
-            constexpr bool LOADS = decltype(loads_c)::value, LANDED = decltype(landed_c)::value;
+        // LANDED: k-tile kt+1 is known to be there.  CARRY (SPREAD): the steps before the barrier issue what the k-tile before this one
+        // left to them of the loads of k-tile kt-1+NS, so at the barrier all loads up to that k-tile are out, as without SPREAD.
+        auto ktile = [&](int kt, int nkt, auto loads_c, auto par_c, auto landed_c, auto carry_c) {
+            constexpr bool LOADS = decltype(loads_c)::value, LANDED = decltype(landed_c)::value, CARRY = decltype(carry_c)::value;
+            static_assert(SPREAD || !CARRY, "nothing is left over");
             constexpr int P0 = decltype(par_c)::value;   // fragment set that holds this k-tile's first fragments
             const int sidx = kt % NS;
             PK_LDS char* st = ring + sidx * STAGE;
             PK_LDS char* nx = ring + (sidx + 1 == NS ? 0 : sidx + 1) * STAGE;
             // fragment set `par` is consumed, the other one refilled
-            auto step = [&](auto par, PK_LDS char* rd_stage, int rd_kk, auto lds_c) {
-                if constexpr (decltype(par)::value) kstep(af1, bf1, af0, bf0, rd_stage, rd_kk, sidx, lds_c);
-                else kstep(af0, bf0, af1, bf1, rd_stage, rd_kk, sidx, lds_c);
+            auto step = [&](auto par, PK_LDS char* rd_stage, int rd_kk, auto part_c) {
+                const int ld_stage = decltype(part_c)::value <= 0 ? sidx : sidx == 0 ? NS - 1 : sidx - 1;
+                if constexpr (decltype(par)::value) kstep(af1, bf1, af0, bf0, rd_stage, rd_kk, ld_stage, part_c);
+                else kstep(af0, bf0, af1, bf1, rd_stage, rd_kk, ld_stage, part_c);
             };
-            if constexpr (KS >= 2) step(std::integral_constant<int, P0>{}, st, 1, std::false_type{});
-            if constexpr (KS >= 3) step(std::integral_constant<int, P0 ^ 1>{}, st, 2, std::false_type{});
-            if constexpr (KS >= 4) step(std::integral_constant<int, P0>{}, st, 3, std::false_type{});
+            if constexpr (KS >= 2) step(std::integral_constant<int, P0>{}, st, 1, std::integral_constant<int, CARRY ? 1 : -1>{});
+            if constexpr (KS >= 3) step(std::integral_constant<int, P0 ^ 1>{}, st, 2, std::integral_constant<int, CARRY ? 2 : -1>{});
+            if constexpr (KS >= 4) step(std::integral_constant<int, P0>{}, st, 3, std::integral_constant<int, CARRY ? 3 : -1>{});
             static_assert(KS <= 4, "at most four k-steps per k-tile");
             static_assert(NS >= 2, "a ring has two stages or more");
             if constexpr (LANDED) {
@@ -1018,7 +1032,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
             if constexpr (PRIV) asm volatile("" : : : "memory");   // the loads have written the LDS behind the compiler's back
             else __syncthreads();
-            step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, loads_c);
+            step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, std::integral_constant<int, LOADS ? 0 : -1>{});
         };
         // the k-tiles of one pipeline fill: the first NS are in flight or landed, stage 0 holds the first
         auto run_ktiles = [&](int nkt) {
@@ -1031,42 +1045,52 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             if (DEFER && stores_pending) {
                 // the first NS k-tiles are there; the barrier of k-tile NS-1 waits for k-tile NS, whose loads were issued behind
                 // the previous tile's stores: they are complete then
-                static_assert(!DEFER || KS % 2 == 0 || NS % 2 == 0, "the main loop starts on set 0");
+                static_assert(!DEFER || (!SPREAD && (KS % 2 == 0 || NS % 2 == 0)), "the main loop starts on set 0");
                 if constexpr (KS % 2 == 0) {
 #pragma clang loop unroll(disable)
-                    for (; kt < NS - 1; ++kt) ktile(kt, nkt, T{}, E{}, T{});
-                    ktile(kt, nkt, T{}, E{}, F{});
+                    for (; kt < NS - 1; ++kt) ktile(kt, nkt, T{}, E{}, T{}, F{});
+                    ktile(kt, nkt, T{}, E{}, F{}, F{});
                     ++kt;
                 } else {
 #pragma clang loop unroll(disable)
                     for (; kt < NS - 2; kt += 2) {
-                        ktile(kt, nkt, T{}, E{}, T{});
-                        ktile(kt + 1, nkt, T{}, O{}, T{});
+                        ktile(kt, nkt, T{}, E{}, T{}, F{});
+                        ktile(kt + 1, nkt, T{}, O{}, T{}, F{});
                     }
-                    ktile(kt, nkt, T{}, E{}, T{});
-                    ktile(kt + 1, nkt, T{}, O{}, F{});
+                    ktile(kt, nkt, T{}, E{}, T{}, F{});
+                    ktile(kt + 1, nkt, T{}, O{}, F{}, F{});
                     kt += 2;
                 }
                 signal_prev();
             }
-            if constexpr (KS % 2 == 0) {
+            if constexpr (SPREAD) {
+                if (nkt > NS) {
+                    ktile(0, nkt, T{}, E{}, F{}, F{});
 #pragma clang loop unroll(disable)
-                for (; kt + NS < nkt; ++kt) ktile(kt, nkt, T{}, E{}, F{});
+                    for (kt = 1; kt + NS < nkt; ++kt) ktile(kt, nkt, T{}, E{}, F{}, T{});
+                    ktile(kt, nkt, F{}, E{}, F{}, T{});
+                    ++kt;
+                }
 #pragma clang loop unroll(disable)
-                for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{});
+                for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{}, F{});
+            } else if constexpr (KS % 2 == 0) {
+#pragma clang loop unroll(disable)
+                for (; kt + NS < nkt; ++kt) ktile(kt, nkt, T{}, E{}, F{}, F{});
+#pragma clang loop unroll(disable)
+                for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{}, F{});
             } else {
                 // odd k-steps per k-tile: the starting set alternates, so k-tiles go in pairs (such k-tiles are 64 bytes, and the
                 // host admits only k ranges of whole 128-byte units)
                 static_assert(KS % 2 == 0 || (KB == 64 && NS % 2 == 0), "pairs of k-tiles need an even number of them and an even ring");
 #pragma clang loop unroll(disable)
                 for (; kt + NS < nkt; kt += 2) {
-                    ktile(kt, nkt, T{}, E{}, F{});
-                    ktile(kt + 1, nkt, T{}, O{}, F{});
+                    ktile(kt, nkt, T{}, E{}, F{}, F{});
+                    ktile(kt + 1, nkt, T{}, O{}, F{}, F{});
                 }
 #pragma clang loop unroll(disable)
                 for (; kt < nkt; kt += 2) {
-                    ktile(kt, nkt, F{}, E{}, F{});
-                    ktile(kt + 1, nkt, F{}, O{}, F{});
+                    ktile(kt, nkt, F{}, E{}, F{}, F{});
+                    ktile(kt + 1, nkt, F{}, O{}, F{}, F{});
                 }
             }
         };
