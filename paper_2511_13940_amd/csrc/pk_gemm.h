@@ -95,6 +95,7 @@ struct GemmArgs {
     uint32_t epoch;
     uint32_t* status;
     uint64_t timeout_ticks;
+    uint32_t store_gap;       // ticks between the first stores of neighbouring workgroups of an XCD (0: all at once)
     // stream-K tail: the first sk_dp_slots tile slots are computed whole, one per workgroup and round; the k range of the
     // remaining ones is shared out evenly (sk_dp_slots = all slots: no such tail)
     int32_t sk_dp_slots;
@@ -744,6 +745,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                             for (int e = 0; e < 4; ++e) acc[ti][tj][4 * b + e] += pv[tj][b][e];
                 }
             }
+        }
+        if (DEFER && g.store_gap > 0 && n_tiles_done == 1 && have) {
+            // Launches of two rounds and more: every workgroup ends its first tile at the same time, and so every later one, and all
+            // compute units then wait for the memory (67 MB of a round of 256x256 fp32 tiles in 9-12 us, of which a compute unit alone
+            // needs 2.5) that has nothing to write in between.  The workgroups of an XCD start the first stores one eighth of that time
+            // after the other, in eight groups: the last of them are through no later than all were before, and from then on the
+            // tiles of the groups end at different times.  A guess at the rate is all it takes, so a delay, not a hand-over.
+            const uint64_t t0 = wall_clock64(), gap = (uint64_t)g.store_gap * ((blockIdx.x >> 3) & 7);
+            while (wall_clock64() - t0 < gap) __builtin_amdgcn_s_sleep(2);
         }
         if (p_q >= 0 && !skip_epilogue && (NOWN == WK || wk < NOWN)) {
             // lane holds, for each 32x32 block, rows (l & 31) and columns 8*b + 4*h + {0..3}.  Per pass a slab of

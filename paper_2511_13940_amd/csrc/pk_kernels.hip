@@ -426,10 +426,24 @@ static bool sk_too_small(int64_t slots, int grid, int64_t ktiles, int tile, size
     return sk_applies(slots, grid, ktiles) && ws_bytes < kWsFlagBytes + (size_t)grid * tile * tile * 4;
 }
 
-// Launches a GEMM whose tile space is set up in `a`: with a workspace (256 x 256 tiles only; the caller has checked its size) and a
-// last round that is not full, with the stream-K tail, otherwise whole tiles.
+// The time by which the first stores of neighbouring workgroups are set apart (gemm_kernel: `store_gap`), in ticks: an eighth of what
+// the stores of a round take at 5.6 TB/s.  Only for the shape that is used for many rounds, 256 x 256, and not where the two rounds
+// of a launch are all there is and their stores are short against the rest.  us a call, without / with it: fp32 slots, 4 rounds, 8192 x
+// 8192 x 512 148 / 133, x 256 128 / 122, 16 rounds, 16384 x 16384 x 256 446 / 425, 2 rounds, 2048 x 16384 x 512 85 / 79, 16384 x 2048 x
+// 4096 243 / 242; bf16 slots, 8192 x 8192 x 512 104 / 98 (fp8 79 / 71); all-gather, 16384 x 4096 x 256 49 / 46, 2 rounds, 4096 x 8192 x
+// 256 31 / 28.  Left out: bf16 results in two rounds with a longer k (16384 x 2048 x 4096 212 / 214) or on three quarters of the
+// compute units (6144 x 4096 x 512 43.8 / 44.8), and tiles of shards that fill little of them (1600 x 16384 x 512 72.5 / 74.7).
+static uint32_t store_gap(int tile, int slots, int grid, int cus, bool full, int out_elem, int ktiles) {
+    const int rounds = (slots + grid - 1) / grid;
+    if (tile != T256x256 || rounds < 2) return 0;
+    if (rounds == 2 && (!full || (out_elem == 2 && (ktiles > 8 || grid * 8 < cus * 7)))) return 0;
+    return (uint32_t)((int64_t)grid * 256 * 256 * out_elem * kWallClockTicksPerUs / 8 / 5600000);
+}
+
+// Launches a GEMM whose tile space is set up in `a` (m: rows of the whole product): with a workspace (256 x 256 tiles only; the caller
+// has checked its size) and a last round that is not full, with the stream-K tail, otherwise whole tiles.
 template <int EPI>
-static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt, void* ws, hipStream_t stream) {
+static pk_status run_gemm(GemmArgs& a, int64_t m, int tile, int comm_cus, bool fp8, bool bt, void* ws, hipStream_t stream) {
     const int bm = kTileDim[tile].bm, bn = kTileDim[tile].bn;
     const int64_t G = (int64_t)a.grp_tile_rows * a.tiles_n;
     a.wg_per_group = (int32_t)(8 * ceil_div(G, 8));
@@ -438,6 +452,9 @@ static pk_status run_gemm(GemmArgs& a, int tile, int comm_cus, bool fp8, bool bt
     const int grid = max_grid(comm_cus);
     const int rem = slots % grid;
     a.sk_dp_slots = slots;
+    const int64_t tile_rows = a.all_tile_rows > 0 ? a.all_tile_rows : (int64_t)a.n_groups * a.grp_tile_rows;
+    const bool full = m * a.n * 8 >= tile_rows * a.tiles_n * bm * bn * 7;       // the tiles, seven eighths of them
+    a.store_gap = EPI == EPI_AGK ? 0 : store_gap(tile, slots, schedule_grid(slots, comm_cus), grid, full, EPI == EPI_RS ? 4 : 2, a.ktiles);
     if (ws && sk_applies(slots, grid, a.ktiles)) {
         // With a workspace every compute unit works to the end: whole rounds of tiles, then the k range of the left-over
         // tiles shared out evenly (448 slots on 256 CUs: 256 whole tiles, then 192 tiles as 256 pieces of 3/4 tile).
@@ -743,8 +760,8 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         a.grp_tile_rows = n_rows;
         a.row_rot = row0;
         a.all_tile_rows = (row0 == 0 && n_rows == all_rows) ? 0 : all_rows;
-        return bf16_slots ? run_gemm<EPI_RS16>(a, t.tile, comm_cus, fp8, false, nullptr, s)
-                          : run_gemm<EPI_RS>(a, t.tile, comm_cus, fp8, bt, ws, s);
+        return bf16_slots ? run_gemm<EPI_RS16>(a, m_all, t.tile, comm_cus, fp8, false, nullptr, s)
+                          : run_gemm<EPI_RS>(a, m_all, t.tile, comm_cus, fp8, bt, ws, s);
     };
     if (do_gemm) {
         const int elem = fp8 ? 1 : 2;
@@ -990,8 +1007,8 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
         if (hipGetLastError() != hipSuccess) return PK_ERR_HIP;
         a.ws_epoch = 1;
     }
-    return k_chunks ? run_gemm<EPI_AGK>(a, tile, comm_cus, fp8, false, nullptr, (hipStream_t)stream)
-                    : run_gemm<EPI_AG>(a, tile, comm_cus, fp8, bt, sk ? ws : nullptr, (hipStream_t)stream);
+    return k_chunks ? run_gemm<EPI_AGK>(a, M, tile, comm_cus, fp8, false, nullptr, (hipStream_t)stream)
+                    : run_gemm<EPI_AG>(a, M, tile, comm_cus, fp8, bt, sk ? ws : nullptr, (hipStream_t)stream);
 }
 
 static pk_status make_order(const int* order, int n_order, int P, EmuOrder* o) {
