@@ -1,7 +1,7 @@
 // The MFMA GEMM kernel behind pk_gemm_rs and pk_ag_gemm (gfx950 only).
 //
 // A persistent workgroup of WM x WN waves walks over BM x BN tiles of the local product; each wave owns a
-// (BM/WM) x (BN/WN) sub-tile as 32x32 MFMA accumulators.  The reduction runs in k-tiles of KB bytes of
+// (BM/WM) x (BN/WN) sub-tile as 32x32 or 16x16 MFMA accumulators.  The reduction runs in k-tiles of KB bytes of
 // A-row (KB = 64 or 128: 32 or 64 bf16, 64 or 128 fp8):
 //   * the A tile (BM x KB bytes) and B tile (KB*BN bytes) are copied global -> LDS with 16-byte
 //     direct-to-LDS loads (no VGPR staging) into a ring of NS LDS stages, NS-1 k-tiles ahead of their use,
@@ -12,8 +12,8 @@
 //     panels (the fp8 B tile as swizzled rows); a direct-to-LDS load writes lane l's 16 bytes at
 //     base + 16*l, so a layout is applied by choosing which global chunk each lane fetches;
 //   * the loop is software-pipelined: the fragments of k-step s+1 are read while the MFMAs of step s issue,
-//     and the single barrier of a k-tile sits before its last k-step, so the loads of a later k-tile and
-//     the first fragments of the next k-tile are issued under that step's MFMAs.
+//     and the single barrier of a k-tile sits before its last k-step (16x16 MFMAs: a quarter into it), so the
+//     loads of a later k-tile and the first fragments of the next k-tile are issued under that step's MFMAs.
 // The operands are passed to the MFMA swapped (B fragment first), which leaves each lane with four
 // consecutive columns of one row; the epilogue transposes through a 32 KB LDS staging area so that global
 // stores are 16 bytes per lane over whole row segments of the wave's sub-tile.  The epilogue of tile t runs
@@ -151,14 +151,18 @@ __device__ __forceinline__ void touch_kernel_args() {
 // BT: the second operand is stored k-contiguous (N x K row-major, the transpose of the K x N matrix): its tile then has
 // the layout of the A tile and its fragments come in with the same 16-byte reads, no transposing reads.
 // SK: built with the stream-K tail (its code paths cost registers, so launches that share out no tile use SK = false).
-template <int BM, int BN, int WM, int WN, int WK, int KB, int NS, bool FP8, int EPI, bool BT = false, bool SK = false>
+// M16: bf16 products by 16x16x32 MFMAs instead of 32x32x16 (the same bits: two of those add up as one of these); tile_m16 has when.
+template <int BM, int BN, int WM, int WN, int WK, int KB, int NS, bool FP8, int EPI, bool BT = false, bool SK = false, bool M16 = false>
 __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     PK_LDS char* lds = (PK_LDS char*)smem_generic;
 
     constexpr bool IS_RS = EPI == EPI_RS || EPI == EPI_RS16;
     constexpr int NW = WM * WN * WK;                     // waves per workgroup
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;  // 32x32 accumulators per wave: TM x TN
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;  // 32x32 blocks of accumulators per wave: TM x TN
+    constexpr int MF = M16 ? 16 : 32;                    // rows and columns of one MFMA
+    constexpr int FM = BM / WM / MF, FN = BN / WN / MF;  // fragments per wave and k-step
+    static_assert(!M16 || (!FP8 && BN % 64 == 0), "16x16x32 MFMAs: bf16, panels of 128 bytes");
     constexpr int A_BYTES = BM * KB, B_BYTES = BN * KB, STAGE = A_BYTES + B_BYTES;
     constexpr int ELEM = FP8 ? 1 : 2;
     constexpr int CPA = KB / 16;                         // 16-byte chunks per A tile row (8 or 4)
@@ -174,7 +178,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int NA = A_BYTES / 1024 / NWL, NB = B_BYTES / 1024 / NWL; // wave-wide loads per wave per k-tile
     static_assert(!PRIV || (EPI != EPI_AGK && !SK), "rings of their own: not built for k ranges in pieces");
     constexpr int NL = NA + NB;
-    constexpr int KST = FP8 ? KB / 64 : KB / 32;         // MFMA k-steps per k-tile
+    constexpr int KST = FP8 || M16 ? KB / 64 : KB / 32;  // MFMA k-steps per k-tile
     constexpr int KS = PRIV ? KST : KST / WK;            // ... of which each of the WK wave groups takes its own share
     // SPREAD: the loads of a k-tile are issued a share per k-step over the KS steps that follow the barrier which frees its stage, not
     // all in the first of them: NW * NL KB at once are more than the L1 takes in the time of that step, and a wave whose load does
@@ -218,23 +222,36 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 
     // A-tile swizzle: LDS chunk position = k-chunk ^ fA(row).
     //   128-byte rows: fA(r) = (r & 7) ^ ((r >> 3) & 1);  64-byte rows: fA(r) = ((r >> 1) & 3) ^ ((r >> 3) & 1)
-    auto fA = [](int r) { return KB == 128 ? ((r & 7) ^ ((r >> 3) & 1)) : (((r >> 1) & 3) ^ ((r >> 3) & 1)); };
+    // Reads of 16 rows by four chunks (M16) want them without the last term.  Measured on every pattern used: 250 B/clk per compute
+    // unit, and 128 for the one form's reads with the other form's swizzle.
+    auto fA = [](int r) { return (KB == 128 ? r & 7 : (r >> 1) & 3) ^ (M16 ? 0 : (r >> 3) & 1); };
 
     // ---- per-lane LDS fragment addresses (relative to a stage) ----
     // Set anew for every tile, from a lane id that the compiler cannot follow from one tile to the next: kept in registers
     // across the epilogue (and its addresses across the main loop) they would not fit beside the accumulators.
     int fa = 0, hf = 0;
-    uint32_t a_row_off = 0, b_off[TN];
+    uint32_t a_row_off = 0, b_off[FN];
     auto set_frag_addresses = [&](int l) {
-        fa = fA(l & 31);                                     // rows of a fragment differ from (l & 31) by multiples of 32
-        hf = l >> 5;
+        fa = fA(l & (MF - 1));                               // fA has a period of 16 rows
+        hf = l / MF;
         const int h = l >> 5;
-        a_row_off = (uint32_t)(wm * (BM / WM) + (l & 31)) * KB;
+        a_row_off = (uint32_t)(wm * (BM / WM) + (l & (MF - 1))) * KB;
         const int s16 = l & 15, nhalf = (l >> 4) & 1;
-        const uint32_t bt_row_off = (uint32_t)(A_BYTES + (wn * (BN / WN) + (l & 31)) * KB);   // BT: B tile = BN rows of KB bytes
+        const uint32_t bt_row_off = (uint32_t)(A_BYTES + (wn * (BN / WN) + (l & (MF - 1))) * KB);   // BT: B tile = BN rows of KB bytes
         if constexpr (BT) {
 #pragma unroll
-            for (int tj = 0; tj < TN; ++tj) b_off[tj] = bt_row_off + (uint32_t)(tj * 32 * KB);
+            for (int tj = 0; tj < FN; ++tj) b_off[tj] = bt_row_off + (uint32_t)(tj * MF * KB);
+        } else if constexpr (M16) {
+            // the panels of the branch below; each group of 16 lanes takes eight k-rows of the same 16 columns (one 32-byte piece).  The
+            // pieces trade places by bit 1 of the k-row, and the 64-byte halves of a row by its bit 3: 32 lanes then cover 256
+            // bytes in as many banks (256 B/clk per compute unit; 128 without the latter)
+            const int krow_base = 32 * kk0 + 8 * (l >> 4) + (s16 >> 2);
+#pragma unroll
+            for (int tj = 0; tj < FN; ++tj) {
+                const int c16 = wn * FN + tj;                // 16-column block of the tile
+                const int piece = (c16 & 3) ^ ((krow_base >> 1) & 1) ^ (2 * ((krow_base >> 3) & 1));
+                b_off[tj] = (uint32_t)(A_BYTES + (c16 >> 2) * (B_ROWS * PB) + krow_base * PB + piece * 32 + (s16 & 3) * 8);
+            }
         } else if constexpr (!FP8) {
             // bf16 B tile: panels of 64 columns (128 bytes per k-row, k-rows consecutive);
             // inside a row the two 32-byte pieces of each 64-byte half trade places on k-rows with bit 1 set.  A tile of 32
@@ -259,40 +276,40 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         }
     };
 
-    // Fragment reads of k-step kk of the k-tile held in LDS stage `st`, as NU = TN + TM units in the order the
+    // Fragment reads of k-step kk of the k-tile held in LDS stage `st`, as NU = FN + FM units in the order the
     // MFMAs need them: B fragments first, then A fragments.
-    constexpr int NU = TN + TM;
-    auto read_unit = [&](PK_LDS char* st, int kk, int u, frag_t (&af)[TM], frag_t (&bfr)[TN]) {
+    constexpr int NU = FN + FM;
+    auto read_unit = [&](PK_LDS char* st, int kk, int u, frag_t (&af)[FM], frag_t (&bfr)[FN]) {
         if constexpr (BT) {
-            // both operands: rows of KB bytes, 16-byte chunks XOR-swizzled by row; rows of a fragment differ by multiples of 32
-            const uint32_t base = u < TN ? b_off[u] : a_row_off + (uint32_t)((u - TN) * 32 * KB);
+            // both operands: rows of KB bytes, 16-byte chunks XOR-swizzled by row; rows of a fragment differ by multiples of MF
+            const uint32_t base = u < FN ? b_off[u] : a_row_off + (uint32_t)((u - FN) * MF * KB);
             if constexpr (!FP8) {
-                const bf16x8 v = *(PK_LDS bf16x8*)(st + base + (uint32_t)((((2 * (kk0 + kk) + hf) ^ fa) & (CPA - 1)) * 16));
-                if (u < TN) bfr[u] = v;
-                else af[u - TN] = v;
+                const bf16x8 v = *(PK_LDS bf16x8*)(st + base + (uint32_t)((((64 / MF * (kk0 + kk) + hf) ^ fa) & (CPA - 1)) * 16));
+                if (u < FN) bfr[u] = v;
+                else af[u - FN] = v;
             } else {
                 i32x4 x0 = *(PK_LDS i32x4*)(st + base + (uint32_t)((((4 * (kk0 + kk) + 2 * hf) ^ fa) & (CPA - 1)) * 16));
                 i32x4 x1 = *(PK_LDS i32x4*)(st + base + (uint32_t)((((4 * (kk0 + kk) + 2 * hf + 1) ^ fa) & (CPA - 1)) * 16));
                 const i32x8 v = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
-                if (u < TN) bfr[u] = v;
-                else af[u - TN] = v;
+                if (u < FN) bfr[u] = v;
+                else af[u - FN] = v;
             }
         } else if constexpr (!FP8) {
-            if (u < TN) {
+            if (u < FN) {
                 const int tj = u;
                 s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (PK_LDS s16x4*)(st + b_off[tj] + (16 * kk) * PB));
+                    (PK_LDS s16x4*)(st + b_off[tj] + (512 / MF * kk) * PB));
                 s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (PK_LDS s16x4*)(st + b_off[tj] + (16 * kk + 4) * PB));
+                    (PK_LDS s16x4*)(st + b_off[tj] + (512 / MF * kk + 4) * PB));
                 s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 bfr[tj] = __builtin_bit_cast(bf16x8, both);
             } else {
-                const int ti = u - TN;
-                const uint32_t ao = a_row_off + (uint32_t)((((2 * (kk0 + kk) + hf) ^ fa) & (CPA - 1)) * 16);
-                af[ti] = *(PK_LDS bf16x8*)(st + ao + ti * 32 * KB);
+                const int ti = u - FN;
+                const uint32_t ao = a_row_off + (uint32_t)((((64 / MF * (kk0 + kk) + hf) ^ fa) & (CPA - 1)) * 16);
+                af[ti] = *(PK_LDS bf16x8*)(st + ao + ti * MF * KB);
             }
         } else {
-            if (u < TN) {
+            if (u < FN) {
                 const int tj = u;
                 i32x2 p[4];
 #pragma unroll
@@ -303,7 +320,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 i32x4 q1 = __builtin_shufflevector(p[2], p[3], 0, 1, 2, 3);
                 bfr[tj] = __builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7);
             } else {
-                const int ti = u - TN;
+                const int ti = u - FN;
                 const uint32_t ao0 = a_row_off + (uint32_t)((((4 * (kk0 + kk) + 2 * hf) ^ fa) & (CPA - 1)) * 16);
                 const uint32_t ao1 = a_row_off + (uint32_t)((((4 * (kk0 + kk) + 2 * hf + 1) ^ fa) & (CPA - 1)) * 16);
                 i32x4 x0 = *(PK_LDS i32x4*)(st + ao0 + ti * 32 * KB);
@@ -312,17 +329,35 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
         }
     };
-    auto load_frags = [&](PK_LDS char* st, int kk, frag_t (&af)[TM], frag_t (&bfr)[TN]) {
+    auto load_frags = [&](PK_LDS char* st, int kk, frag_t (&af)[FM], frag_t (&bfr)[FN]) {
 #pragma unroll
         for (int u = 0; u < NU; ++u) read_unit(st, kk, u, af, bfr);
     };
 
-    f32x16 acc[TM][TN];
-    auto mfma_one = [&](int ti, int tj, const frag_t (&af)[TM], const frag_t (&bfr)[TN]) {
-        if constexpr (!FP8)
+    // accumulators, one MFMA's each
+    typename std::conditional<M16, f32x4, f32x16>::type acc[FM][FN];
+    auto mfma_one = [&](int ti, int tj, const frag_t (&af)[FM], const frag_t (&bfr)[FN]) {
+        if constexpr (M16)
+            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[tj], af[ti], acc[ti][tj], 0, 0, 0);
+        else if constexpr (!FP8)
             acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[tj], af[ti], acc[ti][tj], 0, 0, 0);
         else
             acc[ti][tj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bfr[tj], af[ti], acc[ti][tj], 0, 0, 0, 0, 0, 0);
+    };
+
+    // four of the accumulators of 32x32 block (ti, tj), 0 <= b < 4: consecutive columns of one row, row (l & 31), columns 8b + 4(l / 32)
+    // and on; M16: row 16(b / 2) + (l & 15), columns 16(b % 2) + 4(l / 16) and on
+    auto quad = [&](int ti, int tj, int b) -> f32x4 {
+        if constexpr (M16) return acc[2 * ti + (b >> 1)][2 * tj + (b & 1)];
+        else return f32x4{acc[ti][tj][4 * b], acc[ti][tj][4 * b + 1], acc[ti][tj][4 * b + 2], acc[ti][tj][4 * b + 3]};
+    };
+    auto set_quad = [&](int ti, int tj, int b, f32x4 x) {
+        if constexpr (M16) {
+            acc[2 * ti + (b >> 1)][2 * tj + (b & 1)] = x;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[ti][tj][4 * b + e] = x[e];
+        }
     };
 
     // tile bookkeeping carried from one iteration to the next (the epilogue of a tile runs one iteration late)
@@ -639,7 +674,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                     const int bi = j * NWL + wl;
                     const int panel = bi / (B_ROWS / KR);
                     const int kr = (bi % (B_ROWS / KR)) * KR + kr_in;
-                    int colbyte = (col0 + panel * 64) * 2 + (PB == 64 ? cp : cp ^ (2 * ((kr >> 1) & 1))) * 16;
+                    const int sw = PB == 64 ? 0 : 2 * ((kr >> 1) & 1) ^ (M16 ? 4 * ((kr >> 3) & 1) : 0);
+                    int colbyte = (col0 + panel * 64) * 2 + (cp ^ sw) * 16;
                     if (colbyte >= n_bytes) colbyte = n_bytes - 16;   // edge tile: valid memory, never stored
                     b_voff[j] = (uint32_t)((int64_t)kr * g.ldb + colbyte);
                 }
@@ -698,8 +734,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 for (int tj = 0; tj < TN; ++tj)
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
-                        f32x4 val = {acc[ti][tj][4 * b], acc[ti][tj][4 * b + 1], acc[ti][tj][4 * b + 2], acc[ti][tj][4 * b + 3]};
-                        store16_writethrough(wsb + ((ti * TN + tj) * 4 + b) * 1024, __builtin_bit_cast(i32x4, val));
+                        store16_writethrough(wsb + ((ti * TN + tj) * 4 + b) * 1024, __builtin_bit_cast(i32x4, quad(ti, tj, b)));
                     }
             skip_epilogue = true;
         }
@@ -740,9 +775,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 #pragma unroll
                     for (int tj = 0; tj < TN; ++tj)
 #pragma unroll
-                        for (int b = 0; b < 4; ++b)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[ti][tj][4 * b + e] += pv[tj][b][e];
+                        for (int b = 0; b < 4; ++b) set_quad(ti, tj, b, quad(ti, tj, b) + pv[tj][b]);
                 }
             }
         }
@@ -756,7 +789,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             while (wall_clock64() - t0 < gap) __builtin_amdgcn_s_sleep(2);
         }
         if (p_q >= 0 && !skip_epilogue && (NOWN == WK || wk < NOWN)) {
-            // lane holds, for each 32x32 block, rows (l & 31) and columns 8*b + 4*h + {0..3}.  Per pass a slab of
+            // lane holds, for each 32x32 block, four quads of columns (see `quad`).  Per pass a slab of
             // ROWS_PASS rows of the wave's part of the tile goes through the wave's private staging area, then out as whole
             // row segments, 16 bytes per lane.  The passes are a loop, not unrolled, around one read-back: a workgroup runs
             // most of this code once per launch, out of a cold instruction cache (unrolled, with the activation inlined per
@@ -809,7 +842,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 constexpr int HALVES = 32 / ROWS_PASS, CSLABS = WCOLS / CP, NSLABS = OTM * CSLABS, NPASS = NSLABS * HALVES;
                 constexpr int NOUT = ROWS_PASS / ROWS_INSTR;
                 static_assert(NPASS * NOUT == EPI_STORES, "stores per wave and tile");
-                const int cl = lt % LANES_ROW, rl0 = lt / LANES_ROW, h = lt >> 5;
+                const int cl = lt % LANES_ROW, rl0 = lt / LANES_ROW;
                 // write pass ps: lanes whose row falls in it store their quads; chunk position swizzled by row
                 auto write = [&](int ps) {
                     int rl = lt & 31;
@@ -817,26 +850,41 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                     asm volatile("" : "+v"(rl));
                     float sc = scale;
                     if constexpr (FP8) asm volatile("" : "+v"(sc));
-                    const int rs = rl % ROWS_PASS, slab = ps / HALVES;
-                    if (ROWS_PASS == 32 || (rl / ROWS_PASS) == ps % HALVES) {
+                    const int slab = ps / HALVES;
+                    const int row = M16 ? rl & 15 : rl, colq = 4 * (M16 ? lt >> 4 : lt >> 5);
+                    if (M16 || ROWS_PASS == 32 || (rl / ROWS_PASS) == ps % HALVES) {
                         auto put = [&](auto slab_c) {
                             constexpr int ti = decltype(slab_c)::value / CSLABS, tj0 = decltype(slab_c)::value % CSLABS * (CP / 32);
-#pragma unroll
-                            for (int tj = 0; tj < CP / 32; ++tj)
-#pragma unroll
-                                for (int b = 0; b < 4; ++b) {
-                                    const int colw = tj * 32 + 8 * b + 4 * h;     // column inside the slab
-                                    const f32x16& x = acc[ti][tj0 + tj];
-                                    f32x4 val = {x[4 * b] * sc, x[4 * b + 1] * sc, x[4 * b + 2] * sc, x[4 * b + 3] * sc};
-                                    if constexpr (ST_ELEM == 4) {
-                                        const int ch = colw >> 2;                  // 16-byte chunk (4 floats)
-                                        *(PK_LDS f32x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16)) = val;
-                                    } else {
-                                        const int ch = colw >> 3;                  // 16-byte chunk (8 bf16)
-                                        bf16x4 v16 = {(__bf16)val[0], (__bf16)val[1], (__bf16)val[2], (__bf16)val[3]};
-                                        *(PK_LDS bf16x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16) + (h * 8)) = v16;
-                                    }
+                            // one quad of block (ti, tj) into row r, column colw of the slab
+                            auto put_quad = [&](int tj, int b, int r, int colw) {
+                                const int rs = r % ROWS_PASS;
+                                const f32x4 x = quad(ti, tj0 + tj, b);
+                                f32x4 val = {x[0] * sc, x[1] * sc, x[2] * sc, x[3] * sc};
+                                if constexpr (ST_ELEM == 4) {
+                                    const int ch = colw >> 2;                  // 16-byte chunk (4 floats)
+                                    *(PK_LDS f32x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16)) = val;
+                                } else {
+                                    const int ch = colw >> 3;                  // 16-byte chunk (8 bf16)
+                                    bf16x4 v16 = {(__bf16)val[0], (__bf16)val[1], (__bf16)val[2], (__bf16)val[3]};
+                                    *(PK_LDS bf16x4*)(stg + rs * ROW_BYTES + ((ch ^ (rs & (CH - 1))) * 16) + (colw & 4) * 2) = v16;
                                 }
+                            };
+                            if constexpr (M16) {
+#pragma unroll
+                                for (int i2 = 0; i2 < 2; ++i2)
+                                    if (ROWS_PASS == 32 || (16 * i2 + row) / ROWS_PASS == ps % HALVES) {
+#pragma unroll
+                                        for (int tj = 0; tj < CP / 32; ++tj)
+#pragma unroll
+                                            for (int j2 = 0; j2 < 2; ++j2) put_quad(tj, 2 * i2 + j2, 16 * i2 + row, tj * 32 + 16 * j2 + colq);
+                                        if (ROWS_PASS < 32) asm volatile("; half %0" : : "n"(i2));
+                                    }
+                            } else {
+#pragma unroll
+                                for (int tj = 0; tj < CP / 32; ++tj)
+#pragma unroll
+                                    for (int b = 0; b < 4; ++b) put_quad(tj, b, row, tj * 32 + 8 * b + colq);
+                            }
                             // a different last statement in each case: the compiler would otherwise merge the cases into one
                             // that indexes the accumulators at run time, and move them to scratch memory
                             asm volatile("; slab %0" : : "n"(decltype(slab_c)::value));
@@ -936,11 +984,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         if (!have) break;
 
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                for (int e = 0; e < (M16 ? 4 : 16); ++e) acc[i][j][e] = 0.f;
 
         bool stores_pending = false;                     // the previous tile's stores may not be complete yet
         if (p_q < 0 && my_ktiles >= NS) {
@@ -962,7 +1010,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 
         // ---- main loop ----
         set_frag_addresses(lt);
-        frag_t af0[TM], bf0[TN], af1[TM], bf1[TN];
+        frag_t af0[FM], bf0[FN], af1[FM], bf1[FN];
         // One k-tile: KS-1 pipelined k-steps, the barrier, then the last k-step, under which the loads of
         // k-tile kt+NS (LOADS) and the first fragments of k-tile kt+1 are issued (behind the last k-tile: stale bytes that
         // nothing uses).  At the barrier every wave has finished reading k-tile kt's stage, so it can be refilled, and
@@ -971,78 +1019,115 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         // of the next step's fragments into (na, nb) behind the first half of the MFMAs (they then have the
         // second half of the step to arrive) and the direct-to-LDS loads of a later k-tile behind the second half, or (SPREAD)
         // share `part` of them (none if negative) between all of the MFMAs.
-        auto kstep = [&](const frag_t (&ca)[TM], const frag_t (&cb)[TN], frag_t (&na)[TM], frag_t (&nb)[TN],
-                         PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto part_c) {
+        // M16: `sync` (the waits and the barrier of a k-tile, if this is its step) comes behind MFMA number P, the reads and loads after
+        // it.
+        auto kstep = [&](const frag_t (&ca)[FM], const frag_t (&cb)[FN], frag_t (&na)[FM], frag_t (&nb)[FN],
+                         PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto part_c, auto sync_c, auto sync) {
             constexpr int PART = decltype(part_c)::value, PARTS = SPREAD ? KS : 1;
             constexpr bool LOADS = PART >= 0;
             constexpr int X0 = LOADS ? NL * PART / PARTS : 0, XN = LOADS ? NL * (PART + 1) / PARTS - X0 : 0;
-            constexpr int NM = TM * TN, H = NM >= 2 ? NM / 2 : 1, FIRST = SPREAD ? 0 : NM - H;   // MFMAs with loads behind them
+            constexpr int NM = FM * FN, H = NM >= 2 ? NM / 2 : 1, FIRST = SPREAD ? 0 : NM - H;   // MFMAs with loads behind them
+            constexpr int P = M16 && decltype(sync_c)::value ? NM / 4 : 0;
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
-                mfma_one(i / TN, i % TN, ca, cb);
-                if constexpr (FP8) {
-                    // 8-bit fragments are 8 registers each: two full sets next to the accumulators do not fit.  The MFMAs run
-                    // row by row (ti-major), so the A fragment of row ti is dead after MFMA ti*TN + TN-1, and the next step's
-                    // A fragment of that row is read right behind it, into the same registers; only the B fragments are double.
-                    if (i == 0) {
+                const int ti = i / FN;
+                mfma_one(ti, M16 && (ti & 1) ? FN - 1 - i % FN : i % FN, ca, cb);
+                if constexpr (M16) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (P > 0 && i == P - 1) sync();
+                    // The next step's fragments, evenly spread: unit y is A row 0, the B fragments, then the other A rows, each of these into the
+                    // registers of its predecessor, behind the MFMAs that use that one (8-bit operands do likewise, below).
 #pragma unroll
-                        for (int u = 0; u < TN; ++u) read_unit(rd_stage, rd_kk, u, na, nb);
+                    for (int y = 0; y < NU; ++y) {
+                        const int row = y == 0 ? 0 : y - FN, at = P + (NM - P) * y / NU;
+                        const int from = row < 0 ? at : at > row * FN + FN - 1 ? at : row * FN + FN - 1;
+                        if (i == from) read_unit(rd_stage, rd_kk, row < 0 || (y > 0 && y <= FN) ? y - 1 : FN + row, na, nb);
                     }
-                    if (i % TN == TN - 1) read_unit(rd_stage, rd_kk, TN + i / TN, na, nb);
+                    if constexpr (LOADS) {
+#pragma unroll
+                        for (int x = 0; x < XN; ++x)
+                            if (i == P + (2 * x + 1) * (NM - P) / (2 * XN)) issue_load(ld_stage, X0 + x);
+                    }
                 } else {
-                    if (i < H) {
+                    if constexpr (FP8) {
+                        // 8-bit fragments are 8 registers each: two full sets next to the accumulators do not fit.  The MFMAs run
+                        // row by row (ti-major), so the A fragment of row ti is dead after MFMA ti*FN + FN-1, and the next step's
+                        // A fragment of that row is read right behind it, into the same registers; only the B fragments are double.
+                        if (i == 0) {
 #pragma unroll
-                        for (int u = (NU * i) / H; u < (NU * (i + 1)) / H; ++u) read_unit(rd_stage, rd_kk, u, na, nb);
+                            for (int u = 0; u < FN; ++u) read_unit(rd_stage, rd_kk, u, na, nb);
+                        }
+                        if (i % FN == FN - 1) read_unit(rd_stage, rd_kk, FN + ti, na, nb);
+                    } else {
+                        if (i < H) {
+#pragma unroll
+                            for (int u = (NU * i) / H; u < (NU * (i + 1)) / H; ++u) read_unit(rd_stage, rd_kk, u, na, nb);
+                        }
                     }
-                }
-                if constexpr (LOADS) {
-                    if (i >= FIRST) {
+                    if constexpr (LOADS) {
+                        if (i >= FIRST) {
 #pragma unroll
-                        for (int x = XN * (i - FIRST) / (NM - FIRST); x < XN * (i - FIRST + 1) / (NM - FIRST); ++x)
-                            issue_load(ld_stage, X0 + x);
+                            for (int x = XN * (i - FIRST) / (NM - FIRST); x < XN * (i - FIRST + 1) / (NM - FIRST); ++x)
+                                issue_load(ld_stage, X0 + x);
+                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // LANDED: k-tile kt+1 is known to be there.  CARRY (SPREAD): the steps before the barrier issue what the k-tile before this one
+        // LANDED, or kt < landed: k-tile kt+1 is known to be there.  CARRY (SPREAD): the steps before the barrier issue what the k-tile before this one
         // left to them of the loads of k-tile kt-1+NS, so at the barrier all loads up to that k-tile are out, as without SPREAD.
-        auto ktile = [&](int kt, int nkt, auto loads_c, auto par_c, auto landed_c, auto carry_c) {
+        auto ktile = [&](int kt, int nkt, auto loads_c, auto par_c, auto landed_c, auto carry_c, int landed = 0) {
             constexpr bool LOADS = decltype(loads_c)::value, LANDED = decltype(landed_c)::value, CARRY = decltype(carry_c)::value;
             static_assert(SPREAD || !CARRY, "nothing is left over");
             constexpr int P0 = decltype(par_c)::value;   // fragment set that holds this k-tile's first fragments
-            const int sidx = kt % NS;
+            const int sidx = (int)((unsigned)kt % NS);
             PK_LDS char* st = ring + sidx * STAGE;
             PK_LDS char* nx = ring + (sidx + 1 == NS ? 0 : sidx + 1) * STAGE;
             // fragment set `par` is consumed, the other one refilled
-            auto step = [&](auto par, PK_LDS char* rd_stage, int rd_kk, auto part_c) {
+            auto step = [&](auto par, PK_LDS char* rd_stage, int rd_kk, auto part_c, auto sync_c, auto sync) {
                 const int ld_stage = decltype(part_c)::value <= 0 ? sidx : sidx == 0 ? NS - 1 : sidx - 1;
-                if constexpr (decltype(par)::value) kstep(af1, bf1, af0, bf0, rd_stage, rd_kk, ld_stage, part_c);
-                else kstep(af0, bf0, af1, bf1, rd_stage, rd_kk, ld_stage, part_c);
+                if constexpr (decltype(par)::value) kstep(af1, bf1, af0, bf0, rd_stage, rd_kk, ld_stage, part_c, sync_c, sync);
+                else kstep(af0, bf0, af1, bf1, rd_stage, rd_kk, ld_stage, part_c, sync_c, sync);
             };
-            if constexpr (KS >= 2) step(std::integral_constant<int, P0>{}, st, 1, std::integral_constant<int, CARRY ? 1 : -1>{});
-            if constexpr (KS >= 3) step(std::integral_constant<int, P0 ^ 1>{}, st, 2, std::integral_constant<int, CARRY ? 2 : -1>{});
-            if constexpr (KS >= 4) step(std::integral_constant<int, P0>{}, st, 3, std::integral_constant<int, CARRY ? 3 : -1>{});
+            auto none = [] {};
+            using NO = std::false_type;
+            if constexpr (KS >= 2) step(std::integral_constant<int, P0>{}, st, 1, std::integral_constant<int, CARRY ? 1 : -1>{}, NO{}, none);
+            if constexpr (KS >= 3) step(std::integral_constant<int, P0 ^ 1>{}, st, 2, std::integral_constant<int, CARRY ? 2 : -1>{}, NO{}, none);
+            if constexpr (KS >= 4) step(std::integral_constant<int, P0>{}, st, 3, std::integral_constant<int, CARRY ? 3 : -1>{}, NO{}, none);
             static_assert(KS <= 4, "at most four k-steps per k-tile");
             static_assert(NS >= 2, "a ring has two stages or more");
-            if constexpr (LANDED) {
-                __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-            } else if constexpr (LOADS) {
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * NL));
-            } else {
-                // at the end of the range: of the k-tiles left, only those behind the next one may still be in flight
-                const int left = nkt - kt;
-                auto wait = [&](auto self, auto j_c) -> void {
-                    constexpr int J = decltype(j_c)::value;
-                    if constexpr (J < 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-                    else if (left >= J) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((J - 2) * NL));
-                    else self(self, std::integral_constant<int, J - 1>{});
-                };
-                wait(wait, std::integral_constant<int, NS>{});
-            }
-            if constexpr (PRIV) asm volatile("" : : : "memory");   // the loads have written the LDS behind the compiler's back
-            else __syncthreads();
-            step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, std::integral_constant<int, LOADS ? 0 : -1>{});
+            auto sync = [&] {
+                if constexpr (LANDED) {
+                    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                } else if constexpr (LOADS) {
+                    if constexpr (DEFER && M16) {
+                        // (the compiler's form of this branch is ten scalar instructions)
+                        asm volatile("s_cmp_lt_i32 %0, %1\n\ts_cbranch_scc1 .Llanded%=\n\ts_waitcnt vmcnt(%2)\n.Llanded%=:"
+                                     : : "s"(kt), "s"(landed), "n"((NS - 2) * NL) : "scc", "memory");
+                        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                    } else {
+                        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NS - 2) * NL));
+                    }
+                } else {
+                    // at the end of the range: of the k-tiles left, only those behind the next one may still be in flight
+                    const int left = nkt - kt;
+                    auto wait = [&](auto self, auto j_c) -> void {
+                        constexpr int J = decltype(j_c)::value;
+                        if constexpr (J < 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+                        else if (left >= J) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((J - 2) * NL));
+                        else self(self, std::integral_constant<int, J - 1>{});
+                    };
+                    wait(wait, std::integral_constant<int, NS>{});
+                }
+                if constexpr (PRIV) asm volatile("" : : : "memory");   // the loads have written the LDS behind the compiler's back
+                else __syncthreads();
+            };
+            // M16: in the middle of the step.  What a wave does between its k-tiles (branches, addresses, the last fragments' way from the LDS)
+            // then runs beside the other waves' MFMAs; next to the barrier it leaves the matrix cores idle (cycles per 128 bytes of k, 2048
+            // of them MFMAs: 256x256 tiles 2680, in the middle 2400; k-contiguous 2434 and 2263; 256x128, 1024 of them, 1400 and 1300)
+            if constexpr (!M16) sync();
+            step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, std::integral_constant<int, LOADS ? 0 : -1>{}, std::true_type{}, sync);
         };
         // the k-tiles of one pipeline fill: the first NS are in flight or landed, stage 0 holds the first
         auto run_ktiles = [&](int nkt) {
@@ -1052,7 +1137,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             using O = std::integral_constant<int, 1>;    // ... on set 1
             load_frags(ring, 0, af0, bf0);
             int kt = 0;
-            if (DEFER && stores_pending) {
+            if (DEFER && !M16 && stores_pending) {
                 // the first NS k-tiles are there; the barrier of k-tile NS-1 waits for k-tile NS, whose loads were issued behind
                 // the previous tile's stores: they are complete then
                 static_assert(!DEFER || (!SPREAD && (KS % 2 == 0 || NS % 2 == 0)), "the main loop starts on set 0");
@@ -1089,19 +1174,35 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 #pragma clang loop unroll(disable)
                 for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{}, F{});
             } else {
-                // odd k-steps per k-tile: the starting set alternates, so k-tiles go in pairs (such k-tiles are 64 bytes, and the
-                // host admits only k ranges of whole 128-byte units)
-                static_assert(KS % 2 == 0 || (KB == 64 && NS % 2 == 0), "pairs of k-tiles need an even number of them and an even ring");
+                // one k-step per k-tile: the starting set alternates, so k-tiles go in pairs.  64-byte k-tiles come in even numbers
+                // (the host admits only k ranges of whole 128-byte units); of 128-byte ones there may be one more
+                static_assert(KS % 2 == 0 || KB == 128 || NS % 2 == 0, "an even ring, or the pairs would not meet its end");
 #pragma clang loop unroll(disable)
-                for (; kt + NS < nkt; kt += 2) {
+                for (int part = DEFER && M16 && stores_pending ? 0 : 1; part < 2; ++part) {
+                    // part 0: the first NS k-tiles with the previous tile's stores on their way (above), in the same code: a copy of it
+                    // costs 30 registers
+                    const int end = part == 0 ? 2 * NS : nkt - (KB == 128 ? 1 : 0), landed = part == 0 ? NS - 1 : 0;
+#pragma clang loop unroll(disable)
+                    for (; kt + NS < end; kt += 2) {
+                        ktile(kt, nkt, T{}, E{}, F{}, F{}, landed);
+                        ktile(kt + 1, nkt, T{}, O{}, F{}, F{}, landed);
+                    }
+                    if (DEFER && M16 && part == 0) signal_prev();
+                }
+                if (KB == 128 && kt + NS < nkt) {
                     ktile(kt, nkt, T{}, E{}, F{}, F{});
-                    ktile(kt + 1, nkt, T{}, O{}, F{}, F{});
+                    ++kt;
+#pragma unroll
+                    for (int i = 0; i < FM; ++i) af0[i] = af1[i];
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) bf0[j] = bf1[j];
                 }
 #pragma clang loop unroll(disable)
-                for (; kt < nkt; kt += 2) {
+                for (; kt + (KB == 128 ? 1 : 0) < nkt; kt += 2) {
                     ktile(kt, nkt, F{}, E{}, F{}, F{});
                     ktile(kt + 1, nkt, F{}, O{}, F{}, F{});
                 }
+                if (KB == 128 && kt < nkt) ktile(kt, nkt, F{}, E{}, F{}, F{});
             }
         };
         const uint64_t t_loop0 = clock64();
@@ -1152,10 +1253,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                         if (bl / OB != gr) {
                             PK_LDS char* dp = piece(gr, bl / OB, bl % OB);
 #pragma unroll
-                            for (int b = 0; b < 4; ++b) {
-                                const f32x16& x = acc[bl / TN][bl % TN];
-                                *(PK_LDS f32x4*)(dp + b * 1024) = f32x4{x[4 * b], x[4 * b + 1], x[4 * b + 2], x[4 * b + 3]};
-                            }
+                            for (int b = 0; b < 4; ++b) *(PK_LDS f32x4*)(dp + b * 1024) = quad(bl / TN, bl % TN, b);
                         }
                 }
             __syncthreads();
@@ -1163,25 +1261,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             for (int gr = 0; gr < NOWN; ++gr)
                 if (wk == gr) {
 #pragma unroll
-                    for (int i = 0; i < OB; ++i) {
-                        f32x16 sum;
+                    for (int i = 0; i < OB; ++i)
 #pragma unroll
-                        for (int from = 0; from < WK; ++from) {
-                            f32x16 x;
-                            if (from == gr) {
-                                x = acc[(gr * OB + i) / TN][(gr * OB + i) % TN];
-                            } else {
+                        for (int b = 0; b < 4; ++b) {
+                            f32x4 sum;
 #pragma unroll
-                                for (int b = 0; b < 4; ++b) {
-                                    const f32x4 v = *(PK_LDS f32x4*)(piece(from, gr, i) + b * 1024);
-#pragma unroll
-                                    for (int e = 0; e < 4; ++e) x[4 * b + e] = v[e];
-                                }
+                            for (int from = 0; from < WK; ++from) {
+                                const f32x4 x = from == gr ? quad((gr * OB + i) / TN, (gr * OB + i) % TN, b) : *(PK_LDS f32x4*)(piece(from, gr, i) + b * 1024);
+                                sum = from == 0 ? x : sum + x;
                             }
-                            sum = from == 0 ? x : sum + x;
+                            set_quad(i / OTN, i % OTN, b, sum);
                         }
-                        acc[i / OTN][i % OTN] = sum;
-                    }
                 }
             __syncthreads();                                 // the next tile's loads may fill the ring
         }

@@ -38,6 +38,14 @@ constexpr TileWaves tile_waves(int tile, bool fp8, bool bt) {
     }
 }
 
+// bf16 products by 16x16x32 MFMAs.  The large tiles run at the clock that the power limit leaves them, and an MFMA that keeps a quarter
+// of the accumulators for twice as long takes less of it: a loop of nothing else on random operands 1990 TFLOP/s at 2.03 GHz, of
+// 32x32x16 1730 at 1.76 (with 8-bit operands 16x16x128 4270 and 32x32x64 3890).  us a call, 32x32 / 16x16: 8192 x 3584 x 8192 all-gather 381
+// / 354 (k-contiguous 368 / 337), 8192 x 8192 x 3584 reduce-scatter 442 / 411, 4096 x 1792 x 4096 58.0 / 54.5, 1024 x 8192 x 3584 67.4 / 63.4.
+// The 128x128 and 128x64 tiles gain 1-2% (1512 x 1720 x 5120 38.8 / 38.1).  The smallest tiles are bound by their loads; the kernels with a
+// stream-K tail have no registers left for the second form's addresses.
+constexpr bool tile_m16(int tile, bool fp8, bool sk) { return !fp8 && !sk && tile < T64x64; }
+
 // Estimated time, in nanoseconds x grid, of `tiles` tiles over `kt` 128-byte k-tiles on `grid` workgroups: rounds x (fixed part
 // + k-tile time), the k-tile time rising with the share of the compute units at work (clock, L2 and memory traffic).  The
 // figures are fitted to 36 shapes of bf16 and 17 of fp8 GEMMs from 16 x 3584 x 8192 to 8192 x 8192 x 3584, timed with every
@@ -72,7 +80,7 @@ static pk_status launch_kernel(GemmArgs a, int grid, hipStream_t stream) {
     constexpr int BM = kTileDim[TILE].bm, BN = kTileDim[TILE].bn;
     constexpr TileWaves W = tile_waves(TILE, FP8, BT);
     static std::atomic<uint64_t> configured{0};              // bit d = dynamic LDS size raised on device d
-    auto kern = gemm_kernel<BM, BN, W.wm, W.wn, W.wk, W.kb, W.ns, FP8, EPI, BT, SK>;
+    auto kern = gemm_kernel<BM, BN, W.wm, W.wn, W.wk, W.kb, W.ns, FP8, EPI, BT, SK, tile_m16(TILE, FP8, SK)>;
     constexpr int lds = gemm_lds_bytes<BM, BN, W.kb, W.ns * (W.wm * W.wn == 1 ? W.wk : 1)>();
     static_assert(lds <= 160 * 1024, "a compute unit has 160 KB of LDS");
     int dev = 0;

@@ -13,10 +13,17 @@ SHAPES = [
     ("fp8", "nk", 6854, 1072, "256x128"),
     ("bf16", "nk", 4700, 784, "128x256"),
     ("fp8", "nk", 5640, 656, "128x256"),
+    # one k-step per k-tile: pairs of k-tiles, and one more where their number is odd
+    ("bf16", "kn", 1104, 1304, "128x64"),                  # four stages
+    ("bf16", "kn", 4658, 688, "128x128"),
+    ("bf16", "nk", 5890, 536, "128x128"),
+    ("bf16", "kn", 2116, 2776, "128x256"),                 # four stages of 64 bytes
+    ("bf16", "kn", 7704, 5528, "256x256"),                 # the same, several rounds
+    ("bf16", "nk", 7938, 4072, "256x256"),                 # two stages
 ]
 
 
-@pytest.mark.parametrize("ktiles", [2, 3, 4, 5, 7])       # of 128 bytes, in rings of three stages
+@pytest.mark.parametrize("ktiles", [2, 3, 4, 5, 7])       # of 128 bytes, in rings of three stages (if nothing else is said)
 @pytest.mark.parametrize("dtype,layout,M,n,tile", SHAPES)
 def test_short_k(dtype, layout, M, n, tile, ktiles):
     check_ag_gemm(dtype, 2, 1, M, 2 * n, ktiles * (64 if dtype == "bf16" else 128), layout, "none", tile)
