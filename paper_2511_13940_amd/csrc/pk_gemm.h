@@ -162,6 +162,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;  // 32x32 blocks of accumulators per wave: TM x TN
     constexpr int MF = M16 ? 16 : 32;                    // rows and columns of one MFMA
     constexpr int FM = BM / WM / MF, FN = BN / WN / MF;  // fragments per wave and k-step
+    // MID: the barrier of a k-tile comes in the middle of its last step (see kstep and sync).  fp8, cycles per 128 bytes of k: 128x256
+    // 1224 -> 1138 of which 1024 MFMAs (4096 x 3584 x 8192 k-contiguous 90.8 -> 87.0 us a call, 1024 x 3584 x 8192 32.8 -> 32.3).  Not in the fp8 256x256 kernels with a
+    // row-major operand: they need 233 registers then, of which 224 leave room for the reduce beside them (16384 x 16384 x 2048: 694
+    // us a call, 649 without)
+    constexpr bool MID = M16 || (FP8 && FM * FN >= 4 && (BT || BM * BN < 256 * 256));
     static_assert(!M16 || (!FP8 && BN % 64 == 0), "16x16x32 MFMAs: bf16, panels of 128 bytes");
     constexpr int A_BYTES = BM * KB, B_BYTES = BN * KB, STAGE = A_BYTES + B_BYTES;
     constexpr int ELEM = FP8 ? 1 : 2;
@@ -226,6 +231,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     // unit, and 128 for the one form's reads with the other form's swizzle.
     auto fA = [](int r) { return (KB == 128 ? r & 7 : (r >> 1) & 3) ^ (M16 ? 0 : (r >> 3) & 1); };
 
+    // fp8 B tile (rows of B_ROW_BYTES): the 32-byte pieces of a row trade places so that eight k-rows, which 32 lanes of a transposing read
+    // cover, lie in different banks (256 B/clk per compute unit; 128 where two of the rows shared banks)
+    auto fB = [](int kr) { return (kr & 7) / (16 / CPR) % (CPR / 2); };
+
     // ---- per-lane LDS fragment addresses (relative to a stage) ----
     // Set anew for every tile, from a lane id that the compiler cannot follow from one tile to the next: kept in registers
     // across the epilogue (and its addresses across the main loop) they would not fit beside the accumulators.
@@ -254,20 +263,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
         } else if constexpr (!FP8) {
             // bf16 B tile: panels of 64 columns (128 bytes per k-row, k-rows consecutive);
-            // inside a row the two 32-byte pieces of each 64-byte half trade places on k-rows with bit 1 set.  A tile of 32
-            // columns is one panel of 64 bytes per k-row: the 32 lanes of a transposing read then cover 256 bytes in a row.
+            // inside a row the two 64-byte halves trade places on k-rows with bit 1 set.  A tile of 32 columns is one panel of
+            // 64 bytes per k-row.  Either way the 32 lanes of a transposing read cover 256 bytes in as many banks.
             static_assert(BN % 64 == 0 || BN == 32, "the tile is made of whole panels");
             const int krow_base = 16 * kk0 + 8 * h + (s16 >> 2);
 #pragma unroll
             for (int tj = 0; tj < TN; ++tj) {
                 const int c32 = wn * TN + tj;                // 32-column block of the tile
                 const int panel = c32 >> 1;
-                const int piece = BN == 32 ? nhalf : (2 * (c32 & 1) + nhalf) ^ ((s16 >> 3) & 1);
+                const int piece = BN == 32 ? nhalf : (2 * (c32 & 1) + nhalf) ^ (2 * ((s16 >> 3) & 1));
                 b_off[tj] = (uint32_t)(A_BYTES + panel * (B_ROWS * PB) + krow_base * PB + piece * 32 + (s16 & 3) * 8);
             }
         } else {
             const int krow_base = 64 * kk0 + 32 * h + (s16 >> 1);
-            const int gsw = CPR >= 4 ? ((s16 >> 1) & 7) % (CPR / 2) : 0;
+            const int gsw = fB(s16 >> 1);
 #pragma unroll
             for (int tj = 0; tj < TN; ++tj) {
                 const int c = wn * (BN / WN / 16) + tj * 2 + nhalf;
@@ -674,7 +683,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                     const int bi = j * NWL + wl;
                     const int panel = bi / (B_ROWS / KR);
                     const int kr = (bi % (B_ROWS / KR)) * KR + kr_in;
-                    const int sw = PB == 64 ? 0 : 2 * ((kr >> 1) & 1) ^ (M16 ? 4 * ((kr >> 3) & 1) : 0);
+                    const int sw = PB == 64 ? 0 : M16 ? 2 * ((kr >> 1) & 1) + 4 * ((kr >> 3) & 1) : 4 * ((kr >> 1) & 1);
                     int colbyte = (col0 + panel * 64) * 2 + (cp ^ sw) * 16;
                     if (colbyte >= n_bytes) colbyte = n_bytes - 16;   // edge tile: valid memory, never stored
                     b_voff[j] = (uint32_t)((int64_t)kr * g.ldb + colbyte);
@@ -685,8 +694,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
                     const int kr = (j * NWL + wl) * RPI + kr_in;
-                    const int sw = CPR >= 4 ? 2 * ((kr & 7) % (CPR / 2)) : 0;
-                    int colbyte = col0 + (cp ^ sw) * 16;
+                    int colbyte = col0 + (cp ^ (2 * fB(kr))) * 16;
                     if (colbyte >= n_bytes) colbyte = n_bytes - 16;   // edge tile: valid memory, never stored
                     b_voff[j] = (uint32_t)((int64_t)kr * g.ldb + colbyte);
                 }
@@ -1019,7 +1027,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         // of the next step's fragments into (na, nb) behind the first half of the MFMAs (they then have the
         // second half of the step to arrive) and the direct-to-LDS loads of a later k-tile behind the second half, or (SPREAD)
         // share `part` of them (none if negative) between all of the MFMAs.
-        // M16: `sync` (the waits and the barrier of a k-tile, if this is its step) comes behind MFMA number P, the reads and loads after
+        // MID: `sync` (the waits and the barrier of a k-tile, if this is its step) comes behind MFMA number P, the reads and loads after
         // it.
         auto kstep = [&](const frag_t (&ca)[FM], const frag_t (&cb)[FN], frag_t (&na)[FM], frag_t (&nb)[FN],
                          PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto part_c, auto sync_c, auto sync) {
@@ -1027,12 +1035,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             constexpr bool LOADS = PART >= 0;
             constexpr int X0 = LOADS ? NL * PART / PARTS : 0, XN = LOADS ? NL * (PART + 1) / PARTS - X0 : 0;
             constexpr int NM = FM * FN, H = NM >= 2 ? NM / 2 : 1, FIRST = SPREAD ? 0 : NM - H;   // MFMAs with loads behind them
-            constexpr int P = M16 && decltype(sync_c)::value ? NM / 4 : 0;
+            constexpr int P = MID && decltype(sync_c)::value ? NM / 4 : 0;
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 const int ti = i / FN;
-                mfma_one(ti, M16 && (ti & 1) ? FN - 1 - i % FN : i % FN, ca, cb);
-                if constexpr (M16) {
+                mfma_one(ti, MID && (ti & 1) ? FN - 1 - i % FN : i % FN, ca, cb);
+                if constexpr (MID) {
                     __builtin_amdgcn_sched_barrier(0);
                     if (P > 0 && i == P - 1) sync();
                     // The next step's fragments, evenly spread: unit y is A row 0, the B fragments, then the other A rows, each of these into the
@@ -1123,10 +1131,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 if constexpr (PRIV) asm volatile("" : : : "memory");   // the loads have written the LDS behind the compiler's back
                 else __syncthreads();
             };
-            // M16: in the middle of the step.  What a wave does between its k-tiles (branches, addresses, the last fragments' way from the LDS)
+            // MID: in the middle of the step.  What a wave does between its k-tiles (branches, addresses, the last fragments' way from the LDS)
             // then runs beside the other waves' MFMAs; next to the barrier it leaves the matrix cores idle (cycles per 128 bytes of k, 2048
             // of them MFMAs: 256x256 tiles 2680, in the middle 2400; k-contiguous 2434 and 2263; 256x128, 1024 of them, 1400 and 1300)
-            if constexpr (!M16) sync();
+            if constexpr (!MID) sync();
             step(std::integral_constant<int, (P0 + KS - 1) & 1>{}, nx, 0, std::integral_constant<int, LOADS ? 0 : -1>{}, std::true_type{}, sync);
         };
         // the k-tiles of one pipeline fill: the first NS are in flight or landed, stage 0 holds the first
