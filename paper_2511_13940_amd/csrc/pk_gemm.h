@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int OUT_ELEM = EPI == EPI_RS ? 4 : 2;
     constexpr int EPI_STORES = OTM * OTN * OUT_ELEM;     // 16-byte-per-lane stores of a wave for a whole tile (1 KB each)
     // The stores of a tile may still be on their way while the next tile's main loop starts (shapes that run many rounds)
-    constexpr bool DEFER = BM * BN == 256 * 256 && NS >= 4 && !SK && EPI != EPI_AGK && EPI_STORES <= 62;
+    constexpr bool DEFER = BM * BN == 256 * 256 && (NS >= 4 || M16) && !SK && EPI != EPI_AGK && EPI_STORES <= 62;
 
     touch_kernel_args();
 
@@ -1178,7 +1178,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{}, F{});
             } else if constexpr (KS % 2 == 0) {
 #pragma clang loop unroll(disable)
-                for (; kt + NS < nkt; ++kt) ktile(kt, nkt, T{}, E{}, F{}, F{});
+                for (int part = DEFER && M16 && stores_pending ? 0 : 1; part < 2; ++part) {
+                    // part 0: as in the branch below
+                    const int end = part == 0 ? 2 * NS : nkt, landed = part == 0 ? NS - 1 : 0;
+#pragma clang loop unroll(disable)
+                    for (; kt + NS < end; ++kt) ktile(kt, nkt, T{}, E{}, F{}, F{}, landed);
+                    if (DEFER && M16 && part == 0) signal_prev();
+                }
 #pragma clang loop unroll(disable)
                 for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{}, F{});
             } else {

@@ -664,8 +664,7 @@ static RsRoute rs_route(const pk_plan& pl, int P, int rank, int64_t rows, int64_
     r.own_row = rank * pl.tiles_m / r.t.blks_per_tile;
     r.own_rows = ((rank + 1) * pl.tiles_m - 1) / r.t.blks_per_tile - r.own_row + 1;
     // Registers per lane that the 256x256 GEMM kernels of this mode leave beside their two waves per SIMD (512 less twice their own, in
-    // steps of 8): bf16 96 (80 with bf16 slots), fp8 64.  A wave of the reduce kernel takes 64 at most, 48 in the forms that run
-    // beside fp8: the narrow one for fp32 slots and P = 2, 4, 8, else the one for bf16 slots or a run-time P.
+    // steps of 8): 64.  A wave of the reduce kernel takes 64 at most, 48 in the forms that run beside fp8: the narrow one for fp32 slots and P = 2, 4, 8, else the one for bf16 slots or a run-time P.
     // The narrow form is the faster one beside fp8, and beside the 256x256 bf16 kernel with the second operand k-contiguous: with
     // twice the loads in flight the reduce takes more bandwidth and clock from the GEMM (fp8 16384 x 16384 x 2048: 676 us against
     // 706 us a call; bf16 k-contiguous 3624 x 12472 x 576 152 against 165, 8192 x 4096 x 512 91 against 98, 8192 x 8192 x 3584 419

@@ -18,6 +18,9 @@ constexpr TileDim kTileDim[N_TILES] = {{256, 256}, {256, 128}, {128, 256}, {128,
 // only two k-steps in a 128-byte k-tile and half as many fragment reads per flop: there the split gains nothing.
 // A k-contiguous second operand is fetched as one piece per row and k-tile, and 64-byte pieces use half of every 128-byte line
 // they touch: 128-byte k-tiles throughout.
+// 256x256 in bf16: two stages of 128 bytes.  With the barrier in the middle of a k-step (gemm_kernel, MID) they have time enough to land,
+// and there is half the barrier and branch work of 64-byte k-tiles in four stages (2367 cycles per 128 bytes, 2400 so; us a call: 8192 x 8192 x
+// 512 reduce-scatter 128 / 131, 8192 x 3584 x 8192 column chunks 365 / 373, 8192 x 8192 x 3584 0.908 / 0.928 of what it was before).
 // The two smallest serve calls of a few dozen rows, which stream the second operand past a handful of flops: what bounds them is
 // how many compute units load at once, and the time from a load to the MFMA behind it.  A wave that takes every fourth k-tile
 // through a ring of its own needs no barrier per k-tile (64 x 3584 x 8192, second operand k-contiguous: 64x32 tiles 19.3 us with
@@ -25,9 +28,9 @@ constexpr TileDim kTileDim[N_TILES] = {{256, 256}, {256, 128}, {128, 256}, {128,
 struct TileWaves {
     int wm, wn, wk, kb, ns;
 };
-constexpr TileWaves tile_waves(int tile, bool fp8, bool bt) {
+constexpr TileWaves tile_waves(int tile, bool fp8, bool bt, bool sk) {
     switch (tile) {
-        case T256x256: return bt ? TileWaves{2, 4, 1, 128, 2} : TileWaves{2, 4, 1, 64, 4};
+        case T256x256: return bt || !(fp8 || sk) ? TileWaves{2, 4, 1, 128, 2} : TileWaves{2, 4, 1, 64, 4};
         case T256x128: return fp8 ? TileWaves{4, 2, 1, 128, 3} : TileWaves{2, 2, 2, 128, 3};
         case T128x256: return bt ? TileWaves{2, 4, 1, 128, 3} : TileWaves{2, 4, 1, 64, 4};
         case T128x128: return fp8 ? TileWaves{4, 2, 1, 128, 4} : TileWaves{2, 2, 2, 128, 4};
@@ -78,7 +81,7 @@ pk_status launch_gemm(GemmArgs a, int tile, bool fp8, bool bt, bool sk, int grid
 template <int TILE, bool FP8, int EPI, bool BT, bool SK>
 static pk_status launch_kernel(GemmArgs a, int grid, hipStream_t stream) {
     constexpr int BM = kTileDim[TILE].bm, BN = kTileDim[TILE].bn;
-    constexpr TileWaves W = tile_waves(TILE, FP8, BT);
+    constexpr TileWaves W = tile_waves(TILE, FP8, BT, SK);
     static std::atomic<uint64_t> configured{0};              // bit d = dynamic LDS size raised on device d
     auto kern = gemm_kernel<BM, BN, W.wm, W.wn, W.wk, W.kb, W.ns, FP8, EPI, BT, SK, tile_m16(TILE, FP8, SK)>;
     constexpr int lds = gemm_lds_bytes<BM, BN, W.kb, W.ns * (W.wm * W.wn == 1 ? W.wk : 1)>();
