@@ -499,8 +499,8 @@ static uint64_t timeout_ticks(uint64_t timeout_us) {
 // ------------------------------------------------------------------------------------------------
 // Measurement aid (not part of the method): register-only MFMA loop.  Each wave runs `iters` rounds of 16
 // independent 32x32x16 bf16 MFMAs on operands held in registers, either all 1.0 or random sign + mantissa.
-// The sustained rate with random operands is the ceiling a GEMM on random data can reach: the chip lowers its
-// clock under data-dependent power.  One lane also reports wall-clock ticks and core-clock cycles.
+// The chip lowers its clock under data-dependent power: the sustained rate with random operands is the ceiling of a
+// GEMM on random data with this MFMA (16x16x32, which the large bf16 tiles use, sustains about 15% more).  One lane also reports wall-clock ticks and core-clock cycles.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, int random_operands, uint64_t* report) {
     const uint64_t w0 = wall_clock64(), c0 = clock64();
