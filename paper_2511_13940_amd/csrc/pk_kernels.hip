@@ -665,11 +665,11 @@ static RsRoute rs_route(const pk_plan& pl, int P, int rank, int64_t rows, int64_
     r.own_rows = ((rank + 1) * pl.tiles_m - 1) / r.t.blks_per_tile - r.own_row + 1;
     // Registers per lane that the 256x256 GEMM kernels of this mode leave beside their two waves per SIMD (512 less twice their own, in
     // steps of 8): 64.  A wave of the reduce kernel takes 64 at most, 48 in the forms that run beside fp8: the narrow one for fp32 slots and P = 2, 4, 8, else the one for bf16 slots or a run-time P.
-    // The narrow form is the faster one beside fp8, and beside the 256x256 bf16 kernel with the second operand k-contiguous: with
-    // twice the loads in flight the reduce takes more bandwidth and clock from the GEMM (fp8 16384 x 16384 x 2048: 676 us against
-    // 706 us a call; bf16 k-contiguous 3624 x 12472 x 576 152 against 165, 8192 x 4096 x 512 91 against 98, 8192 x 8192 x 3584 419
-    // against 417).
-    r.narrow_reduce = (fp8 || (bt && pl.tile_m == 256)) && !bf16_slots && (P == 2 || P == 4 || P == 8);
+    // The narrow form is the faster one beside fp8 and beside the 256x256 bf16 kernels: with twice the loads in flight the reduce takes
+    // more bandwidth and clock from the GEMM (us a call, narrow / wide: fp8 16384 x 16384 x 2048 676 / 706; bf16, P = 8: 8192 x 8192 x
+    // 3584 402 / 407, x 1024 173 / 178, 16384 x 8192 x 1024 325 / 335, 5120 x 10000 x 2048 239 / 249, 16384 x 16384 x 4096 1734 / 1766; P =
+    // 4, 8192 x 8192 x 3584 404 / 410; P = 2, x 4096 465 / 466; k-contiguous 3624 x 12472 x 576 152 / 165, 8192 x 4096 x 512 91 / 98).
+    r.narrow_reduce = (fp8 || pl.tile_m == 256) && !bf16_slots && (P == 2 || P == 4 || P == 8);
     // Beside fp8 the other forms pay from about 200 MB of slots on (bf16 slots, P = 8: 16384 x 8192 x 2048 288 -> 272 us; 8192 x 8192 x
     // 1024, half the bytes, 102 -> 107 us; 15728 x 1376 x 1152 45 -> 57 us): splitting the GEMM costs about 12 us.  The same line for a
     // k-contiguous second operand (6064 x 2640 x 3328, fp32 slots: 88 -> 95 us; at 128 MB 105 -> 103).
