@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int OUT_ELEM = EPI == EPI_RS ? 4 : 2;
     constexpr int EPI_STORES = OTM * OTN * OUT_ELEM;     // 16-byte-per-lane stores of a wave for a whole tile (1 KB each)
     // The stores of a tile may still be on their way while the next tile's main loop starts (shapes that run many rounds)
-    constexpr bool DEFER = BM * BN == 256 * 256 && (NS >= 4 || M16) && !SK && EPI != EPI_AGK && EPI_STORES <= 62;
+    constexpr bool DEFER = BM * BN == 256 * 256 && (M16 || NS >= 4) && !SK && EPI != EPI_AGK && EPI_STORES <= 62;
 
     touch_kernel_args();
 
@@ -1148,22 +1148,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             if (DEFER && !M16 && stores_pending) {
                 // the first NS k-tiles are there; the barrier of k-tile NS-1 waits for k-tile NS, whose loads were issued behind
                 // the previous tile's stores: they are complete then
-                static_assert(!DEFER || (!SPREAD && (KS % 2 == 0 || NS % 2 == 0)), "the main loop starts on set 0");
-                if constexpr (KS % 2 == 0) {
+                static_assert(!DEFER || M16 || (KS == 1 && NS % 2 == 0), "the main loop starts on set 0");
 #pragma clang loop unroll(disable)
-                    for (; kt < NS - 1; ++kt) ktile(kt, nkt, T{}, E{}, T{}, F{});
-                    ktile(kt, nkt, T{}, E{}, F{}, F{});
-                    ++kt;
-                } else {
-#pragma clang loop unroll(disable)
-                    for (; kt < NS - 2; kt += 2) {
-                        ktile(kt, nkt, T{}, E{}, T{}, F{});
-                        ktile(kt + 1, nkt, T{}, O{}, T{}, F{});
-                    }
+                for (; kt < NS - 2; kt += 2) {
                     ktile(kt, nkt, T{}, E{}, T{}, F{});
-                    ktile(kt + 1, nkt, T{}, O{}, F{}, F{});
-                    kt += 2;
+                    ktile(kt + 1, nkt, T{}, O{}, T{}, F{});
                 }
+                ktile(kt, nkt, T{}, E{}, T{}, F{});
+                ktile(kt + 1, nkt, T{}, O{}, F{}, F{});
+                kt += 2;
                 signal_prev();
             }
             if constexpr (SPREAD) {
@@ -1177,9 +1170,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 #pragma clang loop unroll(disable)
                 for (; kt < nkt; ++kt) ktile(kt, nkt, F{}, E{}, F{}, F{});
             } else if constexpr (KS % 2 == 0) {
+                static_assert(!DEFER || M16, "part 0");
 #pragma clang loop unroll(disable)
                 for (int part = DEFER && M16 && stores_pending ? 0 : 1; part < 2; ++part) {
-                    // part 0: as in the branch below
+                    // part 0: the first NS k-tiles with the previous tile's stores on their way (above), in the same code: a copy of it
+                    // costs 30 registers
                     const int end = part == 0 ? 2 * NS : nkt, landed = part == 0 ? NS - 1 : 0;
 #pragma clang loop unroll(disable)
                     for (; kt + NS < end; ++kt) ktile(kt, nkt, T{}, E{}, F{}, F{}, landed);
@@ -1192,16 +1187,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 // (the host admits only k ranges of whole 128-byte units); of 128-byte ones there may be one more
                 static_assert(KS % 2 == 0 || KB == 128 || NS % 2 == 0, "an even ring, or the pairs would not meet its end");
 #pragma clang loop unroll(disable)
-                for (int part = DEFER && M16 && stores_pending ? 0 : 1; part < 2; ++part) {
-                    // part 0: the first NS k-tiles with the previous tile's stores on their way (above), in the same code: a copy of it
-                    // costs 30 registers
-                    const int end = part == 0 ? 2 * NS : nkt - (KB == 128 ? 1 : 0), landed = part == 0 ? NS - 1 : 0;
-#pragma clang loop unroll(disable)
-                    for (; kt + NS < end; kt += 2) {
-                        ktile(kt, nkt, T{}, E{}, F{}, F{}, landed);
-                        ktile(kt + 1, nkt, T{}, O{}, F{}, F{}, landed);
-                    }
-                    if (DEFER && M16 && part == 0) signal_prev();
+                for (; kt + NS + (KB == 128 ? 1 : 0) < nkt; kt += 2) {
+                    ktile(kt, nkt, T{}, E{}, F{}, F{});
+                    ktile(kt + 1, nkt, T{}, O{}, F{}, F{});
                 }
                 if (KB == 128 && kt + NS < nkt) {
                     ktile(kt, nkt, T{}, E{}, F{}, F{});
