@@ -50,8 +50,9 @@ __device__ __forceinline__ bool flag_wait(const uint32_t* flag, uint32_t epoch, 
     }
 }
 
-__device__ __forceinline__ void report_timeout(uint32_t* status, uint32_t index, uint32_t phase) {
-    if (atomicCAS(&status[0], 0u, (uint32_t)PK_ERR_TIMEOUT) == 0u) {
+__device__ __forceinline__ void report_timeout(uint32_t* status, uint32_t index, uint32_t phase, uint32_t none = 0,
+                                               uint32_t code = PK_ERR_TIMEOUT) {
+    if (atomicCAS(&status[0], none, code) == none) {
         status[1] = index;
         status[2] = phase;
     }

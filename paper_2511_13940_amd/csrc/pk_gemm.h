@@ -138,14 +138,31 @@ constexpr int gemm_lds_bytes() { return NS * (BM + BN) * KB + epi_stage_bytes<BM
 constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 constexpr int kWaitLgkm0 = waitcnt_vm_lgkm0(63);   // vmcnt as high as it goes: not waited for
 
-// Every cache line of the kernel's arguments, fetched at once.  Left to the compiler they come in at their first uses, one trip to
+// The kernel's arguments, every cache line of them fetched at once.  Left to the compiler they come in at their first uses, one trip to
 // memory after the other: the main loop of a short kernel starts that much later (128x128 tiles, 2000 x 1168 x 64 reduce-scatter:
 // 4100 cycles from the start to the main loop, 3100 so).
-__device__ __forceinline__ void touch_kernel_args() {
+// FETCH_BLOCK: as one block, between the loads of which the compiler can put nothing else (256x256 tiles, 5600 x 2064 x 320 all-gather:
+// 17.0 us a call, 16.7 so).  FETCH_FIRST: ahead of every other use of an argument too; each is then loaded where it is used, from the
+// scalar cache, and none takes a register through the main loops.  us a call, FETCH_BLOCK / FETCH_FIRST: all-gather, 128x256 tiles,
+// 2048 x 4096 x 512 13.15 / 12.79, 256x128, 4176 x 1568 x 13248 150.3 / 148.4; column chunks, 256x256, 11347 x 1144 x 1024 34.4 / 33.3.
+// Not with stores on their way through the next main loop (256x256 all-gather, 13176 x 872 x 704 28.3 / 29.6).
+enum Fetch { FETCH_PLAIN, FETCH_BLOCK, FETCH_FIRST };
+template <Fetch HOW>
+__device__ __forceinline__ const GemmArgs& fetched(const GemmArgs& g) {
     typedef const __attribute__((address_space(4))) uint32_t* args_t;
-    const args_t a = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    args_t a = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
     static_assert((sizeof(GemmArgs) + 63) / 64 == 6, "one word of every line below");
-    asm volatile("" : : "s"(a[0]), "s"(a[16]), "s"(a[32]), "s"(a[48]), "s"(a[64]), "s"(a[80]));
+    if constexpr (HOW == FETCH_PLAIN) {
+        asm volatile("" : : "s"(a[0]), "s"(a[16]), "s"(a[32]), "s"(a[48]), "s"(a[64]), "s"(a[80]));
+        return g;
+    } else {
+        uint32_t x[6];
+        asm volatile("s_load_dword %0, %6, 0x0\n\ts_load_dword %1, %6, 0x40\n\ts_load_dword %2, %6, 0x80\n\ts_load_dword %3, %6, 0xc0\n\t"
+                     "s_load_dword %4, %6, 0x100\n\ts_load_dword %5, %6, 0x140\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(x[0]), "=&s"(x[1]), "=&s"(x[2]), "=&s"(x[3]), "=&s"(x[4]), "=&s"(x[5]), "+s"(a));
+        asm volatile("" : : "s"(x[0]), "s"(x[1]), "s"(x[2]), "s"(x[3]), "s"(x[4]), "s"(x[5]));
+        return HOW == FETCH_FIRST ? *(const GemmArgs*)(const __attribute__((address_space(4))) GemmArgs*)a : g;
+    }
 }
 
 // BT: the second operand is stored k-contiguous (N x K row-major, the transpose of the K x N matrix): its tile then has
@@ -153,7 +170,7 @@ __device__ __forceinline__ void touch_kernel_args() {
 // SK: built with the stream-K tail (its code paths cost registers, so launches that share out no tile use SK = false).
 // M16: bf16 products by 16x16x32 MFMAs instead of 32x32x16 (the same bits: two of those add up as one of these); tile_m16 has when.
 template <int BM, int BN, int WM, int WN, int WK, int KB, int NS, bool FP8, int EPI, bool BT = false, bool SK = false, bool M16 = false>
-__global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmArgs args) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     PK_LDS char* lds = (PK_LDS char*)smem_generic;
 
@@ -214,11 +231,28 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     // The stores of a tile may still be on their way while the next tile's main loop starts (shapes that run many rounds)
     constexpr bool DEFER = BM * BN == 256 * 256 && (M16 || NS >= 4) && !SK && EPI != EPI_AGK && EPI_STORES <= 62;
 
-    touch_kernel_args();
+    // TIGHT: kernels that have to leave 80 registers per lane to a communicator's workgroups (pk.h): 216 of their own at most.  They keep
+    // nothing in registers through the main loops that can be computed anew (own_lane, report_late, `fetched`): 220-223 otherwise.
+    constexpr bool TIGHT = !IS_RS && !FP8 && BM * BN >= 256 * 128;
+    constexpr Fetch FETCH = !TIGHT ? FETCH_PLAIN : EPI == EPI_AGK || BM * BN < 256 * 256 ? FETCH_FIRST : FETCH_BLOCK;
+    const GemmArgs& g = fetched<FETCH>(args);
 
     const int tid = threadIdx.x;
     const int l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // The lane id for what is done once per tile or less.  Opaque (TIGHT): what the compiler computes from `l` there (the address of the
+    // lane's chunk flag, its bit in a mask) it computes ahead of the loop over the tiles and keeps.
+    auto own_lane = [&]() -> int {
+        int x = l;
+        if constexpr (TIGHT) asm volatile("" : "+v"(x));
+        return x;
+    };
+    auto first_thread = [&]() -> bool { return TIGHT ? w == 0 && own_lane() == 0 : tid == 0; };
+    auto report_late = [&](uint32_t index, uint32_t phase) {
+        uint32_t none = 0, code = PK_ERR_TIMEOUT;
+        if constexpr (TIGHT) asm volatile("" : "+v"(none), "+v"(code), "+v"(phase));
+        report_timeout(g.status, index, phase, none, code);
+    };
     const int wk = w / (WM * WN), wm = (w / WN) % WM, wn = w % WN;
     const int kk0 = PRIV ? 0 : wk * KS;                  // first k-step of this wave's group in every k-tile
     const int wl = PRIV ? 0 : w;                         // this wave among those that share a k-tile's loads
@@ -414,9 +448,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 #pragma unroll
             for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(x[e]));         // (a NaN passes through either way)
             if (__any(top > (SILU ? 87.f : 9.9f))) {                           // GELU: |y| is 85 at 9.9
+                float limit = 200.f;
+                if constexpr (TIGHT) asm volatile("" : "+v"(limit));           // (see own_lane)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float y = arg(x[e]), ex = exp_minus(__builtin_amdgcn_fmed3f(y, -200.f, 200.f));
+                    const float y = arg(x[e]), ex = exp_minus(__builtin_amdgcn_fmed3f(y, -limit, limit));
                     const bool rest = !SILU && y > 1.f && ex > 0.f;            // (ex = 0: x may be infinite)
                     const float q = (rest ? x[e] * ex : x[e]) / (1.f + ex);
                     o[e] = (__bf16)(rest ? x[e] - q : q);
@@ -438,7 +474,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 
     auto signal_prev = [&]() {   // paper appendix C `signal` for the tile whose stores have completed
         if (SK && p_kind == UNIT_PART) {
-            if (tid == 0) flag_publish(g.ws_flags + blockIdx.x, g.ws_epoch);
+            if (first_thread()) flag_publish(g.ws_flags + blockIdx.x, g.ws_epoch);
         } else if constexpr (IS_RS) {
             if (w == 0 && !p_dead && !g.late_signal) {
                 const int nf = min(g.fcols_per_tile, g.flag_cols - p_fcol);
@@ -573,14 +609,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                     PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
                     PK_LDS uint64_t* landed = (PK_LDS uint64_t*)(lds + EPI_OFF + 8);
                     if (w == 0) {
-                        uint64_t there = __ballot(l < g.n_chunks && flag_ready(g.chunk_flags + l, g.epoch));
+                        const int c = own_lane();
+                        uint64_t there = __ballot(c < g.n_chunks && flag_ready(g.chunk_flags + c, g.epoch));
                         int vd = 0;
                         if (need & ~there) {
                             if (may_defer) {
                                 vd = 2;
                             } else {
-                                const bool late = ((need >> l) & 1) && !flag_wait(g.chunk_flags + l, g.epoch, g.timeout_ticks);
-                                if (late) report_timeout(g.status, (uint32_t)l, 1u);
+                                const bool late = ((need >> c) & 1) && !flag_wait(g.chunk_flags + c, g.epoch, g.timeout_ticks);
+                                if (late) report_late((uint32_t)c, 1u);
                                 if (__ballot(late) != 0) vd = 1;
                                 there |= need;
                             }
@@ -591,7 +628,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                         // all the chunks that have landed (128x64 tiles, 256 workgroups that need one chunk each, 2048 x 1024 x
                         // 2048: 1.2 us of a call; done by all waves 11 us).
                         if (vd == 0) acquire_agent();
-                        if (l == 0) {
+                        if (c == 0) {
                             *verdict = vd;
                             *landed = there;
                         }
@@ -620,8 +657,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         int lt = l;                                  // the lane id, opaque: what is computed from it stays within this tile
         asm volatile("" : "+v"(lt));
         uint32_t a_voff[NA], b_voff[NB];           // per-lane byte offsets from the k-tile base pointers
-        const char* a_base = g.A;                    // wave-uniform, advanced by one k-tile per issue
-        const char* b_base = g.B;
+        const char* const a_first = g.A;
+        const char* const b_first = g.B;
+        const char* a_base = a_first;                // wave-uniform, advanced by one k-tile per issue
+        const char* b_base = b_first;
         const int64_t b_step = BT ? (int64_t)KB : (int64_t)B_ROWS * g.ldb;   // bytes from one k-tile of B to the next
         // k-tiles handled between two pipeline fills: all of them, or one column chunk of A at a time (EPI_AGK, own
         // chunk); once this workgroup has seen every chunk, its later tiles run the whole k range in one go
@@ -629,9 +668,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             // every chunk there already: no pipeline refill per chunk
             PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
             if (w == 0) {
-                const uint64_t missing = __ballot(l < g.n_chunks && !((seen_chunks >> l) & 1) && !flag_ready(g.chunk_flags + l, g.epoch));
+                const int c = own_lane();
+                const uint64_t missing = __ballot(c < g.n_chunks && !((seen_chunks >> c) & 1) && !flag_ready(g.chunk_flags + c, g.epoch));
                 if (!missing) acquire_agent();
-                if (l == 0) *verdict = missing != 0;
+                if (c == 0) *verdict = missing != 0;
             }
             __syncthreads();
             const int missing_all = *verdict;
@@ -713,9 +753,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 a_base += KB * STRIDE;
                 b_base += b_step * STRIDE;
                 if (EPI == EPI_AGK && --until_wrap == 0) {
-                    a_base = g.A;
-                    b_base = g.B;
-                    until_wrap = g.ktiles;
+                    a_base = a_first;
+                    b_base = b_first;
+                    until_wrap = KT;
                 }
             }
         };
@@ -754,9 +794,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 if (sk_bnd(jp + 1) == s0) continue;              // that workgroup has no work
                 const int owner = jp * 8 + sk_x;
                 PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
-                if (tid == 0) {
+                if (first_thread()) {
                     const int late = flag_wait(g.ws_flags + owner, g.ws_epoch, g.timeout_ticks) ? 0 : 1;
-                    if (late) report_timeout(g.status, (uint32_t)owner, 4u);
+                    if (late) report_late((uint32_t)owner, 4u);
                     *verdict = late;
                 }
                 __syncthreads();
@@ -1143,6 +1183,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             using F = std::false_type;
             using E = std::integral_constant<int, 0>;    // k-tile starts on fragment set 0
             using O = std::integral_constant<int, 1>;    // ... on set 1
+            // No argument may still be on its way: scalar loads return out of order with the LDS reads, and the compiler would wait for all
+            // reads of a k-step at its first MFMA
+            if constexpr (FETCH == FETCH_FIRST) __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
             load_frags(ring, 0, af0, bf0);
             int kt = 0;
             if (DEFER && !M16 && stores_pending) {
@@ -1218,9 +1261,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 if (c >= g.n_chunks) c -= g.n_chunks;
                 if (!((seen_chunks >> c) & 1)) {
                     PK_LDS int* verdict = (PK_LDS int*)(lds + EPI_OFF);
-                    if (tid == 0) {
+                    if (first_thread()) {
                         const int late = flag_wait(g.chunk_flags + c, g.epoch, g.timeout_ticks) ? 0 : 1;
-                        if (late) report_timeout(g.status, (uint32_t)c, 1u);
+                        if (late) report_late((uint32_t)c, 1u);
                         *verdict = late;
                         acquire_agent();
                     }
@@ -1243,9 +1286,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             // of the last k-tile after its last fragment reads).  Group r ends up with blocks [r*OB, (r+1)*OB) of the sub-tile,
             // in acc[0..OTM)[0..OTN).
             if constexpr (PRIV) __syncthreads();             // every wave is through with its ring
-            const int sub = w % (WM * WN);
+            const int sub = w % (WM * WN), lane = own_lane();
             auto piece = [&](int from, int to, int i) {      // LDS address of block i of those that group `from` hands to group `to`
-                return lds + ((((sub * NOWN + to) * (WK - 1) + (from < to ? from : from - 1)) * OB + i) * 4096) + l * 16;
+                return lds + ((((sub * NOWN + to) * (WK - 1) + (from < to ? from : from - 1)) * OB + i) * 4096) + lane * 16;
             };
 #pragma unroll
             for (int gr = 0; gr < WK; ++gr)
@@ -1300,7 +1343,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         __syncthreads();
         signal_prev();
     }
-    if (blockIdx.x == 0 && tid == 0) {
+    if (blockIdx.x == 0 && first_thread()) {
         g.status[4] = (uint32_t)(wall_clock64() - t_wall0);
         g.status[5] = (uint32_t)(clock64() - t_core0);
         g.status[6] = (uint32_t)t_loops;
