@@ -12,7 +12,7 @@ HEADERS = [os.path.join(CSRC, n) for n in ("pk_device.h", "pk_gemm.h", "pk_tiles
     os.path.join(os.path.dirname(HERE), "include", "pk.h")]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Werror=division-by-zero",
     # packed-fp32 VALU forms are kept off for every HIP source of this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]

@@ -184,6 +184,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     // row-major operand: they need 233 registers then, of which 224 leave room for the reduce beside them (16384 x 16384 x 2048: 694
     // us a call, 649 without)
     constexpr bool MID = M16 || (FP8 && FM * FN >= 4 && (BT || BM * BN < 256 * 256));
+    static_assert(!MID || FM * FN >= 4, "the barrier comes behind a quarter of a step's MFMAs, and so behind one at least");
     static_assert(!M16 || (!FP8 && BN % 64 == 0), "16x16x32 MFMAs: bf16, panels of 128 bytes");
     constexpr int A_BYTES = BM * KB, B_BYTES = BN * KB, STAGE = A_BYTES + B_BYTES;
     constexpr int ELEM = FP8 ? 1 : 2;
@@ -267,7 +268,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 
     // fp8 B tile (rows of B_ROW_BYTES): the 32-byte pieces of a row trade places so that eight k-rows, which 32 lanes of a transposing read
     // cover, lie in different banks (256 B/clk per compute unit; 128 where two of the rows shared banks)
-    auto fB = [](int kr) { return (kr & 7) / (16 / CPR) % (CPR / 2); };
+    constexpr int ROWS_256 = CPR <= 16 ? 16 / CPR : 1;   // k-rows in 256 bytes
+    auto fB = [](int kr) { return (kr & 7) / ROWS_256 % (CPR / 2); };
 
     // ---- per-lane LDS fragment addresses (relative to a stage) ----
     // Set anew for every tile, from a lane id that the compiler cannot follow from one tile to the next: kept in registers
