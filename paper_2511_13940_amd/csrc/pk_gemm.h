@@ -205,12 +205,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int KS = PRIV ? KST : KST / WK;            // ... of which each of the WK wave groups takes its own share
     // SPREAD: the loads of a k-tile are issued a share per k-step over the KS steps that follow the barrier which frees its stage, not
     // all in the first of them: NW * NL KB at once are more than the L1 takes in the time of that step, and a wave whose load does
-    // not go out issues no MFMA behind it.  Cycles per 128-byte k-tile, at once / spread: 256x128 bf16 1315 / 1132 (k-contiguous 1278 /
-    // 1126), fp8 1295 / 1213; 128x256 k-contiguous 1409 / 1166.  Where few compute units work that is the time (1024 x 1792 x 4096, 56
-    // tiles: 41.9 / 37.6 us), on all of them the clock gives most of it back (1024 x 8192 x 3584 reduce-scatter 65.1 / 63.1 us).
-    // The smaller tiles are bound by what the L1 takes in all (128x128 k-contiguous, 1512 x 1720 x 5120: 38.6 / 39.0 us), two stages
-    // leave no time to land (256x256 k-contiguous 2405 / 2792 cycles), and a 64-byte k-tile has half the loads.
+    // not go out issues no MFMA behind it.  For tiles of two or four k-steps: fp8 256x128 (cycles per 128-byte k-tile, at once / spread,
+    // 1295 / 1213 with the barrier before the last step) and 128x256 with the second operand k-contiguous (1409 / 1166).  Of the bf16
+    // 256x128 tiles each group of waves has one step per k-tile, with the loads all in it.  The smaller tiles are bound by what the L1
+    // takes in all, two stages leave no time to land, and a 64-byte k-tile has half the loads.
     constexpr bool SPREAD = KS % 2 == 0 && KB == 128 && NS >= 3 && BM * BN >= 256 * 128;
+    static_assert(!SPREAD || MID, "built for the order of reads and loads that goes with the barrier in the step");
     constexpr int EPI_OFF = RINGS * NS * STAGE;          // LDS offset of the epilogue staging area
     constexpr int EPI_BYTES = epi_stage_bytes<BM, BN, KB, RINGS * NS>();
     // WK > 1: the groups' accumulators are summed at the end of a tile and shared out, OTM x OTN blocks to each wave of the
@@ -1067,16 +1067,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         // k-tile kt+1 has landed: in the steady state only the loads of the NS-2 k-tiles after it may still be in flight.
         // One k-step: the NM MFMAs on fragment set (ca, cb), with, pinned between them in this order, the reads
         // of the next step's fragments into (na, nb) behind the first half of the MFMAs (they then have the
-        // second half of the step to arrive) and the direct-to-LDS loads of a later k-tile behind the second half, or (SPREAD)
-        // share `part` of them (none if negative) between all of the MFMAs.
-        // MID: `sync` (the waits and the barrier of a k-tile, if this is its step) comes behind MFMA number P, the reads and loads after
-        // it.
+        // second half of the step to arrive) and the direct-to-LDS loads of a later k-tile behind the second half.
+        // MID: `sync` (the waits and the barrier of a k-tile, if this is its step) comes behind MFMA number P, and after it, between the
+        // rest of them, the reads and the loads (SPREAD: share `part` of these; none if `part` is negative).
         auto kstep = [&](const frag_t (&ca)[FM], const frag_t (&cb)[FN], frag_t (&na)[FM], frag_t (&nb)[FN],
                          PK_LDS char* rd_stage, int rd_kk, int ld_stage, auto part_c, auto sync_c, auto sync) {
             constexpr int PART = decltype(part_c)::value, PARTS = SPREAD ? KS : 1;
             constexpr bool LOADS = PART >= 0;
             constexpr int X0 = LOADS ? NL * PART / PARTS : 0, XN = LOADS ? NL * (PART + 1) / PARTS - X0 : 0;
-            constexpr int NM = FM * FN, H = NM >= 2 ? NM / 2 : 1, FIRST = SPREAD ? 0 : NM - H;   // MFMAs with loads behind them
+            constexpr int NM = FM * FN, H = NM >= 2 ? NM / 2 : 1;
             constexpr int P = MID && decltype(sync_c)::value ? NM / 4 : 0;
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
@@ -1115,10 +1114,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                         }
                     }
                     if constexpr (LOADS) {
-                        if (i >= FIRST) {
+                        if (i >= NM - H) {
 #pragma unroll
-                            for (int x = XN * (i - FIRST) / (NM - FIRST); x < XN * (i - FIRST + 1) / (NM - FIRST); ++x)
-                                issue_load(ld_stage, X0 + x);
+                            for (int x = NL * (i - (NM - H)) / H; x < NL * (i - (NM - H) + 1) / H; ++x) issue_load(ld_stage, x);
                         }
                     }
                 }
