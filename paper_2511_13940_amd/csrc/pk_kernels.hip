@@ -664,12 +664,14 @@ static RsRoute rs_route(const pk_plan& pl, int P, int rank, int64_t rows, int64_
     r.own_row = rank * pl.tiles_m / r.t.blks_per_tile;
     r.own_rows = ((rank + 1) * pl.tiles_m - 1) / r.t.blks_per_tile - r.own_row + 1;
     // Registers per lane that the 256x256 GEMM kernels of this mode leave beside their two waves per SIMD (512 less twice their own, in
-    // steps of 8): 64.  A wave of the reduce kernel takes 64 at most, 48 in the forms that run beside fp8: the narrow one for fp32 slots and P = 2, 4, 8, else the one for bf16 slots or a run-time P.
-    // The narrow form is the faster one beside fp8 and beside the 256x256 bf16 kernels: with twice the loads in flight the reduce takes
-    // more bandwidth and clock from the GEMM (us a call, narrow / wide: fp8 16384 x 16384 x 2048 676 / 706; bf16, P = 8: 8192 x 8192 x
-    // 3584 402 / 407, x 1024 173 / 178, 16384 x 8192 x 1024 325 / 335, 5120 x 10000 x 2048 239 / 249, 16384 x 16384 x 4096 1734 / 1766; P =
-    // 4, 8192 x 8192 x 3584 404 / 410; P = 2, x 4096 465 / 466; k-contiguous 3624 x 12472 x 576 152 / 165, 8192 x 4096 x 512 91 / 98).
-    r.narrow_reduce = (fp8 || pl.tile_m == 256) && !bf16_slots && (P == 2 || P == 4 || P == 8);
+    // steps of 8): 64.  A wave of the reduce kernel takes 64 at most, 48 in the forms that run beside fp8: the narrow one for fp32
+    // slots and P = 2, 4, 8, else the one for bf16 slots or a run-time P.
+    // The narrow form is the faster one beside every GEMM: with twice the loads in flight the reduce takes more bandwidth and clock
+    // from it (us a call, narrow / wide: fp8 16384 x 16384 x 2048 676 / 706; bf16, 256x256 tiles, P = 8: 8192 x 8192 x 3584 402 / 407,
+    // 16384 x 8192 x 1024 325 / 335, 1600 x 12304 x 128 57.5 / 65.2; P = 4, 8192 x 8192 x 3584 404 / 410; P = 2, x 4096 465 / 466;
+    // k-contiguous 3624 x 12472 x 576 152 / 165; 128x256 tiles, 1600 x 10152 x 768 83.2 / 93.1; 256x128, 1896 x 11800 x 1984 144.4 /
+    // 148.5; 128x128, P = 2, 15178 x 640 x 4480 108.3 / 109.4).
+    r.narrow_reduce = !bf16_slots && (P == 2 || P == 4 || P == 8);
     // Beside fp8 the other forms pay from about 200 MB of slots on (bf16 slots, P = 8: 16384 x 8192 x 2048 288 -> 272 us; 8192 x 8192 x
     // 1024, half the bytes, 102 -> 107 us; 15728 x 1376 x 1152 45 -> 57 us): splitting the GEMM costs about 12 us.  The same line for a
     // k-contiguous second operand (6064 x 2640 x 3328, fp32 slots: 88 -> 95 us; at 128 MB 105 -> 103).
@@ -1273,7 +1275,8 @@ pk_status pk_partition_destroy(void* compute_stream, void* comm_stream) {
 
 // Which way a call goes, for the tests: host only, launches nothing, not part of the interface.  op: 0 pk_gemm_rs, 1 pk_gemm_rs_cols,
 // 2 pk_gemm_ar, 3 pk_ag_gemm, 4 pk_ag_gemm_k.  route: rows and columns of the tiles; 1 if their ready flags are published behind the
-// GEMM; tiles of the first and of the second launch (0: one launch); 1 with a stream-K tail; 1 if tile rows run over all chunks.
+// GEMM; tiles of the first and of the second launch (0: one launch); 1 with a stream-K tail; all-gather: 1 if tile rows run over all
+// chunks, reduce-scatter: 1 with two launches and the narrow reduce beside the second.
 pk_status pk_test_route(int op, int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype dt, int partial_dt, int b_layout, uint32_t phases,
                         int comm_cus, int has_workspace, int32_t* route) {
     const bool fp8 = dt == PK_FP8_E4M3, bt = b_layout == PK_B_K_CONTIGUOUS, s16 = partial_dt == PK_PARTIAL_BF16;
@@ -1300,7 +1303,8 @@ pk_status pk_test_route(int op, int P, int rank, int64_t M, int64_t N, int64_t K
     const int tiles = r.all_rows * r.tiles_n, first = r.first_rows * r.tiles_n;
     const int kt = (int)(pl.local_k / (fp8 ? 128 : 64));
     const bool sk = has_workspace && op == 0 && rs_takes_tail(pl, r, bt, s16) && sk_applies(ceil_div(tiles, 8) * 8, grid, kt);
-    const int32_t v[7] = {kTileDim[r.t.tile].bm, kTileDim[r.t.tile].bn, r.t.late, r.overlap ? first : tiles, r.overlap ? tiles - first : 0, sk, 0};
+    const int32_t v[7] = {kTileDim[r.t.tile].bm, kTileDim[r.t.tile].bn, r.t.late, r.overlap ? first : tiles, r.overlap ? tiles - first : 0, sk,
+                          r.overlap && r.narrow_reduce};
     for (int i = 0; i < 7; ++i) route[i] = v[i];
     return PK_OK;
 }

@@ -12,19 +12,21 @@ NAN_POISON = float("nan")
 
 
 OPS = {"gemm_rs": 0, "gemm_rs_cols": 1, "gemm_ar": 2, "ag_gemm": 3, "ag_gemm_k": 4}
-Route = collections.namedtuple("Route", "tile late first second stream_k one_span")
+Route = collections.namedtuple("Route", "tile late first second stream_k one_span narrow_reduce")
 
 
 def route(op, P, rank, M, N, K, dtype, phases=pk.PHASE_ALL, partial_dtype="f32", b_layout="kn", comm_cus=0, workspace=False):
     """Which way a call goes (decided on the host; needs no GPU): tile "rows x columns", flags published behind the GEMM or not, tiles
-    of the first and the second launch (0: one launch), stream-K tail or not, tile rows over all chunks or not."""
+    of the first and the second launch (0: one launch), stream-K tail or not, all-gather: tile rows over all chunks or not,
+    reduce-scatter in two launches: the narrow form of the reduce or not."""
     r = (ctypes.c_int32 * 7)()
     f = pk.lib().pk_test_route
     f.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64] * 3 + [ctypes.c_int] * 3 + [ctypes.c_uint32] + [ctypes.c_int] * 2 + [ctypes.c_void_p]
     st = f(OPS[op], P, rank, M, N, K, pk.DTYPES[dtype], pk.PARTIALS[partial_dtype], pk.B_LAYOUTS[b_layout], phases, comm_cus,
            1 if workspace else 0, r)
     assert st == pk.OK, pk.status_str(st)
-    return Route(f"{r[0]}x{r[1]}", bool(r[2]), r[3], r[4], bool(r[5]), bool(r[6]))
+    return Route(f"{r[0]}x{r[1]}", bool(r[2]), r[3], r[4], bool(r[5]), op.startswith("ag") and bool(r[6]),
+                 not op.startswith("ag") and bool(r[6]))
 
 
 def dev(x):

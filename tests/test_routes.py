@@ -59,3 +59,17 @@ def test_two_launches_never_take_a_tail_and_their_tiles_add_up():
 def test_overlap_cases(P, rank, M, N, K, dtype, tile, parts):
     assert pk.pk_gemm_rs_plan(P, M, N, K, dtype).tile_m == tile
     assert ov.launches(P, rank, M, N, K, dtype) == parts
+
+
+def test_the_reduce_beside_a_gemm_is_the_narrow_one():
+    """fp32 slots, P = 2, 4, 8: whatever the tiles and the flags' granularity (bf16 slots and a run-time P have one form each)."""
+    rng, seen = random.Random(8), set()
+    for _ in range(30000):
+        dtype, P = rng.choice(["bf16", "fp8"]), rng.choice([2, 3, 4, 8])
+        M, N, K = P * rng.randrange(30, 2400), 16 * rng.randrange(10, 800), P * 128 * rng.choice([1, 2, 4, 16, 24, 32])
+        slots = rng.choice(["f32", "f32", "f32", "bf16"])
+        r = hz.route("gemm_rs", P, rng.randrange(P), M, N, K, dtype, phases=OVERLAP, partial_dtype=slots)
+        if r.second:
+            seen.add((dtype, pk.pk_gemm_rs_plan(P, M, N, K, dtype).tile_m, r.tile))
+            assert r.narrow_reduce == (slots == "f32" and P != 3), (P, M, N, K, dtype, slots, r)
+    assert {("bf16", 128, t) for t in ("256x256", "256x128", "128x256")} | {("bf16", 256, "256x256"), ("fp8", 256, "256x256")} <= seen
