@@ -651,7 +651,7 @@ static RsRoute rs_route(const pk_plan& pl, int P, int rank, int64_t rows, int64_
                 rs_tile_space(pl, c, P, m_all, slot_cols, n_blks, cols, &tile_rows, &tile_cols);
                 const int tiles = tile_rows * tile_cols;
                 if (late && (tiles + 7) / 8 * 8 > grid) continue;
-                const int64_t cost = tile_cost(id, fp8, tiles, (int)(pl.local_k >> (fp8 ? 7 : 6)), grid) + (late && !do_reduce ? 4000 * grid : 0);
+                const int64_t cost = tile_cost(id, fp8, bt, tiles, (int)(pl.local_k >> (fp8 ? 7 : 6)), grid) + (late && !do_reduce ? 4000 * grid : 0);
                 if (cost < best) {
                     best = cost;
                     r.t = c;
@@ -914,7 +914,7 @@ struct AgRoute {
     bool sk;                  // with the stream-K tail
 };
 static int64_t ag_plan_slots(const pk_plan& pl, int P) { return ((int64_t)pl.tiles_m * pl.tiles_n + 7) / 8 * 8 * P; }
-static AgRoute ag_route(const pk_plan& pl, int P, int64_t M, bool fp8, bool k_chunks, bool ws, int grid) {
+static AgRoute ag_route(const pk_plan& pl, int P, int64_t M, bool fp8, bool bt, bool k_chunks, bool ws, int grid) {
     const int ktiles = (int)(pl.local_k / (fp8 ? 128 : 64));
     AgRoute r = {T256x256, k_chunks, ws && !k_chunks && pl.tile_m == 256 && sk_applies(ag_plan_slots(pl, P), grid, ktiles)};
     if (r.sk) return r;
@@ -931,7 +931,7 @@ static AgRoute ag_route(const pk_plan& pl, int P, int64_t M, bool fp8, bool k_ch
     int64_t best = INT64_MAX;
     for (int id = 0; id < (k_chunks ? T32x64 : N_TILES); ++id) {
         bool span;
-        int64_t cost = tile_cost(id, fp8, tiles_of(id, &span), ktiles, grid);
+        int64_t cost = tile_cost(id, fp8, bt, tiles_of(id, &span), ktiles, grid);
         // Many rounds of fp8 tiles run at a lower clock than those the estimate was fitted to, and the largest tile loses least by
         // it: another one has to be a sixteenth better (6960 x 7728 x 4096: 128x256, estimated at 3% less than 256x256, takes 284
         // us for 210; 5000 x 5200 x 4096 129 for 109)
@@ -977,7 +977,7 @@ static pk_status ag_gemm_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
     const int64_t chunk_rows = M / P;
     const int grid = max_grid(comm_cus);
     if (ws && !bt && !k_chunks && sk_too_small(ag_plan_slots(pl, P), grid, a.ktiles, pl.tile_m, ws_bytes)) return PK_ERR_ARG;
-    const AgRoute rt = ag_route(pl, P, M, fp8, k_chunks, ws && !bt, grid);
+    const AgRoute rt = ag_route(pl, P, M, fp8, bt, k_chunks, ws && !bt, grid);
     const int tile = rt.tile;
     const bool one_span = rt.one_span, sk = rt.sk;
     const int bm = kTileDim[tile].bm;
@@ -1288,7 +1288,7 @@ pk_status pk_test_route(int op, int P, int rank, int64_t M, int64_t N, int64_t K
     if (op >= 3) {
         const pk_status st = k_chunks ? make_plan_ag_k(P, M, N, K, dt, &pl) : make_plan(P, M, N, K, dt, false, &pl);
         if (st != PK_OK) return st;
-        const AgRoute r = ag_route(pl, P, M, fp8, k_chunks, has_workspace && !bt, grid);
+        const AgRoute r = ag_route(pl, P, M, fp8, bt, k_chunks, has_workspace && !bt, grid);
         const TileDim d = kTileDim[r.tile];
         const int64_t rows = r.one_span ? tiles_across(M, d.bm) : P * (int64_t)tiles_across(M / P, d.bm);
         const int32_t v[7] = {d.bm, d.bn, 0, (int32_t)(rows * tiles_across(pl.local_n, d.bn)), 0, r.sk, r.one_span};

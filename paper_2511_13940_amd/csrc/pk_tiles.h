@@ -50,19 +50,26 @@ constexpr TileWaves tile_waves(int tile, bool fp8, bool bt, bool sk) {
 constexpr bool tile_m16(int tile, bool fp8, bool sk) { return !fp8 && !sk && tile < T64x64; }
 
 // Estimated time, in nanoseconds x grid, of `tiles` tiles over `kt` 128-byte k-tiles on `grid` workgroups: rounds x (fixed part
-// + k-tile time), the k-tile time rising with the share of the compute units at work (clock, L2 and memory traffic).  The
-// figures are fitted to 36 shapes of bf16 and 17 of fp8 GEMMs from 16 x 3584 x 8192 to 8192 x 8192 x 3584, timed with every
-// tile shape: the tile of least estimated time was the fastest one, or within 3.2% of it, on those (and on 17 shapes with
-// a k-contiguous second operand).  Elsewhere it can be further off: many rounds of fp8 tiles (see ag_route), or calls that the
-// stores of fp32 slots bound, which the estimate does not count.
+// + k-tile time), the k-tile time rising with the share of the compute units at work (clock, L2 and memory traffic).  The figures are
+// fitted, per layout of the second operand, to 5260 calls of all ops (16 .. 16384 rows, 256 .. 8192 columns, k from 256 to 16384, half of
+// them chosen near a tie, on seven cards), each timed with every tile shape.  Of the 2720 that were not, the choice is the fastest tile or
+// within 3% of it for 98% (fp8 97%), 0.2% off on average (fp8 0.3%) and more than 6% off for 0.7% (fp8 1.4%); the figures from before the
+// 16x16x32 MFMAs, which put the large bf16 tiles too high, were more than 6% off for 2% (fp8 5%).  us a call, by those / by these: 11944 x
+// 280 x 6400 k-contiguous 89.5 (128x64) / 58.5 (256x128), 6524 x 2584 x 16256 741 (128x128) / 612 (256x128), 2356 x 7760 x 5376 k-contiguous
+// 259 (128x128) / 204 (128x256), fp8 4914 x 3984 x 15360 315 (128x256) / 277 (256x128).  Some are slower: of 130 calls that changed 87 gained
+// more than 1% and 11 lost as much (fp8 13131 x 592 x 15872 155 / 178, the worst).  What the estimate does not count are the stores of
+// fp32 slots; and many rounds of fp8 tiles are off (see ag_route).
 struct TileCost {
     int lo, hi, fixed;        // ns per k-tile with few and with all compute units at work, ns per tile
 };
-constexpr TileCost kTileCost[2][N_TILES] = {
-    {{765, 1584, 6699}, {445, 825, 5628}, {537, 901, 3314}, {293, 464, 3635}, {197, 321, 2071}, {170, 217, 2498}, {150, 176, 1767}, {119, 151, 1343}},
-    {{754, 1401, 6071}, {442, 770, 4585}, {509, 749, 4034}, {313, 472, 2616}, {277, 376, 1982}, {245, 295, 1913}, {196, 248, 1638}, {162, 220, 1349}}};
-inline int64_t tile_cost(int tile, bool fp8, int tiles, int kt, int grid) {
-    const TileCost& c = kTileCost[fp8 ? 1 : 0][tile];
+// [fp8][second operand k-contiguous]
+constexpr TileCost kTileCost[2][2][N_TILES] = {
+    {{{547, 1429, 6055}, {299, 761, 5537}, {399, 887, 3060}, {281, 435, 3247}, {201, 368, 1742}, {170, 217, 2498}, {150, 176, 1767}, {119, 151, 1343}},
+     {{469, 1378, 8306}, {319, 719, 6483}, {388, 779, 4348}, {281, 423, 3949}, {210, 295, 2623}, {170, 217, 2498}, {150, 176, 1767}, {119, 151, 1343}}},
+    {{{754, 1401, 6071}, {312, 766, 4820}, {399, 885, 2841}, {313, 472, 2616}, {277, 376, 1982}, {245, 295, 1913}, {196, 248, 1638}, {162, 220, 1349}},
+     {{754, 1401, 6071}, {297, 802, 4372}, {304, 803, 4313}, {313, 472, 2616}, {277, 376, 1982}, {245, 295, 1913}, {196, 248, 1638}, {162, 220, 1349}}}};
+inline int64_t tile_cost(int tile, bool fp8, bool bt, int tiles, int kt, int grid) {
+    const TileCost& c = kTileCost[fp8 ? 1 : 0][bt ? 1 : 0][tile];
     const int rounds = (int)((((unsigned)tiles + 7) / 8 * 8 + grid - 1) / (unsigned)grid);
     return (int64_t)rounds * grid * (c.fixed + (int64_t)kt * c.lo) + (int64_t)kt * (c.hi - c.lo) * tiles;
 }

@@ -73,3 +73,17 @@ def test_the_reduce_beside_a_gemm_is_the_narrow_one():
             seen.add((dtype, pk.pk_gemm_rs_plan(P, M, N, K, dtype).tile_m, r.tile))
             assert r.narrow_reduce == (slots == "f32" and P != 3), (P, M, N, K, dtype, slots, r)
     assert {("bf16", 128, t) for t in ("256x256", "256x128", "128x256")} | {("bf16", 256, "256x256"), ("fp8", 256, "256x256")} <= seen
+
+
+@pytest.mark.parametrize("op,P,M,N,K,dtype,layout,tile", [
+    ("ag_gemm", 8, 11944, 8 * 280, 6400, "bf16", "nk", "256x128"),           # 59 us; as 128x64 90
+    ("ag_gemm", 4, 6524, 4 * 2584, 16256, "bf16", "kn", "256x128"),          # 612 us; as 128x128 741
+    ("ag_gemm", 8, 14696, 8 * 584, 14656, "bf16", "kn", "256x256"),          # 327 us; as 128x128 421
+    ("ag_gemm", 4, 2356, 4 * 7760, 5376, "bf16", "nk", "128x256"),           # 204 us; as 128x128 259
+    ("gemm_rs_cols", 2, 793, 12992, 2 * 5952, "bf16", "kn", "256x256"),      # 134 us; as 128x128 152
+    ("ag_gemm", 1, 3098, 6832, 256, "fp8", "kn", "128x256"),                 # 19.3 us; as 256x256 22.4
+    ("ag_gemm_k", 8, 4914, 8 * 3984, 15360, "fp8", "kn", "256x128"),         # 277 us; as 128x256 315
+])
+def test_the_faster_tile(op, P, M, N, K, dtype, layout, tile):
+    """Calls that a tile shape measured far slower was estimated below the fastest one for."""
+    assert hz.route(op, P, 0, M, N, K, dtype, b_layout=layout).tile == tile
