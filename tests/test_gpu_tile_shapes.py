@@ -33,9 +33,9 @@ RS_CASES = [
     ("bf16", 4, 2, 4 * 75, 1000, 1088, "nk", "f32", "32x64 late", "32x64 late"),      # shards of 75 rows, 17 k-tiles over four waves
     ("bf16", 2, 1, 256, 248, 64, "kn", "f32", "32x32 late", "128x256"),       # one k-tile, three of the four waves without work
     ("bf16", 8, 7, 64, 520, 4032, "kn", "f32", "32x32 late", "32x32 late"),   # shards of 8 rows, 63 k-tiles
-    ("bf16", 3, 1, 6000, 5008, 512, "kn", "f32", "256x256", "256x256"),       # two rounds: stores under way in the next main loop
-    ("bf16", 2, 1, 5124, 4840, 320, "kn", "f32", "256x256", "256x256"),       # the same, rows that do not start on 64 bytes
-    ("fp8", 2, 0, 4600, 8208, 512, "kn", "f32", "256x256", "256x256"),        # the same in three rounds
+    ("bf16", 3, 1, 6000, 5008, 512, "kn", "f32", "256x256", "256x256"),       # two rounds; rows that start on 64 bytes: each tile's stores are waited for
+    ("bf16", 2, 1, 5124, 4840, 320, "kn", "f32", "256x256", "256x256"),       # the same, rows that start on 32 bytes
+    ("fp8", 2, 0, 4600, 8208, 512, "kn", "f32", "256x256", "256x256"),        # the same, 64 bytes and three rounds (on 128: test_gpu_k_ranges.py)
     ("fp8", 8, 2, 8 * 33, 4112, 256, "kn", "f32", "128x64 late", "128x128"),
     ("fp8", 2, 0, 2000, 4112, 256, "nk", "f32", "256x256", "256x256"),        # shards of 1000 rows
     ("fp8", 3, 2, 3 * 500, 2064, 2176, "kn", "f32", "128x128", "128x128"),    # 17 k-tiles
