@@ -233,8 +233,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr bool DEFER = BM * BN == 256 * 256 && (M16 || NS >= 4) && !SK && EPI != EPI_AGK && EPI_STORES <= 62;
 
     // TIGHT: kernels that have to leave 80 registers per lane to a communicator's workgroups (pk.h): 216 of their own at most.  They keep
-    // nothing in registers through the main loops that can be computed anew (own_lane, report_late, `fetched`): 220-223 otherwise.
-    constexpr bool TIGHT = !IS_RS && !FP8 && BM * BN >= 256 * 128;
+    // nothing in registers through the main loops that can be computed anew (own_lane, report_late, `fetched`): 220-223 otherwise.  Those
+    // with a stream-K tail leave none either way (16640 x 1024 x 4096 296 us a call so, 286 without).
+    constexpr bool TIGHT = !IS_RS && !FP8 && !SK && BM * BN >= 256 * 128;
     constexpr Fetch FETCH = !TIGHT ? FETCH_PLAIN : EPI == EPI_AGK || BM * BN < 256 * 256 ? FETCH_FIRST : FETCH_BLOCK;
     const GemmArgs& g = fetched<FETCH>(args);
 
