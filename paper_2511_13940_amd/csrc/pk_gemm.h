@@ -814,19 +814,24 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(g.ws_tiles + (int64_t)owner * (BM * BN * 4), 0, BM * BN * 4,
                                                                     0x00020000);
                 const uint32_t off0 = (uint32_t)((w * (TM * TN * 4)) * 1024 + l * 16);
+                // Eight loads of a wave on their way at all times, each register loaded anew as soon as it has been added: the owner adds its
+                // pieces one after the other, 15 or 63 of them where few tiles are left over, and the time from a load to its use
+                // is all that counts.  In this order, or the compiler makes some wait for one another (us a call, without / with it: 16640 x
+                // 1024 x 4096, 4 tiles left over, 286 / 265, 8704 x 2048 x 4096, 16, 211 / 200, fp8 x 8192 211 / 194; cfg4, 192, 400 / 400).
+                constexpr int NQ = TM * TN * 4, AHEAD = 8;
+                f32x4 pv[AHEAD];
+                auto fetch = [&](int i) {
+                    pv[i % AHEAD] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off0, i * 1024, 1 | 2 | 16));
+                };
 #pragma unroll
-                for (int ti = 0; ti < TM; ++ti) {
-                    f32x4 pv[TN][4];
+                for (int i = 0; i < AHEAD; ++i) fetch(i);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int tj = 0; tj < TN; ++tj)
-#pragma unroll
-                        for (int b = 0; b < 4; ++b)
-                            pv[tj][b] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                rsrc, off0 + (uint32_t)(((ti * TN + tj) * 4 + b) * 1024), 0, 1 | 2 | 16));
-#pragma unroll
-                    for (int tj = 0; tj < TN; ++tj)
-#pragma unroll
-                        for (int b = 0; b < 4; ++b) set_quad(ti, tj, b, quad(ti, tj, b) + pv[tj][b]);
+                for (int i = 0; i < NQ; ++i) {
+                    const int ti = i / (TN * 4), tj = i / 4 % TN, b = i % 4;
+                    set_quad(ti, tj, b, quad(ti, tj, b) + pv[i % AHEAD]);
+                    if (i + AHEAD < NQ) fetch(i + AHEAD);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
