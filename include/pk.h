@@ -123,6 +123,9 @@ typedef struct {
  * call to call, and two calls that may run at the same time must not share it.  workspace = NULL: whole tiles only (also
  * with PK_B_K_CONTIGUOUS, with bf16 slots and with plans of 128 x 128 tiles, for which the tail is not built, and where
  * PK_PHASE_OVERLAP splits the GEMM into two launches).
+ * The tail is taken wherever it can be, and pays where the k range is long and few tiles are left over (us a call on 256 units,
+ * whole tiles / with it: 8704 x 2048 x 16384 per rank 609 / 533); elsewhere whole tiles are faster, most of all with short k ranges
+ * (8704 x 2048 x 4096 135 / 200, 6144 x 4096 x 4096 160 / 174, 8192 x 3584 x 8192 342 / 384): pass NULL there.
  * A workspace smaller than plan.workspace_bytes may be rejected with PK_ERR_ARG, also where the call would not use it (plans
  * of 128 x 128 tiles report and check the size that a tail of theirs would take).
  */
@@ -152,7 +155,12 @@ const char* pk_status_str(int status);
  *   outgoing  [P][M/P][N]  same element type.  Slot q != rank receives this rank's tiles for rank q; slot `rank` unused.
  *                          May be NULL when P == 1.
  *   flags_in  [P][flags_per_slot] readiness of partials[q][tile]; slot `rank` is signalled by this call.
- *   flags_out [P][flags_per_slot] signalled by this call when outgoing[q][tile] is complete.
+ *   flags_out [P][flags_per_slot] signalled by this call when outgoing[q][tile] is complete: during the first k-tiles of the
+ *                          workgroup's next tile, or for some sizes (tiles that all run at once) behind the GEMM.  In a launch
+ *                          of several rounds of 256 x 256 tiles the workgroups store their first tiles one group after the
+ *                          other, up to 7/8 of the time that a round's stores take at 5.6 TB/s apart (fp32 slots 10 us, bf16
+ *                          5): the call is shorter for it (8192 x 8192 x 512 per rank, fp32 slots: 133 us for 148), and a peer
+ *                          that waits for one of these first tiles sees it that much later.
  *   out_shard M/P x N      bf16
  *
  * Requirements: M % P == 0, K % P == 0, (K/P) % 64 == 0 (bf16) or % 128 == 0 (fp8), N % 8 == 0 (bf16) or

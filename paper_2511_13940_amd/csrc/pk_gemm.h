@@ -180,9 +180,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     constexpr int MF = M16 ? 16 : 32;                    // rows and columns of one MFMA
     constexpr int FM = BM / WM / MF, FN = BN / WN / MF;  // fragments per wave and k-step
     // MID: the barrier of a k-tile comes in the middle of its last step (see kstep and sync).  fp8, cycles per 128 bytes of k: 128x256
-    // 1224 -> 1138 of which 1024 MFMAs (4096 x 3584 x 8192 k-contiguous 90.8 -> 87.0 us a call, 1024 x 3584 x 8192 32.8 -> 32.3).  Not in the fp8 256x256 kernels with a
-    // row-major operand: they need 233 registers then, of which 224 leave room for the reduce beside them (16384 x 16384 x 2048: 694
-    // us a call, 649 without)
+    // 1224 -> 1138 of which 1024 MFMAs (4096 x 3584 x 8192 k-contiguous 90.8 -> 87.0 us a call, 1024 x 3584 x 8192 32.8 -> 32.3; with a
+    // row-major operand the clock takes back most: reduce-scatter 808 x 4704 x 2048 21.17 -> 21.03, 8768 x 720 x 2048 28.59 -> 28.42).
+    // Not in the fp8 256x256 kernels with a row-major operand: they need 233 registers then, of which 224 leave room for the reduce
+    // beside them (16384 x 16384 x 2048: 694 us a call, 649 without)
     constexpr bool MID = M16 || (FP8 && FM * FN >= 4 && (BT || BM * BN < 256 * 256));
     static_assert(!MID || FM * FN >= 4, "the barrier comes behind a quarter of a step's MFMAs, and so behind one at least");
     static_assert(!M16 || (!FP8 && BN % 64 == 0), "16x16x32 MFMAs: bf16, panels of 128 bytes");

@@ -45,7 +45,7 @@ constexpr TileWaves tile_waves(int tile, bool fp8, bool bt, bool sk) {
 // of the accumulators for twice as long takes less of it: a loop of nothing else on random operands 1990 TFLOP/s at 2.03 GHz, of
 // 32x32x16 1730 at 1.76 (with 8-bit operands 16x16x128 4270 and 32x32x64 3890).  us a call, 32x32 / 16x16: 8192 x 3584 x 8192 all-gather 381
 // / 354 (k-contiguous 368 / 337), 8192 x 8192 x 3584 reduce-scatter 442 / 411, 4096 x 1792 x 4096 58.0 / 54.5, 1024 x 8192 x 3584 67.4 / 63.4.
-// The 128x128 and 128x64 tiles gain 1-2% (1512 x 1720 x 5120 38.8 / 38.1).  The smallest tiles are bound by their loads; the kernels with a
+// The 128x128 and 128x64 tiles gain up to 2% (296 x 7440 x 1088 16.6 / 16.3; 1512 x 1720 x 5120 37.9 / 38.0, nothing).  The smallest tiles are bound by their loads; the kernels with a
 // stream-K tail have no registers left for the second form's addresses.
 constexpr bool tile_m16(int tile, bool fp8, bool sk) { return !fp8 && !sk && tile < T64x64; }
 
