@@ -651,7 +651,7 @@ static RsRoute rs_route(const pk_plan& pl, int P, int rank, int64_t rows, int64_
                 rs_tile_space(pl, c, P, m_all, slot_cols, n_blks, cols, &tile_rows, &tile_cols);
                 const int tiles = tile_rows * tile_cols;
                 if (late && (tiles + 7) / 8 * 8 > grid) continue;
-                const int64_t cost = tile_cost(id, fp8, bt, tiles, (int)(pl.local_k >> (fp8 ? 7 : 6)), grid) + (late && !do_reduce ? 4000 * grid : 0);
+                const int64_t cost = tile_cost(id, fp8, bt, false, tiles, (int)(pl.local_k >> (fp8 ? 7 : 6)), grid) + (late && !do_reduce ? 4000 * grid : 0);
                 if (cost < best) {
                     best = cost;
                     r.t = c;
@@ -931,7 +931,7 @@ static AgRoute ag_route(const pk_plan& pl, int P, int64_t M, bool fp8, bool bt, 
     int64_t best = INT64_MAX;
     for (int id = 0; id < (k_chunks ? T32x64 : N_TILES); ++id) {
         bool span;
-        int64_t cost = tile_cost(id, fp8, bt, tiles_of(id, &span), ktiles, grid);
+        int64_t cost = tile_cost(id, fp8, bt, !k_chunks, tiles_of(id, &span), ktiles, grid);
         // Many rounds of fp8 tiles run at a lower clock than those the estimate was fitted to, and the largest tile loses least by
         // it: another one has to be a sixteenth better (6960 x 7728 x 4096: 128x256, estimated at 3% less than 256x256, takes 284
         // us for 210; 5000 x 5200 x 4096 129 for 109)

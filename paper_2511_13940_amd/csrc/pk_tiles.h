@@ -68,8 +68,15 @@ constexpr TileCost kTileCost[2][2][N_TILES] = {
      {{469, 1378, 8306}, {319, 719, 6483}, {388, 779, 4348}, {281, 423, 3949}, {210, 295, 2623}, {170, 217, 2498}, {150, 176, 1767}, {119, 151, 1343}}},
     {{{754, 1401, 6071}, {312, 766, 4820}, {399, 885, 2841}, {313, 472, 2616}, {277, 376, 1982}, {245, 295, 1913}, {196, 248, 1638}, {162, 220, 1349}},
      {{754, 1401, 6071}, {297, 802, 4372}, {304, 803, 4313}, {313, 472, 2616}, {277, 376, 1982}, {245, 295, 1913}, {196, 248, 1638}, {162, 220, 1349}}}};
-inline int64_t tile_cost(int tile, bool fp8, bool bt, int tiles, int kt, int grid) {
-    const TileCost& c = kTileCost[fp8 ? 1 : 0][bt ? 1 : 0][tile];
+// row_chunks: pk_ag_gemm.  The other calls fill the load ring anew behind the own column chunk or store more of a tile, which costs the 128x64
+// tiles of bf16 and a row-major operand more than the smaller 64x64 ones: 600 ns as fitted to 77 calls, in which the choice
+// between the two is 0.5% off on average with it and 7% without for pk_ag_gemm_k, 1.4% and 2.3% for the reduce-scatters, but 6% and
+// 0.2% for pk_ag_gemm.  us a call, 128x64 / 64x64: ag_gemm_k 180 x 1616 x 768 9.6 / 8.9, 50 x 472 x 512 8.69 / 7.72, gemm_ar 552 x 1400 x
+// 704 16.3 / 15.3; ag_gemm 384 x 2688 x 384 15% less.  Of 70 other calls that it moved 59 gained more than 1% and 5
+// lost as much (ag_gemm_k 853 x 824 x 512 7.8 -> 8.3; the others are two kernels in 10-15 us, bound by host time), 6% less on average.
+inline int64_t tile_cost(int tile, bool fp8, bool bt, bool row_chunks, int tiles, int kt, int grid) {
+    TileCost c = kTileCost[fp8 ? 1 : 0][bt ? 1 : 0][tile];
+    if (tile == T128x64 && !fp8 && !bt && !row_chunks) c.fixed += 600;
     const int rounds = (int)((((unsigned)tiles + 7) / 8 * 8 + grid - 1) / (unsigned)grid);
     return (int64_t)rounds * grid * (c.fixed + (int64_t)kt * c.lo) + (int64_t)kt * (c.hi - c.lo) * tiles;
 }

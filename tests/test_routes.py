@@ -83,6 +83,10 @@ def test_the_reduce_beside_a_gemm_is_the_narrow_one():
     ("gemm_rs_cols", 2, 793, 12992, 2 * 5952, "bf16", "kn", "256x256"),      # 134 us; as 128x128 152
     ("ag_gemm", 1, 3098, 6832, 256, "fp8", "kn", "128x256"),                 # 19.3 us; as 256x256 22.4
     ("ag_gemm_k", 8, 4914, 8 * 3984, 15360, "fp8", "kn", "256x128"),         # 277 us; as 128x256 315
+    ("ag_gemm_k", 4, 180, 6464, 768, "bf16", "kn", "64x64"),                 # 8.9 us; as 128x64 9.6
+    ("ag_gemm_k", 1, 42, 600, 960, "bf16", "kn", "64x64"),                   # 8.7 us; as 128x64 9.6
+    ("gemm_ar", 8, 552, 1400, 8 * 704, "bf16", "kn", "64x64"),               # 15.3 us; as 128x64 16.3
+    ("ag_gemm", 8, 384, 8 * 2688, 384, "bf16", "kn", "128x64"),              # as 64x64 15% more
 ])
 def test_the_faster_tile(op, P, M, N, K, dtype, layout, tile):
     """Calls that a tile shape measured far slower was estimated below the fastest one for."""
