@@ -1,11 +1,13 @@
-"""Builds libpk.so (the C-ABI library with the gfx950 kernels) in-tree with hipcc."""
+"""Builds libpk.so (the C-ABI library with the gfx950 kernels) and the CPython binding of its op calls in-tree with hipcc."""
 import os
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libpk.so")
+CALL_PATH = os.path.join(HERE, "_pk_call.so")
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = [os.path.join(CSRC, n) for n in ("pk_kernels.hip", "gemm_rs.hip", "gemm_rs16.hip", "gemm_ag.hip", "gemm_agk.hip")]
 HEADERS = [os.path.join(CSRC, n) for n in ("pk_device.h", "pk_gemm.h", "pk_tiles.h")] + [
@@ -39,6 +41,19 @@ def _run(cmd, verbose):
         raise RuntimeError("hipcc failed building libpk.so")
 
 
+def build_binding(verbose=False):
+    """Compile csrc/pk_call.cpp (host code only) against torch and libpk.so, which has to be there."""
+    import torch
+    from torch.utils import cpp_extension
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    include = [sysconfig.get_path("include")] + cpp_extension.include_paths("cuda")
+    _run([hipcc, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-isystem" + i for i in include] +
+         [os.path.join(CSRC, "pk_call.cpp"), "-L", HERE, "-l:libpk.so", "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-o", CALL_PATH], verbose)
+    return CALL_PATH
+
+
 C_LAUNCH_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi_launch.c")
 C_LAUNCH_LIB = os.path.join(os.path.dirname(HERE), "tests", "libc_abi_launch.so")
 
@@ -60,4 +75,5 @@ def build_c_launch_check():
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_binding(verbose=True))
     print(build_c_launch_check())

@@ -1,17 +1,23 @@
-"""ctypes binding of libpk.so: argument marshalling only.
+"""Binding of libpk.so: argument marshalling only.
 
 Every function has the name and argument order of its C entry point in
 include/pk.h.  Tensors are torch CUDA tensors (PyTorch is used for device
 memory and streams only); their data pointers are passed through unchanged.
-There is no fallback: if libpk.so has not been built, loading raises.
+The op calls go through the extension module _pk_call (csrc/pk_call.cpp) as
+long as their arguments are plain ints, tensors and names, everything else
+through ctypes.  There is no fallback: if libpk.so has not been built,
+loading raises.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpk.so")
+CALL_PATH = os.path.join(_HERE, "_pk_call.so")
 
 OK, ERR_NULL, ERR_SHAPE, ERR_DTYPE, ERR_ALIGN, ERR_RANK, ERR_ARG, ERR_HIP, ERR_TIMEOUT = range(9)
 BF16, FP8_E4M3 = 0, 1
@@ -96,6 +102,33 @@ def lib():
     return _lib
 
 
+def load_binding():
+    """The extension module of the op calls; raises if it has not been built."""
+    lib()
+    if not os.path.exists(CALL_PATH):
+        raise RuntimeError(f"{CALL_PATH} is missing: build it with `python -m paper_2511_13940_amd.build` "
+                           "(or __graft_entry__.build())")
+    loader = importlib.machinery.ExtensionFileLoader("_pk_call", CALL_PATH)
+    spec = importlib.util.spec_from_file_location("_pk_call", CALL_PATH, loader=loader)
+    module = importlib.util.module_from_spec(spec)
+    loader.exec_module(module)
+    return module
+
+
+class _Calls:
+    """The functions of the extension module, loaded at the first of them.  They return the call's status, or None, before they
+    have done anything, for arguments that are not of the plain kinds."""
+
+    def __getattr__(self, name):
+        module = load_binding()
+        for f in ("pk_gemm_rs", "pk_gemm_rs_cols", "pk_gemm_ar", "pk_ag_gemm", "pk_ag_gemm_static", "pk_ag_gemm_k"):
+            setattr(self, f, getattr(module, f))
+        return getattr(module, name)
+
+
+_calls = _Calls()
+
+
 def _ptr(t):
     if t is None:
         return None
@@ -153,11 +186,14 @@ def pk_ag_gemm_plan(P, M, N, K, dtype):
 def pk_gemm_rs(P, rank, M, N, K, dtype, A_local, B_local, scale_a, scale_b, partials, outgoing,
                flags_in, flags_out, epoch, out_shard, phases, status, timeout_us=0, stream=None, comm_cus=0,
                partial_dtype="f32", workspace=None, b_layout="kn"):
-    _check(lib().pk_gemm_rs(P, rank, M, N, K, _dt(dtype), _ptr(A_local), _ptr(B_local), _ptr(scale_a), _ptr(scale_b),
-                            _ptr(partials), _ptr(outgoing), _ptr(flags_in), _ptr(flags_out), epoch,
-                            _ptr(out_shard), phases, comm_cus, _pdt(partial_dtype), B_LAYOUTS[b_layout], _ptr(workspace),
-                            _nbytes(workspace),
-                            _ptr(status), timeout_us, _stream(stream)), "pk_gemm_rs")
+    st = _calls.pk_gemm_rs(P, rank, M, N, K, dtype, A_local, B_local, scale_a, scale_b, partials, outgoing, flags_in, flags_out,
+                           epoch, out_shard, phases, status, timeout_us, stream, comm_cus, partial_dtype, workspace, b_layout)
+    if st is None:
+        st = lib().pk_gemm_rs(P, rank, M, N, K, _dt(dtype), _ptr(A_local), _ptr(B_local), _ptr(scale_a), _ptr(scale_b),
+                              _ptr(partials), _ptr(outgoing), _ptr(flags_in), _ptr(flags_out), epoch, _ptr(out_shard), phases,
+                              comm_cus, _pdt(partial_dtype), B_LAYOUTS[b_layout], _ptr(workspace), _nbytes(workspace),
+                              _ptr(status), timeout_us, _stream(stream))
+    _check(st, "pk_gemm_rs")
 
 
 def pk_gemm_rs_cols_plan(P, M, N, K, dtype):
@@ -169,10 +205,13 @@ def pk_gemm_rs_cols_plan(P, M, N, K, dtype):
 def pk_gemm_rs_cols(P, rank, M, N, K, dtype, A_local, B_local, scale_a, scale_b, partials, outgoing,
                     flags_in, flags_out, epoch, out_shard, phases, status, timeout_us=0, stream=None, comm_cus=0,
                     partial_dtype="f32"):
-    _check(lib().pk_gemm_rs_cols(P, rank, M, N, K, _dt(dtype), _ptr(A_local), _ptr(B_local), _ptr(scale_a),
-                                 _ptr(scale_b), _ptr(partials), _ptr(outgoing), _ptr(flags_in), _ptr(flags_out), epoch,
-                                 _ptr(out_shard), phases, comm_cus, _pdt(partial_dtype), _ptr(status), timeout_us,
-                                 _stream(stream)), "pk_gemm_rs_cols")
+    st = _calls.pk_gemm_rs_cols(P, rank, M, N, K, dtype, A_local, B_local, scale_a, scale_b, partials, outgoing, flags_in,
+                                flags_out, epoch, out_shard, phases, status, timeout_us, stream, comm_cus, partial_dtype)
+    if st is None:
+        st = lib().pk_gemm_rs_cols(P, rank, M, N, K, _dt(dtype), _ptr(A_local), _ptr(B_local), _ptr(scale_a), _ptr(scale_b),
+                                   _ptr(partials), _ptr(outgoing), _ptr(flags_in), _ptr(flags_out), epoch, _ptr(out_shard),
+                                   phases, comm_cus, _pdt(partial_dtype), _ptr(status), timeout_us, _stream(stream))
+    _check(st, "pk_gemm_rs_cols")
 
 
 def pk_gemm_ar_plan(P, M, N, K, dtype):
@@ -184,27 +223,38 @@ def pk_gemm_ar_plan(P, M, N, K, dtype):
 def pk_gemm_ar(P, rank, M, N, K, dtype, A_local, B_local, scale_a, scale_b, partials, outgoing, flags_in, flags_out,
                out_full, bcast_out, ar_flags_in, ar_flags_out, epoch, phases, status, timeout_us=0, stream=None,
                comm_cus=0, partial_dtype="f32"):
-    _check(lib().pk_gemm_ar(P, rank, M, N, K, _dt(dtype), _ptr(A_local), _ptr(B_local), _ptr(scale_a), _ptr(scale_b),
-                            _ptr(partials), _ptr(outgoing), _ptr(flags_in), _ptr(flags_out), _ptr(out_full),
-                            _ptr(bcast_out), _ptr(ar_flags_in), _ptr(ar_flags_out), epoch, phases, comm_cus,
-                            _pdt(partial_dtype), _ptr(status), timeout_us, _stream(stream)), "pk_gemm_ar")
+    st = _calls.pk_gemm_ar(P, rank, M, N, K, dtype, A_local, B_local, scale_a, scale_b, partials, outgoing, flags_in, flags_out,
+                           out_full, bcast_out, ar_flags_in, ar_flags_out, epoch, phases, status, timeout_us, stream, comm_cus,
+                           partial_dtype)
+    if st is None:
+        st = lib().pk_gemm_ar(P, rank, M, N, K, _dt(dtype), _ptr(A_local), _ptr(B_local), _ptr(scale_a), _ptr(scale_b),
+                              _ptr(partials), _ptr(outgoing), _ptr(flags_in), _ptr(flags_out), _ptr(out_full), _ptr(bcast_out),
+                              _ptr(ar_flags_in), _ptr(ar_flags_out), epoch, phases, comm_cus, _pdt(partial_dtype), _ptr(status),
+                              timeout_us, _stream(stream))
+    _check(st, "pk_gemm_ar")
 
 
 def pk_ag_gemm(P, rank, M, N, K, dtype, A_gathered, B_local, scale_a, scale_b, chunk_flags, epoch,
                C_local, status, timeout_us=0, stream=None, comm_cus=0, act="none", workspace=None, b_layout="kn"):
-    _check(lib().pk_ag_gemm(P, rank, M, N, K, _dt(dtype), _ptr(A_gathered), _ptr(B_local), _ptr(scale_a),
-                            _ptr(scale_b), _ptr(chunk_flags), epoch, _ptr(C_local), comm_cus,
-                            ACTIVATIONS[act] if isinstance(act, str) else int(act), B_LAYOUTS[b_layout], _ptr(workspace),
-                            _nbytes(workspace),
-                            _ptr(status), timeout_us, _stream(stream)), "pk_ag_gemm")
+    st = _calls.pk_ag_gemm(P, rank, M, N, K, dtype, A_gathered, B_local, scale_a, scale_b, chunk_flags, epoch, C_local, status,
+                           timeout_us, stream, comm_cus, act, workspace, b_layout)
+    if st is None:
+        st = lib().pk_ag_gemm(P, rank, M, N, K, _dt(dtype), _ptr(A_gathered), _ptr(B_local), _ptr(scale_a), _ptr(scale_b),
+                              _ptr(chunk_flags), epoch, _ptr(C_local), comm_cus, ACTIVATIONS[act] if isinstance(act, str) else
+                              int(act), B_LAYOUTS[b_layout], _ptr(workspace), _nbytes(workspace), _ptr(status), timeout_us,
+                              _stream(stream))
+    _check(st, "pk_ag_gemm")
 
 
 def pk_ag_gemm_static(P, rank, M, N, K, dtype, A_gathered, B_local, scale_a, scale_b, chunk_flags, epoch,
                       C_local, status, timeout_us=0, stream=None, comm_cus=0, act="none"):
-    _check(lib().pk_ag_gemm_static(P, rank, M, N, K, _dt(dtype), _ptr(A_gathered), _ptr(B_local), _ptr(scale_a),
-                                   _ptr(scale_b), _ptr(chunk_flags), epoch, _ptr(C_local), comm_cus,
-                                   ACTIVATIONS[act] if isinstance(act, str) else int(act), _ptr(status),
-                                   timeout_us, _stream(stream)), "pk_ag_gemm_static")
+    st = _calls.pk_ag_gemm_static(P, rank, M, N, K, dtype, A_gathered, B_local, scale_a, scale_b, chunk_flags, epoch, C_local,
+                                  status, timeout_us, stream, comm_cus, act)
+    if st is None:
+        st = lib().pk_ag_gemm_static(P, rank, M, N, K, _dt(dtype), _ptr(A_gathered), _ptr(B_local), _ptr(scale_a),
+                                     _ptr(scale_b), _ptr(chunk_flags), epoch, _ptr(C_local), comm_cus, ACTIVATIONS[act] if
+                                     isinstance(act, str) else int(act), _ptr(status), timeout_us, _stream(stream))
+    _check(st, "pk_ag_gemm_static")
 
 
 def pk_ag_gemm_k_plan(P, M, N, K, dtype):
@@ -215,10 +265,13 @@ def pk_ag_gemm_k_plan(P, M, N, K, dtype):
 
 def pk_ag_gemm_k(P, rank, M, N, K, dtype, A_gathered, B_local, scale_a, scale_b, chunk_flags, epoch,
                  C_local, status, timeout_us=0, stream=None, comm_cus=0, act="none"):
-    _check(lib().pk_ag_gemm_k(P, rank, M, N, K, _dt(dtype), _ptr(A_gathered), _ptr(B_local), _ptr(scale_a),
-                              _ptr(scale_b), _ptr(chunk_flags), epoch, _ptr(C_local), comm_cus,
-                              ACTIVATIONS[act] if isinstance(act, str) else int(act), _ptr(status),
-                              timeout_us, _stream(stream)), "pk_ag_gemm_k")
+    st = _calls.pk_ag_gemm_k(P, rank, M, N, K, dtype, A_gathered, B_local, scale_a, scale_b, chunk_flags, epoch, C_local,
+                             status, timeout_us, stream, comm_cus, act)
+    if st is None:
+        st = lib().pk_ag_gemm_k(P, rank, M, N, K, _dt(dtype), _ptr(A_gathered), _ptr(B_local), _ptr(scale_a), _ptr(scale_b),
+                                _ptr(chunk_flags), epoch, _ptr(C_local), comm_cus, ACTIVATIONS[act] if isinstance(act, str) else
+                                int(act), _ptr(status), timeout_us, _stream(stream))
+    _check(st, "pk_ag_gemm_k")
 
 
 def _order(order):
