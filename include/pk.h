@@ -235,8 +235,10 @@ pk_status pk_gemm_rs_cols(int P, int rank, int64_t M, int64_t N, int64_t K, pk_d
  *   ar_flags_in   [P][ar_flags_per_slot], ar_flags_out likewise (NULL allowed when P == 1); flag b covers rows
  *                 [PK_AR_ROWS * (b / tiles_n), +PK_AR_ROWS) x columns of tile b % tiles_n of one row block.
  *
- * phases: PK_PHASE_GEMM | PK_PHASE_REDUCE as pk_gemm_rs; PK_PHASE_WAIT adds a kernel that waits (bounded) until all
- * of ar_flags_in has reached `epoch`, so that work queued behind this call on `stream` may read all of out_full.
+ * phases: PK_PHASE_GEMM | PK_PHASE_REDUCE as pk_gemm_rs; PK_PHASE_WAIT waits (bounded, from the end of the own reduce)
+ * until all of ar_flags_in has reached `epoch`, so that work queued behind this call on `stream` may read all of
+ * out_full: in the last workgroups of the reduce's launch, or, for more than 8192 flags of peers or without
+ * PK_PHASE_REDUCE, in a kernel of its own.
  * PK_PHASE_OVERLAP is not built for this call (PK_ERR_ARG).
  * Shape requirements, comm_cus, partial_dt, status and timeout_us as pk_gemm_rs.
  */

@@ -1,6 +1,7 @@
 // libpk: kernels other than the GEMM, and the C-ABI entry points (see include/pk.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -36,12 +37,38 @@ struct ReduceArgs {
     uint32_t* ar_flags_out;   // [P][ar_flags_per_slot]
     int64_t ar_flags_per_slot;
     int32_t rank;
+    int32_t n_items;          // workgroups that reduce; those behind them wait for the peers' rows (PK_PHASE_WAIT in the same launch)
 };
 
 // cache policy of the partial-slot loads: system-coherent (sc0 sc1) and streaming (nt).  The slots are written
 // by other workgroups / kernels (write-through) and announced through flags; loading them past this XCD's L2
 // makes an acquire fence (a whole-L2 invalidate per workgroup) unnecessary.
 constexpr int kCoherentStream = 1 | 2 | 16;
+
+// PK_PHASE_WAIT as part of the reduce's launch, by the last few workgroups of it: a launch of its own takes 2 us on the device (64 x 8192 x
+// 28672 over 8 ranks: 21.5 us a call, 19.8 so; 1024 x 8192 x 8192 36.5 and 35.1) and 4 us of host time.  They are dispatched when every workgroup that reduces is on its
+// way, so those never queue behind them.  Flags that are there at the first look are all there is to do; the own rows' need no look,
+// as the launch ends with them.  Otherwise the bound of the wait counts, as with a launch of its own, from the end of the own
+// reduce, which itself may wait that long.
+constexpr int kRowFlags = 4;                                 // flags that a thread looks at
+__device__ __forceinline__ void wait_for_rows(const ReduceArgs& r) {
+    const int64_t fps = r.ar_flags_per_slot, own = r.rank * fps, n = (r.P - 1) * fps;
+    const int64_t stride = (int64_t)(gridDim.x - r.n_items) * 256, first = (int64_t)(blockIdx.x - r.n_items) * 256 + threadIdx.x;
+    auto index = [&](int k) { return first + k * stride < own ? first + k * stride : first + k * stride + fps; };
+    bool late[kRowFlags], any = false;
+#pragma unroll
+    for (int k = 0; k < kRowFlags; ++k) {
+        late[k] = first + k * stride < n && !flag_ready(r.ar_flags_in + index(k), r.epoch);
+        any |= late[k];
+    }
+    if (!__syncthreads_or(any)) return;
+    const uint64_t twice = r.timeout_ticks >> 62 ? r.timeout_ticks : 2 * r.timeout_ticks;
+    for (int64_t i = first; i < fps; i += stride) flag_wait(r.ar_flags_in + own + i, r.epoch, twice);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRowFlags; ++k)
+        if (late[k] && !flag_wait(r.ar_flags_in + index(k), r.epoch, r.timeout_ticks)) report_timeout(r.status, (uint32_t)index(k), 3u);
+}
 
 // PT > 0: compile-time P; PT == 0: runtime P.  S16: the slots hold bf16.  AR: all-reduce mode (the reduced rows are also
 // pushed to the other ranks and announced).  NARROW: 4 output elements per thread and pass instead of 8 (one 16-byte load
@@ -50,6 +77,11 @@ template <int PT, bool S16, bool AR, bool NARROW = false>
 __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     const int tid = threadIdx.x;
     const int P = PT > 0 ? PT : r.P;
+    if constexpr (AR)
+        if ((int)blockIdx.x >= r.n_items) {
+            wait_for_rows(r);
+            return;
+        }
     const int tile = r.by_sub.div(blockIdx.x);
     const int sb = blockIdx.x - tile * r.by_sub.d;
     const int tmi = r.by_tiles_n.div(tile), tc = tile - tmi * r.tiles_n;
@@ -602,6 +634,7 @@ struct AllReduceOut {
     uint32_t* ar_flags_in;
     uint32_t* ar_flags_out;
     int64_t ar_flags_per_slot;
+    bool wait;                           // the peers' rows are still to be waited for; cleared by a launch that does
 };
 
 // Tile rows in the first part of an overlapped GEMM + reduce-scatter: the own block's rows rounded up to whole bands of 4, then as
@@ -693,7 +726,7 @@ static bool rs_takes_tail(const pk_plan& pl, const RsRoute& r, bool bt, bool bf1
 static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype dt,
                               const void* A_local, const void* B_local, const float* scale_a, const float* scale_b,
                               void* partials, void* outgoing, uint32_t* flags_in, uint32_t* flags_out,
-                              uint32_t epoch, void* out_shard, const AllReduceOut* ar, uint32_t phases, int comm_cus,
+                              uint32_t epoch, void* out_shard, AllReduceOut* ar, uint32_t phases, int comm_cus,
                               int partial_dt, bool cols, void* ws, size_t ws_bytes, uint32_t* status, uint64_t timeout_us,
                               void* stream, int b_layout = PK_B_ROW_MAJOR) {
     pk_plan pl;
@@ -858,7 +891,17 @@ static pk_status gemm_rs_impl(int P, int rank, int64_t M, int64_t N, int64_t K, 
             r.ar_flags_out = ar->ar_flags_out;
             r.ar_flags_per_slot = ar->ar_flags_per_slot;
         }
-        const int grid = (int)(pl.flags_per_slot * sub);   // one workgroup per work item
+        int grid = (int)(pl.flags_per_slot * sub);         // one workgroup per work item
+        r.n_items = grid;
+        if (ar && ar->wait) {
+            // up to eight more that wait for the peers' rows (wait_for_rows); a call with more flags than these look at takes several
+            // times as long and a launch of its own for the wait
+            const int64_t n = (P - 1) * ar->ar_flags_per_slot;
+            if (n <= 8 * 256 * kRowFlags) {
+                grid += (int)std::min<int64_t>(8, ceil_div(n, 256));
+                ar->wait = false;
+            }
+        }
         hipStream_t s = reduce_stream;
         auto launch = [&](auto s16, auto armode) {
             constexpr bool S16 = decltype(s16)::value, AR = decltype(armode)::value;
@@ -1101,7 +1144,7 @@ pk_status pk_gemm_ar(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype 
     pk_status st = pk_gemm_ar_plan(P, M, N, K, dt, &pl);
     if (st != PK_OK) return st;
     if (rank < 0 || rank >= P) return PK_ERR_RANK;
-    AllReduceOut ar = {(uint16_t*)bcast_out, ar_flags_in, ar_flags_out, pl.ar_flags_per_slot};
+    AllReduceOut ar = {(uint16_t*)bcast_out, ar_flags_in, ar_flags_out, pl.ar_flags_per_slot, (phases & PK_PHASE_WAIT) != 0};
     if (phases & PK_PHASE_ALL) {
         // the reduce phase writes rows R_rank of out_full
         uint16_t* own_rows = (uint16_t*)out_full + (int64_t)rank * (M / P) * N;
@@ -1110,7 +1153,7 @@ pk_status pk_gemm_ar(int P, int rank, int64_t M, int64_t N, int64_t K, pk_dtype 
                           timeout_us, stream);
         if (st != PK_OK) return st;
     }
-    if (phases & PK_PHASE_WAIT) {
+    if (ar.wait) {
         const int64_t n_flags = (int64_t)P * pl.ar_flags_per_slot;
         hipLaunchKernelGGL(ar_wait_kernel, dim3((unsigned)ceil_div(n_flags, 256)), dim3(256), 0, (hipStream_t)stream,
                            (const uint32_t*)ar_flags_in, n_flags, epoch, status, timeout_ticks(timeout_us));

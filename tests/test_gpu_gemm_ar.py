@@ -160,3 +160,21 @@ def test_missing_row_block_times_out_instead_of_hanging():
     got = codec.bf16_decode(res["full_bits"].reshape(P, M // P, N)[rank])
     assert gate_err(got, ref["out"]) <= GATE["bf16"]
     assert np.all(res["ar_out"][1] == 5)
+
+
+# the wait for the peers' rows as the last workgroups of the reduce's launch: one of them, several, all eight with four flags a thread;
+# and more flags than that, a launch of its own (flags per slot: 1, 128, 7936, 8246)
+@pytest.mark.parametrize("P,M,N", [(2, 16, 128), (8, 64, 16384), (2, 2048, 7936), (2, 2128, 7936)])
+@pytest.mark.parametrize("last_rank", [False, True])
+def test_every_row_block_of_the_peers_is_waited_for(P, M, N, last_rank):
+    rank, K = (P - 1 if last_rank else 0), P * 64
+    inp = wl.gemm_rs_inputs(P, M, N, K, "bf16", rank, seed=3)
+    peer = peer_rows_for(P, M // P, N, seed=2)
+    run = lambda **kw: hz.run_gemm_ar(P, rank, M, N, K, "bf16", inp["A_local"], inp["B_local"], inp["partials"], peer, epoch=9, **kw)
+    base = run()
+    assert base["status"][0] == 0
+    afps = base["plan"].ar_flags_per_slot
+    for q, b in {((rank + 1) % P, 0), ((rank + P - 1) % P, afps - 1)}:
+        res = run(withhold_rows=(q, b), timeout_us=1000)
+        assert tuple(res["status"][:3]) == (pk.ERR_TIMEOUT, q * afps + b, 3)
+        assert np.array_equal(res["full_bits"], base["full_bits"])          # the own rows are reduced all the same
