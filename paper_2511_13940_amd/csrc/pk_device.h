@@ -58,15 +58,17 @@ __device__ __forceinline__ void report_timeout(uint32_t* status, uint32_t index,
     }
 }
 
-// 16-byte-per-lane direct-to-LDS load: lane l's 16 bytes from (sbase + voff) land at LDS byte address lds_addr + 16*l.
+// 16-byte-per-lane direct-to-LDS load: lane l's 16 bytes from (sbase + voff) land at LDS byte address lds_addr + imm + 16*l.  `imm` is
+// a constant once the caller is unrolled: with the sum in one operand the compiler computes the address of every load of the ring ahead
+// of the loop over the tiles and keeps them all, 15 to 60 scalar registers (see `fetched` in pk_gemm.h for what that costs).
 // Written as inline assembly on purpose: for the builtin form the compiler cannot tell which LDS bytes the load
 // writes and makes every later LDS read wait for it (vmcnt(0)), which serialises the pipeline.  The kernel waits
 // for these loads itself (s_waitcnt vmcnt + workgroup barrier) before any wave reads what they wrote.
-__device__ __forceinline__ void dma_load16(const char* sbase, uint32_t voff, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+__device__ __forceinline__ void dma_load16(const char* sbase, uint32_t voff, uint32_t lds_addr, int imm) {
+    asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
-                 : "s"(lds_addr), "v"(voff), "s"(sbase)
-                 : "m0");
+                 : "s"(lds_addr), "v"(voff), "s"(sbase), "i"(imm)
+                 : "m0", "scc");
 }
 
 // 16-byte store that writes through to memory (system-coherent cache policy, streaming).  Together with an

@@ -143,8 +143,12 @@ constexpr int kWaitLgkm0 = waitcnt_vm_lgkm0(63);   // vmcnt as high as it goes: 
 // 4100 cycles from the start to the main loop, 3100 so).
 // FETCH_BLOCK: as one block, between the loads of which the compiler can put nothing else (256x256 tiles, 5600 x 2064 x 320 all-gather:
 // 17.0 us a call, 16.7 so).  FETCH_FIRST: ahead of every other use of an argument too; each is then loaded where it is used, from the
-// scalar cache, and none takes a register through the main loops.  us a call, FETCH_BLOCK / FETCH_FIRST: all-gather, 128x256 tiles,
+// scalar cache, and none takes a register (or, with a hundred scalar registers in use, a lane of a vector register) through the main
+// loops.  us a call, FETCH_BLOCK / FETCH_FIRST: all-gather, 128x256 tiles,
 // 2048 x 4096 x 512 13.15 / 12.79, 256x128, 4176 x 1568 x 13248 150.3 / 148.4; column chunks, 256x256, 11347 x 1144 x 1024 34.4 / 33.3.
+// For every kernel below 256x256, with the LDS addresses of dma_load16, over 128 calls drawn evenly over the tiles: 1.5% less on average, 2% for
+// 256x128 (1024 x 8192 x 3584 reduce-scatter 59.4 / 58.2), 2-6% for the small ones.  The arguments of the tile mapping as one block of
+// 192 bytes per tile, so that they come in together, was half a percent slower than one by one: the registers it takes.
 // Not with stores on their way through the next main loop (256x256 all-gather, 13176 x 872 x 704 28.3 / 29.6).
 enum Fetch { FETCH_PLAIN, FETCH_BLOCK, FETCH_FIRST };
 template <Fetch HOW>
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     // nothing in registers through the main loops that can be computed anew (own_lane, report_late, `fetched`): 220-223 otherwise.  Those
     // with a stream-K tail leave none either way (16640 x 1024 x 4096 296 us a call so, 286 without).
     constexpr bool TIGHT = !IS_RS && !FP8 && !SK && BM * BN >= 256 * 128;
-    constexpr Fetch FETCH = !TIGHT ? FETCH_PLAIN : EPI == EPI_AGK || BM * BN < 256 * 256 ? FETCH_FIRST : FETCH_BLOCK;
+    constexpr Fetch FETCH = SK ? FETCH_PLAIN : BM * BN < 256 * 256 || (TIGHT && EPI == EPI_AGK) ? FETCH_FIRST : TIGHT ? FETCH_BLOCK : FETCH_PLAIN;
     const GemmArgs& g = fetched<FETCH>(args);
 
     const int tid = threadIdx.x;
@@ -495,9 +499,14 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
 
     // chunks of A known to have landed (the own one, and those this workgroup has waited for): EPI_AG, EPI_AGK
     // workgroup 0 reports how long it ran, in ticks of the 100 MHz wall clock and in core-clock cycles, and how many of
-    // those cycles its main loops took: status[4..7] (the ratio of the first two is the clock the chip held)
-    const uint64_t t_wall0 = wall_clock64(), t_core0 = clock64();
-    uint64_t t_loops = 0;
+    // those cycles its main loops took: status[4..7] (the ratio of the first two is the clock the chip held).  The others read no
+    // clocks: each reading is waited for (a quarter of a percent of the calls of `fetched`'s comment)
+    const bool reports = blockIdx.x == 0;
+    uint64_t t_wall0 = 0, t_core0 = 0, t_loops = 0;
+    if (reports) {
+        t_wall0 = wall_clock64();
+        t_core0 = clock64();
+    }
     uint32_t n_tiles_done = 0;
     uint64_t seen_chunks = 1ull << (g.rank & 63);
     const uint64_t all_chunks = g.n_chunks >= 64 ? ~0ull : (1ull << g.n_chunks) - 1;
@@ -745,14 +754,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
         }
         // load number i (0 .. NL-1) of this wave for the next k-tile to fetch, into LDS stage `stage`
-        const uint32_t lds_base = (uint32_t)(uintptr_t)ring;
+        const uint32_t lds_wave = (uint32_t)(uintptr_t)ring + wl * 1024;
         // k-tiles of this wave: all, or (a ring of its own) every WK-th from the wk-th on
         const int my_ktiles = PRIV ? (seg_ktiles - wk + WK - 1) / WK : seg_ktiles;
         constexpr int STRIDE = PRIV ? WK : 1;
-        auto issue_load = [&](int stage, int i) {
-            const uint32_t sa = lds_base + stage * STAGE + wl * 1024;
-            if (i < NA) dma_load16(a_base, a_voff[i], sa + i * NWL * 1024);
-            else dma_load16(b_base, b_voff[i - NA], sa + A_BYTES + (i - NA) * NWL * 1024);
+        auto issue_load_at = [&](uint32_t sa, int imm, int i) {
+            if (i < NA) dma_load16(a_base, a_voff[i], sa, imm + i * NWL * 1024);
+            else dma_load16(b_base, b_voff[i - NA], sa, imm + A_BYTES + (i - NA) * NWL * 1024);
             if (i == NL - 1) {
                 a_base += KB * STRIDE;
                 b_base += b_step * STRIDE;
@@ -763,9 +771,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 }
             }
         };
+        auto issue_load = [&](int stage, int i) { issue_load_at(lds_wave + stage * STAGE, 0, i); };
+        // all of a k-tile's, into stage number `stage` (a constant)
         auto issue_loads = [&](int stage) {
 #pragma unroll
-            for (int i = 0; i < NL; ++i) issue_load(stage, i);
+            for (int i = 0; i < NL; ++i) issue_load_at(lds_wave, stage * STAGE, i);
         };
         // the LDS stages are free here: every wave passed the last barrier of the previous tile's loop
         // after its final fragment reads were issued and waited for
@@ -1257,7 +1267,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 if (KB == 128 && kt < nkt) ktile(kt, nkt, F{}, E{}, F{}, F{});
             }
         };
-        const uint64_t t_loop0 = clock64();
+        if (reports) t_loops -= clock64();
         const int n_seg = by_chunk ? g.n_chunks : 1;
 #pragma clang loop unroll(disable)
         for (int sgm = 0; sgm < n_seg; ++sgm) {
@@ -1328,7 +1338,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             __syncthreads();                                 // the next tile's loads may fill the ring
         }
 
-        t_loops += clock64() - t_loop0;
+        if (reports) t_loops += clock64();
         ++n_tiles_done;
         p_dead = false;
         p_kind = kind;
@@ -1350,7 +1360,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         __syncthreads();
         signal_prev();
     }
-    if (blockIdx.x == 0 && first_thread()) {
+    if (reports && first_thread()) {
         g.status[4] = (uint32_t)(wall_clock64() - t_wall0);
         g.status[5] = (uint32_t)(clock64() - t_core0);
         g.status[6] = (uint32_t)t_loops;
