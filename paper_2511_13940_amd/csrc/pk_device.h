@@ -81,8 +81,15 @@ __device__ __forceinline__ void store16_writethrough(void* p, i32x4 v) {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 
+__device__ __forceinline__ void store8_writethrough(void* p, i32x2 v) {
+    asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1 nt" : : "v"(p), "v"(v) : "memory");
+}
+
 // The same for data that only later kernels read: streaming, write-back.  An assembly block as well, so that a kernel that
 // counts its outstanding loads and stores knows their order.
+__device__ __forceinline__ void store8_stream(void* p, i32x2 v) {
+    asm volatile("global_store_dwordx2 %0, %1, off nt" : : "v"(p), "v"(v) : "memory");
+}
 __device__ __forceinline__ void store16_stream(void* p, i32x4 v) {
     asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }

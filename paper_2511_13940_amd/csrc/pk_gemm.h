@@ -17,7 +17,8 @@
 // The operands are passed to the MFMA swapped (B fragment first), which leaves each lane with four
 // consecutive columns of one row; the epilogue transposes through a 32 KB LDS staging area so that global
 // stores are 16 bytes per lane over whole row segments of the wave's sub-tile.  The epilogue of tile t runs
-// after the first loads of tile t+1 have been issued.
+// after the first loads of tile t+1 have been issued.  Tiles below 256x256, most of them (ROWX), leave behind their own
+// main loop instead, all at once through the LDS of the ring.
 //
 // Roles of the paper's program template (section 3.2.3, appendix D): the direct-to-LDS loads are the
 // loader, the MFMA loop the consumer, the epilogue the storer; the epilogue of the reduce-scatter mode
@@ -218,12 +219,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     static_assert(!SPREAD || MID, "built for the order of reads and loads that goes with the barrier in the step");
     constexpr int EPI_OFF = RINGS * NS * STAGE;          // LDS offset of the epilogue staging area
     constexpr int EPI_BYTES = epi_stage_bytes<BM, BN, KB, RINGS * NS>();
-    // WK > 1: the groups' accumulators are summed at the end of a tile and shared out, OTM x OTN blocks to each wave of the
-    // first NOWN groups
-    constexpr int OB = TM * TN >= WK ? TM * TN / WK : 1, NOWN = TM * TN / OB;
+    // WK > 1 (and not ROWX): the groups' accumulators are summed at the end of a tile and shared out, OTM x OTN blocks to each wave
+    constexpr int OB = TM * TN >= WK ? TM * TN / WK : 1;
     constexpr int OTM = OB >= TN ? OB / TN : 1, OTN = OB >= TN ? TN : OB;
-    static_assert(NOWN <= WK && OB * NOWN == TM * TN && OTM * OTN == OB, "the blocks of a wave's sub-tile are shared out evenly");
-    static_assert(WK == 1 || (!SK && WM * WN * NOWN * (WK - 1) * OB * 4096 <= gemm_lds_bytes<BM, BN, KB, RINGS * NS>()), "the exchange fits the LDS");
+    // ROWX: a tile leaves behind its own main loop, row by row (see there), and not under the first loads of the next one through
+    // the staging area: in one wave of four for the 32x32 tile, in up to sixteen passes for others, of which a small call saw every latency.
+    // All tiles up to 128x128: 2-10% less a call for 32-row tiles (64 x 3584 x 8192 SiLU 25.0 -> 24.0 us, 44 x 3840 x 1152 fp8 5.40 ->
+    // 4.81), 1-4% for 64x64, 1-3% for 128x64 and 128x128.  Of 256x128 and 128x256 where it was the faster one over 140 calls: fp32 slots (256x128 1-2%
+    // less, fp8 5%), all-gathers (fp8 and 128x256: 1% less, 3-6% with an activation; not bf16 256x128, which has no register left for it);
+    // not bf16 slots (0-6% more) and fp8 128x256 with a row-major operand (2% more).  256x256 tiles run many rounds and keep the
+    // stores under the next main loop.
+    constexpr bool ROWX = BM * BN <= 128 * 128 || (BM * BN == 256 * 128 && EPI != EPI_RS16 &&
+                                                   (FP8 ? BM == 256 || BT : EPI == EPI_RS || BM == 128));
+    static_assert(ROWX || (OB * WK == TM * TN && OTM * OTN == OB), "the blocks of a wave's sub-tile are shared out evenly");
+    static_assert(ROWX || WK == 1 || (!SK && WM * WN * WK * (WK - 1) * OB * 4096 <= gemm_lds_bytes<BM, BN, KB, RINGS * NS>()), "the exchange fits the LDS");
     static_assert(KB == 64 || KB == 128, "k-tile is 64 or 128 bytes of A row");
     static_assert(KS >= 1, "a k-tile holds at least one MFMA k-step");
     static_assert(CPR >= 2 && RPI >= 1, "tile too narrow");
@@ -478,6 +487,28 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
         if (g.act == PK_ACT_SILU) smooth(std::true_type{});
         else smooth(std::false_type{});
         return o;
+    };
+
+    // destination of row r, column c of a tile: dst + r * pitch + c * OUT_ELEM, + own_delta for rows own_row0 .. own_row0 + own_rows - 1.
+    // Scatter along rows: shard q's slot lies behind those of the shards before it, so row r of the product is row r of
+    // `outgoing` (of `partials` if it is own).  Along the last dimension: the tile goes to rank q.
+    auto destination = [&](int q, uint64_t& dst, int64_t& pitch, int64_t& own_delta, int& own_row0, int& own_rows) {
+        pitch = (int64_t)g.n * OUT_ELEM;
+        own_delta = 0;
+        own_row0 = own_rows = 0;
+        if constexpr (IS_RS) {
+            if (g.cols_per_shard > 0) {
+                pitch = (int64_t)g.cols_per_shard * OUT_ELEM;
+                dst = (uint64_t)(q == g.rank ? g.partials : g.outgoing) + (int64_t)q * (g.slot_elems - g.cols_per_shard) * OUT_ELEM;
+            } else {
+                dst = (uint64_t)g.outgoing;
+                own_delta = (int64_t)((uint64_t)g.partials - (uint64_t)g.outgoing);
+                own_row0 = g.rank * g.rows_per_shard;
+                own_rows = g.rows_per_shard;
+            }
+        } else {
+            dst = (uint64_t)g.C;
+        }
     };
 
     auto signal_prev = [&]() {   // paper appendix C `signal` for the tile whose stores have completed
@@ -861,7 +892,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             const uint64_t t0 = wall_clock64(), gap = (uint64_t)g.store_gap * ((blockIdx.x >> 3) & 7);
             while (wall_clock64() - t0 < gap) __builtin_amdgcn_s_sleep(2);
         }
-        if (p_q >= 0 && !skip_epilogue && (NOWN == WK || wk < NOWN)) {
+        if (!ROWX && p_q >= 0 && !skip_epilogue) {
             // lane holds, for each 32x32 block, four quads of columns (see `quad`).  Per pass a slab of
             // ROWS_PASS rows of the wave's part of the tile goes through the wave's private staging area, then out as whole
             // row segments, 16 bytes per lane.  The passes are a loop, not unrolled, around one read-back: a workgroup runs
@@ -871,25 +902,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             PK_LDS char* stg = lds + EPI_OFF + w * (EPI_BYTES / NW);
             const int row_w0 = p_row0 + wm * (BM / WM) + (wk * OB / TN) * 32;
             const int col_w0 = p_col0 + wn * (BN / WN) + (wk * OB % TN) * 32;
-            // destination of row r, column c: dst + r * dst_pitch + c * OUT_ELEM.  Scatter along rows: shard q's slot lies
-            // behind those of the shards before it, so row r of the product is row r of `outgoing` (of `partials` if it is own)
             uint64_t dst;
-            int64_t own_delta = 0;
-            int64_t dst_pitch = (int64_t)g.n * OUT_ELEM;
-            int own_row0 = 0, own_rows = 0;
-            if constexpr (IS_RS) {
-                if (g.cols_per_shard > 0) {
-                    dst_pitch = (int64_t)g.cols_per_shard * OUT_ELEM;
-                    dst = (uint64_t)(p_q == g.rank ? g.partials : g.outgoing) + (int64_t)p_q * (g.slot_elems - g.cols_per_shard) * OUT_ELEM;
-                } else {
-                    dst = (uint64_t)g.outgoing;
-                    own_delta = (int64_t)((uint64_t)g.partials - (uint64_t)g.outgoing);
-                    own_row0 = g.rank * g.rows_per_shard;
-                    own_rows = g.rows_per_shard;
-                }
-            } else {
-                dst = (uint64_t)g.C;
-            }
+            int64_t own_delta, dst_pitch;
+            int own_row0, own_rows;
+            destination(p_q, dst, dst_pitch, own_delta, own_row0, own_rows);
             // FULL: the tile lies inside the matrix and goes to one buffer, so no store is predicated and a wave issues exactly
             // EPI_STORES of them (fp32 slots: and its rows start on 128-byte lines).
             constexpr bool BIG = BM * BN == 256 * 256 && !SK;    // shapes that run many rounds
@@ -1304,14 +1320,98 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
             run_ktiles(my_ktiles);
         }
-        if constexpr (WK > 1) {
+        if constexpr (ROWX) {
+            // Every wave lays its accumulators down row by row (the ring is free; a wave with a ring of its own has it to itself), and of the
+            // WK waves that share a sub-tile each adds up a share of its rows, in group order, and stores them: whole row segments straight
+            // out of registers, all waves at work.  Where the LDS does not hold all of them at once, in HP turns.
+            constexpr int HP = BM * BN * WK * 4 > 160 * 1024 ? 2 : 1;
+            constexpr int SR = BM / WM / HP, SC = BN / WN;   // the sub-tile
+            constexpr int CH = SC / 4;                       // 16-byte chunks per row
+            constexpr int RI = 64 / CH, NI = SR / WK / RI;   // rows of a wave-wide access, accesses to a wave's share
+            static_assert((CH == 8 || CH == 16) && NI * RI * WK == SR && TM % HP == 0, "rows of 128 or 256 bytes, shared out evenly");
+            constexpr int PART = PRIV ? NS * STAGE : SR * SC * 4;      // bytes from one wave's sums to the next one's
+            static_assert(SR * SC * 4 <= PART && WM * WN * WK * PART <= gemm_lds_bytes<BM, BN, KB, RINGS * NS>(), "the sums fit the LDS");
+            PK_LDS char* sums = lds + (PRIV ? 0 : (w % (WM * WN)) * WK * PART);
+            const int lane = lt;
+            // the chunks of a row trade places so that 16 lanes, of a column or of a row, lie in different banks
+            auto at = [](int r, int ch) { return r * (SC * 4) + ((ch ^ (CH == 8 ? (r & 7) ^ ((r >> 3) & 1) : r & 15)) * 16); };
+            uint64_t dst;
+            int64_t own_delta, dst_pitch;
+            int own_row0, own_rows;
+            destination(q, dst, dst_pitch, own_delta, own_row0, own_rows);
+            const int r0 = wk * (SR / WK) + lane / CH, ch = lane % CH;
+            auto sum = [&](int i) -> f32x4 {
+                f32x4 x = *(PK_LDS f32x4*)(sums + at(r0 + i * RI, ch));
+#pragma unroll
+                for (int from = 1; from < WK; ++from) x += *(PK_LDS f32x4*)(sums + from * PART + at(r0 + i * RI, ch));
+                if constexpr (FP8) x = f32x4{x[0] * scale, x[1] * scale, x[2] * scale, x[3] * scale};
+                return x;
+            };
+            const int col = col0 + wn * SC + ch * 4;
+            int row_w0 = row0 + wm * (BM / WM) + r0;
+            auto put = [&](int i, auto x) {
+                const int row = row_w0 + i * RI;
+                if (row >= row_end || col >= col_end) return;
+                uint64_t d = dst + (int64_t)row * dst_pitch + (int64_t)col * OUT_ELEM;
+                if (IS_RS && (uint32_t)(row - own_row0) < (uint32_t)own_rows) d += own_delta;
+                // reduce-scatter tiles are consumed by another kernel through a flag: write through
+                if constexpr (EPI == EPI_RS) store16_writethrough((void*)d, __builtin_bit_cast(i32x4, x));
+                else if constexpr (EPI == EPI_RS16) store8_writethrough((void*)d, __builtin_bit_cast(i32x2, x));
+                else store8_stream((void*)d, __builtin_bit_cast(i32x2, x));
+            };
+#pragma unroll
+            for (int hp = 0; hp < HP; ++hp) {
+                if (hp > 0) {
+                    __syncthreads();                         // the sums of the turn before have been read
+                    row_w0 += SR;
+                }
+#pragma unroll
+                for (int ti = 0; ti < TM / HP; ++ti)
+#pragma unroll
+                    for (int tj = 0; tj < TN; ++tj)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const int r = 32 * ti + (M16 ? 16 * (b >> 1) + (lane & 15) : lane & 31);
+                            const int ch = 8 * tj + (M16 ? 4 * (b & 1) + (lane >> 4) : 2 * b + (lane >> 5));
+                            *(PK_LDS f32x4*)(sums + wk * PART + at(r, ch)) = quad(hp * (TM / HP) + ti, tj, b);
+                        }
+                if constexpr (WK > 1) __syncthreads();
+                bool stored = false;
+                if constexpr (!IS_RS) {
+                    if (g.act != PK_ACT_NONE) {
+                        stored = true;
+#pragma clang loop unroll(disable)
+                        for (int i = 0; i < NI; i += 2) {
+                            const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+                            const bf16x8 o = activate8(sum(i), NI > 1 ? sum(i + 1) : none);
+                            put(i, __builtin_shufflevector(o, o, 0, 1, 2, 3));
+                            if constexpr (NI > 1) put(i + 1, __builtin_shufflevector(o, o, 4, 5, 6, 7));
+                        }
+                    }
+                }
+                if (!stored) {
+                    constexpr int NX = NI < 8 ? NI : 8;          // at once
+#pragma clang loop unroll(disable)
+                    for (int i0 = 0; i0 < NI; i0 += NX) {
+                        f32x4 x[NX];
+#pragma unroll
+                        for (int i = 0; i < NX; ++i) x[i] = sum(i0 + i);
+#pragma unroll
+                        for (int i = 0; i < NX; ++i) {
+                            if constexpr (EPI == EPI_RS) put(i0 + i, x[i]);
+                            else put(i0 + i, bf16x4{(__bf16)x[i][0], (__bf16)x[i][1], (__bf16)x[i][2], (__bf16)x[i][3]});
+                        }
+                    }
+                }
+            }
+            __syncthreads();                                 // the next tile's loads may fill the ring
+        } else if constexpr (WK > 1) {
             // The groups' accumulators are added in group order through the LDS (the ring is free: every wave passed the barrier
             // of the last k-tile after its last fragment reads).  Group r ends up with blocks [r*OB, (r+1)*OB) of the sub-tile,
             // in acc[0..OTM)[0..OTN).
-            if constexpr (PRIV) __syncthreads();             // every wave is through with its ring
             const int sub = w % (WM * WN), lane = own_lane();
             auto piece = [&](int from, int to, int i) {      // LDS address of block i of those that group `from` hands to group `to`
-                return lds + ((((sub * NOWN + to) * (WK - 1) + (from < to ? from : from - 1)) * OB + i) * 4096) + lane * 16;
+                return lds + ((((sub * WK + to) * (WK - 1) + (from < to ? from : from - 1)) * OB + i) * 4096) + lane * 16;
             };
 #pragma unroll
             for (int gr = 0; gr < WK; ++gr)
@@ -1326,7 +1426,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
                 }
             __syncthreads();
 #pragma unroll
-            for (int gr = 0; gr < NOWN; ++gr)
+            for (int gr = 0; gr < WK; ++gr)
                 if (wk == gr) {
 #pragma unroll
                     for (int i = 0; i < OB; ++i)
