@@ -1320,6 +1320,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             }
             run_ktiles(my_ktiles);
         }
+        if (reports) t_loops += clock64();
         if constexpr (ROWX) {
             // Every wave lays its accumulators down row by row (the ring is free; a wave with a ring of its own has it to itself), and of the
             // WK waves that share a sub-tile each adds up a share of its rows, in group order, and stores them: whole row segments straight
@@ -1444,7 +1445,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
             __syncthreads();                                 // the next tile's loads may fill the ring
         }
 
-        if (reports) t_loops += clock64();
         ++n_tiles_done;
         p_dead = false;
         p_kind = kind;
