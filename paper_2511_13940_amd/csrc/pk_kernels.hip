@@ -45,11 +45,11 @@ struct ReduceArgs {
 // makes an acquire fence (a whole-L2 invalidate per workgroup) unnecessary.
 constexpr int kCoherentStream = 1 | 2 | 16;
 
-// PK_PHASE_WAIT as part of the reduce's launch, by the last few workgroups of it: a launch of its own takes 2 us on the device (64 x 8192 x
-// 28672 over 8 ranks: 21.5 us a call, 19.8 so; 1024 x 8192 x 8192 36.5 and 35.1) and 4 us of host time.  They are dispatched when every workgroup that reduces is on its
-// way, so those never queue behind them.  Flags that are there at the first look are all there is to do; the own rows' need no look,
-// as the launch ends with them.  Otherwise the bound of the wait counts, as with a launch of its own, from the end of the own
-// reduce, which itself may wait that long.
+// PK_PHASE_WAIT as part of the reduce's launch, by the last few workgroups of it: a launch of its own takes 2 us on the device (64 x
+// 8192 x 28672 over 8 ranks: 21.5 us a call, 19.8 so; 1024 x 8192 x 8192 36.5 and 35.1) and 4 us of host time.  They are dispatched when
+// every workgroup that reduces on their XCD is on its way, so those never queue behind them.  Flags that are there at the first look
+// are all there is to do; the own rows' need no look, as the launch ends with them.  Otherwise the bound of the wait counts, as with a
+// launch of its own, from the end of the own reduce: each of these workgroups looks at all the own flags first.
 constexpr int kRowFlags = 4;                                 // flags that a thread looks at
 __device__ __forceinline__ void wait_for_rows(const ReduceArgs& r) {
     const int64_t fps = r.ar_flags_per_slot, own = r.rank * fps, n = (r.P - 1) * fps;
@@ -62,8 +62,22 @@ __device__ __forceinline__ void wait_for_rows(const ReduceArgs& r) {
         any |= late[k];
     }
     if (!__syncthreads_or(any)) return;
-    const uint64_t twice = r.timeout_ticks >> 62 ? r.timeout_ticks : 2 * r.timeout_ticks;
-    for (int64_t i = first; i < fps; i += stride) flag_wait(r.ar_flags_in + own + i, r.epoch, twice);
+    // A workgroup of the reduce either publishes its flag or reports in `status` that it gave up.  The latter is believed after one bound
+    // (`status` may hold an older report), and nothing is waited for longer than the reduce can take with 64 workgroups at a time,
+    // those of eight compute units.
+    const uint64_t t0 = wall_clock64();
+    const uint64_t rounds = (uint64_t)(r.n_items / 64 + 1);
+    const uint64_t most = r.timeout_ticks > ~0ull / rounds ? ~0ull : rounds * r.timeout_ticks;
+    auto given_up = [&] {
+        const uint64_t t = wall_clock64() - t0;
+        return t > r.timeout_ticks && (t > most || __hip_atomic_load(r.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
+    };
+    bool wait = true;
+    for (int64_t i = threadIdx.x; i < fps && wait; i += 256)
+        while (wait && !flag_ready(r.ar_flags_in + own + i, r.epoch)) {
+            __builtin_amdgcn_s_sleep(8);
+            wait = !given_up();
+        }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kRowFlags; ++k)

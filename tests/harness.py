@@ -2,6 +2,7 @@
 downloads the results.  No arithmetic of the method happens here."""
 import collections
 import ctypes
+import time
 
 import numpy as np
 import torch
@@ -212,7 +213,7 @@ def run_ag_gemm(P, rank, M, N, K, dtype, chunks, B_bits, scale_a=None, scale_b=N
 
 def run_gemm_ar(P, rank, M, N, K, dtype, A_bits, B_bits, partials, peer_rows, scale_a=None, scale_b=None, epoch=1,
                 deliver="pre", order=None, gap_us=0, timeout_us=0, phases=pk.PHASE_ALL | pk.PHASE_WAIT,
-                withhold_rows=None, partial_dtype="f32"):
+                withhold_rows=None, partial_dtype="f32", before=None, meanwhile=None, stream=None):
     """One pk_gemm_ar call.  partials as run_gemm_rs; peer_rows: numpy [P][M/P][N] uint16, block q != rank is what
     rank q hands out for rows R_q of out_full.
 
@@ -220,6 +221,9 @@ def run_gemm_ar(P, rank, M, N, K, dtype, A_bits, B_bits, partials, peer_rows, sc
     deliver = "emu": both arrive through pk_emu_deliver_partials on a second stream (the bf16 rows as fp32 pairs),
                      into NaN-poisoned memory, partial slots first.
     withhold_rows: (q, flag index) of ar_flags_in never set ("pre" only).
+    before, meanwhile: called with (flags_in, ar_flags_in) when all is in place ("pre" only), and behind the launch, with a stream of
+    its own as the current one.  stream: a handle to run the call on.
+    The result's "seconds" are those from the launch to the end of the call.
     """
     plan = pk.pk_gemm_ar_plan(P, M, N, K, dtype)
     mp, fps, afps = M // P, plan.flags_per_slot, plan.ar_flags_per_slot
@@ -237,7 +241,7 @@ def run_gemm_ar(P, rank, M, N, K, dtype, A_bits, B_bits, partials, peer_rows, sc
     peers = [q for q in range(P) if q != rank]
     if order is None:
         order = peers
-    main = torch.cuda.current_stream()
+    main = torch.cuda.current_stream() if stream is None else torch.cuda.ExternalStream(stream)
     peer_rows = np.ascontiguousarray(peer_rows, dtype=np.uint16)
     if deliver == "pre":
         part = slot_upload(partials, s16)
@@ -250,6 +254,8 @@ def run_gemm_ar(P, rank, M, N, K, dtype, A_bits, B_bits, partials, peer_rows, sc
             ar_in[q].fill_(epoch)
         if withhold_rows is not None:
             ar_in[withhold_rows[0], withhold_rows[1]] = epoch - 1
+        if before is not None:
+            before(flags_in, ar_in)
         torch.cuda.synchronize()
     else:
         staging = slot_upload(partials, s16)
@@ -262,11 +268,16 @@ def run_gemm_ar(P, rank, M, N, K, dtype, A_bits, B_bits, partials, peer_rows, sc
         # the bf16 row blocks as fp32 pairs: N/2 columns, PK_AR_ROWS x tile_n/2 per flag
         pk.pk_emu_deliver_partials(P, M, N // 2, pk.AR_ROWS, plan.tile_n // 2, staging_rows, full, ar_in, epoch,
                                    list(order), gap_us, stream=side)
+    t0 = time.perf_counter()
     pk.pk_gemm_ar(P, rank, M, N, K, dtype, A, B, sa, sb, part, outgoing if P > 1 else None, flags_in,
                   flags_out if P > 1 else None, full, bcast if P > 1 else None, ar_in, ar_out if P > 1 else None, epoch,
                   phases, status, timeout_us, stream=main, partial_dtype=partial_dtype)
+    if meanwhile is not None:
+        with torch.cuda.stream(torch.cuda.Stream()):
+            meanwhile(flags_in, ar_in)
     torch.cuda.synchronize()
-    return {"full_bits": bits_of(full), "bcast_bits": bits_of(bcast), "ar_in": ar_in.cpu().numpy(),
+    seconds = time.perf_counter() - t0
+    return {"seconds": seconds, "full_bits": bits_of(full), "bcast_bits": bits_of(bcast), "ar_in": ar_in.cpu().numpy(),
             "ar_out": ar_out.cpu().numpy(), "flags_out": flags_out.cpu().numpy(), "status": status.cpu().numpy(),
             "outgoing": slot_download(outgoing, s16), "plan": plan}
 

@@ -3,6 +3,8 @@
 Gate as for GEMM + reduce-scatter: max |gpu - ref| / (|ref| + 1) <= 1e-2 (bf16 inputs), <= 5e-2 (fp8), plus the bound
 derived from fp32 accumulation and slot additions and half a bf16 ulp.  Everything that is only moved (the blocks
 handed to the other ranks, the rows received from them, flags) is compared bit for bit."""
+import time
+
 import numpy as np
 import pytest
 
@@ -178,3 +180,69 @@ def test_every_row_block_of_the_peers_is_waited_for(P, M, N, last_rank):
         res = run(withhold_rows=(q, b), timeout_us=1000)
         assert tuple(res["status"][:3]) == (pk.ERR_TIMEOUT, q * afps + b, 3)
         assert np.array_equal(res["full_bits"], base["full_bits"])          # the own rows are reduced all the same
+
+
+def _row_flags_run(P, M, N, timeout_us, epoch=9):
+    inp = wl.gemm_rs_inputs(P, M, N, P * 64, "bf16", 0, seed=3)
+    peer = peer_rows_for(P, M // P, N, seed=2)
+    run = lambda **kw: hz.run_gemm_ar(P, 0, M, N, P * 64, "bf16", inp["A_local"], inp["B_local"], inp["partials"], peer, epoch=epoch,
+                                      timeout_us=timeout_us, **kw)
+    base = run()                                                # (and the kernels are loaded)
+    assert base["status"][0] == 0
+    return run, base
+
+
+def _at(t0, seconds):
+    time.sleep(max(0.0, t0 + seconds - time.perf_counter()))
+
+
+# Two workgroups wait, each with half of the 512 row blocks.  One partial tile is late, and a row block of the peer that belongs to the
+# workgroup whose own rows are all there long before: its time runs from the end of the whole own reduce all the same.
+def test_time_for_the_peers_rows_runs_from_the_end_of_the_own_reduce():
+    T, epoch = 0.3, 9
+    run, base = _row_flags_run(2, 16, 512 * 128, int(T * 1e6), epoch)
+    assert base["plan"].flags_per_slot == base["plan"].ar_flags_per_slot == 512
+
+    def before(flags_in, ar_in):
+        flags_in[1, 400] = epoch - 1
+        ar_in[1, 3] = epoch - 1
+
+    def meanwhile(flags_in, ar_in):
+        t0 = time.perf_counter()
+        _at(t0, 0.8 * T)
+        flags_in[1, 400:401].fill_(epoch)
+        _at(t0, 1.4 * T)
+        ar_in[1, 3:4].fill_(epoch)
+
+    res = run(before=before, meanwhile=meanwhile)
+    assert res["status"][0] == 0, res["status"]
+    assert res["seconds"] >= 1.4 * T
+    assert np.array_equal(res["full_bits"], base["full_bits"])
+
+
+# The same where the own reduce takes 2.8 times the bound: eight compute units, on one of which every workgroup finds its partial late,
+# eight at a time, none by more than 0.7 of the bound.
+def test_time_for_the_peers_rows_behind_a_reduce_of_several_rounds():
+    T, epoch = 0.2, 9
+    run, base = _row_flags_run(2, 16, 512 * 128, int(T * 1e6), epoch)
+    comp, comm = pk.pk_partition_create(8)
+
+    def before(flags_in, ar_in):
+        flags_in[1, 1::8] = epoch - 1
+        ar_in[1, 3] = epoch - 1
+
+    def meanwhile(flags_in, ar_in):
+        t0 = time.perf_counter()
+        for i in range(4):
+            _at(t0, 0.7 * T * (i + 1))
+            flags_in[1, 1 + 128 * i:128 * (i + 1):8].fill_(epoch)
+        _at(t0, 3.4 * T)
+        ar_in[1, 3:4].fill_(epoch)
+
+    try:
+        res = run(before=before, meanwhile=meanwhile, stream=comm)
+    finally:
+        pk.pk_partition_destroy(comp, comm)
+    assert res["status"][0] == 0, res["status"]
+    assert res["seconds"] >= 3.4 * T
+    assert np.array_equal(res["full_bits"], base["full_bits"])
