@@ -79,9 +79,17 @@ __device__ __forceinline__ void wait_for_rows(const ReduceArgs& r) {
             wait = !given_up();
         }
     __syncthreads();
+    // one bound for all the flags of a thread together
+    const uint64_t t1 = wall_clock64();
 #pragma unroll
     for (int k = 0; k < kRowFlags; ++k)
-        if (late[k] && !flag_wait(r.ar_flags_in + index(k), r.epoch, r.timeout_ticks)) report_timeout(r.status, (uint32_t)index(k), 3u);
+        while (late[k] && !flag_ready(r.ar_flags_in + index(k), r.epoch)) {
+            __builtin_amdgcn_s_sleep(8);
+            if (wall_clock64() - t1 > r.timeout_ticks) {
+                if (!flag_ready(r.ar_flags_in + index(k), r.epoch)) report_timeout(r.status, (uint32_t)index(k), 3u);
+                break;
+            }
+        }
 }
 
 // PT > 0: compile-time P; PT == 0: runtime P.  S16: the slots hold bf16.  AR: all-reduce mode (the reduced rows are also

@@ -246,3 +246,23 @@ def test_time_for_the_peers_rows_behind_a_reduce_of_several_rounds():
     assert res["status"][0] == 0, res["status"]
     assert res["seconds"] >= 3.4 * T
     assert np.array_equal(res["full_bits"], base["full_bits"])
+
+
+# A peer that hands out nothing costs one bound and not one for each of the flags that a thread looks at (four here), with every own row
+# there, and behind a partial tile that never comes (16 row blocks of the own rows are then missing as well).
+@pytest.mark.parametrize("partial_too", [False, True])
+def test_a_peer_that_hands_out_nothing_takes_one_bound(partial_too):
+    T, epoch = 0.1, 9
+    run, base = _row_flags_run(2, 2048, 7936, int(T * 1e6), epoch)
+    afps = base["plan"].ar_flags_per_slot
+    assert 3 * 2048 < afps <= 4 * 2048
+
+    def before(flags_in, ar_in):
+        ar_in[1].fill_(epoch - 1)
+        if partial_too:
+            flags_in[1, 0] = epoch - 1
+
+    res = run(before=before)
+    waits = 2 if partial_too else 1                             # the reduce's own, then the one for the rows
+    assert res["status"][0] == pk.ERR_TIMEOUT and res["status"][2] == (2 if partial_too else 3)
+    assert waits * T <= res["seconds"] <= (waits + 0.8) * T
