@@ -5,13 +5,15 @@ include/pk.h.  Tensors are torch CUDA tensors (PyTorch is used for device
 memory and streams only); their data pointers are passed through unchanged.
 The op calls go through the extension module _pk_call (csrc/pk_call.cpp) as
 long as their arguments are plain ints, tensors and names, everything else
-through ctypes.  There is no fallback: if libpk.so has not been built,
-loading raises.
+through ctypes, and so do all calls, with a warning, where that module is not
+there or does not load.  There is no fallback for the library: if libpk.so has
+not been built, loading raises.
 """
 import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -117,13 +119,21 @@ def load_binding():
 
 class _Calls:
     """The functions of the extension module, loaded at the first of them.  They return the call's status, or None, before they
-    have done anything, for arguments that are not of the plain kinds."""
+    have done anything, for arguments that are not of the plain kinds.  Without the module they return None for all."""
+    _OPS = ("pk_gemm_rs", "pk_gemm_rs_cols", "pk_gemm_ar", "pk_ag_gemm", "pk_ag_gemm_static", "pk_ag_gemm_k")
 
     def __getattr__(self, name):
-        module = load_binding()
-        for f in ("pk_gemm_rs", "pk_gemm_rs_cols", "pk_gemm_ar", "pk_ag_gemm", "pk_ag_gemm_static", "pk_ag_gemm_k"):
-            setattr(self, f, getattr(module, f))
-        return getattr(module, name)
+        if name not in self._OPS:
+            raise AttributeError(name)
+        lib()
+        try:
+            module = load_binding()
+        except (RuntimeError, ImportError) as e:
+            warnings.warn(f"calls of libpk.so go through ctypes, which takes 2 us of host time more each: {e}", RuntimeWarning, stacklevel=3)
+            module = None
+        for f in self._OPS:
+            setattr(self, f, getattr(module, f) if module else lambda *args: None)
+        return getattr(self, name)
 
 
 _calls = _Calls()

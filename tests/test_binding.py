@@ -1,5 +1,5 @@
 """The extension module of the op calls (csrc/pk_call.cpp) against the ctypes conversions of pk.py: same status for every single changed
-argument, and None, nothing done, for arguments that are not plain ints, tensors or names.  Needs no GPU, and runs only where there
+argument, and None, nothing done, for arguments that are not plain ints, tensors or names; without the module all through ctypes.  Needs no GPU, and runs only where there
 is none: the pointers are made up, and a call that passes the library's checks ends at its launch."""
 import numpy as np
 import pytest
@@ -74,3 +74,17 @@ def test_other_kinds_of_arguments_are_left_to_ctypes(op):
     assert call(*list(OPS[op].values())[:-1]) is None                       # an argument too few
     with pytest.raises(ValueError):
         getattr(pk, op)(*dict(OPS[op], A=cpu).values())
+
+
+@pytest.mark.parametrize("content", [None, "no shared object"])
+def test_without_the_module_the_ops_go_through_ctypes(content, monkeypatch, tmp_path):
+    path = tmp_path / "_pk_call.so"
+    if content is not None:
+        path.write_text(content)
+    monkeypatch.setattr(pk, "CALL_PATH", str(path))
+    monkeypatch.setattr(pk, "_calls", pk._Calls())
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        first = _status(pk.pk_gemm_rs, dict(OPS["pk_gemm_rs"], M=255))
+    assert first == pk.ERR_SHAPE
+    for op in OPS:
+        assert _status(getattr(pk, op), OPS[op]) == _through_ctypes(op, OPS[op], monkeypatch)
