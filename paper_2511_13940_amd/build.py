@@ -1,4 +1,5 @@
 """Builds libpk.so (the C-ABI library with the gfx950 kernels) and the CPython binding of its op calls in-tree with hipcc."""
+import hashlib
 import os
 import subprocess
 import sysconfig
@@ -20,12 +21,19 @@ HIPCC_FLAGS = [
 ]
 
 
+def header_digest():
+    """What tells the interface that a library and an extension module were compiled with from another one."""
+    with open(HEADERS[-1], "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
 def build_library(verbose=False):
     """Compile libpk.so; always recompiles (the sources side by side).  Returns the path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     with tempfile.TemporaryDirectory() as tmp:
         objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in SOURCES]
-        cmds = [[hipcc] + HIPCC_FLAGS + ["-c", s, "-o", o] for s, o in zip(SOURCES, objs)]
+        digest = '-DPK_HEADER_DIGEST="%s"' % header_digest()
+        cmds = [[hipcc] + HIPCC_FLAGS + [digest, "-c", s, "-o", o] for s, o in zip(SOURCES, objs)]
         with ThreadPoolExecutor(max_workers=min(8, len(cmds))) as pool:
             list(pool.map(lambda c: _run(c, verbose), cmds))
         _run([hipcc] + HIPCC_FLAGS + ["-shared"] + objs + ["-o", LIB_PATH], verbose)
@@ -42,15 +50,17 @@ def _run(cmd, verbose):
 
 
 def build_binding(verbose=False):
-    """Compile csrc/pk_call.cpp (host code only) against torch and libpk.so, which has to be there."""
+    """Compile csrc/pk_call.cpp (host code only) against torch."""
     import torch
     from torch.utils import cpp_extension
+    from . import pk
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     include = [sysconfig.get_path("include")] + cpp_extension.include_paths("cuda")
     _run([hipcc, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
-          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-isystem" + i for i in include] +
-         [os.path.join(CSRC, "pk_call.cpp"), "-L", HERE, "-l:libpk.so", "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
-          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-o", CALL_PATH], verbose)
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DPK_BUILT_FOR="%s"' % pk.built_for(header_digest())] +
+         ["-isystem" + i for i in include] +
+         [os.path.join(CSRC, "pk_call.cpp"), "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", CALL_PATH], verbose)
     return CALL_PATH
 
 

@@ -2,6 +2,10 @@
 // torch.Tensor, the names of the enumerations, None.  Given anything else a function returns None before it has done anything,
 // and pk.py converts the arguments itself.
 //
+// The module is not linked against libpk.so: pk.py hands it the addresses of the entry points of the library that it has loaded (bind),
+// so that all calls of a process go to one library, wherever a search path or another copy of the package would lead.  `built_for` names
+// what it was compiled against (interface, torch, interpreter), and pk.py takes it only where all of that is what it runs with.
+//
 // What bounds a small call is the host: through ctypes a reduce-scatter of 256 x 256 x 512 (two launches) takes 11.8 us of it and 7.2
 // us on the device, 11.6 us a call; through this 9.1 us, 9.2 us a call.  What is left are 0.7 us here and in pk.py and about 4 us a
 // launch (the runtime writes a launch's arguments to device memory and reads them back).
@@ -11,7 +15,21 @@
 
 #include "../../include/pk.h"
 
+#ifndef PK_BUILT_FOR
+#define PK_BUILT_FOR ""
+#endif
+
 namespace {
+
+// in the order that bind takes
+struct {
+    decltype(&pk_gemm_rs) gemm_rs;
+    decltype(&pk_gemm_rs_cols) gemm_rs_cols;
+    decltype(&pk_gemm_ar) gemm_ar;
+    decltype(&pk_ag_gemm) ag_gemm;
+    decltype(&pk_ag_gemm_static) ag_gemm_static;
+    decltype(&pk_ag_gemm_k) ag_gemm_k;
+} lib;
 
 bool as_i64(PyObject* o, int64_t* v) {
     if (!PyLong_CheckExact(o)) return false;
@@ -135,7 +153,7 @@ PyObject* gemm_rs_of(PyObject* const* a, Py_ssize_t n, bool cols) {
     int comm_cus, pdt, layout = 0;
     uint64_t timeout;
     size_t ws_bytes = 0;
-    if (n != (cols ? 22 : 24) || !p.read(a) || !as_ptr(a[10], &part) || !as_ptr(a[11], &outg) || !as_ptr(a[12], &fin) ||
+    if (!lib.gemm_rs || n != (cols ? 22 : 24) || !p.read(a) || !as_ptr(a[10], &part) || !as_ptr(a[11], &outg) || !as_ptr(a[12], &fin) ||
         !as_ptr(a[13], &fout) || !as_u32(a[14], &epoch) || !as_ptr(a[15], &out) || !as_u32(a[16], &phases) || !as_ptr(a[17], &status) ||
         !as_u64(a[18], &timeout) || !as_int(a[20], &comm_cus) || !as_enum(a[21], kPartials, &pdt))
         Py_RETURN_NONE;
@@ -144,11 +162,11 @@ PyObject* gemm_rs_of(PyObject* const* a, Py_ssize_t n, bool cols) {
     if (!as_stream(a[19], &stream)) Py_RETURN_NONE;
     if (cols)
         return run([&] {
-            return pk_gemm_rs_cols(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, part, outg, (uint32_t*)fin,
+            return lib.gemm_rs_cols(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, part, outg, (uint32_t*)fin,
                                    (uint32_t*)fout, epoch, out, phases, comm_cus, pdt, (uint32_t*)status, timeout, stream);
         });
     return run([&] {
-        return pk_gemm_rs(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, part, outg, (uint32_t*)fin,
+        return lib.gemm_rs(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, part, outg, (uint32_t*)fin,
                           (uint32_t*)fout, epoch, out, phases, comm_cus, pdt, layout, ws, ws_bytes, (uint32_t*)status, timeout, stream);
     });
 }
@@ -161,13 +179,13 @@ PyObject* gemm_ar(PyObject*, PyObject* const* a, Py_ssize_t n) {
     uint32_t epoch, phases;
     int comm_cus, pdt;
     uint64_t timeout;
-    if (n != 25 || !p.read(a) || !as_ptr(a[10], &part) || !as_ptr(a[11], &outg) || !as_ptr(a[12], &fin) || !as_ptr(a[13], &fout) ||
+    if (!lib.gemm_ar || n != 25 || !p.read(a) || !as_ptr(a[10], &part) || !as_ptr(a[11], &outg) || !as_ptr(a[12], &fin) || !as_ptr(a[13], &fout) ||
         !as_ptr(a[14], &full) || !as_ptr(a[15], &bcast) || !as_ptr(a[16], &arin) || !as_ptr(a[17], &arout) || !as_u32(a[18], &epoch) ||
         !as_u32(a[19], &phases) || !as_ptr(a[20], &status) || !as_u64(a[21], &timeout) || !as_int(a[23], &comm_cus) ||
         !as_enum(a[24], kPartials, &pdt) || !as_stream(a[22], &stream))
         Py_RETURN_NONE;
     return run([&] {
-        return pk_gemm_ar(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, part, outg, (uint32_t*)fin,
+        return lib.gemm_ar(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, part, outg, (uint32_t*)fin,
                           (uint32_t*)fout, full, bcast, (uint32_t*)arin, (uint32_t*)arout, epoch, phases, comm_cus, pdt, (uint32_t*)status,
                           timeout, stream);
     });
@@ -181,7 +199,7 @@ PyObject* ag_gemm_of(PyObject* const* a, Py_ssize_t n, Gather kind) {
     int comm_cus, act, layout = 0;
     uint64_t timeout;
     size_t ws_bytes = 0;
-    if (n != (kind == ROWS ? 20 : 18) || !p.read(a) || !as_ptr(a[10], &flags) || !as_u32(a[11], &epoch) || !as_ptr(a[12], &C) ||
+    if (!lib.ag_gemm || n != (kind == ROWS ? 20 : 18) || !p.read(a) || !as_ptr(a[10], &flags) || !as_u32(a[11], &epoch) || !as_ptr(a[12], &C) ||
         !as_ptr(a[13], &status) || !as_u64(a[14], &timeout) || !as_int(a[16], &comm_cus) || !as_enum(a[17], kActivations, &act))
         Py_RETURN_NONE;
     if (kind == ROWS && ((a[18] != Py_None && !as_tensor(a[18], &ws, &ws_bytes)) || !as_enum(a[19], kLayouts, &layout) || (layout & ~1)))
@@ -189,11 +207,11 @@ PyObject* ag_gemm_of(PyObject* const* a, Py_ssize_t n, Gather kind) {
     if (!as_stream(a[15], &stream)) Py_RETURN_NONE;
     if (kind == ROWS)
         return run([&] {
-            return pk_ag_gemm(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, (uint32_t*)flags, epoch, C,
+            return lib.ag_gemm(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa, (float*)p.sb, (uint32_t*)flags, epoch, C,
                               comm_cus, act, layout, ws, ws_bytes, (uint32_t*)status, timeout, stream);
         });
     return run([&] {
-        return (kind == K_CHUNKS ? pk_ag_gemm_k : pk_ag_gemm_static)(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa,
+        return (kind == K_CHUNKS ? lib.ag_gemm_k : lib.ag_gemm_static)(p.P, p.rank, p.M, p.N, p.K, (pk_dtype)p.dt, p.A, p.B, (float*)p.sa,
                                                                      (float*)p.sb, (uint32_t*)flags, epoch, C, comm_cus, act,
                                                                      (uint32_t*)status, timeout, stream);
     });
@@ -202,11 +220,32 @@ PyObject* ag_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) { return ag_gemm_
 PyObject* ag_gemm_static(PyObject*, PyObject* const* a, Py_ssize_t n) { return ag_gemm_of(a, n, ROWS_STATIC); }
 PyObject* ag_gemm_k(PyObject*, PyObject* const* a, Py_ssize_t n) { return ag_gemm_of(a, n, K_CHUNKS); }
 
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    void* f[6];
+    bool ok = n == 6;
+    for (int i = 0; ok && i < 6; ++i) ok = as_ptr(a[i], &f[i]) && f[i];
+    if (!ok) {
+        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of the six entry points");
+        return nullptr;
+    }
+    lib = {(decltype(lib.gemm_rs))f[0], (decltype(lib.gemm_rs_cols))f[1], (decltype(lib.gemm_ar))f[2], (decltype(lib.ag_gemm))f[3],
+           (decltype(lib.ag_gemm_static))f[4], (decltype(lib.ag_gemm_k))f[5]};
+    Py_RETURN_NONE;
+}
+
 #define PK_METHOD(f) {"pk_" #f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
 PyMethodDef kMethods[] = {PK_METHOD(gemm_rs), PK_METHOD(gemm_rs_cols), PK_METHOD(gemm_ar), PK_METHOD(ag_gemm),
-                          PK_METHOD(ag_gemm_static), PK_METHOD(ag_gemm_k), {nullptr, nullptr, 0, nullptr}};
+                          PK_METHOD(ag_gemm_static), PK_METHOD(ag_gemm_k),
+                          {"bind", (PyCFunction)(void (*)(void))bind, METH_FASTCALL, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_pk_call", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__pk_call(void) { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit__pk_call(void) {
+    PyObject* m = PyModule_Create(&kModule);
+    if (m && PyModule_AddStringConstant(m, "built_for", PK_BUILT_FOR) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1345,6 +1345,13 @@ pk_status pk_partition_destroy(void* compute_stream, void* comm_stream) {
     return st;
 }
 
+// Digest of the interface that this library was compiled with, by which pk.py tells whether the extension module belongs to it: not
+// part of the interface.
+#ifndef PK_HEADER_DIGEST
+#define PK_HEADER_DIGEST ""
+#endif
+const char* pk_header_digest(void) { return PK_HEADER_DIGEST; }
+
 // Which way a call goes, for the tests: host only, launches nothing, not part of the interface.  op: 0 pk_gemm_rs, 1 pk_gemm_rs_cols,
 // 2 pk_gemm_ar, 3 pk_ag_gemm, 4 pk_ag_gemm_k.  route: rows and columns of the tiles; 1 if their ready flags are published behind the
 // GEMM; tiles of the first and of the second launch (0: one launch); 1 with a stream-K tail; all-gather: 1 if tile rows run over all

@@ -6,13 +6,14 @@ memory and streams only); their data pointers are passed through unchanged.
 The op calls go through the extension module _pk_call (csrc/pk_call.cpp) as
 long as their arguments are plain ints, tensors and names, everything else
 through ctypes, and so do all calls, with a warning, where that module is not
-there or does not load.  There is no fallback for the library: if libpk.so has
+there, does not load or was built for another library, torch or interpreter.  There is no fallback for the library: if libpk.so has
 not been built, loading raises.
 """
 import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sysconfig
 import warnings
 
 import torch
@@ -104,9 +105,17 @@ def lib():
     return _lib
 
 
+_OPS = ("pk_gemm_rs", "pk_gemm_rs_cols", "pk_gemm_ar", "pk_ag_gemm", "pk_ag_gemm_static", "pk_ag_gemm_k")
+
+
+def built_for(header_digest):
+    """What the extension module has to have been compiled against, the library's interface, torch and the interpreter, as one text."""
+    return f"{header_digest} torch {torch.__version__} {sysconfig.get_config_var('SOABI')}"
+
+
 def load_binding():
-    """The extension module of the op calls; raises if it has not been built."""
-    lib()
+    """The extension module of the op calls, for the loaded library; raises if it has not been built or is not for this one."""
+    L = lib()
     if not os.path.exists(CALL_PATH):
         raise RuntimeError(f"{CALL_PATH} is missing: build it with `python -m paper_2511_13940_amd.build` "
                            "(or __graft_entry__.build())")
@@ -114,16 +123,22 @@ def load_binding():
     spec = importlib.util.spec_from_file_location("_pk_call", CALL_PATH, loader=loader)
     module = importlib.util.module_from_spec(spec)
     loader.exec_module(module)
+    digest = getattr(L, "pk_header_digest", None)
+    if digest is not None:
+        digest.restype = ctypes.c_char_p
+    have, want = getattr(module, "built_for", ""), built_for(digest().decode() if digest else "")
+    if have != want:
+        raise RuntimeError(f"{CALL_PATH} was built for '{have}' and this is '{want}': build it again")
+    module.bind(*(ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in _OPS))
     return module
 
 
 class _Calls:
     """The functions of the extension module, loaded at the first of them.  They return the call's status, or None, before they
     have done anything, for arguments that are not of the plain kinds.  Without the module they return None for all."""
-    _OPS = ("pk_gemm_rs", "pk_gemm_rs_cols", "pk_gemm_ar", "pk_ag_gemm", "pk_ag_gemm_static", "pk_ag_gemm_k")
 
     def __getattr__(self, name):
-        if name not in self._OPS:
+        if name not in _OPS:
             raise AttributeError(name)
         lib()
         try:
@@ -131,7 +146,7 @@ class _Calls:
         except (RuntimeError, ImportError) as e:
             warnings.warn(f"calls of libpk.so go through ctypes, which takes 2 us of host time more each: {e}", RuntimeWarning, stacklevel=3)
             module = None
-        for f in self._OPS:
+        for f in _OPS:
             setattr(self, f, getattr(module, f) if module else lambda *args: None)
         return getattr(self, name)
 

@@ -1,6 +1,11 @@
 """The extension module of the op calls (csrc/pk_call.cpp) against the ctypes conversions of pk.py: same status for every single changed
 argument, and None, nothing done, for arguments that are not plain ints, tensors or names; without the module all through ctypes.  Needs no GPU, and runs only where there
 is none: the pointers are made up, and a call that passes the library's checks ends at its launch."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -88,3 +93,27 @@ def test_without_the_module_the_ops_go_through_ctypes(content, monkeypatch, tmp_
     assert first == pk.ERR_SHAPE
     for op in OPS:
         assert _status(getattr(pk, op), OPS[op]) == _through_ctypes(op, OPS[op], monkeypatch)
+
+
+def test_a_module_built_for_something_else_is_not_used(monkeypatch, tmp_path):
+    built = open(pk.CALL_PATH, "rb").read()
+    for name, old in (("interface", pk.load_binding().built_for.split()[0].encode()), ("torch", b" torch " + torch.__version__.encode())):
+        assert old in built
+        path = tmp_path / name / "_pk_call.so"
+        path.parent.mkdir()
+        path.write_bytes(built.replace(old, old[:-1] + b"?"))
+        monkeypatch.setattr(pk, "CALL_PATH", str(path))
+        with pytest.raises(RuntimeError, match="was built for"):
+            pk.load_binding()
+        monkeypatch.setattr(pk, "_calls", pk._Calls())
+        with pytest.warns(RuntimeWarning, match="was built for"):
+            assert _status(pk.pk_gemm_rs, dict(OPS["pk_gemm_rs"], M=255)) == pk.ERR_SHAPE
+
+
+def test_the_module_calls_the_library_that_pk_has_loaded(tmp_path):
+    shutil.copy(pk.LIB_PATH, tmp_path / "libpk.so")                         # another one, where the loader would look first
+    code = ("from paper_2511_13940_amd import pk; pk.load_binding(); "
+            "print({l.split()[-1] for l in open('/proc/self/maps') if 'libpk.so' in l} == {pk.LIB_PATH})")
+    env = dict(os.environ, LD_LIBRARY_PATH=os.pathsep.join([str(tmp_path), os.environ.get("LD_LIBRARY_PATH", "")]))
+    run = subprocess.run([sys.executable, "-c", code], env=env, cwd=os.path.dirname(os.path.dirname(pk.LIB_PATH)), capture_output=True, text=True)
+    assert run.stdout.strip() == "True", run
