@@ -283,7 +283,7 @@ def run_gemm_ar(P, rank, M, N, K, dtype, A_bits, B_bits, partials, peer_rows, sc
 
 
 def run_ag_gemm_k(P, rank, M, N, K, dtype, chunks, B_bits, scale_a=None, scale_b=None, epoch=1, deliver="pre",
-                  order=None, timeout_us=0, withhold=None, act="none"):
+                  order=None, timeout_us=0, withhold=None, act="none", comm_cus=0):
     """One pk_ag_gemm_k call.  chunks: list of P numpy bit arrays (M x K/P), chunk q = columns K_q of A.
 
     deliver = "pre": every chunk is in A_gathered with its flag set before the call.
@@ -321,6 +321,6 @@ def run_ag_gemm_k(P, rank, M, N, K, dtype, chunks, B_bits, scale_a=None, scale_b
         side = torch.cuda.Stream()
         pk.pk_emu_deliver_kchunks_dma(P, M, K, elem, staging, A, flags, epoch, list(order), stream=side)
     pk.pk_ag_gemm_k(P, rank, M, N, K, dtype, A, B, sa, sb, flags if P > 1 else None, epoch, C, status, timeout_us,
-                    stream=main, act=act)
+                    stream=main, comm_cus=comm_cus, act=act)
     torch.cuda.synchronize()
     return {"C_bits": bits_of(C), "status": status.cpu().numpy(), "A_after": A.cpu().numpy(), "flags": flags.cpu().numpy()}
