@@ -6,9 +6,9 @@
 // so that all calls of a process go to one library, wherever a search path or another copy of the package would lead.  `built_for` names
 // what it was compiled against (interface, torch, interpreter), and pk.py takes it only where all of that is what it runs with.
 //
-// What bounds a small call is the host: through ctypes a reduce-scatter of 256 x 256 x 512 (two launches) takes 11.8 us of it and 7.2
-// us on the device, 11.6 us a call; through this 9.1 us, 9.2 us a call.  What is left are 0.7 us here and in pk.py and about 4 us a
-// launch (the runtime writes a launch's arguments to device memory and reads them back).
+// What bounds a small call is the host: a reduce-scatter of 256 x 256 x 512 (two launches, 6.14 us on the device) takes 13.0 us of host
+// time on an idle device and 12.0 us a call back to back through ctypes, 10.1 and 9.4 through this (medians of three processes).  What
+// is left are 0.7 us here and in pk.py and about 4 us a launch (the runtime writes a launch's arguments to device memory and reads them back).
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>

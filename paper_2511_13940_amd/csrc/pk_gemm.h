@@ -147,9 +147,10 @@ constexpr int kWaitLgkm0 = waitcnt_vm_lgkm0(63);   // vmcnt as high as it goes: 
 // scalar cache, and none takes a register (or, with a hundred scalar registers in use, a lane of a vector register) through the main
 // loops.  us a call, FETCH_BLOCK / FETCH_FIRST: all-gather, 128x256 tiles,
 // 2048 x 4096 x 512 13.15 / 12.79, 256x128, 4176 x 1568 x 13248 150.3 / 148.4; column chunks, 256x256, 11347 x 1144 x 1024 34.4 / 33.3.
-// For every kernel below 256x256, with the LDS addresses of dma_load16, over 128 calls drawn evenly over the tiles: 1.5% less on average, 2% for
-// 256x128 (1024 x 8192 x 3584 reduce-scatter 59.4 / 58.2), 2-6% for the small ones.  The arguments of the tile mapping as one block of
-// 192 bytes per tile, so that they come in together, was half a percent slower than one by one: the registers it takes.
+// For every kernel below 256x256, over 128 calls drawn evenly over the tiles: 0.5% less on average, beside 0.8% by the LDS addresses of
+// dma_load16 and 0.2% by the clocks that only workgroup 0 reads; all three together 2% for 256x128 (1024 x 8192 x 3584 reduce-scatter
+// 59.4 / 58.2), 2-6% for the small ones.  The arguments of the tile mapping as one block of 192 bytes per tile, so that they come in
+// together, was half a percent slower than one by one: the registers it takes.
 // Not with stores on their way through the next main loop (256x256 all-gather, 13176 x 872 x 704 28.3 / 29.6).
 enum Fetch { FETCH_PLAIN, FETCH_BLOCK, FETCH_FIRST };
 template <Fetch HOW>
@@ -227,8 +228,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 1) void gemm_kernel(const GemmAr
     // All tiles up to 128x128: 2-10% less a call for 32-row tiles (64 x 3584 x 8192 SiLU 25.0 -> 24.0 us, 44 x 3840 x 1152 fp8 5.40 ->
     // 4.81), 1-4% for 64x64, 1-3% for 128x64 and 128x128.  Of 256x128 and 128x256 where it was the faster one over 140 calls: fp32 slots (256x128 1-2%
     // less, fp8 5%), all-gathers (fp8 and 128x256: 1% less, 3-6% with an activation; not bf16 256x128, which has no register left for it);
-    // not bf16 slots (0-6% more) and fp8 128x256 with a row-major operand (2% more).  256x256 tiles run many rounds and keep the
-    // stores under the next main loop.
+    // not bf16 slots (0-6% more: one 16-byte chunk of sums a lane, so bf16 rows leave in 8-byte stores; 16 bytes from two chunks have
+    // not been tried) and fp8 128x256 with a row-major operand (2% more).  256x256 tiles run many rounds and keep the stores under the
+    // next main loop.
     constexpr bool ROWX = BM * BN <= 128 * 128 || (BM * BN == 256 * 128 && EPI != EPI_RS16 &&
                                                    (FP8 ? BM == 256 || BT : EPI == EPI_RS || BM == 128));
     static_assert(ROWX || (OB * WK == TM * TN && OTM * OTN == OB), "the blocks of a wave's sub-tile are shared out evenly");

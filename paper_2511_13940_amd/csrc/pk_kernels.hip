@@ -109,8 +109,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceArgs r) {
     // 256x256x512 on 2 ranks 6.36 us -> 6.16, of 16x448x512 on 8 ranks 6.37 -> 6.20 (device time of both kernels, 37 calls of 16 to
     // 9776 rows 0.2 to 0.4 us less each).  In all-reduce mode it gave -0.1 and +0.2 us, so there it is left out.
     if constexpr (!AR)
-        asm volatile("" ::"s"(r.partials), "s"(r.out), "s"(r.flags_in), "s"(r.flags_out), "s"(r.late_signal), "s"(r.n), "s"(r.tile_n), "s"(r.by_sub.d),
-                     "s"(r.by_cpr.d), "s"(r.by_cpr.m), "s"(r.by_cpr_last.d), "s"(r.by_cpr_last.m), "s"(r.slot_elems), "s"(r.flags_per_slot), "s"(r.rank));
+        asm volatile("" ::"s"(r.partials), "s"(r.out), "s"(r.flags_in), "s"(r.flags_out), "s"(r.late_signal), "s"(r.n), "s"(r.tile_n),
+                     "s"(r.by_sub.d), "s"(r.by_cpr.d), "s"(r.by_cpr.m), "s"(r.by_cpr_last.d), "s"(r.by_cpr_last.m), "s"(r.slot_elems),
+                     "s"(r.flags_per_slot), "s"(r.rank));
     const int tile = r.by_sub.div(blockIdx.x);
     const int sb = blockIdx.x - tile * r.by_sub.d;
     const int tmi = r.by_tiles_n.div(tile), tc = tile - tmi * r.tiles_n;
